@@ -3,7 +3,7 @@
 // Host side: argument validation, the mini-sequence driver (Algorithm 1, else-branch), the
 // last-token LM head launch and the KV offload copies.  Nothing here allocates or synchronises.
 // The only state is what mom_init resolves per device (compute-unit count, address of the static
-// workspace) and the two testing overrides of mom_debug_force_gemm_form / mom_debug_force_pipeline.
+// workspace) and the testing overrides of the mom_debug_force_ calls.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -11,8 +11,10 @@
 #include <type_traits>
 
 #include "mom.h"
+#include "mom_gemm_forms.h"
 #include "mom_gemm_schedule.h"
 #include "mom_gemm.hip.inc"
+#include "mom_gemm_short.hip.inc"
 #include "mom_gemv.hip.inc"
 #include "mom_probe.hip.inc"
 
@@ -70,8 +72,9 @@ DeviceInfo g_dev[kMaxDevices];
 constexpr int kGateUpNarrowPerMille = 1070;
 constexpr int kGateUpMixMinGainPerMille = 15;
 
-// Testing overrides (mom_debug_force_gemm_form / mom_debug_force_pipeline); 0 = the library chooses.
-std::atomic<int> g_force_edge{0}, g_force_slots{0}, g_force_width{0}, g_force_pipeline{0};
+// Testing overrides (the mom_debug_force_ calls); 0 = the library chooses.
+std::atomic<int> g_force_edge{0}, g_force_width{0}, g_force_pipeline{0};
+std::atomic<int> g_force_short{0};      // token rows << 16 | weight rows
 
 DeviceInfo* current_device_info() {
     int dev = 0;
@@ -132,55 +135,60 @@ bool set_tile_grid(momk::GemmArgs& a, int edge, int width) {
     a.tiles_m = (a.M + edge - 1) / edge;
     a.tiles_n = (a.N + tile_n - 1) / tile_n;
     const int64_t t = (int64_t)a.tiles_m * a.tiles_n;
-    if (t <= 0 || t > (int64_t)0x1fffffff) return false;
+    if (t <= 0 || t > momk::kMaxTiles) return false;
     a.tiles_per_xcd = (int)((t + 7) / 8);
     return true;
 }
 
-// One launch of gemm4_kernel<EPI, edge, slots, width> over the operands in `a` (M, N, K, ldo set).
+// One launch of gemm4_kernel<EPI, edge, width> over the operands in `a` (M, N, K, ldo set).
 template <int EPI>
-hipError_t launch_gemm_form(momk::GemmArgs a, int edge, int slots, int width, hipStream_t st) {
+hipError_t launch_gemm_form(momk::GemmArgs a, int edge, int width, hipStream_t st) {
     if (!set_tile_grid<EPI>(a, edge, width)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(a.tiles_per_xcd * 8)), block(momk::k4Threads);
-#define MOM_LAUNCH4(E, S, W) hipLaunchKernelGGL((momk::gemm4_kernel<EPI, E, S, W>), grid, block, 0, st, a)
-    if (edge == 256 && slots == 5) {
-        if constexpr (EPI == momk::EPI_DOWN) {
-            if (width == 256) MOM_LAUNCH4(256, 5, 256);
-            else if (width == 224) MOM_LAUNCH4(256, 5, 224);
-            else if (width == 192) MOM_LAUNCH4(256, 5, 192);
-            else if (width == 160) MOM_LAUNCH4(256, 5, 160);
-            else if (width == 128) MOM_LAUNCH4(256, 5, 128);
-            else return hipErrorInvalidValue;
-        } else {
-            if (width == 256) MOM_LAUNCH4(256, 5, 256);
-            else if (width == 192) MOM_LAUNCH4(256, 5, 192);
-            else return hipErrorInvalidValue;
-        }
+#define MOM_LAUNCH4(E, W) hipLaunchKernelGGL((momk::gemm4_kernel<EPI, E, W>), grid, block, 0, st, a)
+    if (edge == 256 && width == 256) MOM_LAUNCH4(256, 256);
+    else if (edge == 256 && width == 192) MOM_LAUNCH4(256, 192);
+    else if constexpr (EPI == momk::EPI_DOWN) {
+        if (edge == 256 && width == 224) MOM_LAUNCH4(256, 224);
+        else if (edge == 256 && width == 160) MOM_LAUNCH4(256, 160);
+        else if (edge == 256 && width == 128) MOM_LAUNCH4(256, 128);
+        else return hipErrorInvalidValue;
+    } else {
+        if (edge == 128 && width == 128) MOM_LAUNCH4(128, 128);
+        else return hipErrorInvalidValue;
     }
-    else if (edge == 128 && slots == 5 && width == 128) MOM_LAUNCH4(128, 5, 128);
-    else if (edge == 128 && slots == 10 && width == 128) MOM_LAUNCH4(128, 10, 128);
-    else if (edge == 64 && slots == 5 && width == 64) MOM_LAUNCH4(64, 5, 64);
-    else if (edge == 64 && slots == 10 && width == 64) MOM_LAUNCH4(64, 10, 64);
-    else if (edge == 64 && slots == 20 && width == 64) MOM_LAUNCH4(64, 20, 64);
-    else return hipErrorInvalidValue;
 #undef MOM_LAUNCH4
+    return hipGetLastError();
+}
+
+// One launch in the short form `form` (mom_gemm_forms.h).
+template <int EPI>
+hipError_t launch_short_form(momk::GemmArgs a, int form, hipStream_t st) {
+    const momk::ShortShape f = momk::short_shape(EPI == momk::EPI_GATEUP, form);
+    if (!set_tile_grid<EPI>(a, f.tm, f.tn)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(a.tiles_per_xcd * 8)), block(momk::k4Threads);
+    int i = 0;
+#define MOM_LAUNCH_SHORT(TM, TN, WM, WN, KSUB, NSTG)                                                              \
+    if (i++ == form)                                                                                              \
+        hipLaunchKernelGGL((momk::gemm_short_kernel<EPI, TM, TN, WM, WN, KSUB, NSTG>), grid, block, 0, st, a);
+    if constexpr (EPI == momk::EPI_GATEUP) { MOM_SHORT_FORMS_GATEUP(MOM_LAUNCH_SHORT) }
+    else { MOM_SHORT_FORMS_DOWN(MOM_LAUNCH_SHORT) }
+#undef MOM_LAUNCH_SHORT
     return hipGetLastError();
 }
 
 template <int EPI>
 hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const unsigned short* W1,
                        unsigned short* O, int M, int N, int K, hipStream_t st, bool never_small = false) {
+    constexpr bool GU = EPI == momk::EPI_GATEUP;
     momk::GemmArgs a;
     a.X = X; a.W0 = W0; a.W1 = W1; a.O = O;
     a.M = M; a.N = N; a.K = K; a.ldo = N;
-    // tiles of a launch with `tile` token rows and `cols` output columns per tile
-    auto tiles_of = [&](int tile, int cols) { return (int64_t)((M + tile - 1) / tile) * ((N + cols - 1) / cols); };
-    const int gu = (EPI == momk::EPI_GATEUP) ? 2 : 1;        // weight rows staged per output column
-    if (tiles_of(momk::kBM, momk::kBW / gu) > (int64_t)0x1fffffff) return hipErrorInvalidValue;
+    // tiles of a launch with 256 token rows and `cols` output columns per tile
+    auto tiles_of = [&](int cols) { return (int64_t)((M + 255) / 256) * ((N + cols - 1) / cols); };
+    if (tiles_of(GU ? 128 : 256) > momk::kMaxTiles) return hipErrorInvalidValue;
     // All forms give identical bits (every output element sees the same MFMA sequence over k), so the
-    // choice is free.  Tile edge and ring depth: 256-tiles unless they would leave a quarter or more of
-    // the CUs without work; then 128-tiles, or 64-tiles when even those fill less than half of the CUs;
-    // the small tiles get a deeper ring the fewer workgroups a CU has to hide latency with.
+    // choice is free.
     // Down projection with 256-row tiles: 256, 224, 192, 160 or 128 weight rows per tile, whichever needs
     // the least time in rounds of the CUs (rounds x width, a narrower tile charged more per column for the
     // token fragments it shares among fewer MFMAs, a partly filled last round less than a whole one): 3584
@@ -190,75 +198,81 @@ hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const 
     // Gate/up with 256-row tiles: the first columns in tiles of 128 columns, the rest in tiles of 96, in one
     // launch of the two-width kernel, where the same model says that saves time: 14336 columns with 12 token
     // tiles are 1344 tiles = 5.25 rounds, but 64 x 128 + 64 x 96 columns are three rounds of each width.
-    // mom_debug_force_gemm_form overrides the choice (for tests, which need every form on shapes of
-    // every size).
+    // Few tiles: the short forms where their cost is lower.  Then the operand rows that a CU moves count,
+    // and the best form is the one that gives every CU one tile with the fewest of them (mom_gemm_forms.h).
+    // Gate/up with a short contraction: 128-row tiles, two workgroups per CU, by the same cost.
+    // The mom_debug_force_ calls override the choice (for tests, which need every form on shapes of every size).
     const int cus = compute_units();
     if (cus <= 0) return hipErrorInvalidDevice;
-    int edge = 256, slots = 0, width = 256;
-    int64_t narrow_tiles_n = 0;          // gate/up: column tiles of the narrow width behind the wide ones
+    const int fs = g_force_short.load(std::memory_order_relaxed);
+    if (fs) {
+        const int form = momk::find_short_form(GU, fs >> 16, fs & 0xffff);
+        if (form >= 0) return launch_short_form<EPI>(a, form, st);
+    }
     const int force = g_force_edge.load(std::memory_order_relaxed);
-    if (force) {
-        edge = force;
-        width = edge;
+    if (force == 256) {
         const int fw = g_force_width.load(std::memory_order_relaxed);
-        if (edge == 256 && fw && (EPI == momk::EPI_DOWN || fw == 192)) width = fw;
-        slots = g_force_slots.load(std::memory_order_relaxed);
+        return launch_gemm_form<EPI>(a, 256, (fw && (!GU || fw == 192)) ? fw : 256, st);
+    }
+    if (force == 128 && GU) return launch_gemm_form<EPI>(a, 128, 128, st);
+    if (force) return launch_short_form<EPI>(a, momk::find_short_form(GU, force, force), st);
+
+    // Rounds of the CUs a launch of `tiles` 256-row tiles takes, in 1/1000.  A last round that fills only part of the
+    // CUs is not as dear as a whole one: the chip is power-limited and clocks the busy CUs higher (measured:
+    // a round on a quarter / half / three quarters of the CUs takes about 0.55 / 0.8 / 0.8-0.9 of a full one).
+    auto rounds_pm = [&](int64_t tiles) {
+        const int64_t full = tiles / cus, rem = tiles % cus;
+        return full * 1000 + (rem ? 500 + 500 * rem / cus : 0);
+    };
+    int width = 256;
+    int64_t narrow_tiles_n = 0;          // gate/up: column tiles of the narrow width behind the wide ones
+    int64_t cost = 0;                    // rounds x columns of 256 x 256 tiles (128 for gate/up), in 1e-6
+    if (!GU) {
+        // (beside a chip-filling gate/up kernel: full-size tiles, however few)
+        for (int w : {256, 224, 192, 160, 128}) {
+            static const int per_mille[5] = {1000, 1020, 1070, 1170, 1310};     // what the narrower tile costs per column (measured)
+            const int64_t c = rounds_pm(tiles_of(w)) * w * per_mille[(256 - w) / 32];
+            if (cost == 0 || (c < cost && !never_small)) { cost = c; width = w; }
+        }
     } else {
-        // Rounds of the CUs a launch of `tiles` tiles takes, in 1/1000.  A last round that fills only part of the
-        // CUs is not as dear as a whole one: the chip is power-limited and clocks the busy CUs higher (measured:
-        // a round on a quarter / half / three quarters of the CUs takes about 0.55 / 0.8 / 0.8-0.9 of a full one).
-        auto rounds_pm = [&](int64_t tiles) {
-            const int64_t full = tiles / cus, rem = tiles % cus;
-            return full * 1000 + (rem ? 500 + 500 * rem / cus : 0);
+        // b column tiles of 96 behind a of 128: a = ceil((N - 96 b) / 128); time = rounds x columns per tile
+        const int64_t tm = (M + 255) / 256;
+        auto mix_cost = [&](int64_t b) {
+            const int64_t rest = (int64_t)N - 96 * b;
+            const int64_t wide = rest > 0 ? (rest + 127) / 128 : 0;
+            return rounds_pm(tm * wide) * 128 * 1000 + rounds_pm(tm * b) * 96 * kGateUpNarrowPerMille;
         };
-        // time in units of 1e-6 of a 256 x 256 tile per column: rounds x width x (1 + what the narrower tile costs per column)
-        auto down_cost = [&](int w) {
-            static const int per_mille[5] = {1000, 1020, 1070, 1170, 1310};     // 256, 224, 192, 160, 128 (measured)
-            return rounds_pm(tiles_of(256, w)) * w * per_mille[(256 - w) / 32];
-        };
-        int64_t best = 0;
-        if (EPI == momk::EPI_DOWN && !never_small)       // (beside a chip-filling gate/up kernel: full-size tiles, however few)
-            for (int w : {256, 224, 192, 160, 128}) {
-                const int64_t cost = down_cost(w);
-                if (best == 0 || cost < best) { best = cost; width = w; }
-            }
-        const int64_t t256 = tiles_of(256, width / gu);
-        if (!never_small && t256 * 4 <= (int64_t)cus * 3) {     // even so a quarter or more of the CUs without work
-            edge = (tiles_of(128, 128 / gu) * 2 <= cus) ? 64 : 128;
-            width = edge;
-        } else if (EPI == momk::EPI_GATEUP) {
-            // b column tiles of 96 behind a of 128: a = ceil((N - 96 b) / 128); time = rounds x columns per tile
-            const int64_t tm = (M + 255) / 256;
-            auto cost = [&](int64_t b) {
-                const int64_t rest = (int64_t)N - 96 * b;
-                const int64_t wide = rest > 0 ? (rest + 127) / 128 : 0;
-                return rounds_pm(tm * wide) * 128 * 1000 + rounds_pm(tm * b) * 96 * kGateUpNarrowPerMille;
-            };
-            const int64_t plain = cost(0);
-            int64_t best_cost = plain;
-            for (int64_t b = 1; b <= ((int64_t)N + 95) / 96; ++b) {
-                const int64_t c = cost(b);
-                if (c < best_cost && c * 1000 <= plain * (1000 - kGateUpMixMinGainPerMille)) { best_cost = c; narrow_tiles_n = b; }
-            }
+        const int64_t plain = mix_cost(0);
+        cost = plain;
+        for (int64_t b = 1; b <= ((int64_t)N + 95) / 96; ++b) {
+            const int64_t c = mix_cost(b);
+            if (c < cost && c * 1000 <= plain * (1000 - kGateUpMixMinGainPerMille)) { cost = c; narrow_tiles_n = b; }
         }
     }
-    if (edge == 256) slots = 5;
-    else if (slots == 0) {
-        const int64_t t = tiles_of(edge, edge / gu);
-        slots = (edge == 128) ? (t <= cus ? 10 : 5) : (t <= cus ? 20 : (t <= 2 * (int64_t)cus ? 10 : 5));
+    if (!never_small) {
+        const int64_t tiles = GU ? tiles_of(128) : tiles_of(width);
+        const double full_cost = 1e-6 * cost / (GU ? 128 : 256) * momk::kFullTileRows * K +
+                                 (tiles + cus - 1) / cus * momk::kFullTileFixed;
+        double short_cost = 0;
+        const int form = momk::choose_short_form(M, N, K, GU, cus, short_cost);
+        if constexpr (GU) {
+            const double cost128 = momk::short_cost(M, N, K, true, {128, 128, 2}, cus);
+            if (cost128 >= 0 && cost128 < full_cost && cost128 < short_cost) return launch_gemm_form<EPI>(a, 128, 128, st);
+        }
+        if (form >= 0 && short_cost < full_cost) return launch_short_form<EPI>(a, form, st);
     }
-    if constexpr (EPI == momk::EPI_GATEUP) {
+    if constexpr (GU) {
         if (narrow_tiles_n > 0) {
             const int64_t rest = (int64_t)N - 96 * narrow_tiles_n;
             const int wide_cols = rest > 0 ? (int)((rest + 127) / 128) * 128 : 0;     // columns [0, wide_cols) in wide tiles
-            if (wide_cols >= N) return launch_gemm_form<EPI>(a, 256, 5, 256, st);
+            if (wide_cols >= N) return launch_gemm_form<EPI>(a, 256, 256, st);
             momk::GemmArgs2 p;
             p.narrow = a;
             p.narrow.W0 = W0 + (size_t)wide_cols * K;
             p.narrow.W1 = W1 + (size_t)wide_cols * K;
             p.narrow.O = O + wide_cols;
             p.narrow.N = N - wide_cols;
-            if (wide_cols == 0) return launch_gemm_form<EPI>(p.narrow, 256, 5, 192, st);
+            if (wide_cols == 0) return launch_gemm_form<EPI>(p.narrow, 256, 192, st);
             p.wide = a;
             p.wide.N = wide_cols;
             if (!set_tile_grid<EPI>(p.wide, 256, 256) || !set_tile_grid<EPI>(p.narrow, 256, 192)) return hipErrorInvalidValue;
@@ -268,7 +282,7 @@ hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const 
             return hipGetLastError();
         }
     }
-    return launch_gemm_form<EPI>(a, edge, slots, width, st);
+    return launch_gemm_form<EPI>(a, 256, width, st);
 }
 
 template <int MODE>
@@ -402,8 +416,16 @@ int mom_debug_force_gemm_form(int tile_edge, int ring_slots, int tile_width) {
                     (tile_edge == 64 && (ring_slots == 0 || ring_slots == 5 || ring_slots == 10 || ring_slots == 20)));
     if (!ok) return MOM_ERR_SHAPE;
     g_force_width.store(tile_width, std::memory_order_relaxed);
-    g_force_slots.store(ring_slots, std::memory_order_relaxed);
     g_force_edge.store(tile_edge, std::memory_order_relaxed);
+    return MOM_OK;
+}
+
+int mom_debug_force_short_form(int token_rows, int weight_rows) {
+    const bool off = token_rows == 0 && weight_rows == 0;
+    if (!off && momk::find_short_form(false, token_rows, weight_rows) < 0 &&
+        momk::find_short_form(true, token_rows, weight_rows) < 0)
+        return MOM_ERR_SHAPE;
+    g_force_short.store(off ? 0 : (token_rows << 16 | weight_rows), std::memory_order_relaxed);
     return MOM_OK;
 }
 

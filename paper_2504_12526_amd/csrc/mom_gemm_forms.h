@@ -1,0 +1,90 @@
+// Tile forms of the GEMM launches with few token rows, and the rule that picks one.  Plain C++17, no HIP
+// types, so that a host program can walk the rule (tests/gemm_forms_check.cpp).
+//
+// X(TM, TN, WM, WN, KSUB, NSTG): TM token rows x TN staged weight rows per workgroup, WM x WN wavefronts
+// that multiply, stages of 64 KSUB K-elements, NSTG of them in the LDS ring (mom_gemm_short.hip.inc).
+// The smallest tiles take the longest stages (one barrier per stage) and every form a ring that holds
+// more than the 32 KiB a CU's vector cache has in flight at most (measured: 256 lines of 128 bytes).
+#ifndef MOM_GEMM_FORMS_H
+#define MOM_GEMM_FORMS_H
+
+#include <stdint.h>
+
+#define MOM_SHORT_FORMS_DOWN(X)                                                                          \
+    X(16, 16, 1, 1, 2, 8) X(32, 16, 2, 1, 4, 6) X(32, 32, 2, 2, 2, 5) X(48, 32, 1, 2, 2, 8)              \
+    X(64, 32, 2, 2, 2, 6) X(96, 32, 2, 2, 2, 5) X(128, 32, 4, 1, 1, 8) X(32, 64, 2, 2, 1, 6)             \
+    X(64, 64, 2, 2, 1, 5) X(80, 64, 1, 4, 2, 4) X(96, 64, 2, 2, 1, 8) X(128, 64, 2, 2, 1, 6)             \
+    X(160, 64, 2, 2, 1, 5) X(192, 64, 2, 2, 1, 5) X(256, 64, 2, 2, 1, 4) X(96, 128, 2, 2, 1, 5)          \
+    X(128, 128, 2, 2, 1, 5) X(160, 128, 2, 2, 1, 4) X(192, 128, 2, 2, 1, 4) X(224, 128, 2, 2, 1, 3)
+#define MOM_SHORT_FORMS_GATEUP(X)                                                                        \
+    X(16, 32, 1, 1, 4, 6) X(32, 32, 2, 1, 2, 8) X(16, 64, 1, 2, 2, 8) X(32, 64, 2, 2, 2, 6)              \
+    X(64, 64, 2, 2, 1, 3) X(128, 64, 2, 2, 1, 3) X(64, 128, 2, 2, 1, 6) X(96, 128, 2, 2, 1, 5)           \
+    X(128, 128, 2, 2, 1, 5) X(160, 128, 2, 2, 1, 4) X(192, 128, 2, 2, 1, 4) X(224, 128, 2, 2, 1, 3)      \
+    X(64, 192, 2, 2, 1, 5) X(96, 192, 2, 2, 1, 4) X(128, 192, 2, 2, 1, 4)
+
+namespace momk {
+
+struct ShortShape { int tm, tn, per_cu; };       // per_cu: workgroups that a CU's 160 KiB of LDS hold
+#define MOM_SHAPE(TM, TN, WM, WN, KSUB, NSTG) \
+    {TM, TN, 163840 / (NSTG * KSUB * (TM + TN) * 128) > 4 ? 4 : 163840 / (NSTG * KSUB * (TM + TN) * 128)},
+constexpr ShortShape kShortDown[] = {MOM_SHORT_FORMS_DOWN(MOM_SHAPE)};
+constexpr ShortShape kShortGateUp[] = {MOM_SHORT_FORMS_GATEUP(MOM_SHAPE)};
+#undef MOM_SHAPE
+constexpr int kShortDownForms = sizeof(kShortDown) / sizeof(kShortDown[0]);
+constexpr int kShortGateUpForms = sizeof(kShortGateUp) / sizeof(kShortGateUp[0]);
+
+inline int short_forms(bool gateup) { return gateup ? kShortGateUpForms : kShortDownForms; }
+inline ShortShape short_shape(bool gateup, int form) { return gateup ? kShortGateUp[form] : kShortDown[form]; }
+
+// Index of the form with these tiles, or -1.
+inline int find_short_form(bool gateup, int tm, int tn) {
+    for (int i = 0; i < short_forms(gateup); ++i)
+        if (short_shape(gateup, i).tm == tm && short_shape(gateup, i).tn == tn) return i;
+    return -1;
+}
+
+// Costs are in operand rows x K-elements that one CU moves into its LDS: with few token rows that is what a
+// launch takes time for.  A CU's vector cache has 256 lines in flight at most, and at the latency of
+// weights that come from HBM that is 55 GB/s, whatever the ring holds and however little is multiplied
+// (measured over all forms on 1 ... 2048 rows at K = 14336 and 18944: 0.5 us per operand row at K = 14336,
+// i.e. 3.5e-5 us per unit, with a tenth of the spread that the flops per CU have).
+// Once per tile: launch, ring prologue, epilogue, 4 us and a little per output element (silu for gate/up);
+// the workgroups that share a CU overlap these.  A 256-row tile 256 weight rows wide, which the matrix
+// cores bound, takes as long as 550 operand rows and 9.6 us once.
+constexpr double kTileFixed = 115e3, kTileFixedPerGateUp = 5, kTileFixedPerDown = 2;
+constexpr double kFullTileRows = 550, kFullTileFixed = 275e3;
+// From this contraction length on, what a launch waits for is its operands, not the start and end of tiles.
+constexpr int64_t kLongK = 3072;
+constexpr int64_t kMaxTiles = 0x1fffffff;            // tile numbers are 32-bit in the kernels
+
+// Cost of a launch of M token rows x N output columns, contraction length K, in tiles of form f; < 0: too many tiles.
+inline double short_cost(int64_t M, int64_t N, int64_t K, bool gateup, ShortShape f, int cus) {
+    const int64_t cols = gateup ? f.tn / 2 : f.tn;
+    const int64_t tiles_m = (M + f.tm - 1) / f.tm, tiles = tiles_m * ((N + cols - 1) / cols);
+    if (tiles > kMaxTiles) return -1;
+    const int64_t full = tiles / cus, rem = tiles % cus, rounds = full + (rem ? 1 : 0);
+    // a last round on few CUs moves its operands a little faster (3584 / 16 = 224 of 256 CUs: 0.94)
+    const double moved = (K < kLongK || !rem) ? (double)rounds : full + 0.75 + 0.25 * rem / cus;
+    // Operand rows of a tile, averaged over the token tiles.  A clearly shorter last token tile makes a launch
+    // of one round faster than its rows say: its CUs run ahead of the others and bring the weights into the
+    // L2 for them (512 rows in tiles of 160, 160, 160, 32 x 64: 83 us, in four of 128 x 64: 94 us).
+    double rows = (double)M / tiles_m + f.tn;
+    const int64_t last = M - (tiles_m - 1) * f.tm;
+    if (K >= kLongK && rounds == 1 && tiles_m > 1 && 10 * last <= 7 * f.tm) rows *= tiles_m <= 4 ? 0.87 : 0.93;
+    const double fixed = kTileFixed + f.tm * cols * (gateup ? kTileFixedPerGateUp : kTileFixedPerDown);
+    return moved * rows * K + (rounds + f.per_cu - 1) / f.per_cu * fixed;
+}
+
+// The form with the least cost; its cost in `cost`; -1: none.
+inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, int cus, double& cost) {
+    int best = -1;
+    for (int i = 0; i < short_forms(gateup); ++i) {
+        const double c = short_cost(M, N, K, gateup, short_shape(gateup, i), cus);
+        if (c >= 0 && (best < 0 || c < cost)) { best = i; cost = c; }
+    }
+    return best;
+}
+
+}  // namespace momk
+
+#endif  // MOM_GEMM_FORMS_H

@@ -1,6 +1,6 @@
 // The chained stage schedule of the 256-row GEMM tiles, as data.
 //
-// The kernel (gemm4_tile in mom_gemm.hip.inc, stage_c) asks these functions what to do behind each
+// The kernel (gemm4_tile in mom_gemm.hip.inc) asks these functions what to do behind each
 // MFMA; a host program (tests/stage_schedule_check.cpp, run by the CPU tests) walks the same
 // functions over many stages and checks what no compiler checks: every index in range, every
 // fragment read behind a barrier that covers the loads of its data, every ring slot overwritten only

@@ -1,0 +1,72 @@
+// Host check of the short GEMM forms and of the rule that picks one (csrc/mom_gemm_forms.h): what a form assumes
+// about its sizes, and that every launch size gets a form that the kernels can run.
+#include <cstdio>
+#include <cmath>
+#include <initializer_list>
+#include "mom_gemm_forms.h"
+
+static int bad = 0;
+#define CHECK(c, ...) do { if (!(c)) { printf("FAILED %s: ", #c); printf(__VA_ARGS__); printf("\n"); ++bad; } } while (0)
+
+static void form(bool gu, int tm, int tn, int wm, int wn, int ksub, int nstg) {
+    const int stage = ksub * (tm + tn) * 128, loads = ksub * (tm + tn) / 32;
+    const int cols = gu ? tn / 2 : tn;
+    CHECK(nstg * stage <= 163840 && stage <= 65536 && nstg >= 2, "ring of %d x %d", tm, tn);
+    CHECK((nstg - 2) * loads <= 63, "loads in flight of %d x %d", tm, tn);
+    CHECK(wm * wn <= 4 && tm % (16 * wm) == 0 && tn % (16 * wn) == 0, "wavefront grid of %d x %d", tm, tn);
+    CHECK(!gu || (tn / 16 / wn) % 2 == 0, "gate and up blocks of %d x %d", tm, tn);
+    CHECK((ksub * tm) % 32 == 0 && (ksub * tn) % (gu ? 64 : 32) == 0, "loads per wavefront of %d x %d", tm, tn);
+    CHECK(tm * (cols * 2 + 16) <= nstg * stage, "epilogue of %d x %d", tm, tn);
+    const int f = momk::find_short_form(gu, tm, tn);
+    CHECK(f >= 0 && momk::short_shape(gu, f).per_cu >= 1 && momk::short_shape(gu, f).per_cu * nstg * stage <= 163840,
+          "workgroups per CU of %d x %d", tm, tn);
+    // Every 1-KiB block of a stage is loaded once, to a place of its own: the kernel's mapping of wavefront and
+    // load index to sub-tile and row
+    bool seen[2][16][64] = {};                        // [operand][sub][row / 8]
+    for (int wave = 0; wave < 4; ++wave)
+        for (int j = 0; j < loads; ++j) {
+            const int lt = ksub * tm / 32;
+            int op, sub, row;
+            if (j < lt) {
+                const int b = wave + 4 * j;
+                op = 0; sub = b / (tm / 8); row = (b % (tm / 8)) * 8;
+            } else {
+                const int hr = gu ? tn / 2 : tn, w = wave + 4 * (j - lt);
+                const int half = w / (ksub * hr / 8), b = w % (ksub * hr / 8);
+                op = 1; sub = b / (hr / 8); row = half * hr + (b % (hr / 8)) * 8;
+                // the weight matrix is picked by the load index alone
+                CHECK(!gu || half == (j - lt >= (loads - lt) / 2), "weight matrix of a load of %d x %d", tm, tn);
+            }
+            CHECK(sub < ksub && row + 8 <= (op ? tn : tm), "block of %d x %d", tm, tn);
+            CHECK(!seen[op][sub][row / 8], "block loaded twice in %d x %d", tm, tn);
+            seen[op][sub][row / 8] = true;
+        }
+}
+
+int main() {
+#define D(TM, TN, WM, WN, KSUB, NSTG) form(false, TM, TN, WM, WN, KSUB, NSTG);
+#define G(TM, TN, WM, WN, KSUB, NSTG) form(true, TM, TN, WM, WN, KSUB, NSTG);
+    MOM_SHORT_FORMS_DOWN(D)
+    MOM_SHORT_FORMS_GATEUP(G)
+    const int64_t Ms[] = {1, 15, 16, 17, 61, 128, 317, 1000, 4096, 131071, 1 << 20, 0x7fffff00};
+    const int64_t dims[] = {32, 96, 256, 1056, 3584, 4096, 14336, 18944, 1 << 20};
+    int n = 0;
+    for (int64_t M : Ms)
+        for (int64_t N : dims)
+            for (int64_t K : dims)
+                for (bool gu : {false, true})
+                    for (int cus : {1, 80, 256, 304}) {
+                        double cost = -1;
+                        const int f = momk::choose_short_form(M, N, K, gu, cus, cost);
+                        ++n;
+                        if (f < 0) { CHECK(M > 1 << 20, "no form for M=%lld N=%lld", (long long)M, (long long)N); continue; }
+                        CHECK(f < momk::short_forms(gu) && std::isfinite(cost) && cost > 0, "choice");
+                        const momk::ShortShape s = momk::short_shape(gu, f);
+                        const int64_t cols = gu ? s.tn / 2 : s.tn;
+                        CHECK(((M + s.tm - 1) / s.tm) * ((N + cols - 1) / cols) <= momk::kMaxTiles, "tiles");
+                        CHECK(cost <= momk::short_cost(M, N, K, gu, momk::short_shape(gu, 0), cus) ||
+                              momk::short_cost(M, N, K, gu, momk::short_shape(gu, 0), cus) < 0, "least cost");
+                    }
+    printf("%d forms, %d choices: %s\n", momk::short_forms(0) + momk::short_forms(1), n, bad ? "FAILED" : "ok");
+    return bad != 0;
+}

@@ -1,0 +1,82 @@
+"""The GEMM forms for few token rows on the GPU: every form against the 256-row tiles bit for bit at the edges of its
+tiles and with every length of the final, shorter stage; the library's own choice at production contraction lengths."""
+import os
+import re
+
+import pytest
+import torch
+
+import oracle
+from paper_2504_12526_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+_TEXT = open(os.path.join(ROOT, "paper_2504_12526_amd", "csrc", "mom_gemm_forms.h")).read()
+FORMS = sorted({tuple(int(v) for v in f.split(",")[:2]) for f in re.findall(r"X\(([\d, ]+)\)", _TEXT)})
+
+
+@pytest.fixture
+def short_form():
+    yield binding.mom_debug_force_short_form
+    binding.mom_debug_force_short_form(0, 0)
+    binding.mom_debug_force_gemm_form(0, 0, 0)
+
+
+def _inputs(S, H, I, seed, std):
+    wl = synth.Workload("short", S=S, H=H, I=I, mini_seq=0, seed=seed, w_std=std)
+    return synth.mlp_inputs(wl, device="cuda")
+
+
+def _run(x, wg, wu, wd):
+    """out and the intermediate, both poisoned before."""
+    S, I = x.shape[0], wg.shape[0]
+    out = torch.full_like(x, float("nan"))
+    ws = torch.full((S * I,), float("nan"), dtype=torch.bfloat16, device=x.device)
+    binding.mom_mlp_prefill(x, wg, wu, wd, 0, out, ws)
+    return out.view(torch.int16), ws.view(torch.int16)
+
+
+def _full_tiles(*t):
+    binding.mom_debug_force_short_form(0, 0)
+    binding.mom_debug_force_gemm_form(256, 5, 256)
+    r = _run(*t)
+    binding.mom_debug_force_gemm_form(0, 0, 0)
+    return r
+
+
+@pytest.mark.parametrize("tm,tn", FORMS)
+def test_form_gives_the_bits_of_the_full_tiles(tm, tn, short_form):
+    # rows around one and two token tiles; K = 32 (nothing but a final stage) ... several turns of the ring, with
+    # final stages of 32 ... 224 elements; columns that end inside a tile
+    for S, H, I in ((1, 64, 32), (tm - 1 or 1, 32, 96), (tm, 160, 224), (tm + 1, 288, 352), (2 * tm + 5, 1056, 480),
+                    (2 * tm - 3, 736, 2080)):
+        t = _inputs(S, H, I, S + H, 0.05)
+        ref = _full_tiles(*t)
+        short_form(tm, tn)
+        got = _run(*t)
+        torch.cuda.synchronize()
+        assert torch.equal(got[1], ref[1]), f"intermediate S={S} H={H} I={I}"
+        assert torch.equal(got[0], ref[0]), f"out S={S} H={H} I={I}"
+
+
+@pytest.mark.parametrize("name", ["llama3_8b_32k", "qwen25_7b_256k"])
+def test_few_token_rows_at_production_contraction_lengths(name, short_form):
+    wl = synth.WORKLOADS[name]
+    x, wg, wu, wd = synth.mlp_inputs(wl, device="cuda", S=2048)
+    for S in (1, 16, 17, 40, 61, 80, 128, 150, 192, 224, 256, 317, 512, 900, 1000, 1536, 1800, 2048):
+        t = (x[:S].contiguous(), wg, wu, wd)
+        ref = _full_tiles(*t)
+        got = _run(*t)
+        torch.cuda.synchronize()
+        assert torch.equal(got[1], ref[1]) and torch.equal(got[0], ref[0]), f"S={S}"
+        if S == 40:
+            r = oracle.mlp_rows(*(synth.bits(a) for a in t))
+            g = got[0].view(torch.bfloat16).float().cpu().numpy()
+            assert abs(g - r).max() <= 2e-2 * abs(r).max()      # the bar of the parity tests
+
+
+def test_forced_short_form_validation(short_form):
+    L = binding.lib()
+    for f in ((48, 16), (0, 64), (-16, 16), (256, 256)):
+        assert L.mom_debug_force_short_form(*f) == binding.MOM_ERR_SHAPE
