@@ -145,7 +145,14 @@ template <int EPI>
 hipError_t launch_gemm_form(momk::GemmArgs a, int edge, int width, hipStream_t st) {
     if (!set_tile_grid<EPI>(a, edge, width)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(a.tiles_per_xcd * 8)), block(momk::k4Threads);
-#define MOM_LAUNCH4(E, W) hipLaunchKernelGGL((momk::gemm4_kernel<EPI, E, W>), grid, block, 0, st, a)
+    const bool nt = EPI == momk::EPI_GATEUP && momk::weights_once(a.tiles_m, a.N, a.K);
+#define MOM_LAUNCH4(E, W)                                                                                         \
+    do {                                                                                                          \
+        if constexpr (EPI == momk::EPI_GATEUP && E == 256) {                                                      \
+            if (nt) { hipLaunchKernelGGL((momk::gemm4_kernel<EPI, E, W, true>), grid, block, 0, st, a); break; }  \
+        }                                                                                                         \
+        hipLaunchKernelGGL((momk::gemm4_kernel<EPI, E, W, false>), grid, block, 0, st, a);                        \
+    } while (0)
     if (edge == 256 && width == 256) MOM_LAUNCH4(256, 256);
     else if (edge == 256 && width == 192) MOM_LAUNCH4(256, 192);
     else if constexpr (EPI == momk::EPI_DOWN) {
@@ -167,10 +174,16 @@ hipError_t launch_short_form(momk::GemmArgs a, int form, hipStream_t st) {
     const momk::ShortShape f = momk::short_shape(EPI == momk::EPI_GATEUP, form);
     if (!set_tile_grid<EPI>(a, f.tm, f.tn)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(a.tiles_per_xcd * 8)), block(momk::k4Threads);
+    const bool nt = EPI == momk::EPI_GATEUP && momk::weights_once(a.tiles_m, a.N, a.K);
     int i = 0;
 #define MOM_LAUNCH_SHORT(TM, TN, WM, WN, KSUB, NSTG)                                                              \
-    if (i++ == form)                                                                                              \
-        hipLaunchKernelGGL((momk::gemm_short_kernel<EPI, TM, TN, WM, WN, KSUB, NSTG>), grid, block, 0, st, a);
+    if (i++ == form) {                                                                                            \
+        if (EPI == momk::EPI_GATEUP && nt)                                                                        \
+            hipLaunchKernelGGL((momk::gemm_short_kernel<EPI, TM, TN, WM, WN, KSUB, NSTG, EPI == momk::EPI_GATEUP>),  \
+                               grid, block, 0, st, a);                                                            \
+        else                                                                                                      \
+            hipLaunchKernelGGL((momk::gemm_short_kernel<EPI, TM, TN, WM, WN, KSUB, NSTG, false>), grid, block, 0, st, a);  \
+    }
     if constexpr (EPI == momk::EPI_GATEUP) { MOM_SHORT_FORMS_GATEUP(MOM_LAUNCH_SHORT) }
     else { MOM_SHORT_FORMS_DOWN(MOM_LAUNCH_SHORT) }
 #undef MOM_LAUNCH_SHORT
@@ -278,7 +291,10 @@ hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const 
             if (!set_tile_grid<EPI>(p.wide, 256, 256) || !set_tile_grid<EPI>(p.narrow, 256, 192)) return hipErrorInvalidValue;
             const int64_t wgs = 8 * ((int64_t)p.wide.tiles_per_xcd + p.narrow.tiles_per_xcd);
             if (wgs > (int64_t)0x7fffffff) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
+            if (momk::weights_once(p.wide.tiles_m, N, K))
+                hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192, true>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
+            else
+                hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192, false>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
             return hipGetLastError();
         }
     }

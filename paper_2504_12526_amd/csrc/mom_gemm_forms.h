@@ -75,6 +75,19 @@ inline double short_cost(int64_t M, int64_t N, int64_t K, bool gateup, ShortShap
     return moved * rows * K + (rounds + f.per_cu - 1) / f.per_cu * fixed;
 }
 
+// Whether a gate/up launch reads its weights by non-temporal loads: where one group of token tiles covers
+// all rows, so that the fabric is asked for every weight line once, and the weights of the layer (half as
+// much again for the down projection) are more than the Infinity Cache holds.  Then W_down stays there from
+// mini-sequence to mini-sequence instead of being displaced each time, and the stream itself is faster.
+// Measured, gate/up and down: 16 rows 43.2 -> 41.8 us and 27.3 (first use, as before), Qwen-shaped 61 rows 54.7 ->
+// 51.5, mini-sequences of 512 rows 91.2 + 83.4 -> 87.3 + 79.8, of 1024 rows 162.4 + 122.6 -> 161.0 + 114.1.  With
+// four groups (4096 rows) the other groups miss what the first had brought: 615 -> 635 us, so not there.
+// The down projection itself loses with it wherever tiles share a weight line: 61 rows 39 -> 51 us.
+constexpr int kTokenGroup = 4;                       // token tiles of a group
+inline bool weights_once(int64_t tiles_m, int64_t N, int64_t K) {
+    return tiles_m <= kTokenGroup && 6 * N * K > ((int64_t)256 << 20);
+}
+
 // The form with the least cost; its cost in `cost`; -1: none.
 inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, int cus, double& cost) {
     int best = -1;
