@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -132,6 +133,7 @@ template <int EPI>
 bool set_tile_grid(momk::GemmArgs& a, int edge, int width) {
     const int tile_n = (EPI == momk::EPI_GATEUP) ? width / 2 : width;
     a.group_m = momk::kGroupM;
+    a.group_rows = edge * a.group_m;
     a.tiles_m = (a.M + edge - 1) / edge;
     a.tiles_n = (a.N + tile_n - 1) / tile_n;
     const int64_t t = (int64_t)a.tiles_m * a.tiles_n;
@@ -140,12 +142,13 @@ bool set_tile_grid(momk::GemmArgs& a, int edge, int width) {
     return true;
 }
 
-// One launch of gemm4_kernel<EPI, edge, width> over the operands in `a` (M, N, K, ldo set).
+// One launch of gemm4_kernel<EPI, edge, width> over the operands in `a` (M, N, K, ldo set).  more: the call has more
+// than one mini-sequence.
 template <int EPI>
-hipError_t launch_gemm_form(momk::GemmArgs a, int edge, int width, hipStream_t st) {
+hipError_t launch_gemm_form(momk::GemmArgs a, int edge, int width, bool more, hipStream_t st) {
     if (!set_tile_grid<EPI>(a, edge, width)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(a.tiles_per_xcd * 8)), block(momk::k4Threads);
-    const bool nt = EPI == momk::EPI_GATEUP && momk::weights_once(a.tiles_m, a.N, a.K);
+    const bool nt = EPI == momk::EPI_GATEUP && momk::weights_once(a.tiles_m, a.N, a.K, more);
 #define MOM_LAUNCH4(E, W)                                                                                         \
     do {                                                                                                          \
         if constexpr (EPI == momk::EPI_GATEUP && E == 256) {                                                      \
@@ -170,11 +173,19 @@ hipError_t launch_gemm_form(momk::GemmArgs a, int edge, int width, hipStream_t s
 
 // One launch in the short form `form` (mom_gemm_forms.h).
 template <int EPI>
-hipError_t launch_short_form(momk::GemmArgs a, int form, hipStream_t st) {
+hipError_t launch_short_form(momk::GemmArgs a, int form, bool more, hipStream_t st) {
     const momk::ShortShape f = momk::short_shape(EPI == momk::EPI_GATEUP, form);
-    if (!set_tile_grid<EPI>(a, f.tm, f.tn)) return hipErrorInvalidValue;
+    const momk::TokenTiles tt = momk::token_tiles(a.M, f.tm);
+    const int cols = (EPI == momk::EPI_GATEUP) ? f.tn / 2 : f.tn;
+    const int64_t tiles_n = (a.N + cols - 1) / cols, t = tt.tiles * tiles_n;
+    if (t <= 0 || t > momk::kMaxTiles) return hipErrorInvalidValue;
+    a.tiles_m = (int)tt.tiles;
+    a.tiles_n = (int)tiles_n;
+    a.group_m = (int)tt.per_group;
+    a.group_rows = (int)tt.group_rows;
+    a.tiles_per_xcd = (int)((t + 7) / 8);
     const dim3 grid((unsigned)(a.tiles_per_xcd * 8)), block(momk::k4Threads);
-    const bool nt = EPI == momk::EPI_GATEUP && momk::weights_once(a.tiles_m, a.N, a.K);
+    const bool nt = EPI == momk::EPI_GATEUP && momk::weights_once(a.tiles_m, a.N, a.K, more);
     int i = 0;
 #define MOM_LAUNCH_SHORT(TM, TN, WM, WN, KSUB, NSTG)                                                              \
     if (i++ == form) {                                                                                            \
@@ -192,7 +203,7 @@ hipError_t launch_short_form(momk::GemmArgs a, int form, hipStream_t st) {
 
 template <int EPI>
 hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const unsigned short* W1,
-                       unsigned short* O, int M, int N, int K, hipStream_t st, bool never_small = false) {
+                       unsigned short* O, int M, int N, int K, hipStream_t st, bool more, bool never_small = false) {
     constexpr bool GU = EPI == momk::EPI_GATEUP;
     momk::GemmArgs a;
     a.X = X; a.W0 = W0; a.W1 = W1; a.O = O;
@@ -220,15 +231,15 @@ hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const 
     const int fs = g_force_short.load(std::memory_order_relaxed);
     if (fs) {
         const int form = momk::find_short_form(GU, fs >> 16, fs & 0xffff);
-        if (form >= 0) return launch_short_form<EPI>(a, form, st);
+        if (form >= 0) return launch_short_form<EPI>(a, form,more, st);
     }
     const int force = g_force_edge.load(std::memory_order_relaxed);
     if (force == 256) {
         const int fw = g_force_width.load(std::memory_order_relaxed);
-        return launch_gemm_form<EPI>(a, 256, (fw && (!GU || fw == 192)) ? fw : 256, st);
+        return launch_gemm_form<EPI>(a, 256, (fw && (!GU || fw == 192)) ? fw : 256,more, st);
     }
-    if (force == 128 && GU) return launch_gemm_form<EPI>(a, 128, 128, st);
-    if (force) return launch_short_form<EPI>(a, momk::find_short_form(GU, force, force), st);
+    if (force == 128 && GU) return launch_gemm_form<EPI>(a, 128, 128,more, st);
+    if (force) return launch_short_form<EPI>(a, momk::find_short_form(GU, force, force),more, st);
 
     // Rounds of the CUs a launch of `tiles` 256-row tiles takes, in 1/1000.  A last round that fills only part of the
     // CUs is not as dear as a whole one: the chip is power-limited and clocks the busy CUs higher (measured:
@@ -264,41 +275,43 @@ hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const 
     }
     if (!never_small) {
         const int64_t tiles = GU ? tiles_of(128) : tiles_of(width);
-        const double full_cost = 1e-6 * cost / (GU ? 128 : 256) * momk::kFullTileRows * K +
-                                 (tiles + cus - 1) / cus * momk::kFullTileFixed;
+        double full_cost = 1e-6 * cost / (GU ? 128 : 256) * momk::kFullTileRows * K +
+                           (tiles + cus - 1) / cus * momk::kFullTileFixed;
+        // a narrow tile is bound by its operands, too (1536 rows x 3584 columns: 233 us in tiles 128 wide)
+        if (!GU) full_cost = std::max(full_cost, momk::short_cost(M, N, K, false, {256, width, 1}, cus));
         double short_cost = 0;
         const int form = momk::choose_short_form(M, N, K, GU, cus, short_cost);
         if constexpr (GU) {
             const double cost128 = momk::short_cost(M, N, K, true, {128, 128, 2}, cus);
-            if (cost128 >= 0 && cost128 < full_cost && cost128 < short_cost) return launch_gemm_form<EPI>(a, 128, 128, st);
+            if (cost128 >= 0 && cost128 < full_cost && cost128 < short_cost) return launch_gemm_form<EPI>(a, 128, 128,more, st);
         }
-        if (form >= 0 && short_cost < full_cost) return launch_short_form<EPI>(a, form, st);
+        if (form >= 0 && short_cost < full_cost) return launch_short_form<EPI>(a, form,more, st);
     }
     if constexpr (GU) {
         if (narrow_tiles_n > 0) {
             const int64_t rest = (int64_t)N - 96 * narrow_tiles_n;
             const int wide_cols = rest > 0 ? (int)((rest + 127) / 128) * 128 : 0;     // columns [0, wide_cols) in wide tiles
-            if (wide_cols >= N) return launch_gemm_form<EPI>(a, 256, 256, st);
+            if (wide_cols >= N) return launch_gemm_form<EPI>(a, 256, 256,more, st);
             momk::GemmArgs2 p;
             p.narrow = a;
             p.narrow.W0 = W0 + (size_t)wide_cols * K;
             p.narrow.W1 = W1 + (size_t)wide_cols * K;
             p.narrow.O = O + wide_cols;
             p.narrow.N = N - wide_cols;
-            if (wide_cols == 0) return launch_gemm_form<EPI>(p.narrow, 256, 192, st);
+            if (wide_cols == 0) return launch_gemm_form<EPI>(p.narrow, 256, 192,more, st);
             p.wide = a;
             p.wide.N = wide_cols;
             if (!set_tile_grid<EPI>(p.wide, 256, 256) || !set_tile_grid<EPI>(p.narrow, 256, 192)) return hipErrorInvalidValue;
             const int64_t wgs = 8 * ((int64_t)p.wide.tiles_per_xcd + p.narrow.tiles_per_xcd);
             if (wgs > (int64_t)0x7fffffff) return hipErrorInvalidValue;
-            if (momk::weights_once(p.wide.tiles_m, N, K))
+            if (momk::weights_once(p.wide.tiles_m, N, K, more))
                 hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192, true>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
             else
                 hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192, false>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
             return hipGetLastError();
         }
     }
-    return launch_gemm_form<EPI>(a, 256, width, st);
+    return launch_gemm_form<EPI>(a, 256, width,more, st);
 }
 
 template <int MODE>
@@ -341,12 +354,12 @@ int mlp_driver(const void* x, const void* wg, const void* wu, const void* wd, in
         const int rows = (int)((r0 + C <= S) ? C : (S - r0));
         if (launch_gemm<momk::EPI_GATEUP>(xs + r0 * H, static_cast<const unsigned short*>(wg),
                                           static_cast<const unsigned short*>(wu), w, rows, (int)I, (int)H,
-                                          st) != hipSuccess)
+                                          st, n > 1) != hipSuccess)
             return MOM_ERR_HIP;
         if (events && hipEventRecord(static_cast<hipEvent_t>(events[1 + 2 * c]), st) != hipSuccess)
             return MOM_ERR_HIP;
         if (launch_gemm<momk::EPI_DOWN>(w, static_cast<const unsigned short*>(wd), nullptr, os + r0 * H, rows,
-                                        (int)H, (int)I, st) != hipSuccess)
+                                        (int)H, (int)I, st, n > 1) != hipSuccess)
             return MOM_ERR_HIP;
         if (events && hipEventRecord(static_cast<hipEvent_t>(events[2 + 2 * c]), st) != hipSuccess)
             return MOM_ERR_HIP;
@@ -381,7 +394,7 @@ int mlp_pipelined(const void* x, const void* wg, const void* wu, const void* wd,
         if (c >= 1 && hipStreamWaitEvent(sa, ev[4], 0) != hipSuccess) return MOM_ERR_HIP;
         if (launch_gemm<momk::EPI_GATEUP>(xs + r0 * H, static_cast<const unsigned short*>(wg),
                                           static_cast<const unsigned short*>(wu), half[h], rows, (int)I, (int)H,
-                                          sa) != hipSuccess)
+                                          sa, true) != hipSuccess)
             return MOM_ERR_HIP;
         if (hipEventRecord(ev[h], sa) != hipSuccess || hipStreamWaitEvent(sb, ev[h], 0) != hipSuccess)
             return MOM_ERR_HIP;
@@ -390,7 +403,7 @@ int mlp_pipelined(const void* x, const void* wg, const void* wu, const void* wd,
         // down projection however few they are; the last one runs alone and follows the usual rule
         const bool beside_big = c + 1 < n;
         if (launch_gemm<momk::EPI_DOWN>(half[h], static_cast<const unsigned short*>(wd), nullptr, os + r0 * H, rows,
-                                        (int)H, (int)I, sb, beside_big) != hipSuccess)
+                                        (int)H, (int)I, sb, true, beside_big) != hipSuccess)
             return MOM_ERR_HIP;
         if (hipEventRecord(ev[2 + h], sb) != hipSuccess) return MOM_ERR_HIP;
     }

@@ -57,20 +57,39 @@ constexpr double kFullTileRows = 550, kFullTileFixed = 275e3;
 constexpr int64_t kLongK = 3072;
 constexpr int64_t kMaxTiles = 0x1fffffff;            // tile numbers are 32-bit in the kernels
 
+// Token tiles of a launch: groups of at most kTokenGroup tiles (their weights are fetched by one XCD at a time), the
+// rows spread evenly over the groups.
+constexpr int kTokenGroup = 4;
+struct TokenTiles { int64_t groups, group_rows, per_group, tiles; };
+inline TokenTiles token_tiles(int64_t M, int tm) {
+    TokenTiles t;
+    t.groups = (M + (int64_t)kTokenGroup * tm - 1) / ((int64_t)kTokenGroup * tm);
+    t.group_rows = (M + t.groups - 1) / t.groups;
+    t.groups = (M + t.group_rows - 1) / t.group_rows;
+    t.per_group = (t.group_rows + tm - 1) / tm;
+    t.tiles = (t.groups - 1) * t.per_group + (M - (t.groups - 1) * t.group_rows + tm - 1) / tm;
+    return t;
+}
+
 // Cost of a launch of M token rows x N output columns, contraction length K, in tiles of form f; < 0: too many tiles.
 inline double short_cost(int64_t M, int64_t N, int64_t K, bool gateup, ShortShape f, int cus) {
     const int64_t cols = gateup ? f.tn / 2 : f.tn;
-    const int64_t tiles_m = (M + f.tm - 1) / f.tm, tiles = tiles_m * ((N + cols - 1) / cols);
+    const TokenTiles t = token_tiles(M, f.tm);
+    const int64_t tiles = t.tiles * ((N + cols - 1) / cols);
     if (tiles > kMaxTiles) return -1;
     const int64_t full = tiles / cus, rem = tiles % cus, rounds = full + (rem ? 1 : 0);
     // a last round on few CUs moves its operands a little faster (3584 / 16 = 224 of 256 CUs: 0.94)
-    const double moved = (K < kLongK || !rem) ? (double)rounds : full + 0.75 + 0.25 * rem / cus;
-    // Operand rows of a tile, averaged over the token tiles.  A clearly shorter last token tile makes a launch
-    // of one round faster than its rows say: its CUs run ahead of the others and bring the weights into the
-    // L2 for them (512 rows in tiles of 160, 160, 160, 32 x 64: 83 us, in four of 128 x 64: 94 us).
-    double rows = (double)M / tiles_m + f.tn;
-    const int64_t last = M - (tiles_m - 1) * f.tm;
-    if (K >= kLongK && rounds == 1 && tiles_m > 1 && 10 * last <= 7 * f.tm) rows *= tiles_m <= 4 ? 0.87 : 0.93;
+    const double moved = (K < kLongK || !rem) ? (double)rounds : full + 0.85 + 0.15 * rem / cus;
+    // Operand rows of a tile, averaged over the token tiles.  Where the last token tile of each group is clearly
+    // shorter, a launch of one round is faster than its rows say: the CUs of that tile run ahead of the
+    // others and bring the weights into the L2 for them (512 rows in tiles of 160, 160, 160, 32 x 64:
+    // 83 us, in four of 128 x 64: 94 us; 1024 rows in two such groups x 128: 126 us, in eight of 128 x 128:
+    // 132 us, both over many passes; one pass at a time 116 and 134).  Larger tiles, which wait less for their operands, gain nothing (1280 rows in tiles of 192 x 128,
+    // the last of each group 64: 154 us, in eight of 160: 149 us).
+    double rows = (double)M / t.tiles + f.tn;
+    const int64_t last = t.group_rows - (t.per_group - 1) * f.tm;
+    if (K >= kLongK && rounds == 1 && t.per_group > 1 && f.tm * f.tn <= 160 * 128)
+        rows *= 10 * last <= 4 * f.tm ? (f.tm * f.tn > 96 * 128 ? 0.92 : 0.87) : 10 * last <= 7 * f.tm ? 0.94 : 1.0;
     const double fixed = kTileFixed + f.tm * cols * (gateup ? kTileFixedPerGateUp : kTileFixedPerDown);
     return moved * rows * K + (rounds + f.per_cu - 1) / f.per_cu * fixed;
 }
@@ -81,11 +100,11 @@ inline double short_cost(int64_t M, int64_t N, int64_t K, bool gateup, ShortShap
 // mini-sequence to mini-sequence instead of being displaced each time, and the stream itself is faster.
 // Measured, gate/up and down: 16 rows 43.2 -> 41.8 us and 27.3 (first use, as before), Qwen-shaped 61 rows 54.7 ->
 // 51.5, mini-sequences of 512 rows 91.2 + 83.4 -> 87.3 + 79.8, of 1024 rows 162.4 + 122.6 -> 161.0 + 114.1.  With
-// four groups (4096 rows) the other groups miss what the first had brought: 615 -> 635 us, so not there.
+// four groups (4096 rows) the other groups miss what the first had brought: 615 -> 635 us, so not there; and where
+// there is only one mini-sequence, only for at most two token tiles (1000 rows: 161.6 -> 163.9 us).
 // The down projection itself loses with it wherever tiles share a weight line: 61 rows 39 -> 51 us.
-constexpr int kTokenGroup = 4;                       // token tiles of a group
-inline bool weights_once(int64_t tiles_m, int64_t N, int64_t K) {
-    return tiles_m <= kTokenGroup && 6 * N * K > ((int64_t)256 << 20);
+inline bool weights_once(int64_t tiles_m, int64_t N, int64_t K, bool more_mini_sequences) {
+    return tiles_m <= (more_mini_sequences ? kTokenGroup : 2) && 6 * N * K > ((int64_t)256 << 20);
 }
 
 // The form with the least cost; its cost in `cost`; -1: none.

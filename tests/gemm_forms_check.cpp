@@ -43,7 +43,25 @@ static void form(bool gu, int tm, int tn, int wm, int wn, int ksub, int nstg) {
         }
 }
 
+// The kernel's walk over the token tiles of a launch covers every row once.
+static void rows(int64_t M, int tm) {
+    const momk::TokenTiles t = momk::token_tiles(M, tm);
+    CHECK(t.per_group <= momk::kTokenGroup, "groups of M=%lld tm=%d", (long long)M, tm);
+    int64_t next = 0;
+    for (int64_t i = 0; i < t.tiles; ++i) {
+        const int64_t grp = i / t.per_group, m0 = grp * t.group_rows + (i % t.per_group) * tm;
+        const int64_t in_group = t.group_rows - (i % t.per_group) * tm;
+        const int64_t end = m0 + (M - m0 < in_group ? M - m0 : in_group);
+        CHECK(m0 == next && m0 < end && m0 <= 0x7fffffff, "tile %lld of M=%lld tm=%d", (long long)i, (long long)M, tm);
+        next = m0 + tm < end ? m0 + tm : end;
+    }
+    CHECK(next == M, "rows of M=%lld tm=%d", (long long)M, tm);
+}
+
 int main() {
+    for (int tm = 16; tm <= 256; tm += 16)
+        for (int64_t M = 1; M < 5000; M += 1 + M / 97) rows(M, tm);
+    rows(0x7fffff00, 256);
 #define D(TM, TN, WM, WN, KSUB, NSTG) form(false, TM, TN, WM, WN, KSUB, NSTG);
 #define G(TM, TN, WM, WN, KSUB, NSTG) form(true, TM, TN, WM, WN, KSUB, NSTG);
     MOM_SHORT_FORMS_DOWN(D)
@@ -63,7 +81,7 @@ int main() {
                         CHECK(f < momk::short_forms(gu) && std::isfinite(cost) && cost > 0, "choice");
                         const momk::ShortShape s = momk::short_shape(gu, f);
                         const int64_t cols = gu ? s.tn / 2 : s.tn;
-                        CHECK(((M + s.tm - 1) / s.tm) * ((N + cols - 1) / cols) <= momk::kMaxTiles, "tiles");
+                        CHECK(momk::token_tiles(M, s.tm).tiles * ((N + cols - 1) / cols) <= momk::kMaxTiles, "tiles");
                         CHECK(cost <= momk::short_cost(M, N, K, gu, momk::short_shape(gu, 0), cus) ||
                               momk::short_cost(M, N, K, gu, momk::short_shape(gu, 0), cus) < 0, "least cost");
                     }
