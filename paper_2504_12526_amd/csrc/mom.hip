@@ -251,12 +251,23 @@ hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const 
     int width = 256;
     int64_t narrow_tiles_n = 0;          // gate/up: column tiles of the narrow width behind the wide ones
     int64_t cost = 0;                    // rounds x columns of 256 x 256 tiles (128 for gate/up), in 1e-6
+    double short_cost = 0;
+    const int form = never_small ? -1 : momk::choose_short_form(M, N, K, GU, cus, short_cost);
+    // the cost of 256-row tiles in the units of the short forms
+    auto full_cost = [&](int64_t c, int64_t tiles) {
+        return 1e-6 * c / (GU ? 128 : 256) * momk::kFullTileRows * K + (tiles + cus - 1) / cus * momk::kFullTileFixed;
+    };
     if (!GU) {
         // (beside a chip-filling gate/up kernel: full-size tiles, however few)
         for (int w : {256, 224, 192, 160, 128}) {
             static const int per_mille[5] = {1000, 1020, 1070, 1170, 1310};     // what the narrower tile costs per column (measured)
             const int64_t c = rounds_pm(tiles_of(w)) * w * per_mille[(256 - w) / 32];
             if (cost == 0 || (c < cost && !never_small)) { cost = c; width = w; }
+        }
+        if (form >= 0) {
+            // a narrow tile is bound by its operands, too (1536 rows x 3584 columns: 233 us in tiles 128 wide)
+            const double full = std::max(full_cost(cost, tiles_of(width)), momk::short_cost(M, N, K, false, {256, width, 1}, cus));
+            if (short_cost < full) return launch_short_form<EPI>(a, form, more, st);
         }
     } else {
         // b column tiles of 96 behind a of 128: a = ceil((N - 96 b) / 128); time = rounds x columns per tile
@@ -268,24 +279,19 @@ hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const 
         };
         const int64_t plain = mix_cost(0);
         cost = plain;
-        for (int64_t b = 1; b <= ((int64_t)N + 95) / 96; ++b) {
+        // (no mix takes less than half of what the plain tiles take: where the short form does, it is not looked for)
+        const bool few = form >= 0 && short_cost < 0.5 * full_cost(plain, 1);
+        for (int64_t b = 1; b <= ((int64_t)N + 95) / 96 && !few; ++b) {
             const int64_t c = mix_cost(b);
             if (c < cost && c * 1000 <= plain * (1000 - kGateUpMixMinGainPerMille)) { cost = c; narrow_tiles_n = b; }
         }
-    }
-    if (!never_small) {
-        const int64_t tiles = GU ? tiles_of(128) : tiles_of(width);
-        double full_cost = 1e-6 * cost / (GU ? 128 : 256) * momk::kFullTileRows * K +
-                           (tiles + cus - 1) / cus * momk::kFullTileFixed;
-        // a narrow tile is bound by its operands, too (1536 rows x 3584 columns: 233 us in tiles 128 wide)
-        if (!GU) full_cost = std::max(full_cost, momk::short_cost(M, N, K, false, {256, width, 1}, cus));
-        double short_cost = 0;
-        const int form = momk::choose_short_form(M, N, K, GU, cus, short_cost);
-        if constexpr (GU) {
+        if (form >= 0) {
+            const double full = full_cost(cost, tiles_of(128));
             const double cost128 = momk::short_cost(M, N, K, true, {128, 128, 2}, cus);
-            if (cost128 >= 0 && cost128 < full_cost && cost128 < short_cost) return launch_gemm_form<EPI>(a, 128, 128,more, st);
+            if constexpr (GU)
+                if (cost128 >= 0 && cost128 < full && cost128 < short_cost) return launch_gemm_form<EPI>(a, 128, 128, more, st);
+            if (short_cost < full) return launch_short_form<EPI>(a, form, more, st);
         }
-        if (form >= 0 && short_cost < full_cost) return launch_short_form<EPI>(a, form,more, st);
     }
     if constexpr (GU) {
         if (narrow_tiles_n > 0) {

@@ -60,26 +60,30 @@ constexpr int64_t kMaxTiles = 0x1fffffff;            // tile numbers are 32-bit 
 // Token tiles of a launch: groups of at most kTokenGroup tiles (their weights are fetched by one XCD at a time), the
 // rows spread evenly over the groups.
 constexpr int kTokenGroup = 4;
-struct TokenTiles { int64_t groups, group_rows, per_group, tiles; };
-inline TokenTiles token_tiles(int64_t M, int tm) {
-    TokenTiles t;
-    t.groups = (M + (int64_t)kTokenGroup * tm - 1) / ((int64_t)kTokenGroup * tm);
-    t.group_rows = (M + t.groups - 1) / t.groups;
-    t.groups = (M + t.group_rows - 1) / t.group_rows;
-    t.per_group = (t.group_rows + tm - 1) / tm;
+// (32-bit arithmetic: every launch walks all forms on the host, and M + 1024 < 2^32.)
+struct TokenTiles { uint32_t groups, group_rows, per_group, tiles; };
+inline TokenTiles token_tiles(int64_t rows, uint32_t tm) {
+    const uint32_t M = (uint32_t)rows, most = kTokenGroup * tm;
+    TokenTiles t = {1, M, (M + tm - 1) / tm, 0};
+    if (M > most) {
+        t.groups = (M + most - 1) / most;
+        t.group_rows = (M + t.groups - 1) / t.groups;
+        t.groups = (M + t.group_rows - 1) / t.group_rows;
+        t.per_group = (t.group_rows + tm - 1) / tm;
+    }
     t.tiles = (t.groups - 1) * t.per_group + (M - (t.groups - 1) * t.group_rows + tm - 1) / tm;
     return t;
 }
 
 // Cost of a launch of M token rows x N output columns, contraction length K, in tiles of form f; < 0: too many tiles.
 inline double short_cost(int64_t M, int64_t N, int64_t K, bool gateup, ShortShape f, int cus) {
-    const int64_t cols = gateup ? f.tn / 2 : f.tn;
+    const uint32_t cols = gateup ? f.tn / 2 : f.tn;
     const TokenTiles t = token_tiles(M, f.tm);
-    const int64_t tiles = t.tiles * ((N + cols - 1) / cols);
-    if (tiles > kMaxTiles) return -1;
-    const int64_t full = tiles / cus, rem = tiles % cus, rounds = full + (rem ? 1 : 0);
+    const uint64_t all = (uint64_t)t.tiles * (((uint32_t)N + cols - 1) / cols);
+    if (all > (uint64_t)kMaxTiles) return -1;
+    const uint32_t tiles = (uint32_t)all, full = tiles / cus, rem = tiles % cus, rounds = full + (rem ? 1 : 0);
     // a last round on few CUs moves its operands a little faster (3584 / 16 = 224 of 256 CUs: 0.94)
-    const double moved = (K < kLongK || !rem) ? (double)rounds : full + 0.85 + 0.15 * rem / cus;
+    const double moved = (K < kLongK || !rem) ? rounds : full + 0.85 + 0.15 * rem / cus;
     // Operand rows of a tile, averaged over the token tiles.  Where the last token tile of each group is clearly
     // shorter, a launch of one round is faster than its rows say: the CUs of that tile run ahead of the
     // others and bring the weights into the L2 for them (512 rows in tiles of 160, 160, 160, 32 x 64:
@@ -87,11 +91,11 @@ inline double short_cost(int64_t M, int64_t N, int64_t K, bool gateup, ShortShap
     // 132 us, both over many passes; one pass at a time 116 and 134).  Larger tiles, which wait less for their operands, gain nothing (1280 rows in tiles of 192 x 128,
     // the last of each group 64: 154 us, in eight of 160: 149 us).
     double rows = (double)M / t.tiles + f.tn;
-    const int64_t last = t.group_rows - (t.per_group - 1) * f.tm;
+    const int last = (int)(t.group_rows - (t.per_group - 1) * f.tm);
     if (K >= kLongK && rounds == 1 && t.per_group > 1 && f.tm * f.tn <= 160 * 128)
         rows *= 10 * last <= 4 * f.tm ? (f.tm * f.tn > 96 * 128 ? 0.92 : 0.87) : 10 * last <= 7 * f.tm ? 0.94 : 1.0;
     const double fixed = kTileFixed + f.tm * cols * (gateup ? kTileFixedPerGateUp : kTileFixedPerDown);
-    return moved * rows * K + (rounds + f.per_cu - 1) / f.per_cu * fixed;
+    return moved * rows * K + (rounds + f.per_cu - 1) / (uint32_t)f.per_cu * fixed;
 }
 
 // Whether a gate/up launch reads its weights by non-temporal loads: where one group of token tiles covers
