@@ -49,7 +49,7 @@ inline int find_short_form(bool gateup, int tm, int tn) {
 // (measured over all forms on 1 ... 2048 rows at K = 14336 and 18944: 0.5 us per operand row at K = 14336,
 // i.e. 3.5e-5 us per unit, with a tenth of the spread that the flops per CU have).
 // Once per tile: launch, ring prologue, epilogue, 4 us and a little per output element (silu for gate/up);
-// the workgroups that share a CU overlap these.  A 256-row tile 256 weight rows wide, which the matrix
+// the workgroups that share a CU overlap these where the contraction is short.  A 256-row tile 256 weight rows wide, which the matrix
 // cores bound, takes as long as 550 operand rows and 9.6 us once.
 constexpr double kTileFixed = 115e3, kTileFixedPerGateUp = 5, kTileFixedPerDown = 2;
 constexpr double kFullTileRows = 550, kFullTileFixed = 275e3;
@@ -95,7 +95,10 @@ inline double short_cost(int64_t M, int64_t N, int64_t K, bool gateup, ShortShap
     if (K >= kLongK && rounds == 1 && t.per_group > 1 && f.tm * f.tn <= 160 * 128)
         rows *= 10 * last <= 4 * f.tm ? (f.tm * f.tn > 96 * 128 ? 0.92 : 0.87) : 10 * last <= 7 * f.tm ? 0.94 : 1.0;
     const double fixed = kTileFixed + f.tm * cols * (gateup ? kTileFixedPerGateUp : kTileFixedPerDown);
-    return moved * rows * K + (rounds + f.per_cu - 1) / (uint32_t)f.per_cu * fixed;
+    // (with a long contraction a second workgroup on the CU only shares its loads in flight: 1 row of gate/up in 448
+    // tiles of 64 x 64 48 us, in 224 of 64 x 128 42 us)
+    const uint32_t together = K < kLongK ? f.per_cu : 1;
+    return moved * rows * K + (rounds + together - 1) / together * fixed;
 }
 
 // Whether a gate/up launch reads its weights by non-temporal loads: where one group of token tiles covers
