@@ -96,7 +96,7 @@ inline double short_cost(int64_t M, int64_t N, int64_t K, bool gateup, ShortShap
         rows *= 10 * last <= 4 * f.tm ? (f.tm * f.tn > 96 * 128 ? 0.92 : 0.87) : 10 * last <= 7 * f.tm ? 0.94 : 1.0;
     const double fixed = kTileFixed + f.tm * cols * (gateup ? kTileFixedPerGateUp : kTileFixedPerDown);
     // (with a long contraction a second workgroup on the CU only shares its loads in flight: 1 row of gate/up in 448
-    // tiles of 64 x 64 48 us, in 224 of 64 x 128 42 us)
+    // tiles of 64 x 64 48 us, in 224 of 64 x 128 43 us)
     const uint32_t together = K < kLongK ? f.per_cu : 1;
     return moved * rows * K + (rounds + together - 1) / together * fixed;
 }
