@@ -7,7 +7,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -68,11 +67,6 @@ struct DeviceInfo {
 };
 DeviceInfo g_dev[kMaxDevices];
 
-// Gate/up tiles of 96 columns beside those of 128: a column of the narrow tile costs 7 % more (measured over
-// whole rounds), and the mix has to save this much of the modelled time before it is used.
-constexpr int kGateUpNarrowPerMille = 1070;
-constexpr int kGateUpMixMinGainPerMille = 15;
-
 // Testing overrides (the mom_debug_force_ calls); 0 = the library chooses.
 std::atomic<int> g_force_edge{0}, g_force_width{0}, g_force_pipeline{0};
 std::atomic<int> g_force_short{0};      // token rows << 16 | weight rows
@@ -127,26 +121,21 @@ int check_pinned_host(const void* p, size_t n) {
     return MOM_OK;
 }
 
-// The tile grid of `a` (M, N set) for tiles of `edge` token rows staging `width` weight rows; false if it
-// is empty or too large (tile numbers are 32-bit in the kernels).
-template <int EPI>
-bool set_tile_grid(momk::GemmArgs& a, int edge, int width) {
-    const int tile_n = (EPI == momk::EPI_GATEUP) ? width / 2 : width;
-    a.group_m = momk::kGroupM;
-    a.group_rows = edge * a.group_m;
-    a.tiles_m = (a.M + edge - 1) / edge;
-    a.tiles_n = (a.N + tile_n - 1) / tile_n;
-    const int64_t t = (int64_t)a.tiles_m * a.tiles_n;
-    if (t <= 0 || t > momk::kMaxTiles) return false;
-    a.tiles_per_xcd = (int)((t + 7) / 8);
-    return true;
+// The launch part described by `a` takes the tiles of `g`.
+void set_tile_grid(momk::GemmArgs& a, const momk::TileGrid& g) {
+    a.tiles_m = (int)g.tiles_m;
+    a.tiles_n = (int)g.tiles_n;
+    a.group_m = (int)g.per_group;
+    a.group_rows = (int)g.group_rows;
+    a.tiles_per_xcd = (int)((g.tiles + 7) / 8);
 }
 
-// One launch of gemm4_kernel<EPI, edge, width> over the operands in `a` (M, N, K, ldo set).  more: the call has more
+// One launch of gemm4_kernel<EPI, l.tm, l.tn> over the operands in `a` (M, N, K, ldo set).  more: the call has more
 // than one mini-sequence.
 template <int EPI>
-hipError_t launch_gemm_form(momk::GemmArgs a, int edge, int width, bool more, hipStream_t st) {
-    if (!set_tile_grid<EPI>(a, edge, width)) return hipErrorInvalidValue;
+hipError_t launch_whole_tiles(momk::GemmArgs a, const momk::Launch& l, bool more, hipStream_t st) {
+    set_tile_grid(a, l.grid);
+    const int edge = l.tm, width = l.tn;
     const dim3 grid((unsigned)(a.tiles_per_xcd * 8)), block(momk::k4Threads);
     const bool nt = EPI == momk::EPI_GATEUP && momk::weights_once(a.tiles_m, a.N, a.K, more);
 #define MOM_LAUNCH4(E, W)                                                                                         \
@@ -171,24 +160,15 @@ hipError_t launch_gemm_form(momk::GemmArgs a, int edge, int width, bool more, hi
     return hipGetLastError();
 }
 
-// One launch in the short form `form` (mom_gemm_forms.h).
+// One launch in the short form l.form (mom_gemm_forms.h).
 template <int EPI>
-hipError_t launch_short_form(momk::GemmArgs a, int form, bool more, hipStream_t st) {
-    const momk::ShortShape f = momk::short_shape(EPI == momk::EPI_GATEUP, form);
-    const momk::TokenTiles tt = momk::token_tiles(a.M, f.tm);
-    const int cols = (EPI == momk::EPI_GATEUP) ? f.tn / 2 : f.tn;
-    const int64_t tiles_n = (a.N + cols - 1) / cols, t = tt.tiles * tiles_n;
-    if (t <= 0 || t > momk::kMaxTiles) return hipErrorInvalidValue;
-    a.tiles_m = (int)tt.tiles;
-    a.tiles_n = (int)tiles_n;
-    a.group_m = (int)tt.per_group;
-    a.group_rows = (int)tt.group_rows;
-    a.tiles_per_xcd = (int)((t + 7) / 8);
+hipError_t launch_short_tiles(momk::GemmArgs a, const momk::Launch& l, bool more, hipStream_t st) {
+    set_tile_grid(a, l.grid);
     const dim3 grid((unsigned)(a.tiles_per_xcd * 8)), block(momk::k4Threads);
     const bool nt = EPI == momk::EPI_GATEUP && momk::weights_once(a.tiles_m, a.N, a.K, more);
     int i = 0;
 #define MOM_LAUNCH_SHORT(TM, TN, WM, WN, KSUB, NSTG)                                                              \
-    if (i++ == form) {                                                                                            \
+    if (i++ == l.form) {                                                                                          \
         if (EPI == momk::EPI_GATEUP && nt)                                                                        \
             hipLaunchKernelGGL((momk::gemm_short_kernel<EPI, TM, TN, WM, WN, KSUB, NSTG, EPI == momk::EPI_GATEUP>),  \
                                grid, block, 0, st, a);                                                            \
@@ -201,123 +181,57 @@ hipError_t launch_short_form(momk::GemmArgs a, int form, bool more, hipStream_t 
     return hipGetLastError();
 }
 
+// The launch a mom_debug_force_ call asks for (tests need every form on shapes of every size); kRefused with form -1
+// where none does.
+momk::Launch forced_launch(int64_t M, int64_t N, bool gateup) {
+    const int fs = g_force_short.load(std::memory_order_relaxed);
+    if (fs) {
+        const int form = momk::find_short_form(gateup, fs >> 16, fs & 0xffff);
+        if (form >= 0) return momk::short_launch(M, N, gateup, form);
+    }
+    const int force = g_force_edge.load(std::memory_order_relaxed), fw = g_force_width.load(std::memory_order_relaxed);
+    if (force == 256) return momk::whole_launch(M, N, gateup, 256, (fw && (!gateup || fw == 192)) ? fw : 256);
+    if (force == 128 && gateup) return momk::whole_launch(M, N, gateup, 128, 128);
+    if (force) return momk::short_launch(M, N, gateup, momk::find_short_form(gateup, force, force));
+    return {momk::kRefused, -1, 0, 0, 0, {}, {}};
+}
+
+// O[m, n] of M token rows x N output columns; what runs is chosen in mom_gemm_forms.h.
 template <int EPI>
 hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const unsigned short* W1,
-                       unsigned short* O, int M, int N, int K, hipStream_t st, bool more, bool never_small = false) {
+                       unsigned short* O, int M, int N, int K, hipStream_t st, bool more, bool full_tiles = false) {
     constexpr bool GU = EPI == momk::EPI_GATEUP;
+    const int cus = compute_units();
+    if (cus <= 0) return hipErrorInvalidDevice;
+    momk::Launch l = forced_launch(M, N, GU);
+    if (l.form < 0) l = GU ? momk::choose_gateup(M, N, K, cus) : momk::choose_down(M, N, K, cus, full_tiles);
     momk::GemmArgs a;
     a.X = X; a.W0 = W0; a.W1 = W1; a.O = O;
     a.M = M; a.N = N; a.K = K; a.ldo = N;
-    // tiles of a launch with 256 token rows and `cols` output columns per tile
-    auto tiles_of = [&](int cols) { return (int64_t)((M + 255) / 256) * ((N + cols - 1) / cols); };
-    if (tiles_of(GU ? 128 : 256) > momk::kMaxTiles) return hipErrorInvalidValue;
-    // All forms give identical bits (every output element sees the same MFMA sequence over k), so the
-    // choice is free.
-    // Down projection with 256-row tiles: 256, 224, 192, 160 or 128 weight rows per tile, whichever needs
-    // the least time in rounds of the CUs (rounds x width, a narrower tile charged more per column for the
-    // token fragments it shares among fewer MFMAs, a partly filled last round less than a whole one): 3584
-    // output columns with 32 token tiles are 1.75 rounds of 256-wide tiles on 256 CUs but exactly 2 rounds
-    // of 224-wide ones, and the 128 full-size tiles of a 2048-row mini-sequence at 4096 columns are one
-    // round of 256 tiles 128 wide.
-    // Gate/up with 256-row tiles: the first columns in tiles of 128 columns, the rest in tiles of 96, in one
-    // launch of the two-width kernel, where the same model says that saves time: 14336 columns with 12 token
-    // tiles are 1344 tiles = 5.25 rounds, but 64 x 128 + 64 x 96 columns are three rounds of each width.
-    // Few tiles: the short forms where their cost is lower.  Then the operand rows that a CU moves count,
-    // and the best form is the one that gives every CU one tile with the fewest of them (mom_gemm_forms.h).
-    // Gate/up with a short contraction: 128-row tiles, two workgroups per CU, by the same cost.
-    // The mom_debug_force_ calls override the choice (for tests, which need every form on shapes of every size).
-    const int cus = compute_units();
-    if (cus <= 0) return hipErrorInvalidDevice;
-    const int fs = g_force_short.load(std::memory_order_relaxed);
-    if (fs) {
-        const int form = momk::find_short_form(GU, fs >> 16, fs & 0xffff);
-        if (form >= 0) return launch_short_form<EPI>(a, form,more, st);
+    switch (l.kind) {
+        case momk::kShortTiles: return launch_short_tiles<EPI>(a, l, more, st);
+        case momk::kWholeTiles: return launch_whole_tiles<EPI>(a, l, more, st);
+        case momk::kTwoWidths:
+            if constexpr (GU) {
+                momk::GemmArgs2 p = {a, a};
+                p.wide.N = (int)l.wide_cols;
+                p.narrow.W0 = W0 + (size_t)l.wide_cols * K;
+                p.narrow.W1 = W1 + (size_t)l.wide_cols * K;
+                p.narrow.O = O + l.wide_cols;
+                p.narrow.N = N - (int)l.wide_cols;
+                set_tile_grid(p.wide, l.grid);
+                set_tile_grid(p.narrow, l.narrow);
+                const int64_t wgs = 8 * ((int64_t)p.wide.tiles_per_xcd + p.narrow.tiles_per_xcd);
+                if (wgs > (int64_t)0x7fffffff) return hipErrorInvalidValue;
+                if (momk::weights_once(p.wide.tiles_m, N, K, more))
+                    hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192, true>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
+                else
+                    hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192, false>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
+                return hipGetLastError();
+            }
+            return hipErrorInvalidValue;
+        default: return hipErrorInvalidValue;
     }
-    const int force = g_force_edge.load(std::memory_order_relaxed);
-    if (force == 256) {
-        const int fw = g_force_width.load(std::memory_order_relaxed);
-        return launch_gemm_form<EPI>(a, 256, (fw && (!GU || fw == 192)) ? fw : 256,more, st);
-    }
-    if (force == 128 && GU) return launch_gemm_form<EPI>(a, 128, 128,more, st);
-    if (force) return launch_short_form<EPI>(a, momk::find_short_form(GU, force, force),more, st);
-
-    // Rounds of the CUs a launch of `tiles` 256-row tiles takes, in 1/1000.  A last round that fills only part of the
-    // CUs is not as dear as a whole one: the chip is power-limited and clocks the busy CUs higher (measured:
-    // a round on a quarter / half / three quarters of the CUs takes about 0.55 / 0.8 / 0.8-0.9 of a full one).
-    auto rounds_pm = [&](int64_t tiles) {
-        const int64_t full = tiles / cus, rem = tiles % cus;
-        return full * 1000 + (rem ? 500 + 500 * rem / cus : 0);
-    };
-    int width = 256;
-    int64_t narrow_tiles_n = 0;          // gate/up: column tiles of the narrow width behind the wide ones
-    int64_t cost = 0;                    // rounds x columns of 256 x 256 tiles (128 for gate/up), in 1e-6
-    double short_cost = 0;
-    const int form = never_small ? -1 : momk::choose_short_form(M, N, K, GU, cus, short_cost);
-    // the cost of 256-row tiles in the units of the short forms
-    auto full_cost = [&](int64_t c, int64_t tiles) {
-        return 1e-6 * c / (GU ? 128 : 256) * momk::kFullTileRows * K + (tiles + cus - 1) / cus * momk::kFullTileFixed;
-    };
-    if (!GU) {
-        // (beside a chip-filling gate/up kernel: full-size tiles, however few)
-        for (int w : {256, 224, 192, 160, 128}) {
-            static const int per_mille[5] = {1000, 1020, 1070, 1170, 1310};     // what the narrower tile costs per column (measured)
-            const int64_t c = rounds_pm(tiles_of(w)) * w * per_mille[(256 - w) / 32];
-            if (cost == 0 || (c < cost && !never_small)) { cost = c; width = w; }
-        }
-        if (form >= 0) {
-            // a narrow tile is bound by its operands, too (1536 rows x 3584 columns: 233 us in tiles 128 wide)
-            const double full = std::max(full_cost(cost, tiles_of(width)), momk::short_cost(M, N, K, false, {256, width, 1}, cus));
-            if (short_cost < full) return launch_short_form<EPI>(a, form, more, st);
-        }
-    } else {
-        // b column tiles of 96 behind a of 128: a = ceil((N - 96 b) / 128); time = rounds x columns per tile
-        const int64_t tm = (M + 255) / 256;
-        auto mix_cost = [&](int64_t b) {
-            const int64_t rest = (int64_t)N - 96 * b;
-            const int64_t wide = rest > 0 ? (rest + 127) / 128 : 0;
-            return rounds_pm(tm * wide) * 128 * 1000 + rounds_pm(tm * b) * 96 * kGateUpNarrowPerMille;
-        };
-        const int64_t plain = mix_cost(0);
-        cost = plain;
-        // (no mix takes less than half of what the plain tiles take: where the short form does, it is not looked for)
-        const bool few = form >= 0 && short_cost < 0.5 * full_cost(plain, 1);
-        for (int64_t b = 1; b <= ((int64_t)N + 95) / 96 && !few; ++b) {
-            const int64_t c = mix_cost(b);
-            if (c < cost && c * 1000 <= plain * (1000 - kGateUpMixMinGainPerMille)) { cost = c; narrow_tiles_n = b; }
-        }
-        if (form >= 0) {
-            const double full = full_cost(cost, tiles_of(128));
-            const double cost128 = momk::short_cost(M, N, K, true, {128, 128, 2}, cus);
-            if constexpr (GU)
-                if (cost128 >= 0 && cost128 < full && cost128 < short_cost) return launch_gemm_form<EPI>(a, 128, 128, more, st);
-            if (short_cost < full) return launch_short_form<EPI>(a, form, more, st);
-        }
-    }
-    if constexpr (GU) {
-        if (narrow_tiles_n > 0) {
-            const int64_t rest = (int64_t)N - 96 * narrow_tiles_n;
-            const int wide_cols = rest > 0 ? (int)((rest + 127) / 128) * 128 : 0;     // columns [0, wide_cols) in wide tiles
-            if (wide_cols >= N) return launch_gemm_form<EPI>(a, 256, 256,more, st);
-            momk::GemmArgs2 p;
-            p.narrow = a;
-            p.narrow.W0 = W0 + (size_t)wide_cols * K;
-            p.narrow.W1 = W1 + (size_t)wide_cols * K;
-            p.narrow.O = O + wide_cols;
-            p.narrow.N = N - wide_cols;
-            if (wide_cols == 0) return launch_gemm_form<EPI>(p.narrow, 256, 192,more, st);
-            p.wide = a;
-            p.wide.N = wide_cols;
-            if (!set_tile_grid<EPI>(p.wide, 256, 256) || !set_tile_grid<EPI>(p.narrow, 256, 192)) return hipErrorInvalidValue;
-            const int64_t wgs = 8 * ((int64_t)p.wide.tiles_per_xcd + p.narrow.tiles_per_xcd);
-            if (wgs > (int64_t)0x7fffffff) return hipErrorInvalidValue;
-            if (momk::weights_once(p.wide.tiles_m, N, K, more))
-                hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192, true>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
-            else
-                hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192, false>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
-            return hipGetLastError();
-        }
-    }
-    return launch_gemm_form<EPI>(a, 256, width,more, st);
 }
 
 template <int MODE>

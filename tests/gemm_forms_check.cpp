@@ -43,14 +43,14 @@ static void form(bool gu, int tm, int tn, int wm, int wn, int ksub, int nstg) {
         }
 }
 
-// The kernel's walk over the token tiles of a launch covers every row once.
-static void rows(int64_t M, int tm) {
-    const momk::TokenTiles t = momk::token_tiles(M, tm);
+// The kernels' walk over the token tiles of a grid covers every row once, with a tile of its own for each count that
+// the grid states (and that its cost was reckoned with).
+static void rows(int64_t M, int tm, const momk::TileGrid& t, bool spread) {
     CHECK(t.per_group <= momk::kTokenGroup, "groups of M=%lld tm=%d", (long long)M, tm);
     int64_t next = 0;
-    for (int64_t i = 0; i < t.tiles; ++i) {
+    for (int64_t i = 0; i < t.tiles_m; ++i) {
         const int64_t grp = i / t.per_group, m0 = grp * t.group_rows + (i % t.per_group) * tm;
-        const int64_t in_group = t.group_rows - (i % t.per_group) * tm;
+        const int64_t in_group = spread ? t.group_rows - (i % t.per_group) * tm : tm;
         const int64_t end = m0 + (M - m0 < in_group ? M - m0 : in_group);
         CHECK(m0 == next && m0 < end && m0 <= 0x7fffffff, "tile %lld of M=%lld tm=%d", (long long)i, (long long)M, tm);
         next = m0 + tm < end ? m0 + tm : end;
@@ -58,10 +58,33 @@ static void rows(int64_t M, int tm) {
     CHECK(next == M, "rows of M=%lld tm=%d", (long long)M, tm);
 }
 
+// What choose_down picks at these sizes, against every launch there is, each priced on the grid that runs.
+static int64_t rounds(const momk::TileGrid& g, int cus) { return ((int64_t)g.tiles + cus - 1) / cus; }
+static void down_choice(int64_t M, int64_t N, int64_t K, int cus) {
+    const momk::Launch l = momk::choose_down(M, N, K, cus, false);
+    CHECK(l.kind == momk::kShortTiles || l.kind == momk::kWholeTiles, "down M=%lld N=%lld", (long long)M, (long long)N);
+    if (l.kind == momk::kWholeTiles) return;
+    // With a long contraction a 256-row tile takes at most a little more than a short one of the same width, so short
+    // tiles that need more rounds than 256-row tiles no wider than 192 are never the faster ones (measured at 2400 ... 5500 rows).
+    for (int w : {192, 160, 128})
+        CHECK(K < momk::kLongK || l.tm * l.tn < 160 * 128 || rounds(l.grid, cus) <= rounds(momk::whole_tiles(M, N, 256, w), cus),
+              "down M=%lld N=%lld K=%lld: %d x %d in %lld rounds, 256 x %d in %lld", (long long)M, (long long)N, (long long)K, l.tm, l.tn,
+              (long long)rounds(l.grid, cus), w, (long long)rounds(momk::whole_tiles(M, N, 256, w), cus));
+}
+
 int main() {
     for (int tm = 16; tm <= 256; tm += 16)
-        for (int64_t M = 1; M < 5000; M += 1 + M / 97) rows(M, tm);
-    rows(0x7fffff00, 256);
+        for (int64_t M = 1; M < 5000; M += 1 + M / 97) rows(M, tm, momk::spread_tiles(M, 32, tm, 32), true);
+    rows(0x7fffff00, 256, momk::spread_tiles(0x7fffff00, 32, 256, 32), true);
+    rows(0x7fffff00, 256, momk::whole_tiles(0x7fffff00, 32, 256, 32), false);
+    for (int64_t M = 1; M <= 16384; ++M) {
+        rows(M, 256, momk::whole_tiles(M, 32, 256, 32), false);
+        rows(M, 128, momk::whole_tiles(M, 32, 128, 32), false);
+        down_choice(M, 4096, 14336, 256);
+        down_choice(M, 3584, 18944, 256);
+        down_choice(M, 8192, 28672, 256);
+        CHECK(momk::choose_gateup(M, 14336, 4096, 256).kind != momk::kRefused, "gate/up M=%lld", (long long)M);
+    }
 #define D(TM, TN, WM, WN, KSUB, NSTG) form(false, TM, TN, WM, WN, KSUB, NSTG);
 #define G(TM, TN, WM, WN, KSUB, NSTG) form(true, TM, TN, WM, WN, KSUB, NSTG);
     MOM_SHORT_FORMS_DOWN(D)
@@ -81,9 +104,12 @@ int main() {
                         CHECK(f < momk::short_forms(gu) && std::isfinite(cost) && cost > 0, "choice");
                         const momk::ShortShape s = momk::short_shape(gu, f);
                         const int64_t cols = gu ? s.tn / 2 : s.tn;
-                        CHECK(momk::token_tiles(M, s.tm).tiles * ((N + cols - 1) / cols) <= momk::kMaxTiles, "tiles");
-                        CHECK(cost <= momk::short_cost(M, N, K, gu, momk::short_shape(gu, 0), cus) ||
-                              momk::short_cost(M, N, K, gu, momk::short_shape(gu, 0), cus) < 0, "least cost");
+                        CHECK((int64_t)momk::spread_tiles(M, N, s.tm, cols).tiles <= momk::kMaxTiles, "tiles");
+                        for (int i = 0; i < momk::short_forms(gu); ++i) {
+                            const momk::ShortShape o = momk::short_shape(gu, i);
+                            const double c = momk::moved_cost(momk::short_grid(M, N, gu, o), M, K, gu, o, cus);
+                            CHECK(c < 0 || cost <= c, "least cost: M=%lld N=%lld K=%lld form %d", (long long)M, (long long)N, (long long)K, i);
+                        }
                     }
     printf("%d forms, %d choices: %s\n", momk::short_forms(0) + momk::short_forms(1), n, bad ? "FAILED" : "ok");
     return bad != 0;

@@ -2,13 +2,39 @@
 import os
 import subprocess
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2504_12526_amd", "csrc")
+HEADER = os.path.join(CSRC, "mom_gemm_forms.h")
+
+
+def _build_and_run(tmp_path, include_dir):
+    exe = os.path.join(str(tmp_path), "gemm_forms_check")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", include_dir, "-o", exe,
+                    os.path.join(ROOT, "tests", "gemm_forms_check.cpp")], check=True)
+    return subprocess.run([exe], capture_output=True, text=True)
 
 
 def test_forms_and_choice(tmp_path):
-    exe = os.path.join(str(tmp_path), "gemm_forms_check")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I",
-                    os.path.join(ROOT, "paper_2504_12526_amd", "csrc"), "-o", exe,
-                    os.path.join(ROOT, "tests", "gemm_forms_check.cpp")], check=True)
-    r = subprocess.run([exe], capture_output=True, text=True)
+    r = _build_and_run(tmp_path, CSRC)
     assert r.returncode == 0 and ": ok" in r.stdout, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("old,new,says", [
+    # the 256-row tiles priced on the grid of the short forms, which is not the one they run on
+    ("    const TileGrid g = whole_tiles(M, N, 256, w);\n    const double moved", "    const TileGrid g = spread_tiles(M, N, 256, w);\n    const double moved",
+     "M=2400 N=4096"),
+    # the last, shorter tile of a group forgotten
+    ("        g.per_group = (g.group_rows + tm - 1) / tm;", "        g.per_group = g.group_rows / tm;", "tile 2 of M="),
+])
+def test_a_planted_mistake_is_caught(tmp_path, old, new, says):
+    """Planted in a copy of the header, on the CPU."""
+    inc = os.path.join(str(tmp_path), "inc")
+    os.makedirs(inc)
+    text = open(HEADER).read()
+    assert text.count(old) == 1, f"header text changed: {old}"
+    with open(os.path.join(inc, "mom_gemm_forms.h"), "w") as f:
+        f.write(text.replace(old, new))
+    r = _build_and_run(tmp_path, inc)
+    assert r.returncode != 0 and says in r.stdout, r.stdout[-2000:]
