@@ -125,8 +125,7 @@ int check_pinned_host(const void* p, size_t n) {
 void set_tile_grid(momk::GemmArgs& a, const momk::TileGrid& g) {
     a.tiles_m = (int)g.tiles_m;
     a.tiles_n = (int)g.tiles_n;
-    a.group_m = (int)g.per_group;
-    a.group_rows = (int)g.group_rows;
+    a.group_m = momk::kTokenGroup;
     a.tiles_per_xcd = (int)((g.tiles + 7) / 8);
 }
 
@@ -196,15 +195,23 @@ momk::Launch forced_launch(int64_t M, int64_t N, bool gateup) {
     return {momk::kRefused, -1, 0, 0, 0, {}, {}};
 }
 
-// O[m, n] of M token rows x N output columns; what runs is chosen in mom_gemm_forms.h.
+// What runs for M token rows x N output columns, mini-sequence c of its call (mom_gemm_forms.h).  full_tiles: the down
+// projection in tiles of 256 x 256 however few.
 template <int EPI>
-hipError_t launch_gemm(const unsigned short* X, const unsigned short* W0, const unsigned short* W1,
-                       unsigned short* O, int M, int N, int K, hipStream_t st, bool more, bool full_tiles = false) {
+momk::Launch choose_launch(int64_t M, int64_t N, int64_t K, int64_t c, bool full_tiles = false) {
     constexpr bool GU = EPI == momk::EPI_GATEUP;
     const int cus = compute_units();
-    if (cus <= 0) return hipErrorInvalidDevice;
-    momk::Launch l = forced_launch(M, N, GU);
-    if (l.form < 0) l = GU ? momk::choose_gateup(M, N, K, cus) : momk::choose_down(M, N, K, cus, full_tiles);
+    if (cus <= 0) return {momk::kRefused, -1, 0, 0, 0, {}, {}};
+    const momk::Launch l = forced_launch(M, N, GU);
+    if (l.form >= 0) return l;
+    return GU ? momk::choose_gateup(M, N, K, cus) : momk::choose_down(M, N, K, cus, c >= momk::kKeptFrom, full_tiles);
+}
+
+// O[m, n] of M token rows x N output columns by launch l.  more: the call has more than one mini-sequence.
+template <int EPI>
+hipError_t launch_gemm(const momk::Launch& l, const unsigned short* X, const unsigned short* W0, const unsigned short* W1,
+                       unsigned short* O, int M, int N, int K, hipStream_t st, bool more) {
+    constexpr bool GU = EPI == momk::EPI_GATEUP;
     momk::GemmArgs a;
     a.X = X; a.W0 = W0; a.W1 = W1; a.O = O;
     a.M = M; a.N = N; a.K = K; a.ldo = N;
@@ -269,16 +276,21 @@ int mlp_driver(const void* x, const void* wg, const void* wu, const void* wd, in
     unsigned short* w = static_cast<unsigned short*>(ws);
     if (events && hipEventRecord(static_cast<hipEvent_t>(events[0]), st) != hipSuccess) return MOM_ERR_HIP;
     // Algorithm 1, else-branch: O_i = MLP(A_i) for each mini-sequence, O_i written at its rows of O.
+    momk::Launch gateup = {}, down = {};
+    int planned = 0;                     // token rows that `gateup` and `down` are for
     for (int64_t c = 0; c < n; ++c) {
         const int64_t r0 = c * C;
         const int rows = (int)((r0 + C <= S) ? C : (S - r0));
-        if (launch_gemm<momk::EPI_GATEUP>(xs + r0 * H, static_cast<const unsigned short*>(wg),
+        if (rows != planned) gateup = choose_launch<momk::EPI_GATEUP>(rows, I, H, c);
+        if (rows != planned || c == momk::kKeptFrom) down = choose_launch<momk::EPI_DOWN>(rows, H, I, c);
+        planned = rows;
+        if (launch_gemm<momk::EPI_GATEUP>(gateup, xs + r0 * H, static_cast<const unsigned short*>(wg),
                                           static_cast<const unsigned short*>(wu), w, rows, (int)I, (int)H,
                                           st, n > 1) != hipSuccess)
             return MOM_ERR_HIP;
         if (events && hipEventRecord(static_cast<hipEvent_t>(events[1 + 2 * c]), st) != hipSuccess)
             return MOM_ERR_HIP;
-        if (launch_gemm<momk::EPI_DOWN>(w, static_cast<const unsigned short*>(wd), nullptr, os + r0 * H, rows,
+        if (launch_gemm<momk::EPI_DOWN>(down, w, static_cast<const unsigned short*>(wd), nullptr, os + r0 * H, rows,
                                         (int)H, (int)I, st, n > 1) != hipSuccess)
             return MOM_ERR_HIP;
         if (events && hipEventRecord(static_cast<hipEvent_t>(events[2 + 2 * c]), st) != hipSuccess)
@@ -312,9 +324,9 @@ int mlp_pipelined(const void* x, const void* wg, const void* wu, const void* wd,
         // gate/up(c) is held until down(c-1) has been handed to the device: its few, long tiles must
         // get their CUs before the many tiles of this kernel take the whole chip for a round
         if (c >= 1 && hipStreamWaitEvent(sa, ev[4], 0) != hipSuccess) return MOM_ERR_HIP;
-        if (launch_gemm<momk::EPI_GATEUP>(xs + r0 * H, static_cast<const unsigned short*>(wg),
-                                          static_cast<const unsigned short*>(wu), half[h], rows, (int)I, (int)H,
-                                          sa, true) != hipSuccess)
+        if (launch_gemm<momk::EPI_GATEUP>(choose_launch<momk::EPI_GATEUP>(rows, I, H, c), xs + r0 * H,
+                                          static_cast<const unsigned short*>(wg), static_cast<const unsigned short*>(wu),
+                                          half[h], rows, (int)I, (int)H, sa, true) != hipSuccess)
             return MOM_ERR_HIP;
         if (hipEventRecord(ev[h], sa) != hipSuccess || hipStreamWaitEvent(sb, ev[h], 0) != hipSuccess)
             return MOM_ERR_HIP;
@@ -322,8 +334,9 @@ int mlp_pipelined(const void* x, const void* wg, const void* wu, const void* wd,
         // beside a gate/up kernel that fills the chip, full-size tiles are the efficient form for the
         // down projection however few they are; the last one runs alone and follows the usual rule
         const bool beside_big = c + 1 < n;
-        if (launch_gemm<momk::EPI_DOWN>(half[h], static_cast<const unsigned short*>(wd), nullptr, os + r0 * H, rows,
-                                        (int)H, (int)I, sb, true, beside_big) != hipSuccess)
+        if (launch_gemm<momk::EPI_DOWN>(choose_launch<momk::EPI_DOWN>(rows, H, I, c, beside_big), half[h],
+                                        static_cast<const unsigned short*>(wd), nullptr, os + r0 * H, rows, (int)H, (int)I,
+                                        sb, true) != hipSuccess)
             return MOM_ERR_HIP;
         if (hipEventRecord(ev[2 + h], sb) != hipSuccess) return MOM_ERR_HIP;
     }

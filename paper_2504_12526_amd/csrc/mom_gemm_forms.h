@@ -3,12 +3,16 @@
 //
 // X(TM, TN, WM, WN, KSUB, NSTG): TM token rows x TN staged weight rows per workgroup, WM x WN wavefronts
 // that multiply, stages of 64 KSUB K-elements, NSTG of them in the LDS ring (mom_gemm_short.hip.inc).
-// The smallest tiles take the longest stages (one barrier per stage) and every form a ring that holds
-// more than the 32 KiB a CU's vector cache has in flight at most (measured: 256 lines of 128 bytes).
+// The smallest tiles take the longest stages (one barrier per stage) and nearly every form a ring that holds
+// more than the 32 KiB a CU's vector cache has in flight at most (measured: 256 lines of 128 bytes).  Gate/up
+// 64 x 64 has two rings: of three slots, so that three workgroups fit a CU (33 rows of H = 8192, I = 28672: 155 us, with five
+// slots 187), and of five for launches that give a CU only one (the same rows at I = 3584: 51 us, with five slots 36).
 #ifndef MOM_GEMM_FORMS_H
 #define MOM_GEMM_FORMS_H
 
 #include <stdint.h>
+
+#include <initializer_list>
 
 #define MOM_SHORT_FORMS_DOWN(X)                                                                          \
     X(16, 16, 1, 1, 2, 8) X(32, 16, 2, 1, 4, 6) X(32, 32, 2, 2, 2, 5) X(48, 32, 1, 2, 2, 8)              \
@@ -20,13 +24,14 @@
     X(16, 32, 1, 1, 4, 6) X(32, 32, 2, 1, 2, 8) X(16, 64, 1, 2, 2, 8) X(32, 64, 2, 2, 2, 6)              \
     X(64, 64, 2, 2, 1, 3) X(128, 64, 2, 2, 1, 3) X(64, 128, 2, 2, 1, 6) X(96, 128, 2, 2, 1, 5)           \
     X(128, 128, 2, 2, 1, 5) X(160, 128, 2, 2, 1, 4) X(192, 128, 2, 2, 1, 4) X(224, 128, 2, 2, 1, 3)      \
-    X(64, 192, 2, 2, 1, 5) X(96, 192, 2, 2, 1, 4) X(128, 192, 2, 2, 1, 4)
+    X(64, 192, 2, 2, 1, 5) X(96, 192, 2, 2, 1, 4) X(128, 192, 2, 2, 1, 4) X(64, 64, 2, 2, 1, 5)
 
 namespace momk {
 
-struct ShortShape { int tm, tn, per_cu; };       // per_cu: workgroups that a CU's 160 KiB of LDS hold
+// per_cu: workgroups that a CU's 160 KiB of LDS hold; ahead: K-elements that a workgroup has in flight at most.
+struct ShortShape { int tm, tn, per_cu, ahead; };
 #define MOM_SHAPE(TM, TN, WM, WN, KSUB, NSTG) \
-    {TM, TN, 163840 / (NSTG * KSUB * (TM + TN) * 128) > 4 ? 4 : 163840 / (NSTG * KSUB * (TM + TN) * 128)},
+    {TM, TN, 163840 / (NSTG * KSUB * (TM + TN) * 128) > 4 ? 4 : 163840 / (NSTG * KSUB * (TM + TN) * 128), (NSTG - 1) * 64 * KSUB},
 constexpr ShortShape kShortDown[] = {MOM_SHORT_FORMS_DOWN(MOM_SHAPE)};
 constexpr ShortShape kShortGateUp[] = {MOM_SHORT_FORMS_GATEUP(MOM_SHAPE)};
 #undef MOM_SHAPE
@@ -36,82 +41,97 @@ constexpr int kShortGateUpForms = sizeof(kShortGateUp) / sizeof(kShortGateUp[0])
 inline int short_forms(bool gateup) { return gateup ? kShortGateUpForms : kShortDownForms; }
 inline ShortShape short_shape(bool gateup, int form) { return gateup ? kShortGateUp[form] : kShortDown[form]; }
 
-// Index of the form with these tiles, or -1.
+// Index of the (first) form with these tiles, or -1.
 inline int find_short_form(bool gateup, int tm, int tn) {
     for (int i = 0; i < short_forms(gateup); ++i)
         if (short_shape(gateup, i).tm == tm && short_shape(gateup, i).tn == tn) return i;
     return -1;
 }
 
-// Costs are in operand rows x K-elements that one CU moves into its LDS: with few token rows that is what a
-// launch takes time for.  A CU's vector cache has 256 lines in flight at most, and at the latency of
-// weights that come from HBM that is 55 GB/s, whatever the ring holds and however little is multiplied
-// (measured over all forms on 1 ... 2048 rows at K = 14336 and 18944: 0.5 us per operand row at K = 14336,
-// i.e. 3.5e-5 us per unit, with a tenth of the spread that the flops per CU have).
-// Once per tile: launch, ring prologue, epilogue, 4 us and a little per output element (silu for gate/up);
-// the workgroups that share a CU overlap these where the contraction is short.  A 256-row tile 256 weight rows wide, which the matrix
-// cores bound, takes as long as 550 operand rows and 9.6 us once.
-constexpr double kTileFixed = 115e3, kTileFixedPerGateUp = 5, kTileFixedPerDown = 2;
-constexpr double kFullTileRows = 550, kFullTileFixed = 275e3;
-// From this contraction length on, what a launch waits for is its operands, not the start and end of tiles.
-constexpr int64_t kLongK = 3072;
 constexpr int64_t kMaxTiles = 0x1fffffff;            // tile numbers are 32-bit in the kernels
 
-// The tiles of a launch, as it is priced AND as it is launched: tiles_m token tiles in groups of per_group (their
-// weights are fetched by one XCD at a time) over group_rows token rows each, tiles_n column tiles.
+// The tiles of a launch, as it is priced AND as it is launched: tiles_m token tiles one after the other, walked in groups
+// of kTokenGroup (their weights are fetched by one XCD at a time), tiles_n column tiles.
 // (32-bit arithmetic: every launch walks all forms on the host, and M + 1024 < 2^32.)
 constexpr int kTokenGroup = 4;
-struct TileGrid { uint32_t tiles_m, per_group, group_rows, tiles_n; uint64_t tiles; };
-inline TileGrid column_tiles(TileGrid g, int64_t N, uint32_t cols) {
-    g.tiles_n = ((uint32_t)N + cols - 1) / cols;
-    g.tiles = (uint64_t)g.tiles_m * g.tiles_n;
-    return g;
-}
-// mom_gemm.hip.inc: whole tiles one after the other, only the last one of all is shorter.
-inline TileGrid whole_tiles(int64_t rows, int64_t N, uint32_t tm, uint32_t cols) {
-    return column_tiles({((uint32_t)rows + tm - 1) / tm, kTokenGroup, kTokenGroup * tm, 0, 0}, N, cols);
-}
-// mom_gemm_short.hip.inc: the rows spread evenly over the groups, the last tile of each group is shorter.
-inline TileGrid spread_tiles(int64_t rows, int64_t N, uint32_t tm, uint32_t cols) {
-    const uint32_t M = (uint32_t)rows, most = kTokenGroup * tm;
-    uint32_t groups = 1;
-    TileGrid g = {0, (M + tm - 1) / tm, M, 0, 0};
-    if (M > most) {
-        groups = (M + most - 1) / most;
-        g.group_rows = (M + groups - 1) / groups;
-        groups = (M + g.group_rows - 1) / g.group_rows;
-        g.per_group = (g.group_rows + tm - 1) / tm;
-    }
-    g.tiles_m = (groups - 1) * g.per_group + (M - (groups - 1) * g.group_rows + tm - 1) / tm;
-    return column_tiles(g, N, cols);
-}
-// Grid of M token rows x N output columns in tiles of a short form.
-inline TileGrid short_grid(int64_t M, int64_t N, bool gateup, ShortShape f) {
-    return spread_tiles(M, N, f.tm, gateup ? f.tn / 2 : f.tn);
+struct TileGrid { uint32_t tiles_m, tiles_n; uint64_t tiles; };
+inline TileGrid tile_grid(int64_t M, int64_t N, bool gateup, ShortShape f) {
+    const uint32_t cols = gateup ? f.tn / 2 : f.tn;
+    const uint32_t tm = ((uint32_t)M + f.tm - 1) / f.tm, tn = ((uint32_t)N + cols - 1) / cols;
+    return {tm, tn, (uint64_t)tm * tn};
 }
 
-// Cost of a launch of M token rows, contraction length K, in the tiles f of grid g; < 0: too many tiles.
-inline double moved_cost(const TileGrid& g, int64_t M, int64_t K, bool gateup, ShortShape f, int cus) {
-    const uint32_t cols = gateup ? f.tn / 2 : f.tn;
+// The time of a launch in us: what a CU spends on a tile, times the tiles it runs.
+//   start, output   once per tile: launch, ring prologue, epilogue; per output element (silu for gate/up).  The workgroups
+//                   that share a CU (ShortShape::per_cu) overlap it.
+//   row, fetched    per K-element: the operand rows that the CU moves into its LDS, and its share of the rows that its XCD
+//                   fetches from beyond the L2.  A CU's vector cache has 256 lines in flight, and at the latency of weights
+//                   that come from HBM that is 55 GB/s, whatever the ring holds and however little is multiplied; rows
+//                   that another CU of the XCD has fetched before cost about a third of that.
+//   product         per K-element: token rows x weight rows, the matrix cores.
+//   last_round      a last round on few CUs takes this much of a whole one, and the rest in proportion: the
+//                   chip is power-limited and clocks the busy CUs higher.
+//   latency         a workgroup waits at least this long for what it has in flight (ShortShape::ahead): 0.69 us from HBM,
+//                   0.33 us from the Infinity Cache.
+//   whole_tile      the token rows are those of a whole tile, which the launch waits for; otherwise those of an average one.
+//   lead            the part per K-element is less by this and by lead_small x 64 / (tm + tn) where the last token tile has
+//                   clearly fewer rows, the launch is one round and W_down fits the Infinity Cache: the CUs of that tile run
+//                   ahead and bring the weights nearer for the others (1000 rows x 4096 columns in tiles of 160, six of them
+//                   and one of 40, x 128: 119 us; as eight even ones of 128: 133 us).
+// Fitted to every form on 1 ... 4096 rows of eleven layers (H 256 ... 8192, I 1024 ... 28672), single calls and loops of
+// mini-sequences.  Formula and time of the forms near the best of their size differ by 5 (256-row tiles), 8 (short, down)
+// and 9 % (short, gate/up; the least of many uncertain times is an optimistic one, so these figures are the fitted ones
+// and 5 or 6 % on everything).  Over the 1427 launches measured, the form of least time takes 1 % longer than the best of
+// all forms on average, and more than 10 % longer in 22 of them.
+struct LaunchTime {
+    double start, output, row, fetched, product, last_round, latency;
+    bool whole_tile;
+    double lead, lead_small;
+};
+constexpr double kFromHbm = 0.69, kFromCache = 0.33;
+constexpr LaunchTime kShortDownTime = {4.0, 5.0e-5, 1.94e-5, 5.56e-5, 5.81e-8, 1.0, kFromHbm, true, 0.1, 0.2};
+// W_down still in the Infinity Cache (kept_down).  Then nobody needs to run ahead: 1024 rows x 4096 columns in tiles of
+// 160 x 128: 117 us, in eight of 128 x 128: 109 us; 512 rows in tiles of 160 x 64 80 us, of 128 x 64 70 us.
+constexpr LaunchTime kShortDownKeptTime = {5.9, 1.40e-4, 1.02e-5, 3.58e-5, 1.36e-7, 1.0, kFromCache, true, 0, 0};
+constexpr LaunchTime kShortGateUpTime = {5.95, 1.97e-4, 1.11e-5, 5.61e-5, 1.42e-7, 1.0, kFromHbm, false, 0, 0};
+constexpr LaunchTime kShortGateUpSmallTime = {6.15, 2.28e-4, 1.20e-5, 3.92e-5, 1.41e-7, 1.0, kFromCache, false, 0, 0};
+constexpr LaunchTime kFullDownTime = {4.0, 2.4e-5, 1.09e-5, 4.87e-5, 1.52e-7, 0.80, 0, true, 0, 0};
+constexpr LaunchTime kFullGateUpTime = {4.0, 1.90e-4, 7.3e-6, 2.63e-5, 2.04e-7, 0.72, 0, true, 0, 0};
+// The 128-row gate/up tiles of mom_gemm.hip.inc, two workgroups per CU, a ring of 2.5 stages each of which about one is in
+// flight: one 128 x 128 tile per CU at K = 8192 takes 95 us, in the short form 59 us.  They are looked at for launches of up
+// to two rounds with a short contraction, and of one to two rounds in several groups of token tiles: two rounds at K = 1024
+// 20.4 us, 1.75 rounds at K = 8192 in two groups 110 us, against 22.5 and 116 us in the best other form; but 1.75 rounds
+// at K = 4096 in one group 82 us against 73, and 4.6 rounds at K = 3584 190 us against 124.
+constexpr LaunchTime kPairGateUpTime = {6.6, 9.6e-5, 2.65e-5, 0, 0, 1.0, kFromHbm, false, 0, 0};
+constexpr LaunchTime kPairGateUpSmallTime = {6.6, 9.6e-5, 2.65e-5, 0, 0, 1.0, kFromCache, false, 0, 0};
+constexpr ShortShape kPairShape = {128, 128, 2, 58};
+
+// Whether weight rows x K of them leave the Infinity Cache room (142 MB do, 470 MB do not).
+inline bool weights_fit(int64_t rows, int64_t K) { return 2 * rows * K <= ((int64_t)160 << 20); }
+
+// A layer that stays in the Infinity Cache between calls (tests, small models): a quarter of it.
+inline bool small_layer(int64_t N, int64_t K) { return 6 * N * K <= ((int64_t)64 << 20); }
+
+// A launch of M token rows, contraction length K, in the tiles f of grid g; < 0: too many tiles.
+inline double launch_time(const TileGrid& g, int64_t M, int64_t K, bool gateup, ShortShape f, const LaunchTime& t, int cus) {
     if (g.tiles > (uint64_t)kMaxTiles) return -1;
     const uint32_t tiles = (uint32_t)g.tiles, full = tiles / cus, rem = tiles % cus, rounds = full + (rem ? 1 : 0);
-    // a last round on few CUs moves its operands a little faster (3584 / 16 = 224 of 256 CUs: 0.94)
-    const double moved = (K < kLongK || !rem) ? rounds : full + 0.85 + 0.15 * rem / cus;
-    // Operand rows of a tile, averaged over the token tiles.  Where the last token tile of each group is clearly
-    // shorter, a launch of one round is faster than its rows say: the CUs of that tile run ahead of the
-    // others and bring the weights into the L2 for them (512 rows in tiles of 160, 160, 160, 32 x 64:
-    // 83 us, in four of 128 x 64: 94 us; 1024 rows in two such groups x 128: 126 us, in eight of 128 x 128:
-    // 132 us, both over many passes; one pass at a time 116 and 134).  Larger tiles, which wait less for their operands, gain nothing (1280 rows in tiles of 192 x 128,
-    // the last of each group 64: 154 us, in eight of 160: 149 us).
-    double rows = (double)M / g.tiles_m + f.tn;
-    const int last = (int)(g.group_rows - (g.per_group - 1) * f.tm);
-    if (K >= kLongK && rounds == 1 && g.per_group > 1 && f.tm * f.tn <= 160 * 128)
-        rows *= 10 * last <= 4 * f.tm ? (f.tm * f.tn > 96 * 128 ? 0.92 : 0.87) : 10 * last <= 7 * f.tm ? 0.94 : 1.0;
-    const double fixed = kTileFixed + f.tm * cols * (gateup ? kTileFixedPerGateUp : kTileFixedPerDown);
-    // (with a long contraction a second workgroup on the CU only shares its loads in flight: 1 row of gate/up in 448
-    // tiles of 64 x 64 48 us, in 224 of 64 x 128 43 us)
-    const uint32_t together = K < kLongK ? f.per_cu : 1;
-    return moved * rows * K + (rounds + together - 1) / together * fixed;
+    const double moved = full + (rem ? t.last_round + (1 - t.last_round) * rem / cus : 0);
+    const double token_rows = (double)M / g.tiles_m;       // of an average tile
+    // of a round, an XCD (an eighth of the CUs) runs this many tiles: a group of token tiles by so many weight tiles
+    const uint32_t on_xcd = ((full ? (uint32_t)cus : rem) + 7) / 8, group = g.tiles_m < kTokenGroup ? g.tiles_m : kTokenGroup;
+    const double fetched = (group * token_rows + (on_xcd + group - 1) / group * f.tn) * 8 / cus;
+    const double tile_rows = t.whole_tile ? f.tm : token_rows;
+    double per_k = t.row * (tile_rows + f.tn) + t.fetched * fetched + t.product * tile_rows * f.tn;
+    if (t.lead > 0 && rounds == 1 && g.tiles_m > 1 && weights_fit(g.tiles_n * f.tn, K)) {
+        const double last = (double)(M - (int64_t)(g.tiles_m - 1) * f.tm) / f.tm;      // of the last token tile
+        const double ahead = last < 0.4 ? 1 : last < 0.72 ? (0.72 - last) / 0.32 : 0;
+        per_k *= 1 - ahead * (t.lead + t.lead_small * 64 / (f.tm + f.tn));
+    }
+    const double once = t.start + t.output * f.tm * (gateup ? f.tn / 2 : f.tn);
+    const double starts = (double)rounds / f.per_cu, body = moved * per_k;
+    const double least = (rounds + f.per_cu - 1) / f.per_cu * (f.ahead ? t.latency / f.ahead : 0);
+    return (starts > 1 ? starts : 1) * once + K * (body > least ? body : least);
 }
 
 // Whether a gate/up launch reads its weights by non-temporal loads: where one group of token tiles covers
@@ -127,13 +147,22 @@ inline bool weights_once(int64_t tiles_m, int64_t N, int64_t K, bool more_mini_s
     return tiles_m <= (more_mini_sequences ? kTokenGroup : 2) && 6 * N * K > ((int64_t)256 << 20);
 }
 
-// The short form with the least cost; its cost in `cost`; -1: none.
-inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, int cus, double& cost) {
+// Whether W_down is taken to be in the Infinity Cache: that of a small layer, or (later: from mini-sequence kKeptFrom of a
+// call on) from the mini-sequence before, where the layer fits or the gate/up launch passes it by (one group of 256-row
+// token tiles, as above) and it leaves room.  Down by mini-sequence, other weights in each call: 512 rows in tiles of 128 x 64
+// 97, 93, 72, 72 ... us (of 160 x 64 92, 92, 91, 91); 256 rows in 64 x 64 70, 65, 45, 45 (of 80 x 64 58, 55, 53, 53).
+constexpr int kKeptFrom = 2;
+inline bool kept_down(int64_t M, int64_t N, int64_t K, bool later) {
+    return small_layer(N, K) || (later && (6 * N * K <= ((int64_t)256 << 20) || (M <= 256 * kTokenGroup && weights_fit(N, K))));
+}
+
+// The short form that takes the least time; its time in `least`; -1: none.
+inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, const LaunchTime& time, int cus, double& least) {
     int best = -1;
     for (int i = 0; i < short_forms(gateup); ++i) {
         const ShortShape f = short_shape(gateup, i);
-        const double c = moved_cost(short_grid(M, N, gateup, f), M, K, gateup, f, cus);
-        if (c >= 0 && (best < 0 || c < cost)) { best = i; cost = c; }
+        const double t = launch_time(tile_grid(M, N, gateup, f), M, K, gateup, f, time, cus);
+        if (t >= 0 && (best < 0 || t < least)) { best = i; least = t; }
     }
     return best;
 }
@@ -154,11 +183,11 @@ struct Launch {
 };
 inline Launch short_launch(int64_t M, int64_t N, bool gateup, int form) {
     const ShortShape f = short_shape(gateup, form);
-    const TileGrid g = short_grid(M, N, gateup, f);
+    const TileGrid g = tile_grid(M, N, gateup, f);
     return {g.tiles > 0 && g.tiles <= (uint64_t)kMaxTiles ? kShortTiles : kRefused, form, f.tm, f.tn, 0, g, {}};
 }
 inline Launch whole_launch(int64_t M, int64_t N, bool gateup, int tm, int tn) {
-    const TileGrid g = whole_tiles(M, N, tm, gateup ? tn / 2 : tn);
+    const TileGrid g = tile_grid(M, N, gateup, {tm, tn, 1, 0});
     return {g.tiles > 0 && g.tiles <= (uint64_t)kMaxTiles ? kWholeTiles : kRefused, 0, tm, tn, 0, g, {}};
 }
 
@@ -166,10 +195,6 @@ inline Launch whole_launch(int64_t M, int64_t N, bool gateup, int tm, int tn) {
 // whole rounds), and the mix has to save this much of the modelled time before it is used.
 constexpr int kGateUpNarrowPerMille = 1070;
 constexpr int kGateUpMixMinGainPerMille = 15;
-// Weight rows of the 256-row tiles of the down projection, and what a narrower tile costs per column (measured).
-constexpr int kDownWidths[5] = {256, 224, 192, 160, 128};
-constexpr int kDownWidthPerMille[5] = {1000, 1020, 1070, 1170, 1310};
-
 // Rounds of the CUs a launch of `tiles` 256-row tiles takes, in 1/1000.  A last round that fills only part of the
 // CUs is not as dear as a whole one: the chip is power-limited and clocks the busy CUs higher (measured:
 // a round on a quarter / half / three quarters of the CUs takes about 0.55 / 0.8 / 0.8-0.9 of a full one).
@@ -177,54 +202,51 @@ inline int64_t rounds_per_mille(int64_t tiles, int cus) {
     const int64_t full = tiles / cus, rem = tiles % cus;
     return full * 1000 + (rem ? 500 + 500 * rem / cus : 0);
 }
-// The cost of 256-row tiles that the matrix cores bound, in the units of the short forms: c = rounds x columns in 1e-6.
-inline double full_cost(int64_t c, int64_t tiles, int64_t K, bool gateup, int cus) {
-    return 1e-6 * c / (gateup ? 128 : 256) * kFullTileRows * K + (tiles + cus - 1) / cus * kFullTileFixed;
-}
-// ... of the down projection in tiles w weight rows wide; a narrow one is bound by its operands, too (1536 rows x
-// 3584 columns: 233 us in tiles 128 wide).
-inline double whole_down_cost(int64_t M, int64_t N, int64_t K, int w, int64_t c, int cus) {
-    const TileGrid g = whole_tiles(M, N, 256, w);
-    const double moved = moved_cost(g, M, K, false, {256, w, 1}, cus), full = full_cost(c, (int64_t)g.tiles, K, false, cus);
-    return full > moved ? full : moved;
-}
-
-// Down projection with 256-row tiles: 256, 224, 192, 160 or 128 weight rows per tile, whichever needs the least time
-// in rounds of the CUs (rounds x width, a narrower tile charged more per column for the token fragments it shares
-// among fewer MFMAs, a partly filled last round less than a whole one): 3584 output columns with 32 token tiles are
-// 1.75 rounds of 256-wide tiles on 256 CUs but exactly 2 rounds of 224-wide ones, and the 128 full-size tiles of a
-// 2048-row mini-sequence at 4096 columns are one round of 256 tiles 128 wide.
-// Few tiles: the short forms where their cost is lower.  Then the operand rows that a CU moves count, and the best
-// form is the one that gives every CU one tile with the fewest of them.
+// Down projection: 256-row tiles of 256, 224, 192, 160 or 128 weight rows, or the short forms, whatever takes the least time:
+// 3584 output columns with 32 token tiles are 1.75 rounds of 256-wide tiles on 256 CUs but exactly 2 rounds of
+// 224-wide ones, and the 128 full-size tiles of a 2048-row mini-sequence at 4096 columns are one round of 256 tiles 128 wide.
+// With few token rows the operand rows that a CU moves count, and the best form is the one that gives every CU one
+// tile with the fewest of them.
 // Both sides are priced on the grid that runs: 2400 rows x 4096 columns are 220 tiles of 256 x 192 = one round, 223 us,
 // against two rounds of 160 x 128, 276 us (2700 rows 231 and 302, 4300 402 and 463, 5500 461 and 595 us).
-// full_tiles: tiles of 256 x 256 however few (beside a gate/up kernel that fills the chip).
-inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool full_tiles) {
-    if (whole_tiles(M, N, 256, 256).tiles > (uint64_t)kMaxTiles) return {kRefused, 0, 0, 0, 0, {}, {}};
-    if (full_tiles) return whole_launch(M, N, false, 256, 256);
+// later: see kept_down.  full_tiles: tiles of 256 x 256 however few (beside a gate/up kernel
+// that fills the chip).
+inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool later, bool full_tiles) {
+    const Launch full = whole_launch(M, N, false, 256, 256);
+    if (full.kind == kRefused || full_tiles) return full;
+    double least = 0, time = 0;
+    const LaunchTime& short_time = kept_down(M, N, K, later) ? kShortDownKeptTime : kShortDownTime;
+    const int form = choose_short_form(M, N, K, false, short_time, cus, least);
+    // The width: by time where the widest take no more than one round; over several rounds by rounds x columns, a column of
+    // a narrower tile charged what it was measured to cost more for the token fragments it shares among fewer MFMAs
+    // (12400 rows x 4096 columns: 3.6 rounds of 224-wide tiles 1033 us, 5 of 160-wide ones 1113 us).
+    constexpr int per_mille[5] = {1000, 1020, 1070, 1170, 1310};
     int width = 0;
-    int64_t cost = 0;                    // rounds x columns of 256 x 256 tiles, in 1e-6
+    int64_t columns = 0;
     for (int i = 0; i < 5; ++i) {
-        const int w = kDownWidths[i];
-        const int64_t c = rounds_per_mille((int64_t)whole_tiles(M, N, 256, w).tiles, cus) * w * kDownWidthPerMille[i];
-        if (width == 0 || c < cost) { cost = c; width = w; }
+        const int w = 256 - 32 * i;
+        const ShortShape f = {256, w, 1, 0};
+        const TileGrid g = tile_grid(M, N, false, f);
+        const double t = launch_time(g, M, K, false, f, kFullDownTime, cus);
+        const int64_t c = rounds_per_mille((int64_t)g.tiles, cus) * w * per_mille[i];
+        if (t < 0) continue;
+        if (width == 0 || (full.grid.tiles > (uint64_t)cus ? c < columns : t < time)) { width = w; time = t; columns = c; }
     }
-    double least = 0;
-    const int form = choose_short_form(M, N, K, false, cus, least);
-    if (form >= 0 && least < whole_down_cost(M, N, K, width, cost, cus)) return short_launch(M, N, false, form);
+    if (form >= 0 && least < time) return short_launch(M, N, false, form);
     return whole_launch(M, N, false, 256, width);
 }
 
 // Gate/up with 256-row tiles: the first columns in tiles of 128 columns, the rest in tiles of 96, in one launch of
 // the two-width kernel, where the same model says that saves time: 14336 columns with 12 token tiles are 1344 tiles
 // = 5.25 rounds, but 64 x 128 + 64 x 96 columns are three rounds of each width.
-// Few tiles: the short forms, as for the down projection.  A short contraction: 128-row tiles, two workgroups per CU,
-// by the same cost.
+// Few token rows: the short forms, as for the down projection.  Or 128 x 128 tiles, two workgroups per CU, by the same
+// comparison.
 inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus) {
     const Launch plain_launch = whole_launch(M, N, true, 256, 256);
     if (plain_launch.kind == kRefused) return plain_launch;
     double least = 0;
-    const int form = choose_short_form(M, N, K, true, cus, least);
+    const bool small = small_layer(N, K);
+    const int form = choose_short_form(M, N, K, true, small ? kShortGateUpSmallTime : kShortGateUpTime, cus, least);
     // b column tiles of 96 behind a of 128: a = ceil((N - 96 b) / 128); time = rounds x columns per tile
     const int64_t tm = plain_launch.grid.tiles_m;
     auto mix_cost = [&](int64_t b) {
@@ -233,23 +255,28 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus) {
     };
     const int64_t plain = mix_cost(0);
     int64_t cost = plain, narrow_tiles_n = 0;
+    const double plain_time = launch_time(plain_launch.grid, M, K, true, {256, 256, 1, 0}, kFullGateUpTime, cus);
     // (no mix takes less than half of what the plain tiles take: where the short form does, it is not looked for)
-    const bool few = form >= 0 && least < 0.5 * full_cost(plain, 1, K, true, cus);
+    const bool few = form >= 0 && least < 0.5 * plain_time;
     for (int64_t b = 1; b <= (N + 95) / 96 && !few; ++b) {
         const int64_t c = mix_cost(b);
         if (c < cost && c * 1000 <= plain * (1000 - kGateUpMixMinGainPerMille)) { cost = c; narrow_tiles_n = b; }
     }
-    if (form >= 0) {
-        const double full = full_cost(cost, (int64_t)plain_launch.grid.tiles, K, true, cus);
-        const Launch whole128 = whole_launch(M, N, true, 128, 128);
-        const double cost128 = moved_cost(whole128.grid, M, K, true, {128, 128, 2}, cus);
-        if (cost128 >= 0 && cost128 < full && cost128 < least) return whole128;
-        if (least < full) return short_launch(M, N, true, form);
-    }
     const int64_t rest = N - 96 * narrow_tiles_n, wide_cols = rest > 0 ? (rest + 127) / 128 * 128 : 0;
+    double full = plain_time * cost / plain;
+    if (wide_cols == 0)
+        full = launch_time(tile_grid(M, N, true, {256, 192, 1, 0}), M, K, true, {256, 192, 1, 0}, kFullGateUpTime, cus);
+    const Launch pair = whole_launch(M, N, true, 128, 128);
+    if (pair.kind != kRefused && pair.grid.tiles <= 2 * (uint64_t)cus &&
+        (K <= 2048 || (pair.grid.tiles_m > (uint32_t)kTokenGroup && pair.grid.tiles > (uint64_t)cus))) {
+        const double t = launch_time(pair.grid, M, K, true, kPairShape, small ? kPairGateUpSmallTime : kPairGateUpTime, cus);
+        if (t < full && (form < 0 || t < least)) return pair;
+    }
+    if (form >= 0 && least < full) return short_launch(M, N, true, form);
     if (narrow_tiles_n == 0 || wide_cols >= N) return plain_launch;
     if (wide_cols == 0) return whole_launch(M, N, true, 256, 192);
-    Launch l = {kTwoWidths, 0, 256, 256, wide_cols, whole_tiles(M, wide_cols, 256, 128), whole_tiles(M, N - wide_cols, 256, 96)};
+    Launch l = {kTwoWidths, 0, 256, 256, wide_cols, tile_grid(M, wide_cols, true, {256, 256, 1, 0}),
+                tile_grid(M, N - wide_cols, true, {256, 192, 1, 0})};
     if (l.grid.tiles > (uint64_t)kMaxTiles || l.narrow.tiles > (uint64_t)kMaxTiles) l.kind = kRefused;
     return l;
 }

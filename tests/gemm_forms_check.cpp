@@ -8,7 +8,7 @@
 static int bad = 0;
 #define CHECK(c, ...) do { if (!(c)) { printf("FAILED %s: ", #c); printf(__VA_ARGS__); printf("\n"); ++bad; } } while (0)
 
-static void form(bool gu, int tm, int tn, int wm, int wn, int ksub, int nstg) {
+static void form(bool gu, int f, int tm, int tn, int wm, int wn, int ksub, int nstg) {
     const int stage = ksub * (tm + tn) * 128, loads = ksub * (tm + tn) / 32;
     const int cols = gu ? tn / 2 : tn;
     CHECK(nstg * stage <= 163840 && stage <= 65536 && nstg >= 2, "ring of %d x %d", tm, tn);
@@ -17,9 +17,8 @@ static void form(bool gu, int tm, int tn, int wm, int wn, int ksub, int nstg) {
     CHECK(!gu || (tn / 16 / wn) % 2 == 0, "gate and up blocks of %d x %d", tm, tn);
     CHECK((ksub * tm) % 32 == 0 && (ksub * tn) % (gu ? 64 : 32) == 0, "loads per wavefront of %d x %d", tm, tn);
     CHECK(tm * (cols * 2 + 16) <= nstg * stage, "epilogue of %d x %d", tm, tn);
-    const int f = momk::find_short_form(gu, tm, tn);
-    CHECK(f >= 0 && momk::short_shape(gu, f).per_cu >= 1 && momk::short_shape(gu, f).per_cu * nstg * stage <= 163840,
-          "workgroups per CU of %d x %d", tm, tn);
+    const momk::ShortShape s = momk::short_shape(gu, f);
+    CHECK(s.tm == tm && s.tn == tn && s.per_cu >= 1 && s.per_cu * nstg * stage <= 163840, "workgroups per CU of %d x %d", tm, tn);
     // Every 1-KiB block of a stage is loaded once, to a place of its own: the kernel's mapping of wavefront and
     // load index to sub-tile and row
     bool seen[2][16][64] = {};                        // [operand][sub][row / 8]
@@ -43,50 +42,69 @@ static void form(bool gu, int tm, int tn, int wm, int wn, int ksub, int nstg) {
         }
 }
 
-// The kernels' walk over the token tiles of a grid covers every row once, with a tile of its own for each count that
-// the grid states (and that its cost was reckoned with).
-static void rows(int64_t M, int tm, const momk::TileGrid& t, bool spread) {
-    CHECK(t.per_group <= momk::kTokenGroup, "groups of M=%lld tm=%d", (long long)M, tm);
+// The kernels' walk over the tiles of a grid covers every token row once, with a tile of its own for each count that the
+// grid states (and that its time was reckoned with): tile i starts at row i tm.
+static void rows(int64_t M, int tm, const momk::TileGrid& t) {
     int64_t next = 0;
     for (int64_t i = 0; i < t.tiles_m; ++i) {
-        const int64_t grp = i / t.per_group, m0 = grp * t.group_rows + (i % t.per_group) * tm;
-        const int64_t in_group = spread ? t.group_rows - (i % t.per_group) * tm : tm;
-        const int64_t end = m0 + (M - m0 < in_group ? M - m0 : in_group);
+        const int64_t m0 = i * tm, end = m0 + (M - m0 < tm ? M - m0 : tm);
         CHECK(m0 == next && m0 < end && m0 <= 0x7fffffff, "tile %lld of M=%lld tm=%d", (long long)i, (long long)M, tm);
-        next = m0 + tm < end ? m0 + tm : end;
+        next = end;
     }
     CHECK(next == M, "rows of M=%lld tm=%d", (long long)M, tm);
+    CHECK(t.tiles == (uint64_t)t.tiles_m * t.tiles_n, "tiles of M=%lld tm=%d", (long long)M, tm);
 }
 
 // What choose_down picks at these sizes, against every launch there is, each priced on the grid that runs.
 static int64_t rounds(const momk::TileGrid& g, int cus) { return ((int64_t)g.tiles + cus - 1) / cus; }
-static void down_choice(int64_t M, int64_t N, int64_t K, int cus) {
-    const momk::Launch l = momk::choose_down(M, N, K, cus, false);
+static void down_choice(int64_t M, int64_t N, int64_t K, int cus, bool more) {
+    const momk::Launch l = momk::choose_down(M, N, K, cus, more, false);
     CHECK(l.kind == momk::kShortTiles || l.kind == momk::kWholeTiles, "down M=%lld N=%lld", (long long)M, (long long)N);
     if (l.kind == momk::kWholeTiles) return;
     // With a long contraction a 256-row tile takes at most a little more than a short one of the same width, so short
     // tiles that need more rounds than 256-row tiles no wider than 192 are never the faster ones (measured at 2400 ... 5500 rows).
     for (int w : {192, 160, 128})
-        CHECK(K < momk::kLongK || l.tm * l.tn < 160 * 128 || rounds(l.grid, cus) <= rounds(momk::whole_tiles(M, N, 256, w), cus),
+        CHECK(l.tm * l.tn < 160 * 128 || rounds(l.grid, cus) <= rounds(momk::tile_grid(M, N, false, {256, w, 1, 0}), cus),
               "down M=%lld N=%lld K=%lld: %d x %d in %lld rounds, 256 x %d in %lld", (long long)M, (long long)N, (long long)K, l.tm, l.tn,
-              (long long)rounds(l.grid, cus), w, (long long)rounds(momk::whole_tiles(M, N, 256, w), cus));
+              (long long)rounds(l.grid, cus), w, (long long)rounds(momk::tile_grid(M, N, false, {256, w, 1, 0}), cus));
+}
+
+// Neighbouring row counts don't alternate between two launches.
+static void steady(int64_t N, int64_t K, bool gateup) {
+    momk::Launch before = {}, last = {};
+    int64_t since = 0;
+    auto same = [](const momk::Launch& a, const momk::Launch& b) {
+        return a.kind == b.kind && a.form == b.form && a.tm == b.tm && a.tn == b.tn && a.wide_cols == b.wide_cols;
+    };
+    for (int64_t M = 1; M <= 8192; ++M) {
+        const momk::Launch l = gateup ? momk::choose_gateup(M, N, K, 256) : momk::choose_down(M, N, K, 256, false, false);
+        if (M > 1 && same(l, last)) continue;
+        CHECK(!since || !same(l, before) || M - since >= 4, "M=%lld N=%lld K=%lld: %d x %d between two runs of %d x %d", (long long)since,
+              (long long)N, (long long)K, last.tm, last.tn, l.tm, l.tn);
+        before = last;
+        last = l;
+        since = M;
+    }
 }
 
 int main() {
     for (int tm = 16; tm <= 256; tm += 16)
-        for (int64_t M = 1; M < 5000; M += 1 + M / 97) rows(M, tm, momk::spread_tiles(M, 32, tm, 32), true);
-    rows(0x7fffff00, 256, momk::spread_tiles(0x7fffff00, 32, 256, 32), true);
-    rows(0x7fffff00, 256, momk::whole_tiles(0x7fffff00, 32, 256, 32), false);
+        for (int64_t M = 1; M <= 16384; M += 1 + M / 97) rows(M, tm, momk::tile_grid(M, 32, false, {tm, 32, 1, 0}));
+    rows(0x7fffff00, 256, momk::tile_grid(0x7fffff00, 32, false, {256, 32, 1, 0}));
     for (int64_t M = 1; M <= 16384; ++M) {
-        rows(M, 256, momk::whole_tiles(M, 32, 256, 32), false);
-        rows(M, 128, momk::whole_tiles(M, 32, 128, 32), false);
-        down_choice(M, 4096, 14336, 256);
-        down_choice(M, 3584, 18944, 256);
-        down_choice(M, 8192, 28672, 256);
+        for (bool more : {false, true}) down_choice(M, 4096, 14336, 256, more);
+        for (bool more : {false, true}) down_choice(M, 3584, 18944, 256, more);
+        for (bool more : {false, true}) down_choice(M, 8192, 28672, 256, more);
         CHECK(momk::choose_gateup(M, 14336, 4096, 256).kind != momk::kRefused, "gate/up M=%lld", (long long)M);
     }
-#define D(TM, TN, WM, WN, KSUB, NSTG) form(false, TM, TN, WM, WN, KSUB, NSTG);
-#define G(TM, TN, WM, WN, KSUB, NSTG) form(true, TM, TN, WM, WN, KSUB, NSTG);
+    const int64_t layers[][2] = {{4096, 14336}, {3584, 18944}, {1056, 2080}, {256, 1024}};
+    for (const auto& l : layers) {
+        steady(l[0], l[1], false);
+        steady(l[1], l[0], true);
+    }
+    int down_form = 0, gateup_form = 0;
+#define D(TM, TN, WM, WN, KSUB, NSTG) form(false, down_form++, TM, TN, WM, WN, KSUB, NSTG);
+#define G(TM, TN, WM, WN, KSUB, NSTG) form(true, gateup_form++, TM, TN, WM, WN, KSUB, NSTG);
     MOM_SHORT_FORMS_DOWN(D)
     MOM_SHORT_FORMS_GATEUP(G)
     const int64_t Ms[] = {1, 15, 16, 17, 61, 128, 317, 1000, 4096, 131071, 1 << 20, 0x7fffff00};
@@ -98,16 +116,16 @@ int main() {
                 for (bool gu : {false, true})
                     for (int cus : {1, 80, 256, 304}) {
                         double cost = -1;
-                        const int f = momk::choose_short_form(M, N, K, gu, cus, cost);
+                        const momk::LaunchTime& t = gu ? momk::kShortGateUpTime : momk::kShortDownTime;
+                        const int f = momk::choose_short_form(M, N, K, gu, t, cus, cost);
                         ++n;
                         if (f < 0) { CHECK(M > 1 << 20, "no form for M=%lld N=%lld", (long long)M, (long long)N); continue; }
                         CHECK(f < momk::short_forms(gu) && std::isfinite(cost) && cost > 0, "choice");
                         const momk::ShortShape s = momk::short_shape(gu, f);
-                        const int64_t cols = gu ? s.tn / 2 : s.tn;
-                        CHECK((int64_t)momk::spread_tiles(M, N, s.tm, cols).tiles <= momk::kMaxTiles, "tiles");
+                        CHECK((int64_t)momk::tile_grid(M, N, gu, s).tiles <= momk::kMaxTiles, "tiles");
                         for (int i = 0; i < momk::short_forms(gu); ++i) {
                             const momk::ShortShape o = momk::short_shape(gu, i);
-                            const double c = momk::moved_cost(momk::short_grid(M, N, gu, o), M, K, gu, o, cus);
+                            const double c = momk::launch_time(momk::tile_grid(M, N, gu, o), M, K, gu, o, t, cus);
                             CHECK(c < 0 || cost <= c, "least cost: M=%lld N=%lld K=%lld form %d", (long long)M, (long long)N, (long long)K, i);
                         }
                     }

@@ -22,11 +22,13 @@ def test_forms_and_choice(tmp_path):
 
 
 @pytest.mark.parametrize("old,new,says", [
-    # the 256-row tiles priced on the grid of the short forms, which is not the one they run on
-    ("    const TileGrid g = whole_tiles(M, N, 256, w);\n    const double moved", "    const TileGrid g = spread_tiles(M, N, 256, w);\n    const double moved",
-     "M=2400 N=4096"),
-    # the last, shorter tile of a group forgotten
-    ("        g.per_group = (g.group_rows + tm - 1) / tm;", "        g.per_group = g.group_rows / tm;", "tile 2 of M="),
+    # the 256-row tiles priced on a grid of more tiles than they run on
+    ("        const TileGrid g = tile_grid(M, N, false, f);\n        const double t = launch_time(g,",
+     "        const TileGrid g = tile_grid(M + M / 4, N, false, f);\n        const double t = launch_time(g,", "rounds, 256 x"),
+    # the last, shorter token tile forgotten
+    ("const uint32_t tm = ((uint32_t)M + f.tm - 1) / f.tm,", "const uint32_t tm = M < f.tm ? 1 : (uint32_t)M / f.tm,", "rows of M="),
+    # a step in the time of a launch: neighbouring row counts alternate between forms
+    ("last < 0.72 ? (0.72 - last) / 0.32 : 0;", "last < 0.72 ? (M & 1) : 0;", "between two runs of"),
 ])
 def test_a_planted_mistake_is_caught(tmp_path, old, new, says):
     """Planted in a copy of the header, on the CPU."""
