@@ -1,0 +1,75 @@
+"""Register allocation of the GEMM kernels, from the metadata of the library as built here.  Their MFMAs are assembler
+statements on ACC registers, whose wait states the compiler does not know: it must never put anything else there (a fragment
+that finds no VGPR, moved through an ACC register in front of an MFMA, gave wrong bits), nor spill."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2504_12526_amd", "libmom.so")
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _code_object():
+    """The gfx950 code object in the library: a bundle is a magic, the number of entries, and for each its offset from
+    the magic, size and target."""
+    data = open(LIB, "rb").read()
+    at = data.index(MAGIC)
+    n, = struct.unpack_from("<Q", data, at + 24)
+    p = at + 32
+    for _ in range(n):
+        offset, size, length = struct.unpack_from("<QQQ", data, p)
+        target = data[p + 24:p + 24 + length]
+        p += 24 + length
+        if b"gfx950" in target:
+            return data[at + offset:at + offset + size]
+    raise AssertionError("no gfx950 code object")
+
+
+def _kernels(tmp_path):
+    co = os.path.join(str(tmp_path), "mom.co")
+    with open(co, "wb") as f:
+        f.write(_code_object())
+    notes = subprocess.run([READELF, "--notes", co], capture_output=True, text=True, check=True).stdout
+    found = {}
+    for block in notes.split("  - .agpr_count:")[1:]:
+        v = {k: int(x) for k, x in re.findall(r"\.(vgpr_count|vgpr_spill_count|sgpr_spill_count|private_segment_fixed_size):\s+(\d+)", block)}
+        v["agpr"] = int(block.split()[0])
+        found[re.search(r"\.name:\s+(\S+)", block)[1]] = v
+    return found
+
+
+def accumulators(name):
+    """ACC registers of the accumulator blocks of a GEMM kernel, by its template arguments; None: another kernel."""
+    m = re.search(r"17gemm_short_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", name)
+    if m:
+        _, tm, tn, wm, wn = map(int, m.groups())
+        return 4 * (tm // 16 // wm) * (tn // 16 // wn)
+    m = re.search(r"12gemm4_kernelILi\d+ELi(\d+)ELi(\d+)E", name)
+    if m:
+        return 4 * (int(m[1]) // 32) * (int(m[2]) // 32)
+    return 4 * 8 * 8 if "gemm4_two_width_kernel" in name else None
+
+
+def unsound(kernels):
+    return [(n, v) for n, v in kernels.items() if accumulators(n) is not None and
+            (v["agpr"] != accumulators(n) or v["vgpr_spill_count"] or v["sgpr_spill_count"] or v["private_segment_fixed_size"])]
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="llvm-readelf is not installed")
+def test_acc_registers_hold_the_accumulators_and_nothing_else(tmp_path):
+    if not os.path.exists(LIB):
+        from paper_2504_12526_amd import build
+        build.build()
+    kernels = _kernels(tmp_path)
+    gemms = [n for n in kernels if accumulators(n) is not None]
+    assert len(gemms) >= 20 + 2 * 16 + 5 + 5, gemms        # short: down, gate/up x 2; 256-row and 128-row tiles
+    assert not unsound(kernels), unsound(kernels)
+    # the check sees one register too many, and a spill
+    for key in ("agpr", "vgpr_spill_count"):
+        planted = {gemms[0]: dict(kernels[gemms[0]], **{key: kernels[gemms[0]][key] + 4})}
+        assert unsound(planted)
