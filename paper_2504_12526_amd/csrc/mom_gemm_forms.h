@@ -170,7 +170,7 @@ inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, const
 // How a launch runs.  All forms give identical bits (every output element sees the same MFMA sequence over k), so
 // the choice is free.
 enum LaunchKind {
-    kRefused,        // too many tiles for 32-bit tile numbers
+    kRefused,        // no such form, or too many tiles for 32-bit tile numbers
     kShortTiles,     // gemm_short_kernel, form `form`
     kWholeTiles,     // gemm4_kernel: tiles of tm token rows x tn staged weight rows
     kTwoWidths       // gemm4_two_width_kernel: columns [0, wide_cols) in 256 x 256 tiles (`grid`), the rest in 256 x 192 (`narrow`)
@@ -182,6 +182,7 @@ struct Launch {
     TileGrid grid, narrow;
 };
 inline Launch short_launch(int64_t M, int64_t N, bool gateup, int form) {
+    if (form < 0 || form >= short_forms(gateup)) return {kRefused, 0, 0, 0, 0, {}, {}};
     const ShortShape f = short_shape(gateup, form);
     const TileGrid g = tile_grid(M, N, gateup, f);
     return {g.tiles > 0 && g.tiles <= (uint64_t)kMaxTiles ? kShortTiles : kRefused, form, f.tm, f.tn, 0, g, {}};

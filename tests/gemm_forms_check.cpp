@@ -102,6 +102,10 @@ int main() {
         steady(l[0], l[1], false);
         steady(l[1], l[0], true);
     }
+    // a form that is not there is an error, not a launch of nothing
+    for (bool gu : {false, true})
+        for (int f : {-1, momk::short_forms(gu)})
+            CHECK(momk::short_launch(100, 256, gu, f).kind == momk::kRefused, "form %d", f);
     int down_form = 0, gateup_form = 0;
 #define D(TM, TN, WM, WN, KSUB, NSTG) form(false, down_form++, TM, TN, WM, WN, KSUB, NSTG);
 #define G(TM, TN, WM, WN, KSUB, NSTG) form(true, gateup_form++, TM, TN, WM, WN, KSUB, NSTG);
