@@ -102,6 +102,18 @@ int main() {
         steady(l[0], l[1], false);
         steady(l[1], l[0], true);
     }
+    // What the GPU tests take for granted about the choice: launches of two widths, the second ring of gate/up 64 x 64.
+    const int64_t two[][3] = {{1024, 128, 14336}, {1000, 96, 14304}, {2048, 64, 14336}, {1280, 128, 10112}};
+    for (const auto& t : two) {
+        const momk::Launch l = momk::choose_gateup(t[0], t[2], t[1], 256);
+        CHECK(l.kind == momk::kTwoWidths && l.wide_cols > 0 && l.wide_cols < t[2], "gate/up M=%lld N=%lld", (long long)t[0], (long long)t[2]);
+    }
+    const int64_t ring[][3] = {{33, 8192, 7168}, {61, 8192, 7168}, {100, 8192, 3584}};
+    for (const auto& t : ring) {
+        const momk::Launch l = momk::choose_gateup(t[0], t[2], t[1], 256);
+        CHECK(l.kind == momk::kShortTiles && l.tm == 64 && l.tn == 64 && l.form != momk::find_short_form(true, 64, 64),
+              "gate/up M=%lld N=%lld", (long long)t[0], (long long)t[2]);
+    }
     // a form that is not there is an error, not a launch of nothing
     for (bool gu : {false, true})
         for (int f : {-1, momk::short_forms(gu)})

@@ -1,5 +1,6 @@
 """The GEMM forms for few token rows on the GPU: every form against the 256-row tiles bit for bit at the edges of its
-tiles and with every length of the final, shorter stage; the library's own choice at production contraction lengths."""
+tiles, over several groups of token tiles, with every length of the final, shorter stage, and with weights by non-temporal
+loads; the library's own choice at production contraction lengths."""
 import os
 import re
 
@@ -13,7 +14,9 @@ pytestmark = pytest.mark.gpu
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 _TEXT = open(os.path.join(ROOT, "paper_2504_12526_amd", "csrc", "mom_gemm_forms.h")).read()
-FORMS = sorted({tuple(int(v) for v in f.split(",")[:2]) for f in re.findall(r"X\(([\d, ]+)\)", _TEXT)})
+_SHAPES = {d: sorted({tuple(int(v) for v in f.split(",")[:2]) for f in re.findall(r"X\(([\d, ]+)\)", t)})
+           for d, t in re.findall(r"#define MOM_SHORT_FORMS_(DOWN|GATEUP)\(X\)((?:.*\\\n)*.*\n)", _TEXT)}
+FORMS = sorted(set(_SHAPES["DOWN"] + _SHAPES["GATEUP"]))
 
 
 @pytest.fixture
@@ -28,12 +31,12 @@ def _inputs(S, H, I, seed, std):
     return synth.mlp_inputs(wl, device="cuda")
 
 
-def _run(x, wg, wu, wd):
-    """out and the intermediate, both poisoned before."""
+def _run(x, wg, wu, wd, mini_seq=0):
+    """out and the intermediate (of the last mini-sequence), both poisoned before."""
     S, I = x.shape[0], wg.shape[0]
     out = torch.full_like(x, float("nan"))
-    ws = torch.full((S * I,), float("nan"), dtype=torch.bfloat16, device=x.device)
-    binding.mom_mlp_prefill(x, wg, wu, wd, 0, out, ws)
+    ws = torch.full(((mini_seq or S) * I,), float("nan"), dtype=torch.bfloat16, device=x.device)
+    binding.mom_mlp_prefill(x, wg, wu, wd, mini_seq, out, ws)
     return out.view(torch.int16), ws.view(torch.int16)
 
 
@@ -47,10 +50,10 @@ def _full_tiles(*t):
 
 @pytest.mark.parametrize("tm,tn", FORMS)
 def test_form_gives_the_bits_of_the_full_tiles(tm, tn, short_form):
-    # rows around one and two token tiles; K = 32 (nothing but a final stage) ... several turns of the ring, with
-    # final stages of 32 ... 224 elements; columns that end inside a tile
+    # rows around one and two token tiles and over two and three groups of four of them; K = 32 (nothing but a final
+    # stage) ... several turns of the ring, with final stages of 32 ... 224 elements; columns that end inside a tile
     for S, H, I in ((1, 64, 32), (tm - 1 or 1, 32, 96), (tm, 160, 224), (tm + 1, 288, 352), (2 * tm + 5, 1056, 480),
-                    (2 * tm - 3, 736, 2080)):
+                    (2 * tm - 3, 736, 2080), (4 * tm + 1, 160, 288), (4 * tm + tm // 2 + 3, 352, 416), (9 * tm + 7, 96, 160)):
         t = _inputs(S, H, I, S + H, 0.05)
         ref = _full_tiles(*t)
         short_form(tm, tn)
@@ -58,6 +61,42 @@ def test_form_gives_the_bits_of_the_full_tiles(tm, tn, short_form):
         torch.cuda.synchronize()
         assert torch.equal(got[1], ref[1]), f"intermediate S={S} H={H} I={I}"
         assert torch.equal(got[0], ref[0]), f"out S={S} H={H} I={I}"
+
+
+@pytest.fixture(scope="module")
+def large_layer():
+    """Weights of 336 MiB, which a launch of few token tiles reads past the Infinity Cache."""
+    wl = synth.Workload("large", S=1024, H=8192, I=7168, mini_seq=0, seed=7, w_std=0.02)
+    return synth.mlp_inputs(wl, device="cuda")
+
+
+@pytest.mark.parametrize("tm,tn", _SHAPES["GATEUP"])
+def test_gate_up_form_with_non_temporal_weights(tm, tn, large_layer, short_form):
+    # a call of one mini-sequence: at most two token tiles; of several: four, the last mini-sequence shorter
+    x, *w = large_layer
+    for S, mini_seq in ((1, 0), (tm + 5, 0), (min(4 * tm + 9, 1024), min(4 * tm - 3, 600))):
+        t = (x[:S].contiguous(), *w)
+        ref = _full_tiles(*t)
+        short_form(tm, tn)
+        got = _run(*t, mini_seq)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], ref[0]), f"out S={S} mini_seq={mini_seq}"
+        if not mini_seq:
+            assert torch.equal(got[1], ref[1]), f"intermediate S={S}"
+
+
+def test_the_second_ring_of_the_64_row_gate_up_form(large_layer, short_form):
+    # chosen at these sizes, with weights by non-temporal and by plain loads (tests/gemm_forms_check.cpp says so)
+    x, wg, wu, wd = large_layer
+    for S, I in ((33, 7168), (61, 7168), (100, 3584)):
+        t = (x[:S].contiguous(), wg[:I].contiguous(), wu[:I].contiguous(), wd[:, :I].contiguous())
+        ref = _full_tiles(*t)
+        got = _run(*t)
+        torch.cuda.synchronize()
+        assert torch.equal(got[1], ref[1]) and torch.equal(got[0], ref[0]), f"S={S} I={I}"
+        r = oracle.mlp_rows(*(synth.bits(a) for a in (t[0][:8], *t[1:])))
+        g = got[0][:8].view(torch.bfloat16).float().cpu().numpy()
+        assert abs(g - r).max() <= 2e-2 * abs(r).max()          # the bar of the parity tests
 
 
 @pytest.mark.parametrize("name", ["llama3_8b_32k", "qwen25_7b_256k"])
