@@ -82,13 +82,13 @@ def forced_pipeline():
 
 @pytest.fixture
 def gemm_form():
-    """Callable (edge, slots) that forces a tile form of the matrix-core kernels; the library's own
-    choice is restored afterwards."""
+    """Callable (edge, ring slots, width) that forces a tile form of the matrix-core kernels; the library's
+    own choice is restored afterwards."""
     yield binding.mom_debug_force_gemm_form
     binding.mom_debug_force_gemm_form(0, 0, 0)
 
 
-FORMS = ((256, 5), (128, 5), (128, 10), (64, 5), (64, 10), (64, 20),
+FORMS = ((256, 5), (128, 5), (64, 5),
          # 256-row tiles with 224 ... 128 weight rows for the down projection (192: also 96-column gate/up tiles)
          (256, 5, 224), (256, 5, 192), (256, 5, 160), (256, 5, 128))
 
@@ -611,7 +611,7 @@ def _full_size_case(name, sweep=(), check_unchunked=True):
 
 
 def test_llama3_8b_32k_full_size():
-    # 128 ... 512 rows: the launcher's small-tile, deep-ring forms at the production K (4096 / 14336)
+    # 128 ... 512 rows: the forms for few token rows at the production K (4096 / 14336)
     wl, out = _full_size_case("llama3_8b_32k", sweep=(128, 256, 512, 1024, 2048, 8192))
     # ragged sequence length at the same shape: 32768 - 77 rows, chunk 4096 vs full
     dev = _dev()
@@ -671,23 +671,23 @@ def test_mistral_7b_448k_full_size():
 
 
 @pytest.mark.parametrize("S,H,I", [(257, 64, 64), (300, 128, 192), (700, 384, 640), (1100, 256, 1024),
-                                   # long contractions: 32 / 40 stages, several periods of the 20-slot ring
+                                   # long contractions: 32 / 40 stages, several turns of every ring
                                    (600, 2048, 2560),
                                    # odd multiples of 32: a final half stage (K = 32: nothing but that half stage)
                                    (300, 96, 160), (130, 32, 32), (513, 32, 1056), (450, 352, 96)])
 def test_gemm_tile_forms_give_identical_bits(S, H, I, gemm_form):
-    """The forms of the four-wavefront kernel (tile edge 256 / 128 / 64, LDS ring of 5 / 10 / 20 slots) -
-    the library picks one by the number of tiles in a launch; mom_debug_force_gemm_form overrides it -
-    agree bit for bit, with each other and across mini_seq, and match the oracle."""
+    """The square forms (tile edge 256 / 128 / 64; an edge has one ring depth, whichever is named) and the
+    256-row tiles of 224 ... 128 weight rows - the library picks a form by the time a launch is expected to
+    take; mom_debug_force_gemm_form overrides it - agree bit for bit, with each other and across mini_seq,
+    and match the oracle."""
     dev = _dev()
     wl = synth.Workload("tiles", S=S, H=H, I=I, mini_seq=0, seed=S + I, w_std=0.05 if H < 2048 else 0.02)
     x, wg, wu, wd = synth.mlp_inputs(wl)
     ref = oracle.mlp_rows(*(synth.bits(t) for t in (x, wg, wu, wd)))
     xd, wgd, wud, wdd = (t.to(dev) for t in (x, wg, wu, wd))
     outs = []
-    for form, C in (((256, 0), 0), ((128, 10), 0), ((128, 5), 0), ((64, 5), 0), ((64, 10), 0), ((64, 20), 0),
-                    ((256, 5), 256), ((128, 5), 200), ((128, 10), 100), ((64, 20), 96), ((64, 5), 300),
-                    ((64, 10), 130), ((128, 0), 0), ((64, 0), 0), ((256, 0, 224), 0), ((256, 5, 192), 0),
+    for form, C in (((256, 0), 0), ((128, 5), 0), ((64, 5), 0), ((256, 5), 256), ((128, 10), 200), ((128, 0), 100),
+                    ((64, 20), 96), ((64, 10), 130), ((64, 0), 300), ((256, 0, 224), 0), ((256, 5, 192), 0),
                     ((256, 5, 224), 300), ((256, 0, 192), 77), ((256, 5, 160), 0), ((256, 5, 128), 0),
                     ((256, 0, 160), 200), ((256, 0, 128), 513), ((0, 0), 0)):
         gemm_form(*form)
@@ -697,11 +697,12 @@ def test_gemm_tile_forms_give_identical_bits(S, H, I, gemm_form):
     assert_close_to_oracle(_f32(outs[0]), ref, f"tile forms S={S} H={H} I={I}")
 
 
-@pytest.mark.parametrize("S,H,I", [(1024, 128, 14336), (1000, 96, 14304), (2048, 64, 14336), (1024, 128, 9472)])
+@pytest.mark.parametrize("S,H,I", [(1024, 128, 14336), (1000, 96, 14304), (2048, 64, 14336), (1280, 128, 10112)])
 def test_gate_up_column_split_gives_identical_bits(S, H, I, gemm_form):
     """Where the 256 x 128 gate/up tiles of a launch fill the CUs in a fraction of a round more than whole
-    rounds, the library runs the first columns in tiles of 128 columns and the rest in tiles of 96, as two
-    launches (4 token tiles x 14336 columns: 448 tiles = 1.75 rounds become one round of each width).
+    rounds, the library runs the first columns in tiles of 128 columns and the rest in tiles of 96, in one
+    launch (4 token tiles x 14336 columns: 448 tiles = 1.75 rounds become one round of each width;
+    tests/gemm_forms_check.cpp asserts that each of these sizes gets it).
     Same bits as one width throughout, wide or narrow, and the oracle's values on sampled rows."""
     dev = _dev()
     wl = synth.Workload("split", S=S, H=H, I=I, mini_seq=0, seed=S + I, w_std=0.05)
@@ -729,7 +730,7 @@ def test_forced_form_validation(gemm_form):
 
 @pytest.mark.parametrize("name", ["llama3_8b_32k", "qwen25_7b_256k"])
 def test_every_tile_form_at_production_contraction_lengths(name, gemm_form):
-    """Every (tile edge, ring depth) form on a slice of a full-size workload - K = 4096 / 14336 (Llama) and
+    """Every form of FORMS on a slice of a full-size workload - K = 4096 / 14336 (Llama) and
     3584 / 18944 (Qwen), 56 to 296 stages - against the oracle on sampled rows and bit for bit against
     each other; the slice is ragged in rows so that every form masks a partial tile."""
     dev = _dev()
