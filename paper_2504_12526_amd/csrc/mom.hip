@@ -126,7 +126,7 @@ void set_tile_grid(momk::GemmArgs& a, const momk::TileGrid& g) {
     a.tiles_m = (int)g.tiles_m;
     a.tiles_n = (int)g.tiles_n;
     a.group_m = momk::kTokenGroup;
-    a.tiles_per_xcd = (int)((g.tiles + 7) / 8);
+    a.tiles_per_xcd = momk::tiles_per_xcd(g.tiles);
 }
 
 // One launch of gemm4_kernel<EPI, l.tm, l.tn> over the operands in `a` (M, N, K, ldo set).  more: the call has more

@@ -61,6 +61,41 @@ inline TileGrid tile_grid(int64_t M, int64_t N, bool gateup, ShortShape f) {
     return {tm, tn, (uint64_t)tm * tn};
 }
 
+// Tile number of workgroup bid.  Workgroup ids go round-robin over the 8 XCDs: each gets a contiguous run of tile numbers
+// (tiles_per_xcd of them; those past the last tile have nothing to do).
+constexpr int tiles_per_xcd(uint64_t tiles) { return (int)((tiles + 7) / 8); }
+constexpr int tile_number(int bid, int tiles_per_xcd) { return (bid & 7) * tiles_per_xcd + (bid >> 3); }
+
+// Where tile number vt lies: groups of group_m token tiles one after the other, in a group the token tiles of one column
+// tile first.
+struct TilePlace { int m, n; };
+constexpr TilePlace tile_place(int vt, int tiles_m, int tiles_n, int group_m) {
+    const int per_group = group_m * tiles_n;
+    const int grp = vt / per_group;
+    const int first_m = grp * group_m;
+    const int gsz = tiles_m - first_m < group_m ? tiles_m - first_m : group_m;
+    const int in_grp = vt - grp * per_group;
+    return {first_m + in_grp % gsz, in_grp / gsz};
+}
+
+// What ring load j of a wavefront of a short form moves in each stage: 8 rows of 64 K-elements, from sub-tile sub and row
+// src on of its operand (of W_gate or W_up, for gate/up) to row `row` of the operand tile.  The tokens' LT loads come first.
+struct RingLoad { bool token; int sub, row, src; };
+constexpr RingLoad ring_load(bool gateup, int TM, int TN, int KSUB, int wave, int j) {
+    const int LT = KSUB * TM / 32;
+    if (j < LT) {
+        const int b = wave + 4 * j, row = (b % (TM / 8)) * 8;
+        return {true, b / (TM / 8), row, row};
+    }
+    const int HR = gateup ? TN / 2 : TN;                                // rows of one weight matrix
+    const int w = wave + 4 * (j - LT);
+    const int half = w / (KSUB * HR / 8), b = w % (KSUB * HR / 8);
+    const int src = (b % (HR / 8)) * 8;
+    return {false, b / (HR / 8), half * HR + src, src};
+}
+// Whether weight load j reads W_up, whichever wavefront it is (gate/up).
+constexpr bool ring_load_up(int TM, int TN, int KSUB, int j) { return j - KSUB * TM / 32 >= KSUB * TN / 64; }
+
 // The time of a launch in us: what a CU spends on a tile, times the tiles it runs.
 //   start, output   once per tile: launch, ring prologue, epilogue; per output element (silu for gate/up).  The workgroups
 //                   that share a CU (ShortShape::per_cu) overlap it.

@@ -3,6 +3,7 @@
 #include <cstdio>
 #include <cmath>
 #include <initializer_list>
+#include <vector>
 #include "mom_gemm_forms.h"
 
 static int bad = 0;
@@ -19,40 +20,48 @@ static void form(bool gu, int f, int tm, int tn, int wm, int wn, int ksub, int n
     CHECK(tm * (cols * 2 + 16) <= nstg * stage, "epilogue of %d x %d", tm, tn);
     const momk::ShortShape s = momk::short_shape(gu, f);
     CHECK(s.tm == tm && s.tn == tn && s.per_cu >= 1 && s.per_cu * nstg * stage <= 163840, "workgroups per CU of %d x %d", tm, tn);
-    // Every 1-KiB block of a stage is loaded once, to a place of its own: the kernel's mapping of wavefront and
-    // load index to sub-tile and row
+    // Every 1-KiB block of a stage is loaded once, to a place of its own, from the row that belongs there
     bool seen[2][16][64] = {};                        // [operand][sub][row / 8]
+    int moved = 0;
     for (int wave = 0; wave < 4; ++wave)
-        for (int j = 0; j < loads; ++j) {
-            const int lt = ksub * tm / 32;
-            int op, sub, row;
-            if (j < lt) {
-                const int b = wave + 4 * j;
-                op = 0; sub = b / (tm / 8); row = (b % (tm / 8)) * 8;
-            } else {
-                const int hr = gu ? tn / 2 : tn, w = wave + 4 * (j - lt);
-                const int half = w / (ksub * hr / 8), b = w % (ksub * hr / 8);
-                op = 1; sub = b / (hr / 8); row = half * hr + (b % (hr / 8)) * 8;
-                // the weight matrix is picked by the load index alone
-                CHECK(!gu || half == (j - lt >= (loads - lt) / 2), "weight matrix of a load of %d x %d", tm, tn);
-            }
-            CHECK(sub < ksub && row + 8 <= (op ? tn : tm), "block of %d x %d", tm, tn);
-            CHECK(!seen[op][sub][row / 8], "block loaded twice in %d x %d", tm, tn);
-            seen[op][sub][row / 8] = true;
+        for (int j = 0; j < loads; ++j, ++moved) {
+            const momk::RingLoad l = momk::ring_load(gu, tm, tn, ksub, wave, j);
+            const bool up = gu && !l.token && momk::ring_load_up(tm, tn, ksub, j);     // from W_up
+            CHECK(l.token == (j < ksub * tm / 32), "operand of a load of %d x %d", tm, tn);
+            CHECK(l.sub >= 0 && l.sub < ksub && l.row >= 0 && l.row % 8 == 0 && l.row + 8 <= (l.token ? tm : tn), "block of %d x %d", tm, tn);
+            CHECK(l.src == l.row - (up ? tn / 2 : 0) && (l.token || (l.src >= 0 && l.src + 8 <= cols)), "source of a load of %d x %d", tm, tn);
+            CHECK(!seen[l.token][l.sub][l.row / 8], "block loaded twice in %d x %d", tm, tn);
+            seen[l.token][l.sub][l.row / 8] = true;
         }
+    CHECK(moved * 8 == ksub * (tm + tn), "blocks of %d x %d", tm, tn);
 }
 
-// The kernels' walk over the tiles of a grid covers every token row once, with a tile of its own for each count that the
-// grid states (and that its time was reckoned with): tile i starts at row i tm.
-static void rows(int64_t M, int tm, const momk::TileGrid& t) {
-    int64_t next = 0;
-    for (int64_t i = 0; i < t.tiles_m; ++i) {
-        const int64_t m0 = i * tm, end = m0 + (M - m0 < tm ? M - m0 : tm);
-        CHECK(m0 == next && m0 < end && m0 <= 0x7fffffff, "tile %lld of M=%lld tm=%d", (long long)i, (long long)M, tm);
-        next = end;
+// The workgroups of a launch run every tile of the grid once, and the token tiles cover every token row once: tile i
+// starts at row i tm.
+static void tiles(int64_t M, int64_t N, int tm, int tn) {
+    const momk::TileGrid g = momk::tile_grid(M, N, false, {tm, tn, 1, 0});
+    CHECK(g.tiles == (uint64_t)g.tiles_m * g.tiles_n, "tiles of M=%lld tm=%d", (long long)M, tm);
+    const int xcd = momk::tiles_per_xcd(g.tiles), count = (int)g.tiles;
+    std::vector<int> run(count);
+    std::vector<char> token(M), column(N);
+    for (int bid = 0; bid < 8 * xcd; ++bid) {
+        const int vt = momk::tile_number(bid, xcd);
+        if (vt >= count) continue;
+        const momk::TilePlace p = momk::tile_place(vt, g.tiles_m, g.tiles_n, momk::kTokenGroup);
+        const bool in = p.m >= 0 && p.n >= 0 && p.m < (int)g.tiles_m && p.n < (int)g.tiles_n;
+        CHECK(in, "place of tile %d of M=%lld tm=%d", vt, (long long)M, tm);
+        if (!in) return;
+        CHECK(!run[p.m * g.tiles_n + p.n]++, "tile %d x %d of M=%lld tm=%d run twice", p.m, p.n, (long long)M, tm);
+        CHECK((int64_t)p.m * tm < M && (int64_t)p.n * tn < N, "empty tile %d x %d of M=%lld tm=%d", p.m, p.n, (long long)M, tm);
+        for (int64_t m = (int64_t)p.m * tm; m < M && m < (int64_t)(p.m + 1) * tm; ++m) token[m] = 1;
+        for (int64_t n = (int64_t)p.n * tn; n < N && n < (int64_t)(p.n + 1) * tn; ++n) column[n] = 1;
     }
-    CHECK(next == M, "rows of M=%lld tm=%d", (long long)M, tm);
-    CHECK(t.tiles == (uint64_t)t.tiles_m * t.tiles_n, "tiles of M=%lld tm=%d", (long long)M, tm);
+    int64_t ran = 0, rows = 0, cols = 0;
+    for (int r : run) ran += r;
+    for (char c : token) rows += c;
+    for (char c : column) cols += c;
+    CHECK(ran == count, "tiles run of M=%lld tm=%d", (long long)M, tm);
+    CHECK(rows == M && cols == N, "rows of M=%lld tm=%d", (long long)M, tm);
 }
 
 // What choose_down picks at these sizes, against every launch there is, each priced on the grid that runs.
@@ -89,8 +98,9 @@ static void steady(int64_t N, int64_t K, bool gateup) {
 
 int main() {
     for (int tm = 16; tm <= 256; tm += 16)
-        for (int64_t M = 1; M <= 16384; M += 1 + M / 97) rows(M, tm, momk::tile_grid(M, 32, false, {tm, 32, 1, 0}));
-    rows(0x7fffff00, 256, momk::tile_grid(0x7fffff00, 32, false, {256, 32, 1, 0}));
+        for (int64_t M = 1; M <= 16384; M += 1 + M / 97) tiles(M, 96 + 32 * (M % 11), tm, 64);
+    const momk::TileGrid most = momk::tile_grid(0x7fffff00, 32, false, {256, 32, 1, 0});
+    CHECK(most.tiles_m == 0x7fffff && most.tiles_n == 1 && most.tiles == 0x7fffff, "most token rows");
     for (int64_t M = 1; M <= 16384; ++M) {
         for (bool more : {false, true}) down_choice(M, 4096, 14336, 256, more);
         for (bool more : {false, true}) down_choice(M, 3584, 18944, 256, more);

@@ -29,6 +29,10 @@ def test_forms_and_choice(tmp_path):
     ("const uint32_t tm = ((uint32_t)M + f.tm - 1) / f.tm,", "const uint32_t tm = M < f.tm ? 1 : (uint32_t)M / f.tm,", "rows of M="),
     # a step in the time of a launch: neighbouring row counts alternate between forms
     ("last < 0.72 ? (0.72 - last) / 0.32 : 0;", "last < 0.72 ? (M & 1) : 0;", "between two runs of"),
+    # the last, shorter group of token tiles walked as a whole one
+    ("const int gsz = tiles_m - first_m < group_m ? tiles_m - first_m : group_m;", "const int gsz = group_m;", "of M="),
+    # the rows of W_up behind those of a whole tile instead of half a one
+    ("half * HR + src, src}", "half * TN + src, src}", "block of"),
 ])
 def test_a_planted_mistake_is_caught(tmp_path, old, new, says):
     """Planted in a copy of the header, on the CPU."""
