@@ -174,7 +174,8 @@ inline double launch_time(const TileGrid& g, int64_t M, int64_t K, bool gateup, 
 // much again for the down projection) are more than the Infinity Cache holds.  Then W_down stays there from
 // mini-sequence to mini-sequence instead of being displaced each time, and the stream itself is faster.
 // Measured, gate/up and down: 16 rows 43.2 -> 41.8 us and 27.3 (first use, as before), Qwen-shaped 61 rows 54.7 ->
-// 51.5, mini-sequences of 512 rows 91.2 + 83.4 -> 87.3 + 79.8, of 1024 rows 162.4 + 122.6 -> 161.0 + 114.1.  With
+// 51.5, mini-sequences of 512 rows 91.2 + 83.4 -> 87.3 + 79.8, of 1024 rows 162.4 + 122.6 -> 161.0 + 114.1 (down in 160 x 64
+// and 160 x 128; the even tiles that W_down in the cache has got since, kept_down, take 70 and 105).  With
 // four groups (4096 rows) the other groups miss what the first had brought: 615 -> 635 us, so not there; and where
 // there is only one mini-sequence, only for at most two token tiles (1000 rows: 161.6 -> 163.9 us).
 // The down projection itself loses with it wherever tiles share a weight line: 61 rows 39 -> 51 us.
