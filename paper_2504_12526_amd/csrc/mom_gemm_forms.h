@@ -117,7 +117,8 @@ constexpr bool ring_load_up(int TM, int TN, int KSUB, int j) { return j - KSUB *
 // mini-sequences.  Formula and time of the forms near the best of their size differ by 5 (256-row tiles), 8 (short, down)
 // and 9 % (short, gate/up; the least of many uncertain times is an optimistic one, so these figures are the fitted ones
 // and 5 or 6 % on everything).  Over the 1427 launches measured, the form of least time takes 1 % longer than the best of
-// all forms on average, and more than 10 % longer in 22 of them.
+// all forms on average, and more than 10 % longer in 22 of them; in the down projection of six layers with 48 other row
+// counts from 258 to 2440, 1.1 % and in 6 of 288.
 struct LaunchTime {
     double start, output, row, fetched, product, last_round, latency;
     bool whole_tile;
