@@ -230,11 +230,14 @@ int mom_kv_reload(const void *pinned_host, void *k, void *v, void *stream, size_
  * weight_rows among those for few token rows (csrc/mom_gemm_forms.h), where the projection has one
  * (before mom_debug_force_gemm_form); (0, 0) gives the choice back.  No such form: MOM_ERR_SHAPE.
  *
+ * mom_debug_force_rect_form: the same among the rectangular tiles listed there (before the other two).
+ *
  * mom_debug_force_pipeline: on != 0 makes mom_mlp_prefill_pipelined use its two-stream schedule
  * whenever there is more than one mini-sequence, also where it was measured not to pay.
  */
 int mom_debug_force_gemm_form(int tile_edge, int ring_slots, int tile_width);
 int mom_debug_force_short_form(int token_rows, int weight_rows);
+int mom_debug_force_rect_form(int token_rows, int weight_rows);
 int mom_debug_force_pipeline(int on);
 
 /*

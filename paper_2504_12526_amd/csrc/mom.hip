@@ -12,9 +12,11 @@
 
 #include "mom.h"
 #include "mom_gemm_forms.h"
+#include "mom_gemm_rect_schedule.h"
 #include "mom_gemm_schedule.h"
 #include "mom_gemm.hip.inc"
 #include "mom_gemm_short.hip.inc"
+#include "mom_gemm_rect.hip.inc"
 #include "mom_gemv.hip.inc"
 #include "mom_probe.hip.inc"
 
@@ -69,7 +71,7 @@ DeviceInfo g_dev[kMaxDevices];
 
 // Testing overrides (the mom_debug_force_ calls); 0 = the library chooses.
 std::atomic<int> g_force_edge{0}, g_force_width{0}, g_force_pipeline{0};
-std::atomic<int> g_force_short{0};      // token rows << 16 | weight rows
+std::atomic<int> g_force_short{0}, g_force_rect{0};      // token rows << 16 | weight rows
 
 DeviceInfo* current_device_info() {
     int dev = 0;
@@ -129,7 +131,25 @@ void set_tile_grid(momk::GemmArgs& a, const momk::TileGrid& g) {
     a.tiles_per_xcd = momk::tiles_per_xcd(g.tiles);
 }
 
-// One launch of gemm4_kernel<EPI, l.tm, l.tn> over the operands in `a` (M, N, K, ldo set).  more: the call has more
+// One launch of gemm_rect_kernel<EPI, l.tm, l.tn>.
+template <int EPI>
+hipError_t launch_rect_tiles(const momk::GemmArgs& a, const momk::Launch& l, bool nt, hipStream_t st) {
+    const dim3 grid((unsigned)(a.tiles_per_xcd * 8)), block(momk::k4Threads);
+#define MOM_LAUNCH_RECT(TM, TN)                                                                                   \
+    if (l.tm == TM && l.tn == TN) {                                                                               \
+        if (EPI == momk::EPI_GATEUP && nt)                                                                        \
+            hipLaunchKernelGGL((momk::gemm_rect_kernel<EPI, TM, TN, EPI == momk::EPI_GATEUP>), grid, block, 0, st, a);  \
+        else                                                                                                      \
+            hipLaunchKernelGGL((momk::gemm_rect_kernel<EPI, TM, TN, false>), grid, block, 0, st, a);              \
+        return hipGetLastError();                                                                                 \
+    }
+    if constexpr (EPI == momk::EPI_GATEUP) { MOM_RECT_FORMS_GATEUP(MOM_LAUNCH_RECT) }
+    else { MOM_RECT_FORMS_DOWN(MOM_LAUNCH_RECT) }
+#undef MOM_LAUNCH_RECT
+    return hipErrorInvalidValue;
+}
+
+// One launch of gemm4_kernel<EPI, l.tm, l.tn>, or of the rectangular tiles, over the operands in `a` (M, N, K, ldo set).  more: the call has more
 // than one mini-sequence.
 template <int EPI>
 hipError_t launch_whole_tiles(momk::GemmArgs a, const momk::Launch& l, bool more, hipStream_t st) {
@@ -137,6 +157,7 @@ hipError_t launch_whole_tiles(momk::GemmArgs a, const momk::Launch& l, bool more
     const int edge = l.tm, width = l.tn;
     const dim3 grid((unsigned)(a.tiles_per_xcd * 8)), block(momk::k4Threads);
     const bool nt = EPI == momk::EPI_GATEUP && momk::weights_once(a.tiles_m, a.N, a.K, more);
+    if (momk::is_rect_form(EPI == momk::EPI_GATEUP, edge, width)) return launch_rect_tiles<EPI>(a, l, nt, st);
 #define MOM_LAUNCH4(E, W)                                                                                         \
     do {                                                                                                          \
         if constexpr (EPI == momk::EPI_GATEUP && E == 256) {                                                      \
@@ -183,6 +204,8 @@ hipError_t launch_short_tiles(momk::GemmArgs a, const momk::Launch& l, bool more
 // The launch a mom_debug_force_ call asks for (tests need every form on shapes of every size); kRefused with form -1
 // where none does.
 momk::Launch forced_launch(int64_t M, int64_t N, bool gateup) {
+    const int fr = g_force_rect.load(std::memory_order_relaxed);
+    if (fr && momk::is_rect_form(gateup, fr >> 16, fr & 0xffff)) return momk::whole_launch(M, N, gateup, fr >> 16, fr & 0xffff);
     const int fs = g_force_short.load(std::memory_order_relaxed);
     if (fs) {
         const int form = momk::find_short_form(gateup, fs >> 16, fs & 0xffff);
@@ -388,6 +411,14 @@ int mom_debug_force_short_form(int token_rows, int weight_rows) {
         momk::find_short_form(true, token_rows, weight_rows) < 0)
         return MOM_ERR_SHAPE;
     g_force_short.store(off ? 0 : (token_rows << 16 | weight_rows), std::memory_order_relaxed);
+    return MOM_OK;
+}
+
+int mom_debug_force_rect_form(int token_rows, int weight_rows) {
+    const bool off = token_rows == 0 && weight_rows == 0;
+    if (!off && !momk::is_rect_form(false, token_rows, weight_rows) && !momk::is_rect_form(true, token_rows, weight_rows))
+        return MOM_ERR_SHAPE;
+    g_force_rect.store(off ? 0 : (token_rows << 16 | weight_rows), std::memory_order_relaxed);
     return MOM_OK;
 }
 

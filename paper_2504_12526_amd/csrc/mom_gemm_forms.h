@@ -26,6 +26,14 @@
     X(128, 128, 2, 2, 1, 5) X(160, 128, 2, 2, 1, 4) X(192, 128, 2, 2, 1, 4) X(224, 128, 2, 2, 1, 3)      \
     X(64, 192, 2, 2, 1, 5) X(96, 192, 2, 2, 1, 4) X(128, 192, 2, 2, 1, 4) X(64, 64, 2, 2, 1, 5)
 
+// X(TM, TN) of the rectangular tiles (mom_gemm_rect.hip.inc): those of 54 measured that are the best of some launch by more
+// than the next.
+#define MOM_RECT_FORMS_DOWN(X)                                                                           \
+    X(160, 160) X(160, 256) X(192, 160) X(192, 224) X(192, 256) X(224, 160) X(224, 224) X(224, 256)
+#define MOM_RECT_FORMS_GATEUP(X)                                                                         \
+    X(256, 128) X(160, 160) X(192, 160) X(224, 160) X(256, 160) X(320, 160) X(288, 192) X(320, 192)      \
+    X(160, 224) X(192, 224) X(256, 224) X(288, 224) X(224, 256) X(192, 320)
+
 namespace momk {
 
 // per_cu: workgroups that a CU's 160 KiB of LDS hold; ahead: K-elements that a workgroup has in flight at most.
@@ -46,6 +54,21 @@ inline int find_short_form(bool gateup, int tm, int tn) {
     for (int i = 0; i < short_forms(gateup); ++i)
         if (short_shape(gateup, i).tm == tm && short_shape(gateup, i).tn == tn) return i;
     return -1;
+}
+
+// Rectangular tiles, by their sizes: one workgroup per CU.
+#define MOM_SHAPE(TM, TN) {TM, TN, 1, 0},
+constexpr ShortShape kRectDown[] = {MOM_RECT_FORMS_DOWN(MOM_SHAPE)};
+constexpr ShortShape kRectGateUp[] = {MOM_RECT_FORMS_GATEUP(MOM_SHAPE)};
+#undef MOM_SHAPE
+constexpr int kRectDownForms = sizeof(kRectDown) / sizeof(kRectDown[0]);
+constexpr int kRectGateUpForms = sizeof(kRectGateUp) / sizeof(kRectGateUp[0]);
+inline int rect_forms(bool gateup) { return gateup ? kRectGateUpForms : kRectDownForms; }
+inline ShortShape rect_shape(bool gateup, int form) { return gateup ? kRectGateUp[form] : kRectDown[form]; }
+inline bool is_rect_form(bool gateup, int tm, int tn) {
+    for (int i = 0; i < rect_forms(gateup); ++i)
+        if (rect_shape(gateup, i).tm == tm && rect_shape(gateup, i).tn == tn) return true;
+    return false;
 }
 
 constexpr int64_t kMaxTiles = 0x1fffffff;            // tile numbers are 32-bit in the kernels
@@ -141,6 +164,18 @@ constexpr LaunchTime kFullGateUpTime = {4.0, 1.90e-4, 7.3e-6, 2.63e-5, 2.04e-7, 
 constexpr LaunchTime kPairGateUpTime = {6.6, 9.6e-5, 2.65e-5, 0, 0, 1.0, kFromHbm, false, 0, 0};
 constexpr LaunchTime kPairGateUpSmallTime = {6.6, 9.6e-5, 2.65e-5, 0, 0, 1.0, kFromCache, false, 0, 0};
 constexpr ShortShape kPairShape = {128, 128, 2, 58};
+// Rectangular tiles, fitted to 54 forms of them, those near the best of a launch weighted most: gate/up to 100 ... 16384 rows of
+// four layers above 128 MiB (H 3584 ... 8192; formula and time differ by 4 %), down to 1000 ... 16384 rows of the same (4 %, and the
+// forms by what kRectDownPerMille says).  Times of launches one after the other; between calls that alternate, the two-width and 256 x 256
+// gate/up launches gain 2-5 % on them.  So a rectangular tile has to promise more than the others' formula by the share given:
+// kOverOneRound   gate/up, 256 x 256 tiles of more than one round: at 0.945 ... 0.975 promised 0.95 ... 1.06 of the time came
+//                 (1000 rows x 18944 columns 0.964: 203 -> 212 us), below mostly as promised (850 rows 0.74: 198 -> 161 us)
+// kOverShort      gate/up short forms, whose time at 97 ... 224 rows is overrated: 0.83 ... 0.90 promised 0.97 ... 1.0
+// kOverDown       either kind, after the correction: 2900 rows x 4096 columns 0.89 promised, 247 -> 233 us
+constexpr LaunchTime kRectGateUpTime = {3.73, 3.07e-5, 1.09e-5, 4.22e-5, 1.68e-7, 0.74, 0, true, 0, 0};
+constexpr LaunchTime kRectDownTime = {7.24, 2.95e-5, 2.34e-5, 7.72e-6, 1.02e-7, 0.707, 0, true, 0.048, 0};
+constexpr int kRectDownPerMille[kRectDownForms] = {1000, 970, 970, 975, 1010, 960, 1010, 1040};
+constexpr double kOverOneRound = 0.945, kWithinOneRound = 0.975, kOverShort = 0.83, kOverDown = 0.965;
 
 // Whether weight rows x K of them leave the Infinity Cache room (142 MB do, 470 MB do not).
 inline bool weights_fit(int64_t rows, int64_t K) { return 2 * rows * K <= ((int64_t)160 << 20); }
@@ -204,12 +239,23 @@ inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, const
     return best;
 }
 
+// The rectangular tiles that take the least time; their time in `least`; tm 0: none.
+inline ShortShape choose_rect_form(int64_t M, int64_t N, int64_t K, bool gateup, const LaunchTime& time, int cus, double& least) {
+    ShortShape best = {0, 0, 1, 0};
+    for (int i = 0; i < rect_forms(gateup); ++i) {
+        const ShortShape f = rect_shape(gateup, i);
+        const double t = launch_time(tile_grid(M, N, gateup, f), M, K, gateup, f, time, cus);
+        if (t >= 0 && (best.tm == 0 || t < least)) { best = f; least = t; }
+    }
+    return best;
+}
+
 // How a launch runs.  All forms give identical bits (every output element sees the same MFMA sequence over k), so
 // the choice is free.
 enum LaunchKind {
     kRefused,        // no such form, or too many tiles for 32-bit tile numbers
     kShortTiles,     // gemm_short_kernel, form `form`
-    kWholeTiles,     // gemm4_kernel: tiles of tm token rows x tn staged weight rows
+    kWholeTiles,     // tiles of tm token rows x tn staged weight rows: gemm_rect_kernel for those in its list, else gemm4_kernel
     kTwoWidths       // gemm4_two_width_kernel: columns [0, wide_cols) in 256 x 256 tiles (`grid`), the rest in 256 x 192 (`narrow`)
 };
 struct Launch {
@@ -258,18 +304,29 @@ inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool later, 
     // The width: by time where the widest take no more than one round; over several rounds by rounds x columns, a column of
     // a narrower tile charged what it was measured to cost more for the token fragments it shares among fewer MFMAs
     // (12400 rows x 4096 columns: 3.6 rounds of 224-wide tiles 1033 us, 5 of 160-wide ones 1113 us).
+    // Rectangular tiles by their time, from the fewest rows of the fit on; not for layers that stay in the Infinity Cache, whose
+    // launches end before a large tile's rings have filled (1000 rows x 256 columns, K = 1024: 10.4 us, short 6.3).
     constexpr int per_mille[5] = {1000, 1020, 1070, 1170, 1310};
+    const int rects = M < 1000 || small_layer(N, K) ? 0 : rect_forms(false);
     int width = 0;
     int64_t columns = 0;
-    for (int i = 0; i < 5; ++i) {
+    ShortShape rect = {0, 0, 1, 0};
+    double rect_time = 0;
+    for (int i = 0; i < 5 + rects; ++i) {
         const int w = 256 - 32 * i;
-        const ShortShape f = {256, w, 1, 0};
+        const ShortShape f = i < 5 ? ShortShape{256, w, 1, 0} : rect_shape(false, i - 5);
         const TileGrid g = tile_grid(M, N, false, f);
-        const double t = launch_time(g, M, K, false, f, kFullDownTime, cus);
-        const int64_t c = rounds_per_mille((int64_t)g.tiles, cus) * w * per_mille[i];
+        const double t = launch_time(g, M, K, false, f, i < 5 ? kFullDownTime : kRectDownTime, cus);
         if (t < 0) continue;
+        if (i >= 5) {
+            const double r = t * kRectDownPerMille[i - 5] / 1000;
+            if (rect.tm == 0 || r < rect_time) { rect = f; rect_time = r; }
+            continue;
+        }
+        const int64_t c = rounds_per_mille((int64_t)g.tiles, cus) * w * per_mille[i];
         if (width == 0 || (full.grid.tiles > (uint64_t)cus ? c < columns : t < time)) { width = w; time = t; columns = c; }
     }
+    if (rect.tm && rect_time < kOverDown * time && (form < 0 || rect_time < kOverDown * least)) return whole_launch(M, N, false, rect.tm, rect.tn);
     if (form >= 0 && least < time) return short_launch(M, N, false, form);
     return whole_launch(M, N, false, 256, width);
 }
@@ -304,6 +361,14 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus) {
     double full = plain_time * cost / plain;
     if (wide_cols == 0)
         full = launch_time(tile_grid(M, N, true, {256, 192, 1, 0}), M, K, true, {256, 192, 1, 0}, kFullGateUpTime, cus);
+    // Rectangular tiles, by their time, for layers that come from HBM: 300 rows x 14336 columns, K = 4096: 91 -> 67 us; of a
+    // layer of 69 MiB, which the Infinity Cache keeps, 1 % at most and up to 17 % lost at 128 rows.  Not below the row counts of the fit.
+    if (M > 96 && 6 * N * K > ((int64_t)128 << 20)) {
+        double rect = 0;
+        const ShortShape r = choose_rect_form(M, N, K, true, kRectGateUpTime, cus, rect);
+        const double share = plain_launch.grid.tiles > (uint64_t)cus ? kOverOneRound : kWithinOneRound;
+        if (r.tm && rect < share * full && (form < 0 || least >= full || rect < kOverShort * least)) return whole_launch(M, N, true, r.tm, r.tn);
+    }
     const Launch pair = whole_launch(M, N, true, 128, 128);
     if (pair.kind != kRefused && pair.grid.tiles <= 2 * (uint64_t)cus &&
         (K <= 2048 || (pair.grid.tiles_m > (uint32_t)kTokenGroup && pair.grid.tiles > (uint64_t)cus))) {
