@@ -105,6 +105,8 @@ int mom_mlp_prefill(const void *x, const void *W_gate, const void *W_up, const v
  * MOM_STATIC_WORKSPACE_BYTES array that is part of the library's device image (each device the
  * library is used on holds its copy until the process ends).  The call allocates nothing and
  * frees nothing.
+ *   The array is there at its full size, so as many rows go through it at a time as it holds (in whole
+ *   256-row tiles) where that is at least half as many again as mini_seq.
  *   Limit: min(mini_seq, S) * I * 2 <= MOM_STATIC_WORKSPACE_BYTES (e.g. 2048 rows at I = 14336),
  *   else MOM_ERR_WORKSPACE and nothing is enqueued.  Other arguments and errors as mom_mlp_prefill.
  *   The device address of the array is looked up on the first call on a device (or by mom_init,
@@ -118,23 +120,20 @@ int mom_mlp_prefill_static(const void *x, const void *W_gate, const void *W_up, 
                            int64_t S, int64_t H, int64_t I, int64_t mini_seq, void *out, void *stream);
 
 /*
- * The same computation and the same bits as mom_mlp_prefill, scheduled on two streams with a
- * double-buffered workspace (2 * C * I * 2 bytes: still O(C*I), the bound of the paper's Eq. 3):
- * the down projection of mini-sequence c runs on `stream2` beside the gate/up projection of
- * mini-sequence c+1 on `stream`, so the CUs that the last, partly filled round of tiles of one
- * kernel leaves idle work on the other.  Pays off when a mini-sequence has few tiles (mini_seq
- * of 2048 rows and below on a 256-CU device); with many it equals mom_mlp_prefill.
+ * The same computation and the same bits as mom_mlp_prefill with the workspace of two mini-sequences
+ * (2 * C * I * 2 bytes: still O(C*I), the bound of the paper's Eq. 3), for callers that can spare it and
+ * a second stream.  The library puts it to the use that was measured fastest: two mini-sequences go through
+ * as one on `stream`, or, where a mini-sequence is so long that this gains nothing, one at a time.
+ * mom_debug_force_pipeline makes it the double buffer of a two-stream schedule: the down projection of
+ * mini-sequence c on `stream2` beside the gate/up projection of mini-sequence c+1 on `stream`.
  *   workspace        at least mom_mlp_pipelined_workspace_bytes(S,H,I,mini_seq) bytes
- *   stream, stream2  two streams of the current device (stream2 should differ from stream).  The
- *                    call orders stream2 after the work already enqueued on stream, and stream
+ *   stream, stream2  two streams of the current device (stream2 should differ from stream).  Where the
+ *                    call uses stream2 it orders it after the work already enqueued on stream, and stream
  *                    after the last kernel on stream2: the caller synchronises `stream` only.
  *   events           host array of n_events >= 5 hipEvent_t created by the caller (disable-timing
- *                    events are fine); the first five are re-recorded freely during the call.
+ *                    events are fine); the first five may be re-recorded during the call.
  *                    Fewer than five: MOM_ERR_SHAPE
- * With a single mini-sequence (mini_seq 0 or >= S), or where the schedule was measured not to pay
- * (a down projection that fills more than half of the CUs by itself, or mini-sequences so short
- * that both projections are latency-bound), this is mom_mlp_prefill on `stream`
- * (mom_debug_force_pipeline forces the two-stream schedule, for tests).
+ * With a single mini-sequence (mini_seq 0 or >= S) this is mom_mlp_prefill on `stream`.
  */
 size_t mom_mlp_pipelined_workspace_bytes(int64_t S, int64_t H, int64_t I, int64_t mini_seq);
 int mom_mlp_prefill_pipelined(const void *x, const void *W_gate, const void *W_up, const void *W_down,

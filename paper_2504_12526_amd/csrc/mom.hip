@@ -39,6 +39,28 @@ inline int64_t effective_chunk(int64_t S, int64_t mini_seq) {
     return (mini_seq <= 0 || mini_seq > S) ? S : mini_seq;
 }
 
+// Token rows of a pass of mom_mlp_prefill_static: the static workspace is there at its full size whatever mini_seq is, and a
+// pass of more rows takes less time per row (H = 4096, I = 14336, 12000 rows: mini-sequences of 128 rows 8054 us, of 512 3832, of 1024 3202,
+// passes of 2304 rows 2970).  Whole 256-row token tiles, and only from half as many rows again on: at 12000 -> 16128 rows of I = 2080
+// the shorter last pass costs 2.6 % of 18000 rows, at 8192 -> 16128 14 % are gained.
+int64_t static_rows(int64_t S, int64_t I, int64_t C) {
+    const int64_t fit = (int64_t)MOM_STATIC_WORKSPACE_BYTES / (2 * I);
+    if (S <= fit) return S;
+    const int64_t whole = fit / 256 * 256;
+    return 2 * whole >= 3 * C ? whole : C;
+}
+
+// ... and of mom_mlp_prefill_pipelined, whose workspace is that of two mini-sequences: both at once, up to 14 rounds of the CUs in
+// 256 x 128 gate/up tiles of one of them.  Against down(c) beside gate/up(c+1) on two streams, H = 4096, I = 14336, six mini-sequences
+// of C rows: C = 512 979 -> 824 us, 1024 1675 -> 1545, 2048 3043 -> 2734, 4096 level; H = 3584, I = 18944: 512 1261 -> 1020,
+// 2048 3609 -> 3244, 6000 10109 -> 9676.  From 14 rounds on a pass more costs less than 1 %, and 18000 rows at once 3 % more
+// than 12000 and 6000.
+int64_t pipelined_rows(int64_t S, int64_t I, int64_t C, int cus) {
+    const int64_t tiles = (C + momk::kBM - 1) / momk::kBM * ((I + momk::kBW / 2 - 1) / (momk::kBW / 2));
+    if (tiles >= 14 * (int64_t)cus) return C;
+    return 2 * C < S ? 2 * C : S;
+}
+
 int validate_mlp(const void* x, const void* wg, const void* wu, const void* wd, int64_t S, int64_t H,
                  int64_t I, int64_t mini_seq, const void* out, const void* ws, size_t ws_bytes) {
     if (S < 0 || H <= 0 || I <= 0 || mini_seq < 0) return MOM_ERR_SHAPE;
@@ -285,12 +307,9 @@ hipError_t launch_gemv(const unsigned short* x, const unsigned short* Wa, const 
     return hipGetLastError();
 }
 
-int mlp_driver(const void* x, const void* wg, const void* wu, const void* wd, int64_t S, int64_t H,
-               int64_t I, int64_t mini_seq, void* out, void* ws, size_t ws_bytes, void* stream,
-               void** events, int64_t n_events) {
-    int rc = validate_mlp(x, wg, wu, wd, S, H, I, mini_seq, out, ws, ws_bytes);
-    if (rc != MOM_OK || S == 0) return rc;
-    const int64_t C = effective_chunk(S, mini_seq);
+// The loop over mini-sequences of C rows on one stream.  The arguments have been validated for a workspace of C x I.
+int mlp_loop(const void* x, const void* wg, const void* wu, const void* wd, int64_t S, int64_t H, int64_t I, int64_t C,
+             void* out, void* ws, void* stream, void** events, int64_t n_events) {
     const int64_t n = (S + C - 1) / C;
     if (events && n_events < 1 + 2 * n) return MOM_ERR_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -322,8 +341,16 @@ int mlp_driver(const void* x, const void* wg, const void* wu, const void* wd, in
     return MOM_OK;
 }
 
-// The same loop on two streams with two workspace halves: the down projection of mini-sequence c
-// (stream B) runs beside the gate/up projection of mini-sequence c+1 (stream A), so that the CUs
+int mlp_driver(const void* x, const void* wg, const void* wu, const void* wd, int64_t S, int64_t H,
+               int64_t I, int64_t mini_seq, void* out, void* ws, size_t ws_bytes, void* stream,
+               void** events, int64_t n_events) {
+    const int rc = validate_mlp(x, wg, wu, wd, S, H, I, mini_seq, out, ws, ws_bytes);
+    if (rc != MOM_OK || S == 0) return rc;
+    return mlp_loop(x, wg, wu, wd, S, H, I, effective_chunk(S, mini_seq), out, ws, stream, events, n_events);
+}
+
+// The same loop on two streams with two workspace halves (mom_debug_force_pipeline; otherwise pipelined_rows): the down
+// projection of mini-sequence c (stream B) runs beside the gate/up projection of mini-sequence c+1 (stream A), so that the CUs
 // one kernel's last, partly filled round of tiles leaves idle take tiles of the other.
 //   A: [wait D(c-2)]  gate/up(c) -> half c%2   record G(c)
 //   B:  wait G(c)     down(c)   <- half c%2    record D(c)
@@ -467,8 +494,11 @@ int mom_mlp_prefill_static(const void* x, const void* W_gate, const void* W_up, 
     if (need > (size_t)MOM_STATIC_WORKSPACE_BYTES) return MOM_ERR_WORKSPACE;
     void* ws = static_workspace();
     if (!ws) return MOM_ERR_HIP;
-    return mlp_driver(x, W_gate, W_up, W_down, S, H, I, mini_seq, out, ws, (size_t)MOM_STATIC_WORKSPACE_BYTES, stream,
-                      nullptr, 0);
+    const int rc = validate_mlp(x, W_gate, W_up, W_down, S, H, I, mini_seq, out, ws, (size_t)MOM_STATIC_WORKSPACE_BYTES);
+    if (rc != MOM_OK) return rc;
+    const int64_t C = static_rows(S, I, effective_chunk(S, mini_seq));
+    // the call writes more of the array than `need`, but no argument can lie in any of it
+    return mlp_loop(x, W_gate, W_up, W_down, S, H, I, C, out, ws, stream, nullptr, 0);
 }
 
 size_t mom_mlp_pipelined_workspace_bytes(int64_t S, int64_t H, int64_t I, int64_t mini_seq) {
@@ -503,22 +533,11 @@ int mom_mlp_prefill_pipelined(const void* x, const void* W_gate, const void* W_u
         if (!events[i]) return MOM_ERR_NULL;
         ev[i] = static_cast<hipEvent_t>(events[i]);
     }
-    // The two-stream schedule pays (measured) when the down projection of a mini-sequence leaves at least
-    // half of the CUs idle, the gate/up kernel beside it is one that fills the chip with 256-tiles, and the
-    // single round of long down tiles (K = I) does not outlast that kernel on the remaining CUs by more than
-    // half.  Otherwise this is the plain loop.  mom_debug_force_pipeline forces the schedule (for tests,
-    // which need it on shapes of every size).
-    const int cus = compute_units();
-    if (cus <= 0) return MOM_ERR_HIP;
-    const int64_t tm = (C + momk::kBM - 1) / momk::kBM;
-    const int64_t tiles_dn = tm * ((H + momk::kBW - 1) / momk::kBW);
-    const int64_t tiles_gu = tm * ((I + momk::kBW / 2 - 1) / (momk::kBW / 2));
-    const int64_t cus_left = cus - tiles_dn > 0 ? cus - tiles_dn : 1;
-    const bool pays = 2 * tiles_dn <= cus && tiles_gu * 4 > (int64_t)cus * 3 &&
-                      2 * I <= 3 * ((tiles_gu + cus_left - 1) / cus_left) * H;
-    if (!g_force_pipeline.load(std::memory_order_relaxed) && !pays)
-        return mlp_driver(x, W_gate, W_up, W_down, S, H, I, mini_seq, out, workspace, workspace_bytes, stream,
-                          nullptr, 0);
+    if (!g_force_pipeline.load(std::memory_order_relaxed)) {
+        const int cus = compute_units();
+        if (cus <= 0) return MOM_ERR_HIP;
+        return mlp_loop(x, W_gate, W_up, W_down, S, H, I, pipelined_rows(S, I, C, cus), out, workspace, stream, nullptr, 0);
+    }
     return mlp_pipelined(x, W_gate, W_up, W_down, S, H, I, mini_seq, out, workspace, workspace_bytes,
                          static_cast<hipStream_t>(stream), static_cast<hipStream_t>(stream2), ev);
 }
