@@ -90,7 +90,8 @@ size_t mom_mlp_workspace_bytes(int64_t S, int64_t H, int64_t I, int64_t mini_seq
  * bit-identical `out`.
  *
  * S = 0 is a no-op returning MOM_OK.  H and I must be positive multiples of 32.
- * All work is enqueued on `stream` in order (2 kernels per mini-sequence).
+ * All work is enqueued on `stream` in order (2 kernels per mini-sequence; one for the whole call where a layer is so
+ * small that blocks of rows go through both projections with their intermediate on chip in less time).
  * The kernels exist in several tile forms with bit-identical results; the library picks one per
  * launch (mom_debug_force_gemm_form overrides the choice, for tests).
  */
@@ -231,12 +232,16 @@ int mom_kv_reload(const void *pinned_host, void *k, void *v, void *stream, size_
  *
  * mom_debug_force_rect_form: the same among the rectangular tiles listed there (before the other two).
  *
+ * mom_debug_force_block: every later mom_mlp_prefill, _static and _pipelined call evaluates blocks of token_rows (16 or 32) rows
+ * in one launch, both projections with the intermediate in LDS, where H + I is small enough; 0 gives the choice back.
+ *
  * mom_debug_force_pipeline: on != 0 makes mom_mlp_prefill_pipelined use its two-stream schedule
  * whenever there is more than one mini-sequence, also where it was measured not to pay.
  */
 int mom_debug_force_gemm_form(int tile_edge, int ring_slots, int tile_width);
 int mom_debug_force_short_form(int token_rows, int weight_rows);
 int mom_debug_force_rect_form(int token_rows, int weight_rows);
+int mom_debug_force_block(int token_rows);
 int mom_debug_force_pipeline(int on);
 
 /*

@@ -16,7 +16,7 @@ LIB_PATH = os.path.join(_HERE, "libmom.so")
 SYMBOLS = ("mom_status_string", "mom_mlp_workspace_bytes", "mom_mlp_prefill", "mom_mlp_prefill_events",
            "mom_mlp_pipelined_workspace_bytes", "mom_mlp_prefill_pipelined",
            "mom_lmhead_last", "mom_mlp_last", "mom_kv_offload", "mom_kv_reload",
-           "mom_init", "mom_debug_force_gemm_form", "mom_debug_force_short_form", "mom_debug_force_rect_form", "mom_debug_force_pipeline", "mom_mlp_prefill_static",
+           "mom_init", "mom_debug_force_gemm_form", "mom_debug_force_short_form", "mom_debug_force_rect_form", "mom_debug_force_block", "mom_debug_force_pipeline", "mom_mlp_prefill_static",
            "mom_debug_mfma_probe")
 
 MOM_STATIC_WORKSPACE_BYTES = 64 << 20
@@ -74,6 +74,8 @@ def lib():
         L.mom_debug_force_short_form.argtypes = [ctypes.c_int, ctypes.c_int]
         L.mom_debug_force_rect_form.restype = ctypes.c_int
         L.mom_debug_force_rect_form.argtypes = [ctypes.c_int, ctypes.c_int]
+        L.mom_debug_force_block.restype = ctypes.c_int
+        L.mom_debug_force_block.argtypes = [ctypes.c_int]
         L.mom_debug_mfma_probe.restype = ctypes.c_int
         L.mom_debug_mfma_probe.argtypes = [vp, sz, vp, sz, i64, ctypes.c_int, ctypes.c_int, vp, vp]
         L.mom_debug_force_pipeline.restype = ctypes.c_int
@@ -197,6 +199,14 @@ def mom_debug_force_rect_form(token_rows=0, weight_rows=0):
     rc = lib().mom_debug_force_rect_form(int(token_rows), int(weight_rows))
     if rc != MOM_OK:
         raise MomError(rc, "mom_debug_force_rect_form")
+    return rc
+
+
+def mom_debug_force_block(token_rows=0):
+    """Testing aid: whole blocks of 16 or 32 token rows in one launch, where the layer fits; 0 = the library's choice."""
+    rc = lib().mom_debug_force_block(int(token_rows))
+    if rc != MOM_OK:
+        raise MomError(rc, "mom_debug_force_block")
     return rc
 
 

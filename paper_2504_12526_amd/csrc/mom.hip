@@ -17,6 +17,7 @@
 #include "mom_gemm.hip.inc"
 #include "mom_gemm_short.hip.inc"
 #include "mom_gemm_rect.hip.inc"
+#include "mom_block.hip.inc"
 #include "mom_gemv.hip.inc"
 #include "mom_probe.hip.inc"
 
@@ -94,6 +95,7 @@ DeviceInfo g_dev[kMaxDevices];
 // Testing overrides (the mom_debug_force_ calls); 0 = the library chooses.
 std::atomic<int> g_force_edge{0}, g_force_width{0}, g_force_pipeline{0};
 std::atomic<int> g_force_short{0}, g_force_rect{0};      // token rows << 16 | weight rows
+std::atomic<int> g_force_block{0};      // token rows of a block
 
 DeviceInfo* current_device_info() {
     int dev = 0;
@@ -286,6 +288,36 @@ hipError_t launch_gemm(const momk::Launch& l, const unsigned short* X, const uns
     }
 }
 
+// All S rows by blocks of form `form` (mom_gemm_forms.h).
+hipError_t launch_blocks(int form, const unsigned short* x, const unsigned short* wg, const unsigned short* wu, const unsigned short* wd,
+                         unsigned short* out, int64_t S, int64_t H, int64_t I, hipStream_t st) {
+    int i = 0;
+#define MOM_LAUNCH_BLOCK(TB, WAVES, R)                                                                            \
+    if (i++ == form) {                                                                                            \
+        hipLaunchKernelGGL((momk::mlp_block_kernel<TB, WAVES, R>), dim3((unsigned)((S + 16 * TB - 1) / (16 * TB))), dim3(WAVES * 64),  \
+                           (size_t)momk::block_lds(16 * TB, H, I, WAVES * R), st, x, wg, wu, wd, out, (int)S, (int)H, (int)I);  \
+        return hipGetLastError();                                                                                 \
+    }
+    MOM_BLOCK_FORMS(MOM_LAUNCH_BLOCK)
+#undef MOM_LAUNCH_BLOCK
+    return hipErrorInvalidValue;
+}
+
+// The form of launch_blocks for a call whose mini-sequences of C rows would take the launches given, or -1.
+int block_form(int64_t S, int64_t H, int64_t I, int64_t C, const momk::Launch& gateup, const momk::Launch& down) {
+    const int forced = g_force_block.load(std::memory_order_relaxed);
+    if (forced) {
+        for (int i = 0; i < momk::kBlockFormCount; ++i)
+            if (16 * momk::kBlockForms[i].tb == forced && momk::block_fits(momk::kBlockForms[i], H, I)) return i;
+        return -1;
+    }
+    if (S <= C || g_force_edge.load(std::memory_order_relaxed) || g_force_short.load(std::memory_order_relaxed) ||
+        g_force_rect.load(std::memory_order_relaxed))
+        return -1;
+    const int cus = compute_units();
+    return cus > 0 ? momk::choose_block(S, H, I, C, cus, gateup, down) : -1;
+}
+
 template <int MODE>
 hipError_t launch_gemv(const unsigned short* x, const unsigned short* Wa, const unsigned short* Wb, void* y,
                        int64_t R, int64_t K, hipStream_t st) {
@@ -317,9 +349,15 @@ int mlp_loop(const void* x, const void* wg, const void* wu, const void* wd, int6
     unsigned short* os = static_cast<unsigned short*>(out);
     unsigned short* w = static_cast<unsigned short*>(ws);
     if (events && hipEventRecord(static_cast<hipEvent_t>(events[0]), st) != hipSuccess) return MOM_ERR_HIP;
+    int planned = (int)C;                // token rows that `gateup` and `down` are for
+    momk::Launch gateup = choose_launch<momk::EPI_GATEUP>(C, I, H, 0), down = choose_launch<momk::EPI_DOWN>(C, H, I, 0);
+    if (!events) {
+        const int form = block_form(S, H, I, C, gateup, down);
+        if (form >= 0)
+            return launch_blocks(form, xs, static_cast<const unsigned short*>(wg), static_cast<const unsigned short*>(wu),
+                                 static_cast<const unsigned short*>(wd), os, S, H, I, st) == hipSuccess ? MOM_OK : MOM_ERR_HIP;
+    }
     // Algorithm 1, else-branch: O_i = MLP(A_i) for each mini-sequence, O_i written at its rows of O.
-    momk::Launch gateup = {}, down = {};
-    int planned = 0;                     // token rows that `gateup` and `down` are for
     for (int64_t c = 0; c < n; ++c) {
         const int64_t r0 = c * C;
         const int rows = (int)((r0 + C <= S) ? C : (S - r0));
@@ -446,6 +484,12 @@ int mom_debug_force_rect_form(int token_rows, int weight_rows) {
     if (!off && !momk::is_rect_form(false, token_rows, weight_rows) && !momk::is_rect_form(true, token_rows, weight_rows))
         return MOM_ERR_SHAPE;
     g_force_rect.store(off ? 0 : (token_rows << 16 | weight_rows), std::memory_order_relaxed);
+    return MOM_OK;
+}
+
+int mom_debug_force_block(int token_rows) {
+    if (token_rows != 0 && token_rows != 16 && token_rows != 32) return MOM_ERR_SHAPE;
+    g_force_block.store(token_rows, std::memory_order_relaxed);
     return MOM_OK;
 }
 

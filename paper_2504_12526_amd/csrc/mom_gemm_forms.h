@@ -384,6 +384,60 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus) {
     return l;
 }
 
+// ---- Whole blocks of token rows in one launch (mom_block.hip.inc), for calls of several mini-sequences on a small layer.
+constexpr int kBlockPad = 8;            // elements behind an LDS row: 16 bytes, so that 16 rows at one k lie on different banks
+constexpr int kBlockUnit = 4096;        // bytes of a unit of weights
+// Bytes of LDS of a block of `rows` token rows and `units` units of weights.
+constexpr int64_t block_lds(int64_t rows, int64_t H, int64_t I, int units) {
+    return rows * (H + I + 2 * kBlockPad) * 2 + (int64_t)units * kBlockUnit;
+}
+// X(TB, WAVES, R): 16 TB token rows, WAVES wavefronts with rings of R units.  bytes_per_us: weights through a workgroup, measured at
+// H = 256, I = 1024 (16 rows 17.6 us for 512 token rows, 32 rows 23.7 us for 8192) and H = 1056, I = 2080 (166 us for 3000).  Tokens
+// in and out take 1 us per 10^6 elements more.
+#define MOM_BLOCK_FORMS(X) X(1, 8, 2) X(2, 8, 2) X(1, 6, 2)
+struct BlockForm { int tb, waves, r, bytes_per_us; };
+#define MOM_SHAPE(TB, WAVES, R) {TB, WAVES, R, TB == 2 ? 95000 : WAVES == 8 ? 110000 : 79000},
+constexpr BlockForm kBlockForms[] = {MOM_BLOCK_FORMS(MOM_SHAPE)};
+#undef MOM_SHAPE
+constexpr int kBlockFormCount = sizeof(kBlockForms) / sizeof(kBlockForms[0]);
+inline bool block_fits(const BlockForm& f, int64_t H, int64_t I) { return H + I <= 8192 && block_lds(16 * f.tb, H, I, f.waves * f.r) <= 163840; }
+inline double block_time(const BlockForm& f, int64_t S, int64_t H, int64_t I, int cus) {
+    const int64_t blocks = (S + 16 * f.tb - 1) / (16 * f.tb);
+    return 4.0 + (double)((blocks + cus - 1) / cus) * (6.0 * H * I) / f.bytes_per_us + 1.0e-6 * S * H;
+}
+
+// The formula's time of launch l of M token rows.
+inline double formula_time(const Launch& l, int64_t M, int64_t N, int64_t K, bool gateup, int cus) {
+    const bool small = small_layer(N, K);
+    if (l.kind == kShortTiles) {
+        const LaunchTime& t = gateup ? (small ? kShortGateUpSmallTime : kShortGateUpTime) : (small ? kShortDownKeptTime : kShortDownTime);
+        return launch_time(l.grid, M, K, gateup, short_shape(gateup, l.form), t, cus);
+    }
+    if (gateup && l.tm == 128) return launch_time(l.grid, M, K, true, kPairShape, small ? kPairGateUpSmallTime : kPairGateUpTime, cus);
+    double t = launch_time(l.grid, M, K, gateup, {l.tm, l.tn, 1, 0}, gateup ? kFullGateUpTime : kFullDownTime, cus);
+    if (l.kind == kTwoWidths) t += launch_time(l.narrow, M, K, true, {256, 192, 1, 0}, kFullGateUpTime, cus);
+    return t;
+}
+
+// The form in which S token rows take less time than as mini-sequences of C of them, whose two launches are given; -1: none.  A
+// mini-sequence takes 6 us less than the launches by themselves (H = 256, I = 1024: 128 rows 7.0 us, 512 8.0, 2048 11.0, formula
+// 13.1, 14.2, 17.2; H = 1056, I = 2080: 128 rows 12.3, formula 18.1; where both are longer, 512 rows 21.5 and 24.7, the loop
+// looks better than it is).  7 % off that: 2048 rows by 1024 of the former 17.2 us, formula 18.9, as blocks 18.7.
+inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, const Launch& gateup, const Launch& down) {
+    if (S <= C || !small_layer(I, H)) return -1;
+    int best = -1;
+    double least = 0;
+    for (int i = 0; i < kBlockFormCount; ++i) {
+        const BlockForm& f = kBlockForms[i];
+        if (!block_fits(f, H, I) || (S + 16 * f.tb - 1) / (16 * f.tb) * f.waves * 64 > (int64_t)0x7fffffff) continue;
+        const double t = block_time(f, S, H, I, cus);
+        if (best < 0 || t < least) { best = i; least = t; }
+    }
+    if (best < 0) return -1;
+    const double one = formula_time(gateup, C, I, H, true, cus) + formula_time(down, C, H, I, false, cus) - 6;
+    return least < 0.93 * one * ((S + C - 1) / C) ? best : -1;
+}
+
 }  // namespace momk
 
 #endif  // MOM_GEMM_FORMS_H
