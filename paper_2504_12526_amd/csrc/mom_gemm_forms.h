@@ -16,10 +16,13 @@
 
 #define MOM_SHORT_FORMS_DOWN(X)                                                                          \
     X(16, 16, 1, 1, 2, 8) X(32, 16, 2, 1, 4, 6) X(32, 32, 2, 2, 2, 5) X(48, 32, 1, 2, 2, 8)              \
-    X(64, 32, 2, 2, 2, 6) X(96, 32, 2, 2, 2, 5) X(128, 32, 4, 1, 1, 8) X(32, 64, 2, 2, 1, 6)             \
-    X(64, 64, 2, 2, 1, 5) X(80, 64, 1, 4, 2, 4) X(96, 64, 2, 2, 1, 8) X(128, 64, 2, 2, 1, 6)             \
-    X(160, 64, 2, 2, 1, 5) X(192, 64, 2, 2, 1, 5) X(256, 64, 2, 2, 1, 4) X(96, 128, 2, 2, 1, 5)          \
-    X(128, 128, 2, 2, 1, 5) X(160, 128, 2, 2, 1, 4) X(192, 128, 2, 2, 1, 4) X(224, 128, 2, 2, 1, 3)
+    X(64, 32, 2, 2, 2, 6) X(96, 32, 2, 2, 2, 5) X(32, 64, 2, 2, 1, 6) X(64, 64, 2, 2, 1, 5)              \
+    X(80, 64, 1, 4, 2, 4) X(96, 64, 2, 2, 2, 4) X(128, 64, 2, 2, 1, 6) X(160, 64, 2, 2, 1, 5)            \
+    X(192, 64, 2, 2, 1, 5) X(256, 64, 2, 2, 1, 4) X(96, 128, 2, 2, 1, 5) X(128, 128, 2, 2, 1, 5)         \
+    X(160, 128, 2, 2, 1, 4) X(192, 128, 2, 2, 1, 4) X(224, 128, 2, 2, 1, 3)                              \
+    X(32, 48, 2, 1, 2, 8) X(48, 48, 3, 1, 2, 6) X(64, 48, 4, 1, 2, 5) X(80, 48, 1, 3, 2, 5)              \
+    X(96, 48, 2, 1, 2, 4) X(80, 32, 1, 2, 2, 5) X(48, 64, 1, 4, 2, 5) X(96, 96, 2, 2, 1, 6)              \
+    X(128, 96, 2, 2, 1, 5) X(160, 96, 2, 2, 1, 5)
 #define MOM_SHORT_FORMS_GATEUP(X)                                                                        \
     X(16, 32, 1, 1, 4, 6) X(32, 32, 2, 1, 2, 8) X(16, 64, 1, 2, 2, 8) X(32, 64, 2, 2, 2, 6)              \
     X(64, 64, 2, 2, 1, 3) X(128, 64, 2, 2, 1, 3) X(64, 128, 2, 2, 1, 6) X(96, 128, 2, 2, 1, 5)           \
@@ -46,6 +49,9 @@ constexpr ShortShape kShortGateUp[] = {MOM_SHORT_FORMS_GATEUP(MOM_SHAPE)};
 constexpr int kShortDownForms = sizeof(kShortDown) / sizeof(kShortDown[0]);
 constexpr int kShortGateUpForms = sizeof(kShortGateUp) / sizeof(kShortGateUp[0]);
 
+// Down forms that are looked at for layers that stay in the Infinity Cache: the later ones gain nothing there (their launches take 5
+// ... 20 us, and the formula's best of them 0.4 % more on average).
+constexpr int kSmallDownForms = 19;
 inline int short_forms(bool gateup) { return gateup ? kShortGateUpForms : kShortDownForms; }
 inline ShortShape short_shape(bool gateup, int form) { return gateup ? kShortGateUp[form] : kShortDown[form]; }
 
@@ -134,7 +140,7 @@ constexpr bool ring_load_up(int TM, int TN, int KSUB, int j) { return j - KSUB *
 //   whole_tile      the token rows are those of a whole tile, which the launch waits for; otherwise those of an average one.
 //   lead            the part per K-element is less by this and by lead_small x 64 / (tm + tn) where the last token tile has
 //                   clearly fewer rows, the launch is one round and W_down fits the Infinity Cache: the CUs of that tile run
-//                   ahead and bring the weights nearer for the others (1000 rows x 4096 columns in tiles of 160, six of them
+//                   ahead and bring the weights nearer for the others, less so in tiles below 48 rows (1000 rows x 4096 columns in tiles of 160, six of them
 //                   and one of 40, x 128: 119 us; as eight even ones of 128: 133 us).
 // Fitted to every form on 1 ... 4096 rows of eleven layers (H 256 ... 8192, I 1024 ... 28672), single calls and loops of
 // mini-sequences.  Formula and time of the forms near the best of their size differ by 5 (256-row tiles), 8 (short, down)
@@ -148,10 +154,17 @@ struct LaunchTime {
     double lead, lead_small;
 };
 constexpr double kFromHbm = 0.69, kFromCache = 0.33;
-constexpr LaunchTime kShortDownTime = {4.0, 5.0e-5, 1.94e-5, 5.56e-5, 5.81e-8, 1.0, kFromHbm, true, 0.1, 0.2};
+// Down, weights from HBM and (kShortDownKeptTime) from the Infinity Cache: by what the choice costs, on 59 row counts from 1 to 2048
+// of six layers (H 2048 ... 8192), launches of one form after the other: 0.5 % (236 launches, none above 10 %) and 0.6 % (177, 2 above
+// 10 %) over the best of 37 forms; with the 20 forms and the constants before, 2.5 % (29) and 2.2 % (28).  From 1000 rows on, where
+// it is the 256-row and rectangular tiles that a short form is compared with, kShortDownLongTime, fitted together with those (1536
+// rows x 4096 columns in 192 x 128: 160 us, so 159, by kShortDownTime 178).
+constexpr LaunchTime kShortDownTime = {5.59, 1.42e-5, 1.80e-5, 5.30e-5, 1.29e-7, 1.0, kFromHbm, true, 0.182, 0.219};
+constexpr LaunchTime kShortDownLongTime = {4.0, 5.0e-5, 1.94e-5, 5.56e-5, 5.81e-8, 1.0, kFromHbm, true, 0.1, 0.2};
+constexpr LaunchTime kShortDownKeptTime = {2.28, 9.78e-5, 1.14e-5, 4.14e-5, 7.43e-8, 1.0, kFromCache, true, 0, 0};
 // W_down still in the Infinity Cache (kept_down).  Then nobody needs to run ahead: 1024 rows x 4096 columns in tiles of
 // 160 x 128: 117 us, in eight of 128 x 128: 109 us; 512 rows in tiles of 160 x 64 80 us, of 128 x 64 70 us.
-constexpr LaunchTime kShortDownKeptTime = {5.9, 1.40e-4, 1.02e-5, 3.58e-5, 1.36e-7, 1.0, kFromCache, true, 0, 0};
+constexpr LaunchTime kShortDownSmallTime = {5.9, 1.40e-4, 1.02e-5, 3.58e-5, 1.36e-7, 1.0, kFromCache, true, 0, 0};
 constexpr LaunchTime kShortGateUpTime = {5.95, 1.97e-4, 1.11e-5, 5.61e-5, 1.42e-7, 1.0, kFromHbm, false, 0, 0};
 constexpr LaunchTime kShortGateUpSmallTime = {6.15, 2.28e-4, 1.20e-5, 3.92e-5, 1.41e-7, 1.0, kFromCache, false, 0, 0};
 constexpr LaunchTime kFullDownTime = {4.0, 2.4e-5, 1.09e-5, 4.87e-5, 1.52e-7, 0.80, 0, true, 0, 0};
@@ -197,7 +210,7 @@ inline double launch_time(const TileGrid& g, int64_t M, int64_t K, bool gateup, 
     if (t.lead > 0 && rounds == 1 && g.tiles_m > 1 && weights_fit(g.tiles_n * f.tn, K)) {
         const double last = (double)(M - (int64_t)(g.tiles_m - 1) * f.tm) / f.tm;      // of the last token tile
         const double ahead = last < 0.4 ? 1 : last < 0.72 ? (0.72 - last) / 0.32 : 0;
-        per_k *= 1 - ahead * (t.lead + t.lead_small * 64 / (f.tm + f.tn));
+        per_k *= 1 - ahead * (f.tm < 48 ? f.tm / 48.0 : 1) * (t.lead + t.lead_small * 64 / (f.tm + f.tn));
     }
     const double once = t.start + t.output * f.tm * (gateup ? f.tn / 2 : f.tn);
     const double starts = (double)rounds / f.per_cu, body = moved * per_k;
@@ -229,9 +242,9 @@ inline bool kept_down(int64_t M, int64_t N, int64_t K, bool later) {
 }
 
 // The short form that takes the least time; its time in `least`; -1: none.
-inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, const LaunchTime& time, int cus, double& least) {
+inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, const LaunchTime& time, int cus, double& least, int forms = 0) {
     int best = -1;
-    for (int i = 0; i < short_forms(gateup); ++i) {
+    for (int i = 0; i < (forms ? forms : short_forms(gateup)); ++i) {
         const ShortShape f = short_shape(gateup, i);
         const double t = launch_time(tile_grid(M, N, gateup, f), M, K, gateup, f, time, cus);
         if (t >= 0 && (best < 0 || t < least)) { best = i; least = t; }
@@ -299,15 +312,17 @@ inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool later, 
     const Launch full = whole_launch(M, N, false, 256, 256);
     if (full.kind == kRefused || full_tiles) return full;
     double least = 0, time = 0;
-    const LaunchTime& short_time = kept_down(M, N, K, later) ? kShortDownKeptTime : kShortDownTime;
-    const int form = choose_short_form(M, N, K, false, short_time, cus, least);
+    const bool small = small_layer(N, K);
+    const LaunchTime& short_time = small ? kShortDownSmallTime : kept_down(M, N, K, later) ? kShortDownKeptTime :
+                                   M < 1000 ? kShortDownTime : kShortDownLongTime;
+    const int form = choose_short_form(M, N, K, false, short_time, cus, least, small ? kSmallDownForms : 0);
     // The width: by time where the widest take no more than one round; over several rounds by rounds x columns, a column of
     // a narrower tile charged what it was measured to cost more for the token fragments it shares among fewer MFMAs
     // (12400 rows x 4096 columns: 3.6 rounds of 224-wide tiles 1033 us, 5 of 160-wide ones 1113 us).
     // Rectangular tiles by their time, from the fewest rows of the fit on; not for layers that stay in the Infinity Cache, whose
     // launches end before a large tile's rings have filled (1000 rows x 256 columns, K = 1024: 10.4 us, short 6.3).
     constexpr int per_mille[5] = {1000, 1020, 1070, 1170, 1310};
-    const int rects = M < 1000 || small_layer(N, K) ? 0 : rect_forms(false);
+    const int rects = M < 1000 || small ? 0 : rect_forms(false);
     int width = 0;
     int64_t columns = 0;
     ShortShape rect = {0, 0, 1, 0};
@@ -410,7 +425,7 @@ inline double block_time(const BlockForm& f, int64_t S, int64_t H, int64_t I, in
 inline double formula_time(const Launch& l, int64_t M, int64_t N, int64_t K, bool gateup, int cus) {
     const bool small = small_layer(N, K);
     if (l.kind == kShortTiles) {
-        const LaunchTime& t = gateup ? (small ? kShortGateUpSmallTime : kShortGateUpTime) : (small ? kShortDownKeptTime : kShortDownTime);
+        const LaunchTime& t = gateup ? (small ? kShortGateUpSmallTime : kShortGateUpTime) : (small ? kShortDownSmallTime : kShortDownTime);
         return launch_time(l.grid, M, K, gateup, short_shape(gateup, l.form), t, cus);
     }
     if (gateup && l.tm == 128) return launch_time(l.grid, M, K, true, kPairShape, small ? kPairGateUpSmallTime : kPairGateUpTime, cus);
