@@ -35,7 +35,8 @@
     X(160, 160) X(160, 256) X(192, 160) X(192, 224) X(192, 256) X(224, 160) X(224, 224) X(224, 256)
 #define MOM_RECT_FORMS_GATEUP(X)                                                                         \
     X(256, 128) X(160, 160) X(192, 160) X(224, 160) X(256, 160) X(320, 160) X(288, 192) X(320, 192)      \
-    X(160, 224) X(192, 224) X(256, 224) X(288, 224) X(224, 256) X(192, 320)
+    X(160, 224) X(192, 224) X(256, 224) X(288, 224) X(224, 256) X(192, 320)                              \
+    X(96, 160) X(128, 160) X(96, 224) X(128, 224)
 
 namespace momk {
 
@@ -139,9 +140,12 @@ constexpr bool ring_load_up(int TM, int TN, int KSUB, int j) { return j - KSUB *
 //                   0.33 us from the Infinity Cache.
 //   whole_tile      the token rows are those of a whole tile, which the launch waits for; otherwise those of an average one.
 //   lead            the part per K-element is less by this and by lead_small x 64 / (tm + tn) where the last token tile has
-//                   clearly fewer rows, the launch is one round and W_down fits the Infinity Cache: the CUs of that tile run
+//                   clearly fewer rows, the launch is one round and W_down at most lead_mib: the CUs of that tile run
 //                   ahead and bring the weights nearer for the others, less so in tiles below 48 rows (1000 rows x 4096 columns in tiles of 160, six of them
-//                   and one of 40, x 128: 119 us; as eight even ones of 128: 133 us).
+//                   and one of 40, x 128: 119 us; as eight even ones of 128: 133 us; 512 rows x 5120 columns, K = 25600, in
+//                   160 x 96 166 us, in 128 x 96 200 us).
+//   lead_few        above four token tiles less the more there are: the CUs ahead are fewer of all (512 rows as above in
+//                   96 x 128, five and a third: 192 us); and less in tiles above 160 x 128.
 // Fitted to every form on 1 ... 4096 rows of eleven layers (H 256 ... 8192, I 1024 ... 28672), single calls and loops of
 // mini-sequences.  Formula and time of the forms near the best of their size differ by 5 (256-row tiles), 8 (short, down)
 // and 9 % (short, gate/up; the least of many uncertain times is an optimistic one, so these figures are the fitted ones
@@ -152,14 +156,18 @@ struct LaunchTime {
     double start, output, row, fetched, product, last_round, latency;
     bool whole_tile;
     double lead, lead_small;
+    int lead_mib = 160;
+    bool lead_few = false;
 };
 constexpr double kFromHbm = 0.69, kFromCache = 0.33;
 // Down, weights from HBM and (kShortDownKeptTime) from the Infinity Cache: by what the choice costs, on 59 row counts from 1 to 2048
 // of six layers (H 2048 ... 8192), launches of one form after the other: 0.5 % (236 launches, none above 10 %) and 0.6 % (177, 2 above
-// 10 %) over the best of 37 forms; with the 20 forms and the constants before, 2.5 % (29) and 2.2 % (28).  From 1000 rows on, where
+// 10 %) over the best of 37 forms; with the 20 forms and the constants before, 2.5 % (29) and 2.2 % (28).  Inside calls, behind a
+// gate/up launch and with weights not used before, on 40 ... 1900 rows of ten layers (H 3584 ... 8192) with W_down of up to 470 MB:
+// 0.7 % (179 launches, 2 above 10 %); without lead_mib, lead_few and kOverWhole 3.0 % (20).  From 1000 rows on, where
 // it is the 256-row and rectangular tiles that a short form is compared with, kShortDownLongTime, fitted together with those (1536
 // rows x 4096 columns in 192 x 128: 160 us, so 159, by kShortDownTime 178).
-constexpr LaunchTime kShortDownTime = {5.59, 1.42e-5, 1.80e-5, 5.30e-5, 1.29e-7, 1.0, kFromHbm, true, 0.182, 0.219};
+constexpr LaunchTime kShortDownTime = {5.59, 1.42e-5, 1.80e-5, 5.30e-5, 1.29e-7, 1.0, kFromHbm, true, 0.182, 0.219, 256, true};
 constexpr LaunchTime kShortDownLongTime = {4.0, 5.0e-5, 1.94e-5, 5.56e-5, 5.81e-8, 1.0, kFromHbm, true, 0.1, 0.2};
 constexpr LaunchTime kShortDownKeptTime = {2.28, 9.78e-5, 1.14e-5, 4.14e-5, 7.43e-8, 1.0, kFromCache, true, 0, 0};
 // W_down still in the Infinity Cache (kept_down).  Then nobody needs to run ahead: 1024 rows x 4096 columns in tiles of
@@ -183,12 +191,20 @@ constexpr ShortShape kPairShape = {128, 128, 2, 58};
 // gate/up launches gain 2-5 % on them.  So a rectangular tile has to promise more than the others' formula by the share given:
 // kOverOneRound   gate/up, 256 x 256 tiles of more than one round: at 0.945 ... 0.975 promised 0.95 ... 1.06 of the time came
 //                 (1000 rows x 18944 columns 0.964: 203 -> 212 us), below mostly as promised (850 rows 0.74: 198 -> 161 us)
+// kOneTokenTile   gate/up, 256 x 256 tiles of up to 256 rows: 17920 columns, K = 5120, 256 rows 101 -> 93 us, promised 0.9 ... 1.03
 // kOverShort      gate/up short forms, whose time at 97 ... 224 rows is overrated: 0.83 ... 0.90 promised 0.97 ... 1.0
-// kOverDown       either kind, after the correction: 2900 rows x 4096 columns 0.89 promised, 247 -> 233 us
+// kOverShortFilled  the same at 24 ... 128 rows where one token tile of them keeps 7/8 of the CUs busy or more, and no less than
+//                 the weights take at 5.6 TB/s: 18944 columns, K = 3584, 64 rows 51.4 -> 47.8 us, 25600, K = 5120, 119.7 ->
+//                 94.5; on 180 of 256 CUs (14336 columns, K = 4096) they lose (96 rows 45.7 -> 50.5)
+// kOverDown       down, either kind, after the correction: 2900 rows x 4096 columns 0.89 promised, 247 -> 233 us
+// kOverWhole      down below 1000 rows, where the formula underrates the whole tiles against the short ones: 700 rows x 8192
+//                 columns, K = 28672, in 192 x 128 325, in 256 x 128 362 us at 344 and 326 promised
 constexpr LaunchTime kRectGateUpTime = {3.73, 3.07e-5, 1.09e-5, 4.22e-5, 1.68e-7, 0.74, 0, true, 0, 0};
 constexpr LaunchTime kRectDownTime = {7.24, 2.95e-5, 2.34e-5, 7.72e-6, 1.02e-7, 0.707, 0, true, 0.048, 0};
 constexpr int kRectDownPerMille[kRectDownForms] = {1000, 970, 970, 975, 1010, 960, 1010, 1040};
-constexpr double kOverOneRound = 0.945, kWithinOneRound = 0.975, kOverShort = 0.83, kOverDown = 0.965;
+constexpr double kOverOneRound = 0.945, kWithinOneRound = 0.975, kOneTokenTile = 1.03;
+constexpr double kOverShort = 0.83, kOverShortFilled = 0.975, kOverDown = 0.975, kOverWhole = 0.9;
+constexpr double kRectBytes = 4 / 5.6e6;        // us per weight pair at 5.6 TB/s
 
 // Whether weight rows x K of them leave the Infinity Cache room (142 MB do, 470 MB do not).
 inline bool weights_fit(int64_t rows, int64_t K) { return 2 * rows * K <= ((int64_t)160 << 20); }
@@ -207,10 +223,11 @@ inline double launch_time(const TileGrid& g, int64_t M, int64_t K, bool gateup, 
     const double fetched = (group * token_rows + (on_xcd + group - 1) / group * f.tn) * 8 / cus;
     const double tile_rows = t.whole_tile ? f.tm : token_rows;
     double per_k = t.row * (tile_rows + f.tn) + t.fetched * fetched + t.product * tile_rows * f.tn;
-    if (t.lead > 0 && rounds == 1 && g.tiles_m > 1 && weights_fit(g.tiles_n * f.tn, K)) {
+    if (t.lead > 0 && rounds == 1 && g.tiles_m > 1 && 2 * g.tiles_n * f.tn * K <= (int64_t)t.lead_mib << 20) {
         const double last = (double)(M - (int64_t)(g.tiles_m - 1) * f.tm) / f.tm;      // of the last token tile
         const double ahead = last < 0.4 ? 1 : last < 0.72 ? (0.72 - last) / 0.32 : 0;
-        per_k *= 1 - ahead * (f.tm < 48 ? f.tm / 48.0 : 1) * (t.lead + t.lead_small * 64 / (f.tm + f.tn));
+        const double shared = !t.lead_few ? 1 : (g.tiles_m > 4 ? 4.0 / g.tiles_m : 1) * (f.tm * f.tn > 160 * 128 ? 0.8 : 1);
+        per_k *= 1 - ahead * (f.tm < 48 ? f.tm / 48.0 : 1) * shared * (t.lead + t.lead_small * 64 / (f.tm + f.tn));
     }
     const double once = t.start + t.output * f.tm * (gateup ? f.tn / 2 : f.tn);
     const double starts = (double)rounds / f.per_cu, body = moved * per_k;
@@ -257,6 +274,7 @@ inline ShortShape choose_rect_form(int64_t M, int64_t N, int64_t K, bool gateup,
     ShortShape best = {0, 0, 1, 0};
     for (int i = 0; i < rect_forms(gateup); ++i) {
         const ShortShape f = rect_shape(gateup, i);
+        if (gateup && f.tm < 160 && M > 224) continue;         // tiles for one token tile, or two (256 rows x 13824 columns: 82 -> 94 us)
         const double t = launch_time(tile_grid(M, N, gateup, f), M, K, gateup, f, time, cus);
         if (t >= 0 && (best.tm == 0 || t < least)) { best = f; least = t; }
     }
@@ -316,6 +334,7 @@ inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool later, 
     const LaunchTime& short_time = small ? kShortDownSmallTime : kept_down(M, N, K, later) ? kShortDownKeptTime :
                                    M < 1000 ? kShortDownTime : kShortDownLongTime;
     const int form = choose_short_form(M, N, K, false, short_time, cus, least, small ? kSmallDownForms : 0);
+    if (&short_time == &kShortDownTime) least *= kOverWhole;
     // The width: by time where the widest take no more than one round; over several rounds by rounds x columns, a column of
     // a narrower tile charged what it was measured to cost more for the token fragments it shares among fewer MFMAs
     // (12400 rows x 4096 columns: 3.6 rounds of 224-wide tiles 1033 us, 5 of 160-wide ones 1113 us).
@@ -377,12 +396,16 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus) {
     if (wide_cols == 0)
         full = launch_time(tile_grid(M, N, true, {256, 192, 1, 0}), M, K, true, {256, 192, 1, 0}, kFullGateUpTime, cus);
     // Rectangular tiles, by their time, for layers that come from HBM: 300 rows x 14336 columns, K = 4096: 91 -> 67 us; of a
-    // layer of 69 MiB, which the Infinity Cache keeps, 1 % at most and up to 17 % lost at 128 rows.  Not below the row counts of the fit.
-    if (M > 96 && 6 * N * K > ((int64_t)128 << 20)) {
+    // layer of 69 MiB, which the Infinity Cache keeps, 1 % at most and up to 17 % lost at 128 rows.  Below 97 rows only where they keep the CUs busy.
+    if (M >= 24 && 6 * N * K > ((int64_t)128 << 20)) {
         double rect = 0;
         const ShortShape r = choose_rect_form(M, N, K, true, kRectGateUpTime, cus, rect);
-        const double share = plain_launch.grid.tiles > (uint64_t)cus ? kOverOneRound : kWithinOneRound;
-        if (r.tm && rect < share * full && (form < 0 || least >= full || rect < kOverShort * least)) return whole_launch(M, N, true, r.tm, r.tn);
+        const uint64_t tiles = r.tm ? tile_grid(M, N, true, r).tiles : 0;
+        const bool filled = M <= 128 && tiles <= (uint64_t)cus && 8 * tiles >= 7 * (uint64_t)cus;
+        if (filled && rect < kRectBytes * N * K) rect = kRectBytes * N * K;
+        const double share = plain_launch.grid.tiles > (uint64_t)cus ? kOverOneRound : M <= 256 ? kOneTokenTile : kWithinOneRound;
+        if (r.tm && (M > 96 || filled) && rect < share * full && (form < 0 || least >= full || rect < (filled ? kOverShortFilled : kOverShort) * least))
+            return whole_launch(M, N, true, r.tm, r.tn);
     }
     const Launch pair = whole_launch(M, N, true, 128, 128);
     if (pair.kind != kRefused && pair.grid.tiles <= 2 * (uint64_t)cus &&
