@@ -9,7 +9,7 @@ LIB = os.path.join(HERE, "libmom.so")
 SOURCES = [os.path.join(CSRC, "mom.hip")]
 DEPS = SOURCES + [os.path.join(CSRC, "mom_gemm.hip.inc"), os.path.join(CSRC, "mom_gemm_short.hip.inc"),
                   os.path.join(CSRC, "mom_gemm_rect.hip.inc"), os.path.join(CSRC, "mom_gemm_rect_schedule.h"),
-                  os.path.join(CSRC, "mom_block.hip.inc"),
+                  os.path.join(CSRC, "mom_block.hip.inc"), os.path.join(CSRC, "mom_kv.hip.inc"),
                   os.path.join(CSRC, "mom_gemm_forms.h"), os.path.join(CSRC, "mom_gemm_schedule.h"),
                   os.path.join(CSRC, "mom_gemv.hip.inc"), os.path.join(CSRC, "mom_probe.hip.inc"),
                   os.path.join(ROOT, "include", "mom.h")]

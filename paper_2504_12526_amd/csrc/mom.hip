@@ -1,7 +1,7 @@
 // libmom: C ABI over the gfx950 kernels of the MOM prefill hot path (see include/mom.h).
 //
 // Host side: argument validation, the mini-sequence driver (Algorithm 1, else-branch), the
-// last-token LM head launch and the KV offload copies.  Nothing here allocates or synchronises.
+// last-token LM head launch and the KV offload and reload copies.  Nothing here allocates or synchronises.
 // The only state is what mom_init resolves per device (compute-unit count, address of the static
 // workspace) and the testing overrides of the mom_debug_force_ calls.
 #include <hip/hip_runtime.h>
@@ -19,6 +19,7 @@
 #include "mom_gemm_rect.hip.inc"
 #include "mom_block.hip.inc"
 #include "mom_gemv.hip.inc"
+#include "mom_kv.hip.inc"
 #include "mom_probe.hip.inc"
 
 // Workspace of mom_mlp_prefill_static: one copy per device, held from the moment the library is
@@ -145,6 +146,33 @@ int check_pinned_host(const void* p, size_t n) {
         if (at.type != hipMemoryTypeHost) return MOM_ERR_HOST;
     }
     return MOM_OK;
+}
+
+// The device address of pinned_host if kv_reload_kernel is to copy bytes_each bytes each into k and v on stream st, else nullptr:
+// whole 16-byte chunks, buffers on the current device, which is also the stream's, that do not overlap, up to 256 KiB each.
+// Alone the kernel is the faster one far beyond (256 KiB 34 -> 14 us, 512 KiB 43 -> 23, 2 MiB 98 -> 82), but decoding beside it
+// loses the memory rate of its CUs: 222 us of last-token projections become 225, 231 (512 KiB) and 258 (2 MiB).
+const void* reload_source(const void* pinned_host, const void* k, const void* v, size_t bytes_each, hipStream_t st) {
+    if (bytes_each > ((size_t)256 << 10) || bytes_each % 16 || !aligned16(pinned_host) || !aligned16(k) || !aligned16(v)) return nullptr;
+    if (overlaps(k, bytes_each, v, bytes_each)) return nullptr;
+    int dev = 0, stream_dev = 0;
+    hipPointerAttribute_t at;
+    const void* mapped = nullptr;
+    bool ok = hipGetDevice(&dev) == hipSuccess && (!st || (hipStreamGetDevice(st, &stream_dev) == hipSuccess && stream_dev == dev));
+    for (int i = 0; i < 4 && ok; ++i) {
+        const unsigned char* p = static_cast<const unsigned char*>(i < 2 ? k : v) + (i & 1 ? bytes_each - 1 : 0);
+        ok = hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice && at.device == dev;
+    }
+    for (int i = 0; i < 2 && ok; ++i) {
+        const size_t at_byte = i ? 2 * bytes_each - 1 : 0;
+        ok = hipPointerGetAttributes(&at, static_cast<const unsigned char*>(pinned_host) + at_byte) == hipSuccess && at.devicePointer;
+        if (!ok) break;
+        const unsigned char* d = static_cast<const unsigned char*>(at.devicePointer);
+        if (i == 0) mapped = d;
+        else ok = d == static_cast<const unsigned char*>(mapped) + at_byte;
+    }
+    if (!ok) (void)hipGetLastError();
+    return ok && aligned16(mapped) ? mapped : nullptr;
 }
 
 // The launch part described by `a` takes the tiles of `g`.
@@ -668,7 +696,15 @@ int mom_kv_reload(const void* pinned_host, void* k, void* v, void* stream, size_
         if (rc != MOM_OK) return rc;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (bytes_each != 0) {
+    const void* mapped = bytes_each != 0 ? reload_source(pinned_host, k, v, bytes_each, st) : nullptr;
+    if (mapped) {
+        const uint32_t n = (uint32_t)(bytes_each / 16);
+        const uint32_t full = (2 * n + momk::kReloadThreads * momk::kReloadLoads - 1) / (momk::kReloadThreads * momk::kReloadLoads);
+        hipLaunchKernelGGL(momk::kv_reload_kernel, dim3(full < (uint32_t)momk::kReloadBlocks ? full : momk::kReloadBlocks),
+                           dim3(momk::kReloadThreads), 0, st, static_cast<momk::u32x4*>(k), static_cast<momk::u32x4*>(v),
+                           static_cast<const momk::u32x4*>(mapped), n);
+        if (hipGetLastError() != hipSuccess) return MOM_ERR_HIP;
+    } else if (bytes_each != 0) {
         const unsigned char* src = static_cast<const unsigned char*>(pinned_host);
         if (hipMemcpyAsync(k, src, bytes_each, hipMemcpyHostToDevice, st) != hipSuccess) return MOM_ERR_HIP;
         if (hipMemcpyAsync(v, src + bytes_each, bytes_each, hipMemcpyHostToDevice, st) != hipSuccess)

@@ -1,0 +1,66 @@
+"""KV-cache reload of few tokens by a kernel and of others by copies: the bytes, and none beside them, at the edges of a
+workgroup's pass, of the kernel's range and of its alignment; and captured."""
+import pytest
+import torch
+
+from paper_2504_12526_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+PASS = 16 * 256 * 4 * 16          # bytes of one pass of all workgroups
+LARGEST = 256 << 10               # bytes each of the kernel's range
+GUARD = 64                         # elements on either side
+
+
+def _reload(each, offset, seed):
+    n = each // 2
+    g = torch.Generator().manual_seed(seed)
+    host = torch.randint(-32768, 32767, (2 * n + offset,), dtype=torch.int16, generator=g).pin_memory()
+    bufs = [torch.full((n + 2 * GUARD + offset,), 77 + i, dtype=torch.int16, device="cuda") for i in range(2)]
+    k, v = (b[GUARD + offset: GUARD + offset + n].view(torch.bfloat16) for b in bufs)
+    src = host[offset:].view(torch.bfloat16)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    binding.mom_kv_reload(src, k, v, side)
+    side.synchronize()
+    for i, b in enumerate(bufs):
+        got = b.cpu()
+        lo = GUARD + offset
+        assert torch.equal(got[lo: lo + n], host[offset + i * n: offset + (i + 1) * n])
+        assert bool((got[:lo] == 77 + i).all()) and bool((got[lo + n:] == 77 + i).all())
+
+
+@pytest.mark.parametrize("each", [16, 32, 4096, 8192 - 16, 8192, 8192 + 16, PASS // 2 - 16, PASS // 2, PASS // 2 + 16, PASS - 16,
+                                  LARGEST - 16, LARGEST, LARGEST + 16, 4 * LARGEST])
+def test_bytes(each):
+    _reload(each, 0, each % 1000)
+
+
+@pytest.mark.parametrize("each,offset", [(2, 0), (14, 0), (4098, 0), (4096, 1), (4096, 8), (65536, 3)])
+def test_odd_sizes_and_alignments(each, offset):
+    _reload(each, offset, each + offset)
+
+
+def test_overlapping_buffers_are_copied_one_after_the_other():
+    host = torch.randint(-32768, 32767, (2 * 4096,), dtype=torch.int16).pin_memory()
+    buf = torch.zeros(4096 + 64, dtype=torch.int16, device="cuda")
+    binding.mom_kv_reload(host.view(torch.bfloat16), buf[:4096].view(torch.bfloat16), buf[64:].view(torch.bfloat16), torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert torch.equal(buf.cpu(), torch.cat([host[:64], host[4096:]]))
+
+
+def test_captured():
+    n = 40000
+    host = torch.zeros(2 * n, dtype=torch.int16).pin_memory()
+    k, v = (torch.zeros(n, dtype=torch.int16, device="cuda") for _ in range(2))
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        binding.mom_kv_reload(host.view(torch.bfloat16), k.view(torch.bfloat16), v.view(torch.bfloat16), side)
+    for r in range(4):
+        host.copy_(torch.arange(2 * n).add_(r * 7919).to(torch.int16))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(k.cpu(), host[:n]) and torch.equal(v.cpu(), host[n:])
+        k.zero_()
+        v.zero_()
