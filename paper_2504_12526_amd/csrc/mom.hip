@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <tuple>
 #include <type_traits>
 
 #include "mom.h"
@@ -84,6 +85,14 @@ int validate_mlp(const void* x, const void* wg, const void* wu, const void* wd, 
     return MOM_OK;
 }
 
+// Whether a query succeeded whose failure is an answer like any other: its error is not left for the program to find, and an
+// error that was there before is left alone where the query succeeds.
+inline bool answered(hipError_t e) {
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Per-device data, resolved once per device (by mom_init or by the first call that needs it) with
 // that device current.
 constexpr int kMaxDevices = 64;
@@ -123,10 +132,7 @@ void* static_workspace() {
     if (!d) return nullptr;
     void* p = d->static_ws.load(std::memory_order_acquire);
     if (p) return p;
-    if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
+    if (!answered(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch))) || !p) return nullptr;
     d->static_ws.store(p, std::memory_order_release);
     return p;
 }
@@ -139,11 +145,7 @@ int check_pinned_host(const void* p, size_t n) {
     const unsigned char* ends[2] = {b, b + (n ? n - 1 : 0)};
     for (const unsigned char* q : ends) {
         hipPointerAttribute_t at;
-        if (hipPointerGetAttributes(&at, q) != hipSuccess) {
-            (void)hipGetLastError();          // an unknown pointer must not poison the next HIP call
-            return MOM_ERR_HOST;
-        }
-        if (at.type != hipMemoryTypeHost) return MOM_ERR_HOST;
+        if (!answered(hipPointerGetAttributes(&at, q)) || at.type != hipMemoryTypeHost) return MOM_ERR_HOST;
     }
     return MOM_OK;
 }
@@ -158,21 +160,31 @@ const void* reload_source(const void* pinned_host, const void* k, const void* v,
     int dev = 0, stream_dev = 0;
     hipPointerAttribute_t at;
     const void* mapped = nullptr;
-    bool ok = hipGetDevice(&dev) == hipSuccess && (!st || (hipStreamGetDevice(st, &stream_dev) == hipSuccess && stream_dev == dev));
+    bool ok = answered(hipGetDevice(&dev)) && (!st || (answered(hipStreamGetDevice(st, &stream_dev)) && stream_dev == dev));
     for (int i = 0; i < 4 && ok; ++i) {
         const unsigned char* p = static_cast<const unsigned char*>(i < 2 ? k : v) + (i & 1 ? bytes_each - 1 : 0);
-        ok = hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice && at.device == dev;
+        ok = answered(hipPointerGetAttributes(&at, p)) && at.type == hipMemoryTypeDevice && at.device == dev;
     }
     for (int i = 0; i < 2 && ok; ++i) {
         const size_t at_byte = i ? 2 * bytes_each - 1 : 0;
-        ok = hipPointerGetAttributes(&at, static_cast<const unsigned char*>(pinned_host) + at_byte) == hipSuccess && at.devicePointer;
+        ok = answered(hipPointerGetAttributes(&at, static_cast<const unsigned char*>(pinned_host) + at_byte)) && at.devicePointer;
         if (!ok) break;
         const unsigned char* d = static_cast<const unsigned char*>(at.devicePointer);
         if (i == 0) mapped = d;
         else ok = d == static_cast<const unsigned char*>(mapped) + at_byte;
     }
-    if (!ok) (void)hipGetLastError();
     return ok && aligned16(mapped) ? mapped : nullptr;
+}
+
+// One launch, judged by its own return value: hipGetLastError() would report (and take away) an error that some earlier call of
+// the program left behind, which successful calls don't clear.
+template <typename... P, typename... A>
+hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t st, A... args) {
+    std::tuple<std::remove_cv_t<P>...> values(args...);
+    return std::apply([&](auto&... v) {
+        void* ptrs[] = {static_cast<void*>(&v)...};
+        return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptrs, lds, st);
+    }, values);
 }
 
 // The launch part described by `a` takes the tiles of `g`.
@@ -190,10 +202,8 @@ hipError_t launch_rect_tiles(const momk::GemmArgs& a, const momk::Launch& l, boo
 #define MOM_LAUNCH_RECT(TM, TN)                                                                                   \
     if (l.tm == TM && l.tn == TN) {                                                                               \
         if (EPI == momk::EPI_GATEUP && nt)                                                                        \
-            hipLaunchKernelGGL((momk::gemm_rect_kernel<EPI, TM, TN, EPI == momk::EPI_GATEUP>), grid, block, 0, st, a);  \
-        else                                                                                                      \
-            hipLaunchKernelGGL((momk::gemm_rect_kernel<EPI, TM, TN, false>), grid, block, 0, st, a);              \
-        return hipGetLastError();                                                                                 \
+            return launch(momk::gemm_rect_kernel<EPI, TM, TN, EPI == momk::EPI_GATEUP>, grid, block, 0, st, a);   \
+        return launch(momk::gemm_rect_kernel<EPI, TM, TN, false>, grid, block, 0, st, a);                         \
     }
     if constexpr (EPI == momk::EPI_GATEUP) { MOM_RECT_FORMS_GATEUP(MOM_LAUNCH_RECT) }
     else { MOM_RECT_FORMS_DOWN(MOM_LAUNCH_RECT) }
@@ -211,25 +221,23 @@ hipError_t launch_whole_tiles(momk::GemmArgs a, const momk::Launch& l, bool more
     const bool nt = EPI == momk::EPI_GATEUP && momk::weights_once(a.tiles_m, a.N, a.K, more);
     if (momk::is_rect_form(EPI == momk::EPI_GATEUP, edge, width)) return launch_rect_tiles<EPI>(a, l, nt, st);
 #define MOM_LAUNCH4(E, W)                                                                                         \
-    do {                                                                                                          \
+    if (edge == E && width == W) {                                                                                \
         if constexpr (EPI == momk::EPI_GATEUP && E == 256) {                                                      \
-            if (nt) { hipLaunchKernelGGL((momk::gemm4_kernel<EPI, E, W, true>), grid, block, 0, st, a); break; }  \
+            if (nt) return launch(momk::gemm4_kernel<EPI, E, W, true>, grid, block, 0, st, a);                    \
         }                                                                                                         \
-        hipLaunchKernelGGL((momk::gemm4_kernel<EPI, E, W, false>), grid, block, 0, st, a);                        \
-    } while (0)
-    if (edge == 256 && width == 256) MOM_LAUNCH4(256, 256);
-    else if (edge == 256 && width == 192) MOM_LAUNCH4(256, 192);
-    else if constexpr (EPI == momk::EPI_DOWN) {
-        if (edge == 256 && width == 224) MOM_LAUNCH4(256, 224);
-        else if (edge == 256 && width == 160) MOM_LAUNCH4(256, 160);
-        else if (edge == 256 && width == 128) MOM_LAUNCH4(256, 128);
-        else return hipErrorInvalidValue;
+        return launch(momk::gemm4_kernel<EPI, E, W, false>, grid, block, 0, st, a);                               \
+    }
+    MOM_LAUNCH4(256, 256)
+    MOM_LAUNCH4(256, 192)
+    if constexpr (EPI == momk::EPI_DOWN) {
+        MOM_LAUNCH4(256, 224)
+        MOM_LAUNCH4(256, 160)
+        MOM_LAUNCH4(256, 128)
     } else {
-        if (edge == 128 && width == 128) MOM_LAUNCH4(128, 128);
-        else return hipErrorInvalidValue;
+        MOM_LAUNCH4(128, 128)
     }
 #undef MOM_LAUNCH4
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 // One launch in the short form l.form (mom_gemm_forms.h).
@@ -242,15 +250,14 @@ hipError_t launch_short_tiles(momk::GemmArgs a, const momk::Launch& l, bool more
 #define MOM_LAUNCH_SHORT(TM, TN, WM, WN, KSUB, NSTG)                                                              \
     if (i++ == l.form) {                                                                                          \
         if (EPI == momk::EPI_GATEUP && nt)                                                                        \
-            hipLaunchKernelGGL((momk::gemm_short_kernel<EPI, TM, TN, WM, WN, KSUB, NSTG, EPI == momk::EPI_GATEUP>),  \
-                               grid, block, 0, st, a);                                                            \
-        else                                                                                                      \
-            hipLaunchKernelGGL((momk::gemm_short_kernel<EPI, TM, TN, WM, WN, KSUB, NSTG, false>), grid, block, 0, st, a);  \
+            return launch(momk::gemm_short_kernel<EPI, TM, TN, WM, WN, KSUB, NSTG, EPI == momk::EPI_GATEUP>,      \
+                          grid, block, 0, st, a);                                                                 \
+        return launch(momk::gemm_short_kernel<EPI, TM, TN, WM, WN, KSUB, NSTG, false>, grid, block, 0, st, a);    \
     }
     if constexpr (EPI == momk::EPI_GATEUP) { MOM_SHORT_FORMS_GATEUP(MOM_LAUNCH_SHORT) }
     else { MOM_SHORT_FORMS_DOWN(MOM_LAUNCH_SHORT) }
 #undef MOM_LAUNCH_SHORT
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 // The launch a mom_debug_force_ call asks for (tests need every form on shapes of every size); kRefused with form -1
@@ -306,10 +313,8 @@ hipError_t launch_gemm(const momk::Launch& l, const unsigned short* X, const uns
                 const int64_t wgs = 8 * ((int64_t)p.wide.tiles_per_xcd + p.narrow.tiles_per_xcd);
                 if (wgs > (int64_t)0x7fffffff) return hipErrorInvalidValue;
                 if (momk::weights_once(p.wide.tiles_m, N, K, more))
-                    hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192, true>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
-                else
-                    hipLaunchKernelGGL((momk::gemm4_two_width_kernel<EPI, 192, false>), dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
-                return hipGetLastError();
+                    return launch(momk::gemm4_two_width_kernel<EPI, 192, true>, dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
+                return launch(momk::gemm4_two_width_kernel<EPI, 192, false>, dim3((unsigned)wgs), dim3(momk::k4Threads), 0, st, p);
             }
             return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
@@ -321,11 +326,9 @@ hipError_t launch_blocks(int form, const unsigned short* x, const unsigned short
                          unsigned short* out, int64_t S, int64_t H, int64_t I, hipStream_t st) {
     int i = 0;
 #define MOM_LAUNCH_BLOCK(TB, WAVES, R)                                                                            \
-    if (i++ == form) {                                                                                            \
-        hipLaunchKernelGGL((momk::mlp_block_kernel<TB, WAVES, R>), dim3((unsigned)((S + 16 * TB - 1) / (16 * TB))), dim3(WAVES * 64),  \
-                           (size_t)momk::block_lds(16 * TB, H, I, WAVES * R), st, x, wg, wu, wd, out, (int)S, (int)H, (int)I);  \
-        return hipGetLastError();                                                                                 \
-    }
+    if (i++ == form)                                                                                              \
+        return launch(momk::mlp_block_kernel<TB, WAVES, R>, dim3((unsigned)((S + 16 * TB - 1) / (16 * TB))), dim3(WAVES * 64),  \
+                      (size_t)momk::block_lds(16 * TB, H, I, WAVES * R), st, x, wg, wu, wd, out, (int)S, (int)H, (int)I);
     MOM_BLOCK_FORMS(MOM_LAUNCH_BLOCK)
 #undef MOM_LAUNCH_BLOCK
     return hipErrorInvalidValue;
@@ -362,9 +365,8 @@ hipError_t launch_gemv(const unsigned short* x, const unsigned short* Wa, const 
     const int64_t groups = (R + momk::gemv_rows_per_group(MODE) - 1) / momk::gemv_rows_per_group(MODE);
     int64_t blocks = (groups + WAVES - 1) / WAVES;
     if (blocks > (int64_t)cus * PER_CU) blocks = (int64_t)cus * PER_CU;
-    hipLaunchKernelGGL((momk::gemv_kernel<MODE, WAVES, U>), dim3((unsigned)blocks), dim3(WAVES * 64), (size_t)K * 2, st,
-                       x, Wa, Wb, y, (int)R, (int)K);
-    return hipGetLastError();
+    return launch(momk::gemv_kernel<MODE, WAVES, U>, dim3((unsigned)blocks), dim3(WAVES * 64), (size_t)K * 2, st,
+                  x, Wa, Wb, y, (int)R, (int)K);
 }
 
 // The loop over mini-sequences of C rows on one stream.  The arguments have been validated for a workspace of C x I.
@@ -532,13 +534,8 @@ int mom_debug_mfma_probe(const void* a_bf16, size_t a_bytes, const void* b_bf16,
     const momk::u32x4* a = static_cast<const momk::u32x4*>(a_bf16);
     const momk::u32x4* b = static_cast<const momk::u32x4*>(b_bf16);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (order == 0)
-        hipLaunchKernelGGL(momk::mfma_probe_kernel<0>, grid, block, 0, st, a, (unsigned)(a_bytes / 16), b,
-                           (unsigned)(b_bytes / 16), (long long)iters, sink);
-    else
-        hipLaunchKernelGGL(momk::mfma_probe_kernel<1>, grid, block, 0, st, a, (unsigned)(a_bytes / 16), b,
-                           (unsigned)(b_bytes / 16), (long long)iters, sink);
-    return hipGetLastError() == hipSuccess ? MOM_OK : MOM_ERR_HIP;
+    return launch(order == 0 ? momk::mfma_probe_kernel<0> : momk::mfma_probe_kernel<1>, grid, block, 0, st, a, (unsigned)(a_bytes / 16), b,
+                  (unsigned)(b_bytes / 16), (long long)iters, sink) == hipSuccess ? MOM_OK : MOM_ERR_HIP;
 }
 
 int mom_debug_force_pipeline(int on) {
@@ -700,10 +697,10 @@ int mom_kv_reload(const void* pinned_host, void* k, void* v, void* stream, size_
     if (mapped) {
         const uint32_t n = (uint32_t)(bytes_each / 16);
         const uint32_t full = (2 * n + momk::kReloadThreads * momk::kReloadLoads - 1) / (momk::kReloadThreads * momk::kReloadLoads);
-        hipLaunchKernelGGL(momk::kv_reload_kernel, dim3(full < (uint32_t)momk::kReloadBlocks ? full : momk::kReloadBlocks),
-                           dim3(momk::kReloadThreads), 0, st, static_cast<momk::u32x4*>(k), static_cast<momk::u32x4*>(v),
-                           static_cast<const momk::u32x4*>(mapped), n);
-        if (hipGetLastError() != hipSuccess) return MOM_ERR_HIP;
+        if (launch(momk::kv_reload_kernel, dim3(full < (uint32_t)momk::kReloadBlocks ? full : momk::kReloadBlocks),
+                   dim3(momk::kReloadThreads), 0, st, static_cast<momk::u32x4*>(k), static_cast<momk::u32x4*>(v),
+                   static_cast<const momk::u32x4*>(mapped), n) != hipSuccess)
+            return MOM_ERR_HIP;
     } else if (bytes_each != 0) {
         const unsigned char* src = static_cast<const unsigned char*>(pinned_host);
         if (hipMemcpyAsync(k, src, bytes_each, hipMemcpyHostToDevice, st) != hipSuccess) return MOM_ERR_HIP;
