@@ -150,30 +150,31 @@ int check_pinned_host(const void* p, size_t n) {
     return MOM_OK;
 }
 
+// Whether the n bytes at p lie in one allocation, as the runtime's copies demand (they refuse others, also where the
+// next allocation follows without a gap).
+bool in_one_allocation(const void* p, size_t n) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (!answered(hipMemGetAddressRange(&base, &size, const_cast<void*>(p)))) return false;
+    const size_t at = static_cast<size_t>(static_cast<const unsigned char*>(p) - static_cast<const unsigned char*>(base));
+    return at <= size && n <= size - at;
+}
+
 // The device address of pinned_host if kv_reload_kernel is to copy bytes_each bytes each into k and v on stream st, else nullptr:
-// whole 16-byte chunks, buffers on the current device, which is also the stream's, that do not overlap, up to 256 KiB each.
-// Alone the kernel is the faster one far beyond (256 KiB 34 -> 14 us, 512 KiB 43 -> 23, 2 MiB 98 -> 82), but decoding beside it
-// loses the memory rate of its CUs: 222 us of last-token projections become 225, 231 (512 KiB) and 258 (2 MiB).
+// whole 16-byte chunks, buffers of the current device, which is also the stream's, each in one allocation and not overlapping, up to
+// 256 KiB each.  Alone the kernel is the faster one far beyond (256 KiB 34 -> 14 us, 512 KiB 43 -> 23, 2 MiB 98 -> 82), but decoding
+// beside it loses the memory rate of its CUs: 222 us of last-token projections become 225, 231 (512 KiB) and 258 (2 MiB).
 const void* reload_source(const void* pinned_host, const void* k, const void* v, size_t bytes_each, hipStream_t st) {
     if (bytes_each > ((size_t)256 << 10) || bytes_each % 16 || !aligned16(pinned_host) || !aligned16(k) || !aligned16(v)) return nullptr;
     if (overlaps(k, bytes_each, v, bytes_each)) return nullptr;
     int dev = 0, stream_dev = 0;
+    if (!answered(hipGetDevice(&dev)) || (st && (!answered(hipStreamGetDevice(st, &stream_dev)) || stream_dev != dev))) return nullptr;
     hipPointerAttribute_t at;
-    const void* mapped = nullptr;
-    bool ok = answered(hipGetDevice(&dev)) && (!st || (answered(hipStreamGetDevice(st, &stream_dev)) && stream_dev == dev));
-    for (int i = 0; i < 4 && ok; ++i) {
-        const unsigned char* p = static_cast<const unsigned char*>(i < 2 ? k : v) + (i & 1 ? bytes_each - 1 : 0);
-        ok = answered(hipPointerGetAttributes(&at, p)) && at.type == hipMemoryTypeDevice && at.device == dev;
-    }
-    for (int i = 0; i < 2 && ok; ++i) {
-        const size_t at_byte = i ? 2 * bytes_each - 1 : 0;
-        ok = answered(hipPointerGetAttributes(&at, static_cast<const unsigned char*>(pinned_host) + at_byte)) && at.devicePointer;
-        if (!ok) break;
-        const unsigned char* d = static_cast<const unsigned char*>(at.devicePointer);
-        if (i == 0) mapped = d;
-        else ok = d == static_cast<const unsigned char*>(mapped) + at_byte;
-    }
-    return ok && aligned16(mapped) ? mapped : nullptr;
+    for (const void* p : {k, v})
+        if (!answered(hipPointerGetAttributes(&at, p)) || at.type != hipMemoryTypeDevice || at.device != dev || !in_one_allocation(p, bytes_each))
+            return nullptr;
+    if (!answered(hipPointerGetAttributes(&at, pinned_host)) || !at.devicePointer || !in_one_allocation(pinned_host, 2 * bytes_each)) return nullptr;
+    return aligned16(at.devicePointer) ? at.devicePointer : nullptr;
 }
 
 // One launch, judged by its own return value: hipGetLastError() would report (and take away) an error that some earlier call of

@@ -1,28 +1,23 @@
 """An error of the HIP runtime that the program has left behind is neither taken for an error of a call nor taken away by it: the
 runtime keeps it through calls that succeed."""
-import ctypes
-import os
-
 import pytest
 import torch
 
+from graph_nodes import hip as _runtime
 from paper_2504_12526_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
-
-
-@pytest.fixture(scope="module")
-def hip():
-    binding.lib()
-    paths = {line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line}
-    assert len(paths) == 1, paths                       # the runtime that torch and the library share
-    return ctypes.CDLL(os.path.realpath(paths.pop()))
 
 
 def _recorded(**kw):
     e = torch.cuda.Event(**kw)
     e.record()
     return e
+
+
+@pytest.fixture(scope="module")
+def hip():
+    return _runtime()
 
 
 @pytest.fixture(scope="module")

@@ -1,8 +1,11 @@
 """KV-cache reload of few tokens by a kernel and of others by copies: the bytes, and none beside them, at the edges of a
 workgroup's pass, of the kernel's range and of its alignment; and captured."""
+import ctypes
+
 import pytest
 import torch
 
+from graph_nodes import KERNEL, MEMCPY, hip, node_types
 from paper_2504_12526_amd import binding
 
 pytestmark = pytest.mark.gpu
@@ -64,3 +67,39 @@ def test_captured():
         assert torch.equal(k.cpu(), host[:n]) and torch.equal(v.cpu(), host[n:])
         k.zero_()
         v.zero_()
+
+
+@pytest.mark.parametrize("each,offset,kernel", [(16, 0, True), (4096, 8, True), (LARGEST, 0, True), (LARGEST + 16, 0, False),
+                                                (4098, 0, False), (4096, 1, False)])
+def test_which_of_them_a_reload_takes(each, offset, kernel):
+    n = each // 2
+    host = torch.zeros(2 * n + offset, dtype=torch.int16).pin_memory()[offset:].view(torch.bfloat16)
+    k, v = (torch.zeros(n, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    assert node_types(lambda stream: binding.mom_kv_reload(host, k, v, stream)) == ([KERNEL] if kernel else [MEMCPY, MEMCPY])
+
+
+def test_buffers_that_end_before_the_bytes_do_are_refused():
+    """... also where another allocation follows: its bytes stay."""
+    runtime, each = hip(), 65536
+    host = torch.zeros(each * 4, dtype=torch.uint8).pin_memory()
+    pointers = [ctypes.c_void_p() for _ in range(64)]
+    for p in pointers:
+        assert runtime.hipMalloc(ctypes.byref(p), ctypes.c_size_t(each)) == 0
+    try:
+        at = sorted(p.value for p in pointers)
+        a, b = next((a, b) for a, b in zip(at, at[1:]) if b == a + each)          # nothing lies between the two
+        for p in (a, b):
+            assert runtime.hipMemset(ctypes.c_void_p(p), 0x33, ctypes.c_size_t(each)) == 0
+        other = torch.empty(2 * each, dtype=torch.uint8, device="cuda")
+        for k, v in ((a, other.data_ptr()), (other.data_ptr(), a)):
+            rc = binding.lib().mom_kv_reload(ctypes.c_void_p(host.data_ptr()), ctypes.c_void_p(k), ctypes.c_void_p(v),
+                                             ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), 2 * each, None)
+            runtime.hipGetLastError()
+            torch.cuda.synchronize()
+            assert rc == binding.MOM_ERR_HIP
+        got = torch.empty(each, dtype=torch.uint8)
+        assert runtime.hipMemcpy(ctypes.c_void_p(got.data_ptr()), ctypes.c_void_p(b), ctypes.c_size_t(each), 2) == 0
+        assert bool((got == 0x33).all())
+    finally:
+        for p in pointers:
+            assert runtime.hipFree(p) == 0
