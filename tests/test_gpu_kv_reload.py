@@ -103,3 +103,19 @@ def test_buffers_that_end_before_the_bytes_do_are_refused():
     finally:
         for p in pointers:
             assert runtime.hipFree(p) == 0
+
+
+@pytest.mark.parametrize("flags", [0, 0x40000000, 0x80000000])          # default, coherent, non-coherent
+def test_host_memory_written_between_reloads(flags):
+    runtime, n, p = hip(), 32768, ctypes.c_void_p()
+    assert runtime.hipHostMalloc(ctypes.byref(p), ctypes.c_size_t(2 * n), ctypes.c_uint(flags)) == 0
+    try:
+        k, v = (torch.empty(n, dtype=torch.uint8, device="cuda") for _ in range(2))
+        for r in range(6):
+            ctypes.memset(p.value, 17 * r + 1, 2 * n)
+            assert binding.lib().mom_kv_reload(p, ctypes.c_void_p(k.data_ptr()), ctypes.c_void_p(v.data_ptr()),
+                                               ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), n, None) == binding.MOM_OK
+            assert bool((k == 17 * r + 1).all()) and bool((v == 17 * r + 1).all())
+        torch.cuda.synchronize()
+    finally:
+        assert runtime.hipHostFree(p) == 0

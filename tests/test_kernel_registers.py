@@ -73,3 +73,14 @@ def test_acc_registers_hold_the_accumulators_and_nothing_else(tmp_path):
     for key in ("agpr", "vgpr_spill_count"):
         planted = {gemms[0]: dict(kernels[gemms[0]], **{key: kernels[gemms[0]][key] + 4})}
         assert unsound(planted)
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="llvm-readelf is not installed")
+def test_a_reload_finds_registers_beside_every_gemm_workgroup(tmp_path):
+    """A SIMD has 512 registers per lane, allocated in eights, and a GEMM workgroup one wavefront on each; the reload kernel needs no LDS."""
+    allocated = {n: -(-v["vgpr_count"] // 8) * 8 for n, v in _kernels(tmp_path).items()}
+    reload, = [v for n, v in allocated.items() if "kv_reload_kernel" in n]
+    gemms = {n: v for n, v in allocated.items() if re.search(r"gemm_short_kernel|gemm_rect_kernel|gemm4_", n)}
+    assert len(gemms) > 100
+    crowded = {n: v for n, v in gemms.items() if v + reload > 512}
+    assert not crowded, (reload, crowded)
