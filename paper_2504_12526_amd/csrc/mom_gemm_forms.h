@@ -164,10 +164,14 @@ constexpr double kFromHbm = 0.69, kFromCache = 0.33;
 // of six layers (H 2048 ... 8192), launches of one form after the other: 0.5 % (236 launches, none above 10 %) and 0.6 % (177, 2 above
 // 10 %) over the best of 37 forms; with the 20 forms and the constants before, 2.5 % (29) and 2.2 % (28).  Inside calls, behind a
 // gate/up launch and with weights not used before, on 40 ... 1900 rows of ten layers (H 3584 ... 8192) with W_down of up to 470 MB:
-// 0.7 % (179 launches, 2 above 10 %); without lead_mib, lead_few and kOverWhole 3.0 % (20).  From 1000 rows on, where
+// 0.7 % (179 launches, 2 above 10 %); without lead_mib, lead_few and kOverWhole 3.0 % (20).  kShortDownTime is fitted again to whole
+// calls: 882 of 16 ... 990 rows of 14 layers (H 2048 ... 8192, weights from HBM), all forms near the best of each forced in turn.  The
+// calls take 0.38 % more than with the best form, 5 of them above 6 %; before, 0.47 % and 13, because the lead of small tiles was
+// overrated: 57 ... 64 rows x 2048 columns, K = 8192, as 128 tiles of 48 x 32 (calls of 36.0 us) instead of 256 of 32 x 16 (32.9), 86
+// rows as 128 of 64 x 32 (40.1) instead of 192 of 32 x 32 (37.4).  From 1000 rows on, where
 // it is the 256-row and rectangular tiles that a short form is compared with, kShortDownLongTime, fitted together with those (1536
 // rows x 4096 columns in 192 x 128: 160 us, so 159, by kShortDownTime 178).
-constexpr LaunchTime kShortDownTime = {5.59, 1.42e-5, 1.80e-5, 5.30e-5, 1.29e-7, 1.0, kFromHbm, true, 0.182, 0.219, 256, true};
+constexpr LaunchTime kShortDownTime = {5.46, 2.25e-5, 2.20e-5, 5.11e-5, 7.76e-8, 1.0, kFromHbm, true, 0.212, 0.0855, 256, true};
 constexpr LaunchTime kShortDownLongTime = {4.0, 5.0e-5, 1.94e-5, 5.56e-5, 5.81e-8, 1.0, kFromHbm, true, 0.1, 0.2};
 constexpr LaunchTime kShortDownKeptTime = {2.28, 9.78e-5, 1.14e-5, 4.14e-5, 7.43e-8, 1.0, kFromCache, true, 0, 0};
 // W_down still in the Infinity Cache (kept_down).  Then nobody needs to run ahead: 1024 rows x 4096 columns in tiles of
