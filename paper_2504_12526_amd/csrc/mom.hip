@@ -278,16 +278,20 @@ momk::Launch forced_launch(int64_t M, int64_t N, bool gateup) {
     return {momk::kRefused, -1, 0, 0, 0, {}, {}};
 }
 
-// What runs for M token rows x N output columns, mini-sequence c of its call (mom_gemm_forms.h).  full_tiles: the down
-// projection in tiles of 256 x 256 however few.
-template <int EPI>
-momk::Launch choose_launch(int64_t M, int64_t N, int64_t K, int64_t c, bool full_tiles = false) {
-    constexpr bool GU = EPI == momk::EPI_GATEUP;
+// What runs for M token rows of a layer (mom_gemm_forms.h).  more: the call has more than one mini-sequence.
+momk::Launch gateup_launch(int64_t M, int64_t H, int64_t I, bool more) {
     const int cus = compute_units();
     if (cus <= 0) return {momk::kRefused, -1, 0, 0, 0, {}, {}};
-    const momk::Launch l = forced_launch(M, N, GU);
-    if (l.form >= 0) return l;
-    return GU ? momk::choose_gateup(M, N, K, cus) : momk::choose_down(M, N, K, cus, c >= momk::kKeptFrom, full_tiles);
+    const momk::Launch l = forced_launch(M, I, true);
+    return l.form >= 0 ? l : momk::choose_gateup(M, I, H, cus, more);
+}
+
+// ... behind the gate/up launch of mini-sequence c.  full_tiles: in tiles of 256 x 256 however few.
+momk::Launch down_launch(int64_t M, int64_t H, int64_t I, const momk::Launch& gateup, int64_t c, bool full_tiles = false) {
+    const int cus = compute_units();
+    if (cus <= 0) return {momk::kRefused, -1, 0, 0, 0, {}, {}};
+    const momk::Launch l = forced_launch(M, H, false);
+    return l.form >= 0 ? l : momk::choose_down(M, H, I, cus, c >= momk::kKeptFrom && momk::kept_down(gateup, M, H, I), full_tiles);
 }
 
 // O[m, n] of M token rows x N output columns by launch l.  more: the call has more than one mini-sequence.
@@ -381,7 +385,7 @@ int mlp_loop(const void* x, const void* wg, const void* wu, const void* wd, int6
     unsigned short* w = static_cast<unsigned short*>(ws);
     if (events && hipEventRecord(static_cast<hipEvent_t>(events[0]), st) != hipSuccess) return MOM_ERR_HIP;
     int planned = (int)C;                // token rows that `gateup` and `down` are for
-    momk::Launch gateup = choose_launch<momk::EPI_GATEUP>(C, I, H, 0), down = choose_launch<momk::EPI_DOWN>(C, H, I, 0);
+    momk::Launch gateup = gateup_launch(C, H, I, n > 1), down = down_launch(C, H, I, gateup, 0);
     if (!events) {
         const int form = block_form(S, H, I, C, gateup, down);
         if (form >= 0)
@@ -392,8 +396,8 @@ int mlp_loop(const void* x, const void* wg, const void* wu, const void* wd, int6
     for (int64_t c = 0; c < n; ++c) {
         const int64_t r0 = c * C;
         const int rows = (int)((r0 + C <= S) ? C : (S - r0));
-        if (rows != planned) gateup = choose_launch<momk::EPI_GATEUP>(rows, I, H, c);
-        if (rows != planned || c == momk::kKeptFrom) down = choose_launch<momk::EPI_DOWN>(rows, H, I, c);
+        if (rows != planned) gateup = gateup_launch(rows, H, I, n > 1);
+        if (rows != planned || c == momk::kKeptFrom) down = down_launch(rows, H, I, gateup, c);
         planned = rows;
         if (launch_gemm<momk::EPI_GATEUP>(gateup, xs + r0 * H, static_cast<const unsigned short*>(wg),
                                           static_cast<const unsigned short*>(wu), w, rows, (int)I, (int)H,
@@ -443,8 +447,8 @@ int mlp_pipelined(const void* x, const void* wg, const void* wu, const void* wd,
         // gate/up(c) is held until down(c-1) has been handed to the device: its few, long tiles must
         // get their CUs before the many tiles of this kernel take the whole chip for a round
         if (c >= 1 && hipStreamWaitEvent(sa, ev[4], 0) != hipSuccess) return MOM_ERR_HIP;
-        if (launch_gemm<momk::EPI_GATEUP>(choose_launch<momk::EPI_GATEUP>(rows, I, H, c), xs + r0 * H,
-                                          static_cast<const unsigned short*>(wg), static_cast<const unsigned short*>(wu),
+        const momk::Launch gateup = gateup_launch(rows, H, I, true);
+        if (launch_gemm<momk::EPI_GATEUP>(gateup, xs + r0 * H, static_cast<const unsigned short*>(wg), static_cast<const unsigned short*>(wu),
                                           half[h], rows, (int)I, (int)H, sa, true) != hipSuccess)
             return MOM_ERR_HIP;
         if (hipEventRecord(ev[h], sa) != hipSuccess || hipStreamWaitEvent(sb, ev[h], 0) != hipSuccess)
@@ -453,7 +457,7 @@ int mlp_pipelined(const void* x, const void* wg, const void* wu, const void* wd,
         // beside a gate/up kernel that fills the chip, full-size tiles are the efficient form for the
         // down projection however few they are; the last one runs alone and follows the usual rule
         const bool beside_big = c + 1 < n;
-        if (launch_gemm<momk::EPI_DOWN>(choose_launch<momk::EPI_DOWN>(rows, H, I, c, beside_big), half[h],
+        if (launch_gemm<momk::EPI_DOWN>(down_launch(rows, H, I, gateup, c, beside_big), half[h],
                                         static_cast<const unsigned short*>(wd), nullptr, os + r0 * H, rows, (int)H, (int)I,
                                         sb, true) != hipSuccess)
             return MOM_ERR_HIP;

@@ -174,7 +174,7 @@ constexpr double kFromHbm = 0.69, kFromCache = 0.33;
 constexpr LaunchTime kShortDownTime = {5.46, 2.25e-5, 2.20e-5, 5.11e-5, 7.76e-8, 1.0, kFromHbm, true, 0.212, 0.0855, 256, true};
 constexpr LaunchTime kShortDownLongTime = {4.0, 5.0e-5, 1.94e-5, 5.56e-5, 5.81e-8, 1.0, kFromHbm, true, 0.1, 0.2};
 constexpr LaunchTime kShortDownKeptTime = {2.28, 9.78e-5, 1.14e-5, 4.14e-5, 7.43e-8, 1.0, kFromCache, true, 0, 0};
-// W_down still in the Infinity Cache (kept_down).  Then nobody needs to run ahead: 1024 rows x 4096 columns in tiles of
+// W_down still in the Infinity Cache.  Then nobody needs to run ahead: 1024 rows x 4096 columns in tiles of
 // 160 x 128: 117 us, in eight of 128 x 128: 109 us; 512 rows in tiles of 160 x 64 80 us, of 128 x 64 70 us.
 constexpr LaunchTime kShortDownSmallTime = {5.9, 1.40e-4, 1.02e-5, 3.58e-5, 1.36e-7, 1.0, kFromCache, true, 0, 0};
 constexpr LaunchTime kShortGateUpTime = {5.95, 1.97e-4, 1.11e-5, 5.61e-5, 1.42e-7, 1.0, kFromHbm, false, 0, 0};
@@ -210,8 +210,9 @@ constexpr double kOverOneRound = 0.945, kWithinOneRound = 0.975, kOneTokenTile =
 constexpr double kOverShort = 0.83, kOverShortFilled = 0.975, kOverDown = 0.975, kOverWhole = 0.9;
 constexpr double kRectBytes = 4 / 5.6e6;        // us per weight pair at 5.6 TB/s
 
-// Whether weight rows x K of them leave the Infinity Cache room (142 MB do, 470 MB do not).
-inline bool weights_fit(int64_t rows, int64_t K) { return 2 * rows * K <= ((int64_t)160 << 20); }
+// Whether weight rows x K of them leave the Infinity Cache room (192 MiB do: 6144 columns, K = 16384, in mini-sequences of 256 rows
+// 1154 us in the tiles for weights from HBM, 1047 in those for kept ones; 250 MiB don't, 512 rows x 5120 columns, K = 25600, 4 ... 8 %).
+inline bool weights_fit(int64_t rows, int64_t K) { return 2 * rows * K <= ((int64_t)200 << 20); }
 
 // A layer that stays in the Infinity Cache between calls (tests, small models): a quarter of it.
 inline bool small_layer(int64_t N, int64_t K) { return 6 * N * K <= ((int64_t)64 << 20); }
@@ -253,20 +254,25 @@ inline bool weights_once(int64_t tiles_m, int64_t N, int64_t K, bool more_mini_s
     return tiles_m <= (more_mini_sequences ? kTokenGroup : 2) && 6 * N * K > ((int64_t)256 << 20);
 }
 
-// Whether W_down is taken to be in the Infinity Cache: that of a small layer, or (later: from mini-sequence kKeptFrom of a
-// call on) from the mini-sequence before, where the layer fits or the gate/up launch passes it by (one group of 256-row
-// token tiles, as above) and it leaves room.  Down by mini-sequence, other weights in each call: 512 rows in tiles of 128 x 64
-// 97, 93, 72, 72 ... us (of 160 x 64 92, 92, 91, 91); 256 rows in 64 x 64 70, 65, 45, 45 (of 80 x 64 58, 55, 53, 53).
+// W_down is taken to be in the Infinity Cache: that of a small layer, and from mini-sequence kKeptFrom of a call on where kept_down.
+// Down by mini-sequence, other weights in each call: 512 rows in tiles of 128 x 64 97, 93, 72, 72 ... us (of 160 x 64 92, 92, 91, 91);
+// 256 rows in 64 x 64 70, 65, 45, 45 (of 80 x 64 58, 55, 53, 53).
 constexpr int kKeptFrom = 2;
-inline bool kept_down(int64_t M, int64_t N, int64_t K, bool later) {
-    return small_layer(N, K) || (later && (6 * N * K <= ((int64_t)256 << 20) || (M <= 256 * kTokenGroup && weights_fit(N, K))));
+
+// Rows of a mini-sequence whose gate/up launch is to pass W_down by: as many as one group of 256-row token tiles.  Its other forms are
+// then those of one group too: six mini-sequences of 768 rows x 11008 columns, K = 4096, in five token tiles of 160 x 224, whose weights
+// come through the cache and displace W_down, take 1279 us, in three of 256 x 160 1146.
+inline bool to_pass_by(int64_t M, int64_t N, int64_t K, bool more_mini_sequences) {
+    return more_mini_sequences && M <= 256 * kTokenGroup && 6 * N * K > ((int64_t)256 << 20) && weights_fit(N, K);
 }
 
 // The short form that takes the least time; its time in `least`; -1: none.
-inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, const LaunchTime& time, int cus, double& least, int forms = 0) {
+inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, const LaunchTime& time, int cus, double& least, int forms = 0,
+                             bool one_group = false) {
     int best = -1;
     for (int i = 0; i < (forms ? forms : short_forms(gateup)); ++i) {
         const ShortShape f = short_shape(gateup, i);
+        if (one_group && f.tm * kTokenGroup < M) continue;
         const double t = launch_time(tile_grid(M, N, gateup, f), M, K, gateup, f, time, cus);
         if (t >= 0 && (best < 0 || t < least)) { best = i; least = t; }
     }
@@ -274,10 +280,12 @@ inline int choose_short_form(int64_t M, int64_t N, int64_t K, bool gateup, const
 }
 
 // The rectangular tiles that take the least time; their time in `least`; tm 0: none.
-inline ShortShape choose_rect_form(int64_t M, int64_t N, int64_t K, bool gateup, const LaunchTime& time, int cus, double& least) {
+inline ShortShape choose_rect_form(int64_t M, int64_t N, int64_t K, bool gateup, const LaunchTime& time, int cus, double& least,
+                                   bool one_group = false) {
     ShortShape best = {0, 0, 1, 0};
     for (int i = 0; i < rect_forms(gateup); ++i) {
         const ShortShape f = rect_shape(gateup, i);
+        if (one_group && f.tm * kTokenGroup < M) continue;
         if (gateup && f.tm < 160 && M > 224) continue;         // tiles for one token tile, or two (256 rows x 13824 columns: 82 -> 94 us)
         const double t = launch_time(tile_grid(M, N, gateup, f), M, K, gateup, f, time, cus);
         if (t >= 0 && (best.tm == 0 || t < least)) { best = f; least = t; }
@@ -310,6 +318,14 @@ inline Launch whole_launch(int64_t M, int64_t N, bool gateup, int tm, int tn) {
     return {g.tiles > 0 && g.tiles <= (uint64_t)kMaxTiles ? kWholeTiles : kRefused, 0, tm, tn, 0, g, {}};
 }
 
+// Whether a mini-sequence of M rows leaves W_down (N x K) in the Infinity Cache for the next one, with the gate/up launch given: where
+// the layer fits, or that launch passes it by and it leaves room.  Up to 4096 rows, which the constants for it are fitted to: 6000 rows x
+// 2048 columns, K = 8192, ran in 192 x 128 by them, 1762 us per four mini-sequences, and run in 192 x 256, 1656, by the others.
+inline bool kept_down(const Launch& gateup, int64_t M, int64_t N, int64_t K) {
+    if (M > 4096) return false;
+    return 6 * N * K <= ((int64_t)256 << 20) || (weights_once(gateup.grid.tiles_m, K, N, true) && weights_fit(N, K));
+}
+
 // Gate/up tiles of 96 columns beside those of 128: a column of the narrow tile costs 7 % more (measured over
 // whole rounds), and the mix has to save this much of the modelled time before it is used.
 constexpr int kGateUpNarrowPerMille = 1070;
@@ -328,14 +344,14 @@ inline int64_t rounds_per_mille(int64_t tiles, int cus) {
 // tile with the fewest of them.
 // Both sides are priced on the grid that runs: 2400 rows x 4096 columns are 220 tiles of 256 x 192 = one round, 223 us,
 // against two rounds of 160 x 128, 276 us (2700 rows 231 and 302, 4300 402 and 463, 5500 461 and 595 us).
-// later: see kept_down.  full_tiles: tiles of 256 x 256 however few (beside a gate/up kernel
+// kept: W_down is in the Infinity Cache (kept_down).  full_tiles: tiles of 256 x 256 however few (beside a gate/up kernel
 // that fills the chip).
-inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool later, bool full_tiles) {
+inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool kept, bool full_tiles) {
     const Launch full = whole_launch(M, N, false, 256, 256);
     if (full.kind == kRefused || full_tiles) return full;
     double least = 0, time = 0;
     const bool small = small_layer(N, K);
-    const LaunchTime& short_time = small ? kShortDownSmallTime : kept_down(M, N, K, later) ? kShortDownKeptTime :
+    const LaunchTime& short_time = small ? kShortDownSmallTime : kept ? kShortDownKeptTime :
                                    M < 1000 ? kShortDownTime : kShortDownLongTime;
     const int form = choose_short_form(M, N, K, false, short_time, cus, least, small ? kSmallDownForms : 0);
     if (&short_time == &kShortDownTime) least *= kOverWhole;
@@ -373,13 +389,13 @@ inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool later, 
 // the two-width kernel, where the same model says that saves time: 14336 columns with 12 token tiles are 1344 tiles
 // = 5.25 rounds, but 64 x 128 + 64 x 96 columns are three rounds of each width.
 // Few token rows: the short forms, as for the down projection.  Or 128 x 128 tiles, two workgroups per CU, by the same
-// comparison.
-inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus) {
+// comparison.  more: the call has more than one mini-sequence.
+inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus, bool more) {
     const Launch plain_launch = whole_launch(M, N, true, 256, 256);
     if (plain_launch.kind == kRefused) return plain_launch;
     double least = 0;
-    const bool small = small_layer(N, K);
-    const int form = choose_short_form(M, N, K, true, small ? kShortGateUpSmallTime : kShortGateUpTime, cus, least);
+    const bool small = small_layer(N, K), one_group = to_pass_by(M, N, K, more);
+    const int form = choose_short_form(M, N, K, true, small ? kShortGateUpSmallTime : kShortGateUpTime, cus, least, 0, one_group);
     // b column tiles of 96 behind a of 128: a = ceil((N - 96 b) / 128); time = rounds x columns per tile
     const int64_t tm = plain_launch.grid.tiles_m;
     auto mix_cost = [&](int64_t b) {
@@ -403,7 +419,7 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus) {
     // layer of 69 MiB, which the Infinity Cache keeps, 1 % at most and up to 17 % lost at 128 rows.  Below 97 rows only where they keep the CUs busy.
     if (M >= 24 && 6 * N * K > ((int64_t)128 << 20)) {
         double rect = 0;
-        const ShortShape r = choose_rect_form(M, N, K, true, kRectGateUpTime, cus, rect);
+        const ShortShape r = choose_rect_form(M, N, K, true, kRectGateUpTime, cus, rect, one_group);
         const uint64_t tiles = r.tm ? tile_grid(M, N, true, r).tiles : 0;
         const bool filled = M <= 128 && tiles <= (uint64_t)cus && 8 * tiles >= 7 * (uint64_t)cus;
         if (filled && rect < kRectBytes * N * K) rect = kRectBytes * N * K;
@@ -412,7 +428,7 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus) {
             return whole_launch(M, N, true, r.tm, r.tn);
     }
     const Launch pair = whole_launch(M, N, true, 128, 128);
-    if (pair.kind != kRefused && pair.grid.tiles <= 2 * (uint64_t)cus &&
+    if (pair.kind != kRefused && !(one_group && pair.grid.tiles_m > (uint32_t)kTokenGroup) && pair.grid.tiles <= 2 * (uint64_t)cus &&
         (K <= 2048 || (pair.grid.tiles_m > (uint32_t)kTokenGroup && pair.grid.tiles > (uint64_t)cus))) {
         const double t = launch_time(pair.grid, M, K, true, kPairShape, small ? kPairGateUpSmallTime : kPairGateUpTime, cus);
         if (t < full && (form < 0 || t < least)) return pair;

@@ -67,7 +67,7 @@ static void tiles(int64_t M, int64_t N, int tm, int tn) {
 // What choose_down picks at these sizes, against every launch there is, each priced on the grid that runs.
 static int64_t rounds(const momk::TileGrid& g, int cus) { return ((int64_t)g.tiles + cus - 1) / cus; }
 static void down_choice(int64_t M, int64_t N, int64_t K, int cus, bool more) {
-    const momk::Launch l = momk::choose_down(M, N, K, cus, more, false);
+    const momk::Launch l = momk::choose_down(M, N, K, cus, more && momk::kept_down(momk::choose_gateup(M, K, N, cus, true), M, N, K), false);
     CHECK(l.kind == momk::kShortTiles || l.kind == momk::kWholeTiles, "down M=%lld N=%lld", (long long)M, (long long)N);
     if (l.kind == momk::kWholeTiles) return;
     // With a long contraction a 256-row tile takes at most a little more than a short one of the same width, so short
@@ -86,13 +86,25 @@ static void steady(int64_t N, int64_t K, bool gateup) {
         return a.kind == b.kind && a.form == b.form && a.tm == b.tm && a.tn == b.tn && a.wide_cols == b.wide_cols;
     };
     for (int64_t M = 1; M <= 8192; ++M) {
-        const momk::Launch l = gateup ? momk::choose_gateup(M, N, K, 256) : momk::choose_down(M, N, K, 256, false, false);
+        const momk::Launch l = gateup ? momk::choose_gateup(M, N, K, 256, false) : momk::choose_down(M, N, K, 256, false, false);
         if (M > 1 && same(l, last)) continue;
         CHECK(!since || !same(l, before) || M - since >= 4, "M=%lld N=%lld K=%lld: %d x %d between two runs of %d x %d", (long long)since,
               (long long)N, (long long)K, last.tm, last.tn, l.tm, l.tn);
         before = last;
         last = l;
         since = M;
+    }
+}
+
+// W_down is taken to be in the cache behind launches that pass it by only, and mini-sequences of one group of token tiles pass it by.
+static void kept(int64_t H, int64_t I) {
+    for (int64_t M = 1; M <= 3000; ++M) {
+        const momk::Launch l = momk::choose_gateup(M, I, H, 256, true);
+        const bool once = momk::weights_once(l.grid.tiles_m, I, H, true), down = momk::kept_down(l, M, H, I);
+        if (6 * H * I <= (256 << 20)) continue;
+        CHECK(!down || once, "W_down kept M=%lld H=%lld I=%lld: gate/up %d x %d", (long long)M, (long long)H, (long long)I, l.tm, l.tn);
+        CHECK(!momk::to_pass_by(M, I, H, true) || down, "W_down displaced M=%lld H=%lld I=%lld: gate/up %d x %d", (long long)M, (long long)H,
+              (long long)I, l.tm, l.tn);
     }
 }
 
@@ -105,22 +117,24 @@ int main() {
         for (bool more : {false, true}) down_choice(M, 4096, 14336, 256, more);
         for (bool more : {false, true}) down_choice(M, 3584, 18944, 256, more);
         for (bool more : {false, true}) down_choice(M, 8192, 28672, 256, more);
-        CHECK(momk::choose_gateup(M, 14336, 4096, 256).kind != momk::kRefused, "gate/up M=%lld", (long long)M);
+        CHECK(momk::choose_gateup(M, 14336, 4096, 256, false).kind != momk::kRefused, "gate/up M=%lld", (long long)M);
     }
     const int64_t layers[][2] = {{4096, 14336}, {3584, 18944}, {1056, 2080}, {256, 1024}};
     for (const auto& l : layers) {
         steady(l[0], l[1], false);
         steady(l[1], l[0], true);
     }
+    const int64_t kept_layers[][2] = {{4096, 14336}, {3584, 18944}, {4096, 11008}, {6144, 16384}, {5120, 13824}, {5120, 25600}, {2048, 8192}};
+    for (const auto& l : kept_layers) kept(l[0], l[1]);
     // What the GPU tests take for granted about the choice: launches of two widths, the second ring of gate/up 64 x 64.
     const int64_t two[][3] = {{1024, 128, 14336}, {1000, 96, 14304}, {2048, 64, 14336}, {1280, 128, 10112}};
     for (const auto& t : two) {
-        const momk::Launch l = momk::choose_gateup(t[0], t[2], t[1], 256);
+        const momk::Launch l = momk::choose_gateup(t[0], t[2], t[1], 256, false);
         CHECK(l.kind == momk::kTwoWidths && l.wide_cols > 0 && l.wide_cols < t[2], "gate/up M=%lld N=%lld", (long long)t[0], (long long)t[2]);
     }
     const int64_t ring[][3] = {{33, 8192, 7168}, {61, 8192, 7168}, {100, 8192, 3584}};
     for (const auto& t : ring) {
-        const momk::Launch l = momk::choose_gateup(t[0], t[2], t[1], 256);
+        const momk::Launch l = momk::choose_gateup(t[0], t[2], t[1], 256, false);
         CHECK(l.kind == momk::kShortTiles && l.tm == 64 && l.tn == 64 && l.form != momk::find_short_form(true, 64, 64),
               "gate/up M=%lld N=%lld", (long long)t[0], (long long)t[2]);
     }

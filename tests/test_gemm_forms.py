@@ -29,6 +29,9 @@ def test_forms_and_choice(tmp_path):
     ("const uint32_t tm = ((uint32_t)M + f.tm - 1) / f.tm,", "const uint32_t tm = M < f.tm ? 1 : (uint32_t)M / f.tm,", "rows of M="),
     # a step in the time of a launch: neighbouring row counts alternate between forms
     ("last < 0.72 ? (0.72 - last) / 0.32 : 0;", "last < 0.72 ? (M & 1) : 0;", "between two runs of"),
+    # W_down taken to be in the cache whatever the gate/up launch before it does, and that launch in more than one group
+    ("weights_once(gateup.grid.tiles_m, K, N, true) && weights_fit(N, K)", "weights_fit(N, K)", "W_down kept"),
+    ("one_group = to_pass_by(M, N, K, more);", "one_group = false;", "W_down displaced"),
     # the last, shorter group of token tiles walked as a whole one
     ("const int gsz = tiles_m - first_m < group_m ? tiles_m - first_m : group_m;", "const int gsz = group_m;", "of M="),
     # the rows of W_up behind those of a whole tile instead of half a one
