@@ -287,6 +287,9 @@ inline ShortShape choose_rect_form(int64_t M, int64_t N, int64_t K, bool gateup,
         const ShortShape f = rect_shape(gateup, i);
         if (one_group && f.tm * kTokenGroup < M) continue;
         if (gateup && f.tm < 160 && M > 224) continue;         // tiles for one token tile, or two (256 rows x 13824 columns: 82 -> 94 us)
+        // 192 x 320, whose weights have two ring slots, for two token tiles at most: 384 rows x 18944 columns, K = 3584, calls of 184 us,
+        // 192 against the next form; but 700 ... 768 rows x 9728 0.94 ... 0.97 promised of what 256 x 256 takes, 1.03 ... 1.04 measured
+        if (gateup && f.tn == 320 && M > 2 * f.tm) continue;
         const double t = launch_time(tile_grid(M, N, gateup, f), M, K, gateup, f, time, cus);
         if (t >= 0 && (best.tm == 0 || t < least)) { best = f; least = t; }
     }

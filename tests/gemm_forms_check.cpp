@@ -147,6 +147,12 @@ int main() {
         CHECK(l.kind == momk::kShortTiles && l.tm == t[3] && l.tn == t[4], "down M=%lld N=%lld K=%lld in %d x %d", (long long)t[0],
               (long long)t[1], (long long)t[2], l.tm, l.tn);
     }
+    // ... and gate/up of 684 ... 768 rows x 9728 columns takes the 228 tiles of 256 x 256 (in 244 of 192 x 320 3 ... 4 % slower).
+    for (int64_t M = 684; M <= 768; ++M)
+        for (int64_t K : {2560, 3584}) {
+            const momk::Launch l = momk::choose_gateup(M, 9728, K, 256, false);
+            CHECK(l.kind == momk::kWholeTiles && l.tm == 256 && l.tn == 256, "gate/up M=%lld K=%lld in %d x %d", (long long)M, (long long)K, l.tm, l.tn);
+        }
     // a form that is not there is an error, not a launch of nothing
     for (bool gu : {false, true})
         for (int f : {-1, momk::short_forms(gu)})
