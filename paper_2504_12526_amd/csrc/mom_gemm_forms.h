@@ -168,7 +168,7 @@ constexpr double kFromHbm = 0.69, kFromCache = 0.33;
 // calls: 882 of 16 ... 990 rows of 14 layers (H 2048 ... 8192, weights from HBM), all forms near the best of each forced in turn.  The
 // calls take 0.38 % more than with the best form, 5 of them above 6 %; before, 0.47 % and 13, because the lead of small tiles was
 // overrated: 57 ... 64 rows x 2048 columns, K = 8192, as 128 tiles of 48 x 32 (calls of 36.0 us) instead of 256 of 32 x 16 (32.9), 86
-// rows as 128 of 64 x 32 (40.1) instead of 192 of 32 x 32 (37.4).  From 1000 rows on, where
+// rows as 128 of 64 x 32 (40.1) instead of 192 of 32 x 32 (37.4).  From long_from rows on, where
 // it is the 256-row and rectangular tiles that a short form is compared with, kShortDownLongTime, fitted together with those (1536
 // rows x 4096 columns in 192 x 128: 160 us, so 159, by kShortDownTime 178).
 constexpr LaunchTime kShortDownTime = {5.46, 2.25e-5, 2.20e-5, 5.11e-5, 7.76e-8, 1.0, kFromHbm, true, 0.212, 0.0855, 256, true};
@@ -201,7 +201,7 @@ constexpr ShortShape kPairShape = {128, 128, 2, 58};
 //                 the weights take at 5.6 TB/s: 18944 columns, K = 3584, 64 rows 51.4 -> 47.8 us, 25600, K = 5120, 119.7 ->
 //                 94.5; on 180 of 256 CUs (14336 columns, K = 4096) they lose (96 rows 45.7 -> 50.5)
 // kOverDown       down, either kind, after the correction: 2900 rows x 4096 columns 0.89 promised, 247 -> 233 us
-// kOverWhole      down below 1000 rows, where the formula underrates the whole tiles against the short ones: 700 rows x 8192
+// kOverWhole      down below long_from rows, where the formula underrates the whole tiles against the short ones: 700 rows x 8192
 //                 columns, K = 28672, in 192 x 128 325, in 256 x 128 362 us at 344 and 326 promised
 constexpr LaunchTime kRectGateUpTime = {3.73, 3.07e-5, 1.09e-5, 4.22e-5, 1.68e-7, 0.74, 0, true, 0, 0};
 constexpr LaunchTime kRectDownTime = {7.24, 2.95e-5, 2.34e-5, 7.72e-6, 1.02e-7, 0.707, 0, true, 0.048, 0};
@@ -213,6 +213,12 @@ constexpr double kRectBytes = 4 / 5.6e6;        // us per weight pair at 5.6 TB/
 // Whether weight rows x K of them leave the Infinity Cache room (192 MiB do: 6144 columns, K = 16384, in mini-sequences of 256 rows
 // 1154 us in the tiles for weights from HBM, 1047 in those for kept ones; 250 MiB don't, 512 rows x 5120 columns, K = 25600, 4 ... 8 %).
 inline bool weights_fit(int64_t rows, int64_t K) { return 2 * rows * K <= ((int64_t)200 << 20); }
+
+// Token rows from which the down projection of N columns is priced by kShortDownLongTime.  Up to 192 MiB of W_down both sets choose as well
+// from 1100 to 1300 rows, and at 1150 the same form in every one of 13 layers; with the line at 1000 the form changed for the worse in
+// two of them (1004 rows x 6144 columns, K = 16384, calls of 482 us, now 462; x 2560, K = 9728, 160, 155).  From 250 MiB on it changes
+// for the better there (1005 rows x 5120 columns, K = 25600, 651, by the other set 660).
+inline int64_t long_from(int64_t N, int64_t K) { return weights_fit(N, K) ? 1150 : 1000; }
 
 // A layer that stays in the Infinity Cache between calls (tests, small models): a quarter of it.
 inline bool small_layer(int64_t N, int64_t K) { return 6 * N * K <= ((int64_t)64 << 20); }
@@ -355,7 +361,7 @@ inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool kept, b
     double least = 0, time = 0;
     const bool small = small_layer(N, K);
     const LaunchTime& short_time = small ? kShortDownSmallTime : kept ? kShortDownKeptTime :
-                                   M < 1000 ? kShortDownTime : kShortDownLongTime;
+                                   M < long_from(N, K) ? kShortDownTime : kShortDownLongTime;
     const int form = choose_short_form(M, N, K, false, short_time, cus, least, small ? kSmallDownForms : 0);
     if (&short_time == &kShortDownTime) least *= kOverWhole;
     // The width: by time where the widest take no more than one round; over several rounds by rounds x columns, a column of

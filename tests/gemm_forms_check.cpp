@@ -126,6 +126,15 @@ int main() {
     }
     const int64_t kept_layers[][2] = {{4096, 14336}, {3584, 18944}, {4096, 11008}, {6144, 16384}, {5120, 13824}, {5120, 25600}, {2048, 8192}};
     for (const auto& l : kept_layers) kept(l[0], l[1]);
+    // Where the constants of the short down forms change, and from where the rectangular ones are looked at, the choice doesn't.
+    const int64_t edge_layers[][2] = {{4096, 14336}, {3584, 18944}, {3584, 9728}, {2560, 9728}, {6144, 16384}, {4096, 11008},
+                                      {5120, 13824}, {2048, 8192}, {2048, 5632}, {3072, 8192}, {4608, 12288}, {2304, 9216}, {3200, 8640}};
+    for (const auto& l : edge_layers)
+        for (int64_t M : {(int64_t)1000, momk::long_from(l[0], l[1])}) {
+            const momk::Launch a = momk::choose_down(M - 1, l[0], l[1], 256, false, false), b = momk::choose_down(M, l[0], l[1], 256, false, false);
+            CHECK(a.kind == b.kind && a.tm == b.tm && a.tn == b.tn, "down M=%lld N=%lld K=%lld: %d x %d, one row less %d x %d", (long long)M,
+                  (long long)l[0], (long long)l[1], b.tm, b.tn, a.tm, a.tn);
+        }
     // What the GPU tests take for granted about the choice: launches of two widths, the second ring of gate/up 64 x 64.
     const int64_t two[][3] = {{1024, 128, 14336}, {1000, 96, 14304}, {2048, 64, 14336}, {1280, 128, 10112}};
     for (const auto& t : two) {
