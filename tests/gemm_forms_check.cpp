@@ -162,6 +162,14 @@ int main() {
             const momk::Launch l = momk::choose_gateup(M, 9728, K, 256, false);
             CHECK(l.kind == momk::kWholeTiles && l.tm == 256 && l.tn == 256, "gate/up M=%lld K=%lld in %d x %d", (long long)M, (long long)K, l.tm, l.tn);
         }
+    // Blocks are for mini-sequences of few rows: a layer of 256 x 1024 by 26214 of them and more is faster without.
+    for (int64_t C : {128, 512, 9000, 18022, 26214, 32768}) {
+        const int64_t S = 2 * C + 3956;
+        const momk::Launch g = momk::choose_gateup(C, 1024, 256, 256, true), d = momk::choose_down(C, 256, 1024, 256, false, false);
+        const int form = momk::choose_block(S, 256, 1024, C, 256, g, d);
+        CHECK(C > 18022 || form >= 0, "no blocks for mini-sequences of %lld", (long long)C);
+        CHECK(C <= 18022 || form < 0, "blocks for mini-sequences of %lld", (long long)C);
+    }
     // a form that is not there is an error, not a launch of nothing
     for (bool gu : {false, true})
         for (int f : {-1, momk::short_forms(gu)})
