@@ -106,8 +106,9 @@ int mom_mlp_prefill(const void *x, const void *W_gate, const void *W_up, const v
  * MOM_STATIC_WORKSPACE_BYTES array that is part of the library's device image (each device the
  * library is used on holds its copy until the process ends).  The call allocates nothing and
  * frees nothing.
- *   The array is there at its full size, so as many rows go through it at a time as it holds (in whole
- *   256-row tiles) where that is at least half as many again as mini_seq.
+ *   The array is there at its full size whatever mini_seq is: all rows go through it at once where they
+ *   fit, otherwise as many at a time as it holds in whole 256-row tiles where that is at least half as
+ *   many again as mini_seq, or in passes of the same length where that is expected to take less time.
  *   Limit: min(mini_seq, S) * I * 2 <= MOM_STATIC_WORKSPACE_BYTES (e.g. 2048 rows at I = 14336),
  *   else MOM_ERR_WORKSPACE and nothing is enqueued.  Other arguments and errors as mom_mlp_prefill.
  *   The device address of the array is looked up on the first call on a device (or by mom_init,
@@ -124,7 +125,8 @@ int mom_mlp_prefill_static(const void *x, const void *W_gate, const void *W_up, 
  * The same computation and the same bits as mom_mlp_prefill with the workspace of two mini-sequences
  * (2 * C * I * 2 bytes: still O(C*I), the bound of the paper's Eq. 3), for callers that can spare it and
  * a second stream.  The library puts it to the use that was measured fastest: two mini-sequences go through
- * as one on `stream`, or, where a mini-sequence is so long that this gains nothing, one at a time.
+ * as one on `stream` (or all rows in passes of the same length, up to two mini-sequences), or, where a
+ * mini-sequence is so long that this gains nothing, one at a time.
  * mom_debug_force_pipeline makes it the double buffer of a two-stream schedule: the down projection of
  * mini-sequence c on `stream2` beside the gate/up projection of mini-sequence c+1 on `stream`.
  *   workspace        at least mom_mlp_pipelined_workspace_bytes(S,H,I,mini_seq) bytes

@@ -42,28 +42,6 @@ inline int64_t effective_chunk(int64_t S, int64_t mini_seq) {
     return (mini_seq <= 0 || mini_seq > S) ? S : mini_seq;
 }
 
-// Token rows of a pass of mom_mlp_prefill_static: the static workspace is there at its full size whatever mini_seq is, and a
-// pass of more rows takes less time per row (H = 4096, I = 14336, 12000 rows: mini-sequences of 128 rows 8054 us, of 512 3832, of 1024 3202,
-// passes of 2304 rows 2970).  Whole 256-row token tiles, and only from half as many rows again on: at 12000 -> 16128 rows of I = 2080
-// the shorter last pass costs 2.6 % of 18000 rows, at 8192 -> 16128 14 % are gained.
-int64_t static_rows(int64_t S, int64_t I, int64_t C) {
-    const int64_t fit = (int64_t)MOM_STATIC_WORKSPACE_BYTES / (2 * I);
-    if (S <= fit) return S;
-    const int64_t whole = fit / 256 * 256;
-    return 2 * whole >= 3 * C ? whole : C;
-}
-
-// ... and of mom_mlp_prefill_pipelined, whose workspace is that of two mini-sequences: both at once, up to 14 rounds of the CUs in
-// 256 x 128 gate/up tiles of one of them.  Against down(c) beside gate/up(c+1) on two streams, H = 4096, I = 14336, six mini-sequences
-// of C rows: C = 512 979 -> 824 us, 1024 1675 -> 1545, 2048 3043 -> 2734, 4096 level; H = 3584, I = 18944: 512 1261 -> 1020,
-// 2048 3609 -> 3244, 6000 10109 -> 9676.  From 14 rounds on a pass more costs less than 1 %, and 18000 rows at once 3 % more
-// than 12000 and 6000.
-int64_t pipelined_rows(int64_t S, int64_t I, int64_t C, int cus) {
-    const int64_t tiles = (C + momk::kBM - 1) / momk::kBM * ((I + momk::kBW / 2 - 1) / (momk::kBW / 2));
-    if (tiles >= 14 * (int64_t)cus) return C;
-    return 2 * C < S ? 2 * C : S;
-}
-
 int validate_mlp(const void* x, const void* wg, const void* wu, const void* wd, int64_t S, int64_t H,
                  int64_t I, int64_t mini_seq, const void* out, const void* ws, size_t ws_bytes) {
     if (S < 0 || H <= 0 || I <= 0 || mini_seq < 0) return MOM_ERR_SHAPE;
@@ -570,7 +548,9 @@ int mom_mlp_prefill_static(const void* x, const void* W_gate, const void* W_up, 
     if (!ws) return MOM_ERR_HIP;
     const int rc = validate_mlp(x, W_gate, W_up, W_down, S, H, I, mini_seq, out, ws, (size_t)MOM_STATIC_WORKSPACE_BYTES);
     if (rc != MOM_OK) return rc;
-    const int64_t C = static_rows(S, I, effective_chunk(S, mini_seq));
+    const int cus = compute_units();
+    if (cus <= 0) return MOM_ERR_HIP;
+    const int64_t C = momk::static_rows(S, H, I, effective_chunk(S, mini_seq), MOM_STATIC_WORKSPACE_BYTES, cus);
     // the call writes more of the array than `need`, but no argument can lie in any of it
     return mlp_loop(x, W_gate, W_up, W_down, S, H, I, C, out, ws, stream, nullptr, 0);
 }
@@ -610,7 +590,7 @@ int mom_mlp_prefill_pipelined(const void* x, const void* W_gate, const void* W_u
     if (!g_force_pipeline.load(std::memory_order_relaxed)) {
         const int cus = compute_units();
         if (cus <= 0) return MOM_ERR_HIP;
-        return mlp_loop(x, W_gate, W_up, W_down, S, H, I, pipelined_rows(S, I, C, cus), out, workspace, stream, nullptr, 0);
+        return mlp_loop(x, W_gate, W_up, W_down, S, H, I, momk::pipelined_rows(S, H, I, C, cus), out, workspace, stream, nullptr, 0);
     }
     return mlp_pipelined(x, W_gate, W_up, W_down, S, H, I, mini_seq, out, workspace, workspace_bytes,
                          static_cast<hipStream_t>(stream), static_cast<hipStream_t>(stream2), ev);

@@ -315,7 +315,12 @@ struct Launch {
     int form, tm, tn;
     int64_t wide_cols;
     TileGrid grid, narrow;
+    double time = 0;         // what the choice expects it to take, us (0: not chosen by time)
 };
+inline Launch timed(Launch l, double time) {
+    l.time = time;
+    return l;
+}
 inline Launch short_launch(int64_t M, int64_t N, bool gateup, int form) {
     if (form < 0 || form >= short_forms(gateup)) return {kRefused, 0, 0, 0, 0, {}, {}};
     const ShortShape f = short_shape(gateup, form);
@@ -363,6 +368,7 @@ inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool kept, b
     const LaunchTime& short_time = small ? kShortDownSmallTime : kept ? kShortDownKeptTime :
                                    M < long_from(N, K) ? kShortDownTime : kShortDownLongTime;
     const int form = choose_short_form(M, N, K, false, short_time, cus, least, small ? kSmallDownForms : 0);
+    const double short_least = least;
     if (&short_time == &kShortDownTime) least *= kOverWhole;
     // The width: by time where the widest take no more than one round; over several rounds by rounds x columns, a column of
     // a narrower tile charged what it was measured to cost more for the token fragments it shares among fewer MFMAs
@@ -389,9 +395,9 @@ inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool kept, b
         const int64_t c = rounds_per_mille((int64_t)g.tiles, cus) * w * per_mille[i];
         if (width == 0 || (full.grid.tiles > (uint64_t)cus ? c < columns : t < time)) { width = w; time = t; columns = c; }
     }
-    if (rect.tm && rect_time < kOverDown * time && (form < 0 || rect_time < kOverDown * least)) return whole_launch(M, N, false, rect.tm, rect.tn);
-    if (form >= 0 && least < time) return short_launch(M, N, false, form);
-    return whole_launch(M, N, false, 256, width);
+    if (rect.tm && rect_time < kOverDown * time && (form < 0 || rect_time < kOverDown * least)) return timed(whole_launch(M, N, false, rect.tm, rect.tn), rect_time);
+    if (form >= 0 && least < time) return timed(short_launch(M, N, false, form), short_least);
+    return timed(whole_launch(M, N, false, 256, width), time);
 }
 
 // Gate/up with 256-row tiles: the first columns in tiles of 128 columns, the rest in tiles of 96, in one launch of
@@ -434,19 +440,19 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus, bool more)
         if (filled && rect < kRectBytes * N * K) rect = kRectBytes * N * K;
         const double share = plain_launch.grid.tiles > (uint64_t)cus ? kOverOneRound : M <= 256 ? kOneTokenTile : kWithinOneRound;
         if (r.tm && (M > 96 || filled) && rect < share * full && (form < 0 || least >= full || rect < (filled ? kOverShortFilled : kOverShort) * least))
-            return whole_launch(M, N, true, r.tm, r.tn);
+            return timed(whole_launch(M, N, true, r.tm, r.tn), rect);
     }
     const Launch pair = whole_launch(M, N, true, 128, 128);
     if (pair.kind != kRefused && !(one_group && pair.grid.tiles_m > (uint32_t)kTokenGroup) && pair.grid.tiles <= 2 * (uint64_t)cus &&
         (K <= 2048 || (pair.grid.tiles_m > (uint32_t)kTokenGroup && pair.grid.tiles > (uint64_t)cus))) {
         const double t = launch_time(pair.grid, M, K, true, kPairShape, small ? kPairGateUpSmallTime : kPairGateUpTime, cus);
-        if (t < full && (form < 0 || t < least)) return pair;
+        if (t < full && (form < 0 || t < least)) return timed(pair, t);
     }
-    if (form >= 0 && least < full) return short_launch(M, N, true, form);
-    if (narrow_tiles_n == 0 || wide_cols >= N) return plain_launch;
-    if (wide_cols == 0) return whole_launch(M, N, true, 256, 192);
+    if (form >= 0 && least < full) return timed(short_launch(M, N, true, form), least);
+    if (narrow_tiles_n == 0 || wide_cols >= N) return timed(plain_launch, plain_time);
+    if (wide_cols == 0) return timed(whole_launch(M, N, true, 256, 192), full);
     Launch l = {kTwoWidths, 0, 256, 256, wide_cols, tile_grid(M, wide_cols, true, {256, 256, 1, 0}),
-                tile_grid(M, N - wide_cols, true, {256, 192, 1, 0})};
+                tile_grid(M, N - wide_cols, true, {256, 192, 1, 0}), full};
     if (l.grid.tiles > (uint64_t)kMaxTiles || l.narrow.tiles > (uint64_t)kMaxTiles) l.kind = kRefused;
     return l;
 }
@@ -473,19 +479,6 @@ inline double block_time(const BlockForm& f, int64_t S, int64_t H, int64_t I, in
     return 4.0 + (double)((blocks + cus - 1) / cus) * (6.0 * H * I) / f.bytes_per_us + 1.0e-6 * S * H;
 }
 
-// The formula's time of launch l of M token rows.
-inline double formula_time(const Launch& l, int64_t M, int64_t N, int64_t K, bool gateup, int cus) {
-    const bool small = small_layer(N, K);
-    if (l.kind == kShortTiles) {
-        const LaunchTime& t = gateup ? (small ? kShortGateUpSmallTime : kShortGateUpTime) : (small ? kShortDownSmallTime : kShortDownTime);
-        return launch_time(l.grid, M, K, gateup, short_shape(gateup, l.form), t, cus);
-    }
-    if (gateup && l.tm == 128) return launch_time(l.grid, M, K, true, kPairShape, small ? kPairGateUpSmallTime : kPairGateUpTime, cus);
-    double t = launch_time(l.grid, M, K, gateup, {l.tm, l.tn, 1, 0}, gateup ? kFullGateUpTime : kFullDownTime, cus);
-    if (l.kind == kTwoWidths) t += launch_time(l.narrow, M, K, true, {256, 192, 1, 0}, kFullGateUpTime, cus);
-    return t;
-}
-
 // The form in which S token rows take less time than as mini-sequences of C of them, whose two launches are given; -1: none.  A
 // mini-sequence takes 6 us less than the launches by themselves (H = 256, I = 1024: 128 rows 7.0 us, 512 8.0, 2048 11.0, formula
 // 13.1, 14.2, 17.2; H = 1056, I = 2080: 128 rows 12.3, formula 18.1; where both are longer, 512 rows 21.5 and 24.7, the loop
@@ -504,8 +497,54 @@ inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, con
         if (best < 0 || t < least) { best = i; least = t; }
     }
     if (best < 0) return -1;
-    const double one = formula_time(gateup, C, I, H, true, cus) + formula_time(down, C, H, I, false, cus) - 6;
+    const double one = gateup.time + down.time - 6;
     return least < 0.93 * one * ((S + C - 1) / C) ? best : -1;
+}
+
+// ---- Token rows of a pass of mom_mlp_prefill_static and mom_mlp_prefill_pipelined, whose workspaces hold more than mini_seq of them.
+
+// What the choices expect a call of S rows, R at a time, to take, us.
+inline double call_time(int64_t S, int64_t H, int64_t I, int64_t R, int cus) {
+    if (S > R && small_layer(I, H)) {
+        const int form = choose_block(S, H, I, R, cus, choose_gateup(R, I, H, cus, true), choose_down(R, H, I, cus, false, false));
+        if (form >= 0) return block_time(kBlockForms[form], S, H, I, cus);
+    }
+    auto pass = [&](int64_t rows, int64_t c) {
+        const Launch gateup = choose_gateup(rows, I, H, cus, S > R);
+        return gateup.time + choose_down(rows, H, I, cus, c >= kKeptFrom && kept_down(gateup, rows, H, I), false).time;
+    };
+    const int64_t whole = S / R, first = whole < kKeptFrom ? whole : kKeptFrom;
+    return (first ? first * pass(R, 0) : 0) + (whole > first ? (whole - first) * pass(R, first) : 0) + (S % R ? pass(S % R, whole) : 0);
+}
+
+// `rows` at a time, or, of as few passes as a workspace for `most` rows allows, all of the same length in whole 256-row tiles, where that is
+// expected to take 3.5 % less.  1350 rows of H = 6144, I = 16384 by 600 take 857 us, as 512, 512 and 326 695; static, 33875 rows of H =
+// 1056, I = 2080 by 16128 416, by 11520 379.  Of 1557 calls with two mini-sequences' workspace (S 1.05 ... 4.5 C, 14 layers) 165 change, by
+// 5.5 % on average, 4 for the worse by 2 % or a little more; with 1 % promised 319, 17 for the worse.  Not asked of calls of less than some
+// 40 us, which the asking (3 ... 10 us on the host) would make longer: 690 rows of a 256 x 1024 layer 16.1 -> 17.5 us.
+inline int64_t even_rows(int64_t S, int64_t H, int64_t I, int64_t rows, int64_t most, int cus) {
+    const int64_t n = (S + most - 1) / most, even = ((S + n - 1) / n + 255) / 256 * 256;
+    if (n == 1 || even >= most || even == rows || S * H < ((int64_t)1 << 33) / I) return rows;
+    return call_time(S, H, I, even, cus) < 0.965 * call_time(S, H, I, rows, cus) ? even : rows;
+}
+
+// Static: the array of `bytes` is there at its full size whatever mini_seq (C rows) is, and a pass of more rows takes less time per row
+// (H = 4096, I = 14336, 12000 rows: by 128 rows 8054 us, by 512 3832, by 1024 3202, by 2304 2970).  Whole 256-row token tiles, and only from
+// half as many rows again on: at 8192 -> 16128 rows of I = 2080 14 % are gained.
+inline int64_t static_rows(int64_t S, int64_t H, int64_t I, int64_t C, int64_t bytes, int cus) {
+    const int64_t fit = bytes / (2 * I), whole = fit / 256 * 256;
+    if (S <= fit) return S;
+    return whole ? even_rows(S, H, I, 2 * whole >= 3 * C ? whole : C, whole, cus) : C;
+}
+
+// Two mini-sequences' workspace: both at once, up to 14 rounds of the CUs in 256 x 128 gate/up tiles of one of them.  Against
+// down(c) beside gate/up(c+1) on two streams, H = 4096, I = 14336, six mini-sequences of C rows: C = 512 979 -> 824 us, 1024 1675 ->
+// 1545, 2048 3043 -> 2734, 4096 level; H = 3584, I = 18944: 512 1261 -> 1020, 2048 3609 -> 3244, 6000 10109 -> 9676.  From 14 rounds on a
+// pass more costs less than 1 %, and 18000 rows at once 3 % more than 12000 and 6000.
+inline int64_t pipelined_rows(int64_t S, int64_t H, int64_t I, int64_t C, int cus) {
+    if (S <= C) return S;
+    const int64_t tiles = (int64_t)whole_launch(C, I, true, 256, 256).grid.tiles, both = 2 * C < S ? 2 * C : S;
+    return even_rows(S, H, I, tiles >= 14 * (int64_t)cus ? C : both, both, cus);
 }
 
 }  // namespace momk

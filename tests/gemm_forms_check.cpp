@@ -108,6 +108,37 @@ static void kept(int64_t H, int64_t I) {
     }
 }
 
+// Rows of a pass fit the workspace, and what was measured the faster of the candidates is taken.
+static void passes() {
+    const int64_t layers[][2] = {{4096, 14336}, {3584, 18944}, {6144, 16384}, {3584, 9728}, {1056, 2080}, {256, 1024}, {32, 1 << 20}, {1 << 20, 32}};
+    int even = 0, more = 0;
+    for (const auto& l : layers)
+        for (int64_t C = 1; C < 40000; C += 1 + C * 3 / 7)
+            for (int64_t S : {C + 1, 2 * C - 1, 2 * C, 2 * C + 1, 3 * C + C / 3, 9 * C, 100 * C + 7, (int64_t)0x7fffff00}) {
+                if (S <= C) continue;
+                const int64_t p = momk::pipelined_rows(S, l[0], l[1], C, 256), bytes = 64 << 20;
+                CHECK(p >= 1 && p <= 2 * C && p <= S, "pipelined S=%lld C=%lld: %lld rows", (long long)S, (long long)C, (long long)p);
+                even += p != C && p != 2 * C && p != S;
+                if (2 * C * l[1] > bytes) continue;
+                const int64_t t = momk::static_rows(S, l[0], l[1], C, bytes, 256);
+                CHECK(t >= 1 && t <= S && 2 * t * l[1] <= bytes, "static S=%lld C=%lld I=%lld: %lld rows", (long long)S, (long long)C, (long long)l[1], (long long)t);
+                more += t > C;
+            }
+    CHECK(even > 50 && more > 100, "%d even, %d larger", even, more);
+    const int64_t two[][5] = {{1350, 6144, 16384, 300, 512}, {1350, 4096, 14336, 300, 512}, {4050, 8192, 28672, 1500, 2048}, {8100, 4096, 14336, 3000, 4096},
+                              {3072, 4096, 14336, 512, 1024}, {16384, 4096, 14336, 1024, 2048}, {32768, 4096, 14336, 8192, 8192}};
+    for (const auto& t : two) {
+        const int64_t r = momk::pipelined_rows(t[0], t[1], t[2], t[3], 256);
+        CHECK(r == t[4], "pipelined S=%lld C=%lld: %lld rows, not %lld", (long long)t[0], (long long)t[3], (long long)r, (long long)t[4]);
+    }
+    const int64_t fixed[][5] = {{33875, 1056, 2080, 128, 11520}, {20766, 1056, 2080, 10752, 10496}, {33875, 1056, 2080, 8000, 11520}, {12000, 4096, 14336, 128, 2304},
+                                {2304, 4096, 14336, 128, 2304}, {2457, 4096, 14336, 128, 2304}, {12000, 4096, 14336, 2000, 2000}};
+    for (const auto& t : fixed) {
+        const int64_t r = momk::static_rows(t[0], t[1], t[2], t[3], 64 << 20, 256);
+        CHECK(r == t[4], "static S=%lld C=%lld: %lld rows, not %lld", (long long)t[0], (long long)t[3], (long long)r, (long long)t[4]);
+    }
+}
+
 int main() {
     for (int tm = 16; tm <= 256; tm += 16)
         for (int64_t M = 1; M <= 16384; M += 1 + M / 97) tiles(M, 96 + 32 * (M % 11), tm, 64);
@@ -126,6 +157,7 @@ int main() {
     }
     const int64_t kept_layers[][2] = {{4096, 14336}, {3584, 18944}, {4096, 11008}, {6144, 16384}, {5120, 13824}, {5120, 25600}, {2048, 8192}};
     for (const auto& l : kept_layers) kept(l[0], l[1]);
+    passes();
     // Where the constants of the short down forms change, and from where the rectangular ones are looked at, the choice doesn't.
     const int64_t edge_layers[][2] = {{4096, 14336}, {3584, 18944}, {3584, 9728}, {2560, 9728}, {6144, 16384}, {4096, 11008},
                                       {5120, 13824}, {2048, 8192}, {2048, 5632}, {3072, 8192}, {4608, 12288}, {2304, 9216}, {3200, 8640}};
