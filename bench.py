@@ -44,7 +44,7 @@ def parse():
     p.add_argument("--calib", action="store_true",
                    help="also run a plain 1 GiB elementwise copy kernel (known HBM bytes) to scale profiler counters")
     p.add_argument("--extras", action="store_true",
-                   help="also time the two-stream driver over the sweep and a six-layer offload schedule")
+                   help="also time mom_mlp_prefill_pipelined over the sweep and a six-layer offload schedule")
     return p.parse_args()
 
 
@@ -490,7 +490,7 @@ def main():
 
 
 def extras(args, binding, synth, torch, wl, tensors, out, dev):
-    """Longer side measurements: the two-stream driver over the sweep and a six-layer offload schedule."""
+    """Longer side measurements: mom_mlp_prefill_pipelined over the sweep and a six-layer offload schedule."""
     S, H, I = wl.S, wl.H, wl.I
     ex = {"pipelined_sweep": []}
     side2 = torch.cuda.Stream()
@@ -500,8 +500,7 @@ def extras(args, binding, synth, torch, wl, tensors, out, dev):
         e.record(st)
     x, wg, wu, wd = tensors
     for C in (512, 1024, 2048, 4096):
-        # the same step through mom_mlp_prefill_pipelined: down(c) on a second stream beside gate/up(c+1),
-        # two workspace halves
+        # the same step through mom_mlp_prefill_pipelined: the workspace of two mini-sequences, both at a time
         nb2 = binding.mom_mlp_pipelined_workspace_bytes(S, H, I, C)
         ws2 = torch.empty(nb2, dtype=torch.uint8, device=dev)
         reps = max(3, args.steps // 2)

@@ -127,15 +127,11 @@ int mom_mlp_prefill_static(const void *x, const void *W_gate, const void *W_up, 
  * a second stream.  The library puts it to the use that was measured fastest: two mini-sequences go through
  * as one on `stream` (or all rows in passes of the same length, up to two mini-sequences), or, where a
  * mini-sequence is so long that this gains nothing, one at a time.
- * mom_debug_force_pipeline makes it the double buffer of a two-stream schedule: the down projection of
- * mini-sequence c on `stream2` beside the gate/up projection of mini-sequence c+1 on `stream`.
  *   workspace        at least mom_mlp_pipelined_workspace_bytes(S,H,I,mini_seq) bytes
- *   stream, stream2  two streams of the current device (stream2 should differ from stream).  Where the
- *                    call uses stream2 it orders it after the work already enqueued on stream, and stream
- *                    after the last kernel on stream2: the caller synchronises `stream` only.
- *   events           host array of n_events >= 5 hipEvent_t created by the caller (disable-timing
- *                    events are fine); the first five may be re-recorded during the call.
- *                    Fewer than five: MOM_ERR_SHAPE
+ *   stream           all work is enqueued here
+ *   stream2, events  for the double-buffered schedule that the call had (down(c) on stream2 beside gate/up(c+1));
+ *                    neither is used any more.  With more than one mini-sequence `events` is still a host array of
+ *                    n_events >= 5 hipEvent_t, none of them NULL (MOM_ERR_NULL); fewer: MOM_ERR_SHAPE
  * With a single mini-sequence (mini_seq 0 or >= S) this is mom_mlp_prefill on `stream`.
  */
 size_t mom_mlp_pipelined_workspace_bytes(int64_t S, int64_t H, int64_t I, int64_t mini_seq);
@@ -238,15 +234,11 @@ int mom_kv_reload(const void *pinned_host, void *k, void *v, void *stream, size_
  *
  * mom_debug_force_block: every later mom_mlp_prefill, _static and _pipelined call evaluates blocks of token_rows (16 or 32) rows
  * in one launch, both projections with the intermediate in LDS, where H + I is small enough; 0 gives the choice back.
- *
- * mom_debug_force_pipeline: on != 0 makes mom_mlp_prefill_pipelined use its two-stream schedule
- * whenever there is more than one mini-sequence, also where it was measured not to pay.
  */
 int mom_debug_force_gemm_form(int tile_edge, int ring_slots, int tile_width);
 int mom_debug_force_short_form(int token_rows, int weight_rows);
 int mom_debug_force_rect_form(int token_rows, int weight_rows);
 int mom_debug_force_block(int token_rows);
-int mom_debug_force_pipeline(int on);
 
 /*
  * Measurement aid: the rate the matrix cores of this machine sustain on given operand values.

@@ -16,7 +16,8 @@ LIB_PATH = os.path.join(_HERE, "libmom.so")
 SYMBOLS = ("mom_status_string", "mom_mlp_workspace_bytes", "mom_mlp_prefill", "mom_mlp_prefill_events",
            "mom_mlp_pipelined_workspace_bytes", "mom_mlp_prefill_pipelined",
            "mom_lmhead_last", "mom_mlp_last", "mom_kv_offload", "mom_kv_reload",
-           "mom_init", "mom_debug_force_gemm_form", "mom_debug_force_short_form", "mom_debug_force_rect_form", "mom_debug_force_block", "mom_debug_force_pipeline", "mom_mlp_prefill_static",
+           "mom_init", "mom_debug_force_gemm_form", "mom_debug_force_short_form", "mom_debug_force_rect_form", "mom_debug_force_block",
+           "mom_mlp_prefill_static",
            "mom_debug_mfma_probe")
 
 MOM_STATIC_WORKSPACE_BYTES = 64 << 20
@@ -78,8 +79,6 @@ def lib():
         L.mom_debug_force_block.argtypes = [ctypes.c_int]
         L.mom_debug_mfma_probe.restype = ctypes.c_int
         L.mom_debug_mfma_probe.argtypes = [vp, sz, vp, sz, i64, ctypes.c_int, ctypes.c_int, vp, vp]
-        L.mom_debug_force_pipeline.restype = ctypes.c_int
-        L.mom_debug_force_pipeline.argtypes = [ctypes.c_int]
         _lib = L
     return _lib
 
@@ -149,8 +148,8 @@ def mom_mlp_pipelined_workspace_bytes(S, H, I, mini_seq):
 
 def mom_mlp_prefill_pipelined(x, W_gate, W_up, W_down, mini_seq, out, workspace, stream, stream2, events,
                               check=True):
-    """As mom_mlp_prefill with down(c) on stream2 beside gate/up(c+1) on stream; workspace of
-    mom_mlp_pipelined_workspace_bytes; events: at least 5 torch.cuda.Event whose handles exist."""
+    """As mom_mlp_prefill with a workspace of mom_mlp_pipelined_workspace_bytes, two mini-sequences at a time; enqueues on `stream`.
+    stream2 is not used; events: at least 5 torch.cuda.Event whose handles exist, checked and not used."""
     S, H = x.shape
     I = W_gate.shape[0]
     arr = None if events is None else (ctypes.c_void_p * len(events))(*[e.cuda_event for e in events])
@@ -208,11 +207,6 @@ def mom_debug_force_block(token_rows=0):
     if rc != MOM_OK:
         raise MomError(rc, "mom_debug_force_block")
     return rc
-
-
-def mom_debug_force_pipeline(on):
-    """Testing aid: make mom_mlp_prefill_pipelined always use its two-stream schedule."""
-    return lib().mom_debug_force_pipeline(1 if on else 0)
 
 
 def mom_debug_mfma_probe(a, b, iters, workgroups, sink, stream=None, order=0):

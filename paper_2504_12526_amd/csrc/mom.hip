@@ -81,7 +81,7 @@ struct DeviceInfo {
 DeviceInfo g_dev[kMaxDevices];
 
 // Testing overrides (the mom_debug_force_ calls); 0 = the library chooses.
-std::atomic<int> g_force_edge{0}, g_force_width{0}, g_force_pipeline{0};
+std::atomic<int> g_force_edge{0}, g_force_width{0};
 std::atomic<int> g_force_short{0}, g_force_rect{0};      // token rows << 16 | weight rows
 std::atomic<int> g_force_block{0};      // token rows of a block
 
@@ -264,12 +264,12 @@ momk::Launch gateup_launch(int64_t M, int64_t H, int64_t I, bool more) {
     return l.form >= 0 ? l : momk::choose_gateup(M, I, H, cus, more);
 }
 
-// ... behind the gate/up launch of mini-sequence c.  full_tiles: in tiles of 256 x 256 however few.
-momk::Launch down_launch(int64_t M, int64_t H, int64_t I, const momk::Launch& gateup, int64_t c, bool full_tiles = false) {
+// ... behind the gate/up launch of mini-sequence c.
+momk::Launch down_launch(int64_t M, int64_t H, int64_t I, const momk::Launch& gateup, int64_t c) {
     const int cus = compute_units();
     if (cus <= 0) return {momk::kRefused, -1, 0, 0, 0, {}, {}};
     const momk::Launch l = forced_launch(M, H, false);
-    return l.form >= 0 ? l : momk::choose_down(M, H, I, cus, c >= momk::kKeptFrom && momk::kept_down(gateup, M, H, I), full_tiles);
+    return l.form >= 0 ? l : momk::choose_down(M, H, I, cus, c >= momk::kKeptFrom && momk::kept_down(gateup, M, H, I));
 }
 
 // O[m, n] of M token rows x N output columns by launch l.  more: the call has more than one mini-sequence.
@@ -400,52 +400,6 @@ int mlp_driver(const void* x, const void* wg, const void* wu, const void* wd, in
     return mlp_loop(x, wg, wu, wd, S, H, I, effective_chunk(S, mini_seq), out, ws, stream, events, n_events);
 }
 
-// The same loop on two streams with two workspace halves (mom_debug_force_pipeline; otherwise pipelined_rows): the down
-// projection of mini-sequence c (stream B) runs beside the gate/up projection of mini-sequence c+1 (stream A), so that the CUs
-// one kernel's last, partly filled round of tiles leaves idle take tiles of the other.
-//   A: [wait D(c-2)]  gate/up(c) -> half c%2   record G(c)
-//   B:  wait G(c)     down(c)   <- half c%2    record D(c)
-// ev[0..1] = G of even/odd c, ev[2..3] = D of even/odd c.
-int mlp_pipelined(const void* x, const void* wg, const void* wu, const void* wd, int64_t S, int64_t H, int64_t I,
-                  int64_t mini_seq, void* out, void* ws, size_t ws_bytes, hipStream_t sa, hipStream_t sb,
-                  hipEvent_t* ev) {
-    const int64_t C = effective_chunk(S, mini_seq);
-    const int64_t n = (S + C - 1) / C;
-    const unsigned short* xs = static_cast<const unsigned short*>(x);
-    unsigned short* os = static_cast<unsigned short*>(out);
-    unsigned short* half[2] = {static_cast<unsigned short*>(ws), static_cast<unsigned short*>(ws) + (size_t)C * I};
-    (void)ws_bytes;
-    // B starts after everything already enqueued on A (the inputs)
-    if (hipEventRecord(ev[2], sa) != hipSuccess || hipStreamWaitEvent(sb, ev[2], 0) != hipSuccess) return MOM_ERR_HIP;
-    for (int64_t c = 0; c < n; ++c) {
-        const int64_t r0 = c * C;
-        const int rows = (int)((r0 + C <= S) ? C : (S - r0));
-        const int h = (int)(c & 1);
-        if (c >= 2 && hipStreamWaitEvent(sa, ev[2 + h], 0) != hipSuccess) return MOM_ERR_HIP;
-        // gate/up(c) is held until down(c-1) has been handed to the device: its few, long tiles must
-        // get their CUs before the many tiles of this kernel take the whole chip for a round
-        if (c >= 1 && hipStreamWaitEvent(sa, ev[4], 0) != hipSuccess) return MOM_ERR_HIP;
-        const momk::Launch gateup = gateup_launch(rows, H, I, true);
-        if (launch_gemm<momk::EPI_GATEUP>(gateup, xs + r0 * H, static_cast<const unsigned short*>(wg), static_cast<const unsigned short*>(wu),
-                                          half[h], rows, (int)I, (int)H, sa, true) != hipSuccess)
-            return MOM_ERR_HIP;
-        if (hipEventRecord(ev[h], sa) != hipSuccess || hipStreamWaitEvent(sb, ev[h], 0) != hipSuccess)
-            return MOM_ERR_HIP;
-        if (hipEventRecord(ev[4], sb) != hipSuccess) return MOM_ERR_HIP;
-        // beside a gate/up kernel that fills the chip, full-size tiles are the efficient form for the
-        // down projection however few they are; the last one runs alone and follows the usual rule
-        const bool beside_big = c + 1 < n;
-        if (launch_gemm<momk::EPI_DOWN>(down_launch(rows, H, I, gateup, c, beside_big), half[h],
-                                        static_cast<const unsigned short*>(wd), nullptr, os + r0 * H, rows, (int)H, (int)I,
-                                        sb, true) != hipSuccess)
-            return MOM_ERR_HIP;
-        if (hipEventRecord(ev[2 + h], sb) != hipSuccess) return MOM_ERR_HIP;
-    }
-    // A continues after the last down projection: the caller synchronises A only
-    if (hipStreamWaitEvent(sa, ev[2 + (int)((n - 1) & 1)], 0) != hipSuccess) return MOM_ERR_HIP;
-    return MOM_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -521,11 +475,6 @@ int mom_debug_mfma_probe(const void* a_bf16, size_t a_bytes, const void* b_bf16,
                   (unsigned)(b_bytes / 16), (long long)iters, sink) == hipSuccess ? MOM_OK : MOM_ERR_HIP;
 }
 
-int mom_debug_force_pipeline(int on) {
-    g_force_pipeline.store(on ? 1 : 0, std::memory_order_relaxed);
-    return MOM_OK;
-}
-
 size_t mom_mlp_workspace_bytes(int64_t S, int64_t H, int64_t I, int64_t mini_seq) {
     if (S <= 0 || H <= 0 || I <= 0 || mini_seq < 0) return 0;
     return (size_t)effective_chunk(S, mini_seq) * (size_t)I * 2;
@@ -577,23 +526,17 @@ int mom_mlp_prefill_pipelined(const void* x, const void* W_gate, const void* W_u
         if (overlaps(workspace, need, ins[i], inb[i])) return MOM_ERR_ALIAS;
     if (overlaps(out, xb, workspace, need)) return MOM_ERR_ALIAS;
     const int64_t C = effective_chunk(S, mini_seq);
-    if ((S + C - 1) / C == 1)      // a single mini-sequence: nothing to overlap
+    if ((S + C - 1) / C == 1)      // a single mini-sequence
         return mlp_driver(x, W_gate, W_up, W_down, S, H, I, mini_seq, out, workspace, workspace_bytes, stream,
                           nullptr, 0);
     if (!events) return MOM_ERR_NULL;
     if (n_events < 5) return MOM_ERR_SHAPE;
-    hipEvent_t ev[5];
-    for (int i = 0; i < 5; ++i) {
+    for (int i = 0; i < 5; ++i)
         if (!events[i]) return MOM_ERR_NULL;
-        ev[i] = static_cast<hipEvent_t>(events[i]);
-    }
-    if (!g_force_pipeline.load(std::memory_order_relaxed)) {
-        const int cus = compute_units();
-        if (cus <= 0) return MOM_ERR_HIP;
-        return mlp_loop(x, W_gate, W_up, W_down, S, H, I, momk::pipelined_rows(S, H, I, C, cus), out, workspace, stream, nullptr, 0);
-    }
-    return mlp_pipelined(x, W_gate, W_up, W_down, S, H, I, mini_seq, out, workspace, workspace_bytes,
-                         static_cast<hipStream_t>(stream), static_cast<hipStream_t>(stream2), ev);
+    (void)stream2;
+    const int cus = compute_units();
+    if (cus <= 0) return MOM_ERR_HIP;
+    return mlp_loop(x, W_gate, W_up, W_down, S, H, I, momk::pipelined_rows(S, H, I, C, cus), out, workspace, stream, nullptr, 0);
 }
 
 int mom_mlp_prefill_events(const void* x, const void* W_gate, const void* W_up, const void* W_down,

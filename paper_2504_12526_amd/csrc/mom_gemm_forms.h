@@ -358,11 +358,10 @@ inline int64_t rounds_per_mille(int64_t tiles, int cus) {
 // tile with the fewest of them.
 // Both sides are priced on the grid that runs: 2400 rows x 4096 columns are 220 tiles of 256 x 192 = one round, 223 us,
 // against two rounds of 160 x 128, 276 us (2700 rows 231 and 302, 4300 402 and 463, 5500 461 and 595 us).
-// kept: W_down is in the Infinity Cache (kept_down).  full_tiles: tiles of 256 x 256 however few (beside a gate/up kernel
-// that fills the chip).
-inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool kept, bool full_tiles) {
+// kept: W_down is in the Infinity Cache (kept_down).
+inline Launch choose_down(int64_t M, int64_t N, int64_t K, int cus, bool kept) {
     const Launch full = whole_launch(M, N, false, 256, 256);
-    if (full.kind == kRefused || full_tiles) return full;
+    if (full.kind == kRefused) return full;
     double least = 0, time = 0;
     const bool small = small_layer(N, K);
     const LaunchTime& short_time = small ? kShortDownSmallTime : kept ? kShortDownKeptTime :
@@ -506,12 +505,12 @@ inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, con
 // What the choices expect a call of S rows, R at a time, to take, us.
 inline double call_time(int64_t S, int64_t H, int64_t I, int64_t R, int cus) {
     if (S > R && small_layer(I, H)) {
-        const int form = choose_block(S, H, I, R, cus, choose_gateup(R, I, H, cus, true), choose_down(R, H, I, cus, false, false));
+        const int form = choose_block(S, H, I, R, cus, choose_gateup(R, I, H, cus, true), choose_down(R, H, I, cus, false));
         if (form >= 0) return block_time(kBlockForms[form], S, H, I, cus);
     }
     auto pass = [&](int64_t rows, int64_t c) {
         const Launch gateup = choose_gateup(rows, I, H, cus, S > R);
-        return gateup.time + choose_down(rows, H, I, cus, c >= kKeptFrom && kept_down(gateup, rows, H, I), false).time;
+        return gateup.time + choose_down(rows, H, I, cus, c >= kKeptFrom && kept_down(gateup, rows, H, I)).time;
     };
     const int64_t whole = S / R, first = whole < kKeptFrom ? whole : kKeptFrom;
     return (first ? first * pass(R, 0) : 0) + (whole > first ? (whole - first) * pass(R, first) : 0) + (S % R ? pass(S % R, whole) : 0);
@@ -537,8 +536,8 @@ inline int64_t static_rows(int64_t S, int64_t H, int64_t I, int64_t C, int64_t b
     return whole ? even_rows(S, H, I, 2 * whole >= 3 * C ? whole : C, whole, cus) : C;
 }
 
-// Two mini-sequences' workspace: both at once, up to 14 rounds of the CUs in 256 x 128 gate/up tiles of one of them.  Against
-// down(c) beside gate/up(c+1) on two streams, H = 4096, I = 14336, six mini-sequences of C rows: C = 512 979 -> 824 us, 1024 1675 ->
+// Two mini-sequences' workspace: both at once, up to 14 rounds of the CUs in 256 x 128 gate/up tiles of one of them.  Against the
+// workspace as a double buffer, down(c) beside gate/up(c+1) on two streams, H = 4096, I = 14336, six mini-sequences of C rows: C = 512 979 -> 824 us, 1024 1675 ->
 // 1545, 2048 3043 -> 2734, 4096 level; H = 3584, I = 18944: 512 1261 -> 1020, 2048 3609 -> 3244, 6000 10109 -> 9676.  From 14 rounds on a
 // pass more costs less than 1 %, and 18000 rows at once 3 % more than 12000 and 6000.
 inline int64_t pipelined_rows(int64_t S, int64_t H, int64_t I, int64_t C, int cus) {

@@ -67,7 +67,7 @@ static void tiles(int64_t M, int64_t N, int tm, int tn) {
 // What choose_down picks at these sizes, against every launch there is, each priced on the grid that runs.
 static int64_t rounds(const momk::TileGrid& g, int cus) { return ((int64_t)g.tiles + cus - 1) / cus; }
 static void down_choice(int64_t M, int64_t N, int64_t K, int cus, bool more) {
-    const momk::Launch l = momk::choose_down(M, N, K, cus, more && momk::kept_down(momk::choose_gateup(M, K, N, cus, true), M, N, K), false);
+    const momk::Launch l = momk::choose_down(M, N, K, cus, more && momk::kept_down(momk::choose_gateup(M, K, N, cus, true), M, N, K));
     CHECK(l.kind == momk::kShortTiles || l.kind == momk::kWholeTiles, "down M=%lld N=%lld", (long long)M, (long long)N);
     if (l.kind == momk::kWholeTiles) return;
     // With a long contraction a 256-row tile takes at most a little more than a short one of the same width, so short
@@ -86,7 +86,7 @@ static void steady(int64_t N, int64_t K, bool gateup) {
         return a.kind == b.kind && a.form == b.form && a.tm == b.tm && a.tn == b.tn && a.wide_cols == b.wide_cols;
     };
     for (int64_t M = 1; M <= 8192; ++M) {
-        const momk::Launch l = gateup ? momk::choose_gateup(M, N, K, 256, false) : momk::choose_down(M, N, K, 256, false, false);
+        const momk::Launch l = gateup ? momk::choose_gateup(M, N, K, 256, false) : momk::choose_down(M, N, K, 256, false);
         if (M > 1 && same(l, last)) continue;
         CHECK(!since || !same(l, before) || M - since >= 4, "M=%lld N=%lld K=%lld: %d x %d between two runs of %d x %d", (long long)since,
               (long long)N, (long long)K, last.tm, last.tn, l.tm, l.tn);
@@ -163,7 +163,7 @@ int main() {
                                       {5120, 13824}, {2048, 8192}, {2048, 5632}, {3072, 8192}, {4608, 12288}, {2304, 9216}, {3200, 8640}};
     for (const auto& l : edge_layers)
         for (int64_t M : {(int64_t)1000, momk::long_from(l[0], l[1])}) {
-            const momk::Launch a = momk::choose_down(M - 1, l[0], l[1], 256, false, false), b = momk::choose_down(M, l[0], l[1], 256, false, false);
+            const momk::Launch a = momk::choose_down(M - 1, l[0], l[1], 256, false), b = momk::choose_down(M, l[0], l[1], 256, false);
             CHECK(a.kind == b.kind && a.tm == b.tm && a.tn == b.tn, "down M=%lld N=%lld K=%lld: %d x %d, one row less %d x %d", (long long)M,
                   (long long)l[0], (long long)l[1], b.tm, b.tn, a.tm, a.tn);
         }
@@ -184,7 +184,7 @@ int main() {
     const int64_t few[][5] = {{57, 2048, 8192, 32, 16}, {64, 2048, 8192, 32, 16}, {58, 2048, 5632, 32, 16}, {64, 2048, 5632, 32, 16},
                               {86, 2048, 8192, 32, 32}, {86, 2560, 9728, 32, 32}, {122, 2048, 8192, 32, 32}, {122, 2048, 5632, 32, 32}};
     for (const auto& t : few) {
-        const momk::Launch l = momk::choose_down(t[0], t[1], t[2], 256, false, false);
+        const momk::Launch l = momk::choose_down(t[0], t[1], t[2], 256, false);
         CHECK(l.kind == momk::kShortTiles && l.tm == t[3] && l.tn == t[4], "down M=%lld N=%lld K=%lld in %d x %d", (long long)t[0],
               (long long)t[1], (long long)t[2], l.tm, l.tn);
     }
@@ -197,7 +197,7 @@ int main() {
     // Blocks are for mini-sequences of few rows: a layer of 256 x 1024 by 26214 of them and more is faster without.
     for (int64_t C : {128, 512, 9000, 18022, 26214, 32768}) {
         const int64_t S = 2 * C + 3956;
-        const momk::Launch g = momk::choose_gateup(C, 1024, 256, 256, true), d = momk::choose_down(C, 256, 1024, 256, false, false);
+        const momk::Launch g = momk::choose_gateup(C, 1024, 256, 256, true), d = momk::choose_down(C, 256, 1024, 256, false);
         const int form = momk::choose_block(S, 256, 1024, C, 256, g, d);
         CHECK(C > 18022 || form >= 0, "no blocks for mini-sequences of %lld", (long long)C);
         CHECK(C <= 18022 || form < 0, "blocks for mini-sequences of %lld", (long long)C);

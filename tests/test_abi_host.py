@@ -126,7 +126,6 @@ def test_debug_overrides_validate_their_arguments():
     for bad in ((100, 0, 0), (256, 10, 0), (128, 20, 0), (64, 3, 0), (0, 5, 0), (-64, 0, 0), (224, 5, 0), (128, 5, 128),
                 (256, 5, 96), (0, 0, 224)):
         assert L.mom_debug_force_gemm_form(*bad) == binding.MOM_ERR_SHAPE
-    assert L.mom_debug_force_pipeline(1) == binding.MOM_OK and L.mom_debug_force_pipeline(0) == binding.MOM_OK
 
 
 def test_product_reads_no_environment_variables():

@@ -74,13 +74,6 @@ def bits_equal(a, b):
 
 
 @pytest.fixture
-def forced_pipeline():
-    binding.mom_debug_force_pipeline(True)
-    yield
-    binding.mom_debug_force_pipeline(False)
-
-
-@pytest.fixture
 def gemm_form():
     """Callable (edge, ring slots, width) that forces a tile form of the matrix-core kernels; the library's
     own choice is restored afterwards."""
@@ -183,10 +176,8 @@ def test_seeded_random_shapes_on_the_256_row_tiles(gemm_form):
 
 
 @pytest.mark.parametrize("S,H,I", [(300, 96, 160), (257, 64, 64), (700, 384, 640), (1100, 256, 1024), (2500, 512, 512)])
-def test_pipelined_schedule_gives_the_same_bits(S, H, I, forced_pipeline):
-    """Two streams and a double-buffered workspace change the schedule, not one bit of the result.
-    (The library falls back to the plain loop where the schedule does not pay:
-    mom_debug_force_pipeline forces it, so that it is exercised on small shapes too.)"""
+def test_workspace_of_two_mini_sequences_gives_the_same_bits(S, H, I):
+    """How many rows go through the workspace at a time changes no bit of the result."""
     dev = _dev()
     wl = synth.Workload("pipe", S=S, H=H, I=I, mini_seq=0, seed=S + 2 * I, w_std=0.05)
     xd, wgd, wud, wdd = (t.to(dev) for t in synth.mlp_inputs(wl))
@@ -620,7 +611,7 @@ def test_llama3_8b_32k_full_size():
     b, _ = run_mlp(x, wg, wu, wd, 0)
     assert bits_equal(a, b)
     assert bits_equal(a, out[: wl.S - 77].contiguous())     # same seed, same leading rows
-    # the two-stream schedule at mini-sequence sizes where it overlaps the two projections
+    # the workspace of two mini-sequences: both at a time
     x, wg, wu, wd = synth.mlp_inputs(wl, device=dev)
     for C in (512, 1024, 2048, 4096):
         p, nb = run_mlp_pipelined(x, wg, wu, wd, C)
