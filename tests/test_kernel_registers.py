@@ -14,6 +14,13 @@ READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
+def forms(name):
+    """The argument tuples of a list of forms in the header, in its order."""
+    text = open(os.path.join(ROOT, "paper_2504_12526_amd", "csrc", "mom_gemm_forms.h")).read()
+    listed = re.search(r"#define " + name + r"\(X\)((?:.*\\\n)*.*\n)", text)[1]
+    return [tuple(int(v) for v in f.split(",")) for f in re.findall(r"X\(([\d, ]+)\)", listed)]
+
+
 def _code_object():
     """The gfx950 code object in the library: a bundle is a magic, the number of entries, and for each its offset from
     the magic, size and target."""
@@ -67,7 +74,13 @@ def test_acc_registers_hold_the_accumulators_and_nothing_else(tmp_path):
         build.build()
     kernels = _kernels(tmp_path)
     gemms = [n for n in kernels if accumulators(n) is not None]
-    assert len(gemms) >= 20 + 2 * 16 + 5 + 5, gemms        # short: down, gate/up x 2; 256-row and 128-row tiles
+    short = [tuple(int(x) for x in m.groups()) for n in gemms
+             if (m := re.search(r"17gemm_short_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)E", n))]
+    # (projection, form, non-temporal weights): every form of the lists, and no other
+    want = [(0, *f, 0) for f in forms("MOM_SHORT_FORMS_DOWN")] + [(1, *f, nt) for f in forms("MOM_SHORT_FORMS_GATEUP") for nt in (0, 1)]
+    assert sorted(short) == sorted(want)
+    # 256-row tiles: five widths down, two of gate/up with and without; 128-row gate/up tiles; the two widths in one launch
+    assert len(gemms) - len(short) == 5 + 2 * 2 + 1 + 2, gemms
     assert not unsound(kernels), unsound(kernels)
     # the check sees one register too many, and a spill
     for key in ("agpr", "vgpr_spill_count"):

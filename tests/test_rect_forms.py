@@ -6,7 +6,7 @@ import subprocess
 
 import pytest
 
-from test_kernel_registers import LIB, READELF, _kernels
+from test_kernel_registers import LIB, READELF, _kernels, forms
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2504_12526_amd", "csrc")
@@ -50,11 +50,13 @@ def test_acc_registers_hold_the_accumulators_and_nothing_else(tmp_path):
     if not os.path.exists(LIB):
         from paper_2504_12526_amd import build
         build.build()
-    seen = 0
+    seen = []
     for name, v in _kernels(tmp_path).items():
-        m = re.search(r"16gemm_rect_kernelILi\d+ELi(\d+)ELi(\d+)E", name)
+        m = re.search(r"16gemm_rect_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb(\d)E", name)
         if m:
-            seen += 1
-            assert v["agpr"] == 4 * (int(m[1]) // 32) * (int(m[2]) // 32), (name, v)
+            seen.append(tuple(int(x) for x in m.groups()))
+            assert v["agpr"] == 4 * (int(m[2]) // 32) * (int(m[3]) // 32), (name, v)
             assert not (v["vgpr_spill_count"] or v["sgpr_spill_count"] or v["private_segment_fixed_size"]), (name, v)
-    assert seen >= 8 + 2 * 14      # down, gate/up x 2
+    # (projection, token rows, weight rows, non-temporal weights): every form of the lists, and no other
+    want = [(0, *f, 0) for f in forms("MOM_RECT_FORMS_DOWN")] + [(1, *f, nt) for f in forms("MOM_RECT_FORMS_GATEUP") for nt in (0, 1)]
+    assert sorted(seen) == sorted(want)
