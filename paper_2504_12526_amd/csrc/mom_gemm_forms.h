@@ -464,7 +464,8 @@ constexpr int64_t block_lds(int64_t rows, int64_t H, int64_t I, int units) {
     return rows * (H + I + 2 * kBlockPad) * 2 + (int64_t)units * kBlockUnit;
 }
 // X(TB, WAVES, R): 16 TB token rows, WAVES wavefronts with rings of R units.  bytes_per_us: weights through a workgroup, measured at
-// H = 256, I = 1024 (16 rows 17.6 us for 512 token rows, 32 rows 23.7 us for 8192) and H = 1056, I = 2080 (166 us for 3000).  Tokens
+// H = 256, I = 1024 (16 rows 18.3 us for 512 token rows, 32 rows 24 us for 8192) and H = 1056, I = 2080 (166 us for 3000 with the weights
+// in the Infinity Cache, 240 where other layers have displaced them).  Tokens
 // in and out take 1 us per 10^6 elements more.
 #define MOM_BLOCK_FORMS(X) X(1, 8, 2) X(2, 8, 2) X(1, 6, 2)
 struct BlockForm { int tb, waves, r, bytes_per_us; };
