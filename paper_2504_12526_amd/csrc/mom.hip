@@ -139,11 +139,14 @@ bool in_one_allocation(const void* p, size_t n) {
 }
 
 // The device address of pinned_host if kv_reload_kernel is to copy bytes_each bytes each into k and v on stream st, else nullptr:
-// whole 16-byte chunks, buffers of the current device, which is also the stream's, each in one allocation and not overlapping, up to
-// 256 KiB each.  Alone the kernel is the faster one far beyond (256 KiB 34 -> 14 us, 512 KiB 43 -> 23, 2 MiB 98 -> 82), but decoding
-// beside it loses the memory rate of its CUs: 222 us of last-token projections become 225, 231 (512 KiB) and 258 (2 MiB).
+// whole 16-byte chunks, buffers of the current device, which is also the stream's, each in one allocation and not overlapping.  Of
+// any size (up to 16 GiB each, for its 32-bit chunk numbers), because the runtime's copies hold the calling thread (mom_kv.hip.inc has
+// the times); a captured call, whose copies the graph starts, takes the kernel up to 256 KiB each, where it is the faster one by itself
+// (34 -> 14 us), and beyond that the copies, which leave the CUs to the kernels beside them.
 const void* reload_source(const void* pinned_host, const void* k, const void* v, size_t bytes_each, hipStream_t st) {
-    if (bytes_each > ((size_t)256 << 10) || bytes_each % 16 || !aligned16(pinned_host) || !aligned16(k) || !aligned16(v)) return nullptr;
+    if (bytes_each > ((size_t)16 << 30) || bytes_each % 16 || !aligned16(pinned_host) || !aligned16(k) || !aligned16(v)) return nullptr;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (bytes_each > ((size_t)256 << 10) && (!answered(hipStreamIsCapturing(st, &capture)) || capture != hipStreamCaptureStatusNone)) return nullptr;
     if (overlaps(k, bytes_each, v, bytes_each)) return nullptr;
     int dev = 0, stream_dev = 0;
     if (!answered(hipGetDevice(&dev)) || (st && (!answered(hipStreamGetDevice(st, &stream_dev)) || stream_dev != dev))) return nullptr;

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from graph_nodes import KERNEL, MEMCPY, hip, node_types
-from paper_2504_12526_amd import binding
+from paper_2504_12526_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -42,6 +42,38 @@ def test_bytes(each):
 @pytest.mark.parametrize("each,offset", [(2, 0), (14, 0), (4098, 0), (4096, 1), (4096, 8), (65536, 3)])
 def test_odd_sizes_and_alignments(each, offset):
     _reload(each, offset, each + offset)
+
+
+# passes of the kernel's 48 wavefronts (64 threads, four loads of 16 bytes), K ending and V beginning inside one, and some MiB
+WAVES_PASS = 48 * 64 * 4 * 16
+
+
+@pytest.mark.parametrize("each", [WAVES_PASS // 2 - 16, WAVES_PASS // 2 + 16, WAVES_PASS - 16, WAVES_PASS, WAVES_PASS + 16, 5 * WAVES_PASS // 2 + 48,
+                                  7 * WAVES_PASS - 1024, (4 << 20) - 16, (4 << 20) + 4112, 16 << 20])
+def test_bytes_of_several_passes(each):
+    _reload(each, 0, each % 999)
+
+
+def test_a_large_reload_only_enqueues():
+    """The calling thread is not held until the work ahead of the reload is done."""
+    n = 2 << 20
+    host = torch.randint(-32768, 32767, (2 * n,), dtype=torch.int16).pin_memory()
+    k, v = (torch.zeros(n, dtype=torch.int16, device="cuda") for _ in range(2))
+    t = synth.mlp_inputs(synth.Workload("ahead", S=8192, H=2048, I=8192, mini_seq=0, seed=4), device="cuda")
+    out, ws = torch.empty_like(t[0]), torch.empty(8192 * 8192 * 2, dtype=torch.uint8, device="cuda")
+    main, sides, ahead = torch.cuda.current_stream(), [torch.cuda.Stream() for _ in range(3)], torch.cuda.Event()
+    for side in sides:                                          # (the first reload maps the pages)
+        binding.mom_kv_reload(host.view(torch.bfloat16), k.view(torch.bfloat16), v.view(torch.bfloat16), side)
+    torch.cuda.synchronize()
+    for _ in range(24):                                         # some 15 ms
+        binding.mom_mlp_prefill(*t, 0, out, ws, stream=main)
+    ahead.record(main)
+    for side in sides:
+        side.wait_event(ahead)
+        binding.mom_kv_reload(host.view(torch.bfloat16), k.view(torch.bfloat16), v.view(torch.bfloat16), side)
+    assert not ahead.query()
+    torch.cuda.synchronize()
+    assert torch.equal(k.cpu(), host[:n]) and torch.equal(v.cpu(), host[n:])
 
 
 def test_overlapping_buffers_are_copied_one_after_the_other():
