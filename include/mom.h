@@ -71,7 +71,9 @@ size_t mom_mlp_workspace_bytes(int64_t S, int64_t H, int64_t I, int64_t mini_seq
  * evaluated over ceil(S/C) mini-sequences of C = mini_seq rows (the last one
  * shorter when C does not divide S); each mini-sequence's C x I intermediate is
  * written to `workspace` and consumed before the next one overwrites it, and its
- * output rows land directly at their place in `out` (the concat).
+ * output rows land directly at their place in `out` (the concat).  Several mini-sequences go through as one
+ * where that takes less time and the rest of their intermediate has room in the rows of `out` that are still to
+ * come: until the call is done those rows may hold anything, and nothing beside `workspace` and `out` is written.
  *
  *   x        [S,H] bf16      in
  *   W_gate   [I,H] bf16      in
@@ -90,7 +92,7 @@ size_t mom_mlp_workspace_bytes(int64_t S, int64_t H, int64_t I, int64_t mini_seq
  * bit-identical `out`.
  *
  * S = 0 is a no-op returning MOM_OK.  H and I must be positive multiples of 32.
- * All work is enqueued on `stream` in order (2 kernels per mini-sequence; one for the whole call where a layer is so
+ * All work is enqueued on `stream` in order (2 kernels per mini-sequence, or per several as one; one for the whole call where a layer is so
  * small that blocks of rows go through both projections with their intermediate on chip in less time).
  * The kernels exist in several tile forms with bit-identical results; the library picks one per
  * launch (mom_debug_force_gemm_form overrides the choice, for tests).
@@ -142,7 +144,7 @@ int mom_mlp_prefill_pipelined(const void *x, const void *W_gate, const void *W_u
 
 /*
  * The same computation with a HIP event recorded on `stream` before the first
- * kernel and after every kernel: events[0], then for mini-sequence c the event
+ * kernel and after every kernel, one mini-sequence at a time: events[0], then for mini-sequence c the event
  * events[1+2c] after its gate/up kernel and events[2+2c] after its down kernel.
  * `events` is a host array of n_events `hipEvent_t` created by the caller;
  * n_events must be at least 1 + 2*ceil(S/C).  For per-kernel timing only.

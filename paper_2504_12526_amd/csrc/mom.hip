@@ -275,13 +275,14 @@ momk::Launch down_launch(int64_t M, int64_t H, int64_t I, const momk::Launch& ga
     return l.form >= 0 ? l : momk::choose_down(M, H, I, cus, c >= momk::kKeptFrom && momk::kept_down(gateup, M, H, I));
 }
 
-// O[m, n] of M token rows x N output columns by launch l.  more: the call has more than one mini-sequence.
+// O[m, n] of M token rows x N output columns by launch l, the intermediate from row `split` on at `rest` (GemmArgs).  more: the call has more
+// than one mini-sequence.
 template <int EPI>
 hipError_t launch_gemm(const momk::Launch& l, const unsigned short* X, const unsigned short* W0, const unsigned short* W1,
-                       unsigned short* O, int M, int N, int K, hipStream_t st, bool more) {
+                       unsigned short* O, unsigned short* rest, int split, int M, int N, int K, hipStream_t st, bool more) {
     constexpr bool GU = EPI == momk::EPI_GATEUP;
     momk::GemmArgs a;
-    a.X = X; a.W0 = W0; a.W1 = W1; a.O = O;
+    a.X = X; a.W0 = W0; a.W1 = W1; a.O = O; a.rest = rest; a.split = split;
     a.M = M; a.N = N; a.K = K; a.ldo = N;
     switch (l.kind) {
         case momk::kShortTiles: return launch_short_tiles<EPI>(a, l, more, st);
@@ -293,6 +294,7 @@ hipError_t launch_gemm(const momk::Launch& l, const unsigned short* X, const uns
                 p.narrow.W0 = W0 + (size_t)l.wide_cols * K;
                 p.narrow.W1 = W1 + (size_t)l.wide_cols * K;
                 p.narrow.O = O + l.wide_cols;
+                p.narrow.rest = rest + l.wide_cols;
                 p.narrow.N = N - (int)l.wide_cols;
                 set_tile_grid(p.wide, l.grid);
                 set_tile_grid(p.narrow, l.narrow);
@@ -355,6 +357,18 @@ hipError_t launch_gemv(const unsigned short* x, const unsigned short* Wa, const 
                   x, Wa, Wb, y, (int)R, (int)K);
 }
 
+// The next pass of more than C of the `left` rows, with the launches that are forced, if any.
+momk::Pass next_longer_pass(int64_t left, int64_t H, int64_t I, int64_t C, int cus, double per_row) {
+    momk::Pass p = momk::longer_pass(left, H, I, C, cus, per_row);
+    if (!p.rows) return p;
+    const momk::Launch g = forced_launch(p.rows, I, true), d = forced_launch(p.rows, H, false);
+    if (g.form >= 0) p.gateup = g;
+    if (d.form >= 0) p.down = d;
+    p.split = momk::split_of(p.down, C);
+    if (p.gateup.kind == momk::kRefused || p.down.kind == momk::kRefused || p.rows > momk::most_rows(left, H, I, p.split)) p.rows = 0;
+    return p;
+}
+
 // The loop over mini-sequences of C rows on one stream.  The arguments have been validated for a workspace of C x I.
 int mlp_loop(const void* x, const void* wg, const void* wu, const void* wd, int64_t S, int64_t H, int64_t I, int64_t C,
              void* out, void* ws, void* stream, void** events, int64_t n_events) {
@@ -373,24 +387,44 @@ int mlp_loop(const void* x, const void* wg, const void* wu, const void* wd, int6
             return launch_blocks(form, xs, static_cast<const unsigned short*>(wg), static_cast<const unsigned short*>(wu),
                                  static_cast<const unsigned short*>(wd), os, S, H, I, st) == hipSuccess ? MOM_OK : MOM_ERR_HIP;
     }
-    // Algorithm 1, else-branch: O_i = MLP(A_i) for each mini-sequence, O_i written at its rows of O.
-    for (int64_t c = 0; c < n; ++c) {
-        const int64_t r0 = c * C;
-        const int rows = (int)((r0 + C <= S) ? C : (S - r0));
-        if (rows != planned) gateup = gateup_launch(rows, H, I, n > 1);
-        if (rows != planned || c == momk::kKeptFrom) down = down_launch(rows, H, I, gateup, c);
-        planned = rows;
-        if (launch_gemm<momk::EPI_GATEUP>(gateup, xs + r0 * H, static_cast<const unsigned short*>(wg),
-                                          static_cast<const unsigned short*>(wu), w, rows, (int)I, (int)H,
+    // Algorithm 1, else-branch: O_i = MLP(A_i) for each mini-sequence, O_i written at its rows of O; several of them as one pass where the
+    // rows of O that are still to come have room for the rest of the intermediate.
+    const int cus = compute_units();
+    bool longer = !events && cus > 0 && momk::longer_passes(S, H, I, C);
+    const double per_row = longer ? momk::pass_time(C, H, I, cus) / C : 0;
+    int64_t kept = 0;                    // passes since the last that displaced W_down
+    int64_t c = 0;
+    for (int64_t r0 = 0; r0 < S; ++c) {
+        momk::Pass p;
+        if (longer && S - r0 > C) p = next_longer_pass(S - r0, H, I, C, cus, per_row);
+        unsigned short* rest = nullptr;
+        if (p.rows) {
+            const uintptr_t end = reinterpret_cast<uintptr_t>(os + S * H), at = (end - (size_t)(p.rows - p.split) * I * 2) & ~(uintptr_t)(momk::kSpareAlign - 1);
+            rest = reinterpret_cast<unsigned short*>(at - (size_t)p.split * I * 2);
+            planned = -1;
+        } else {
+            p.rows = r0 + C <= S ? C : S - r0;
+            p.split = 0x7fffffff;
+            if (p.rows != planned) gateup = gateup_launch(p.rows, H, I, n > 1);
+            if (p.rows != planned || kept == momk::kKeptFrom) down = down_launch(p.rows, H, I, gateup, kept);
+            planned = (int)p.rows;
+            p.gateup = gateup;
+            p.down = down;
+        }
+        const int rows = (int)p.rows, split = (int)p.split;
+        if (launch_gemm<momk::EPI_GATEUP>(p.gateup, xs + r0 * H, static_cast<const unsigned short*>(wg),
+                                          static_cast<const unsigned short*>(wu), w, rest, split, rows, (int)I, (int)H,
                                           st, n > 1) != hipSuccess)
             return MOM_ERR_HIP;
         if (events && hipEventRecord(static_cast<hipEvent_t>(events[1 + 2 * c]), st) != hipSuccess)
             return MOM_ERR_HIP;
-        if (launch_gemm<momk::EPI_DOWN>(down, w, static_cast<const unsigned short*>(wd), nullptr, os + r0 * H, rows,
+        if (launch_gemm<momk::EPI_DOWN>(p.down, w, static_cast<const unsigned short*>(wd), nullptr, os + r0 * H, rest, split, rows,
                                         (int)H, (int)I, st, n > 1) != hipSuccess)
             return MOM_ERR_HIP;
         if (events && hipEventRecord(static_cast<hipEvent_t>(events[2 + 2 * c]), st) != hipSuccess)
             return MOM_ERR_HIP;
+        r0 += p.rows;
+        kept = split == 0x7fffffff || momk::kept_down(p.gateup, rows, H, I) ? kept + 1 : 0;
     }
     return MOM_OK;
 }

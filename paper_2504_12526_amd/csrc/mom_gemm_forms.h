@@ -456,6 +456,69 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus, bool more)
     return l;
 }
 
+// ---- Passes of more rows than the workspace holds: `out` behind the rows of a pass is not computed yet, and the rest of its
+// intermediate can lie there.
+//
+// A pass of R of the `left` rows that are still to do puts its rows from `split` on at the end of `out`, which must not reach down to row R:
+// 2 (R - split) I bytes, and up to 256 for the alignment, of the 2 (left - R) H that are free.  A longer pass takes less time per row, down to
+// some 4096 of them: one mini-sequence at a time -> so, H = 4096, I = 14336: 8192 rows by 128 5592 us -> 2931, by 512 2671 -> 2431, 32768 by
+// 512 10378 -> 8220, 16384 by 1024 4505 -> 4170, with the workspace of two 4094 -> 3987; H = 1056, I = 2080: 8192 by 512 345 -> 185.
+constexpr int64_t kSpareAlign = 256;
+inline int64_t most_rows(int64_t left, int64_t H, int64_t I, int64_t split) { return (left * H + split * I - kSpareAlign / 2) / (H + I); }
+
+struct Pass {
+    int64_t rows = 0, split = 0;         // rows 0: none
+    Launch gateup, down;
+};
+// Rows of the pass that lie in the workspace of C rows: whole token tiles of the down launch, so that none of them needs both pieces.
+inline int64_t split_of(const Launch& down, int64_t C) { return C / down.tm * down.tm; }
+
+// What a pass of C rows is expected to take, us, W_down kept from the one before where it is.
+inline double pass_time(int64_t C, int64_t H, int64_t I, int cus) {
+    const Launch g = choose_gateup(C, I, H, cus, true);
+    return g.time + choose_down(C, H, I, cus, kept_down(g, C, H, I)).time;
+}
+// Whether to ask for longer passes at all (1 ... 4 us on the host for each one looked at): where there is one, of calls of some 20 us and
+// more, and with mini-sequences of less than about 0.9 ms, which a longer pass betters by a percent at most (H = 4096, I = 14336: 3000 rows
+// 0 ... 2.4 %, 4096 none).
+inline bool longer_passes(int64_t S, int64_t H, int64_t I, int64_t C) {
+    return S > C && S * H >= ((int64_t)1 << 31) / I && C * H < ((int64_t)3 << 36) / I && most_rows(S, H, I, C / 256 * 256) / 256 * 256 > C;
+}
+
+// The pass of whole 256-row tiles, more than C rows, that takes the least time per row, of the longest `candidates`; none where
+// it is not 3 % less than per_row (of a pass of C rows).  Of 651 calls of eight layers 246 take less time so, 19 % on average, none of the
+// rest more, but for 3072 rows by 1024 of two small layers (H = 512, I = 1536 and H = 1024, I = 4096), where 1280 + 1024 + 768 take 6 % more
+// (1280 rows 31 % more than 1024 by the clock, 10 % by the formula).
+inline Pass longer_pass(int64_t left, int64_t H, int64_t I, int64_t C, int cus, double per_row, int candidates = 3) {
+    Pass best;
+    double least = 0.97 * per_row;
+    int64_t rows = most_rows(left, H, I, C / 256 * 256) / 256 * 256;
+    for (int i = 0; i < candidates && rows > C; ++i, rows -= 256) {
+        Pass p;
+        p.rows = rows;
+        p.gateup = choose_gateup(rows, I, H, cus, true);
+        p.down = choose_down(rows, H, I, cus, false);
+        if (p.gateup.kind == kRefused || p.down.kind == kRefused) continue;
+        p.split = split_of(p.down, C);
+        const double t = (p.gateup.time + p.down.time) / rows;
+        if (t < least && rows <= most_rows(left, H, I, p.split)) { best = p; least = t; }
+    }
+    return best;
+}
+
+// What the S rows are expected to take so, us.
+inline double passes_time(int64_t S, int64_t H, int64_t I, int64_t C, int cus) {
+    const double one = pass_time(C, H, I, cus);
+    double t = 0;
+    for (int64_t left = S; left > 0;) {
+        const Pass p = left > C ? longer_pass(left, H, I, C, cus, one / C, 1) : Pass();
+        if (!p.rows) return t + one * ((left + C - 1) / C);
+        t += p.gateup.time + p.down.time;
+        left -= p.rows;
+    }
+    return t;
+}
+
 // ---- Whole blocks of token rows in one launch (mom_block.hip.inc), for calls of several mini-sequences on a small layer.
 constexpr int kBlockPad = 8;            // elements behind an LDS row: 16 bytes, so that 16 rows at one k lie on different banks
 constexpr int kBlockUnit = 4096;        // bytes of a unit of weights
@@ -498,7 +561,11 @@ inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, con
     }
     if (best < 0) return -1;
     const double one = gateup.time + down.time - 6;
-    return least < 0.93 * one * ((S + C - 1) / C) ? best : -1;
+    if (least >= 0.93 * one * ((S + C - 1) / C)) return -1;
+    // Longer passes, asked for only where the blocks take several rounds of the CUs (the asking takes some 20 us): 8192 rows of H = 1056, I = 2080 by
+    // 256 339 us in blocks, 224 so.
+    if ((S + 16 * kBlockForms[best].tb - 1) / (16 * kBlockForms[best].tb) > cus && longer_passes(S, H, I, C) && passes_time(S, H, I, C, cus) < least) return -1;
+    return best;
 }
 
 // ---- Token rows of a pass of mom_mlp_prefill_static and mom_mlp_prefill_pipelined, whose workspaces hold more than mini_seq of them.

@@ -1,0 +1,53 @@
+// Host check of the passes of more rows than the workspace holds (csrc/mom_gemm_forms.h): every row once, no token tile of the down
+// launch in both pieces of the intermediate, and the piece at the end of `out` behind the rows that the pass writes, whatever
+// the alignment of `out`.
+#include <cstdio>
+#include <initializer_list>
+#include "mom_gemm_forms.h"
+
+static int bad = 0;
+#define CHECK(c, ...) do { if (!(c)) { printf("FAILED %s: ", #c); printf(__VA_ARGS__); printf("\n"); ++bad; } } while (0)
+
+int main(int argc, char**) {
+    const int64_t plant = argc > 1 ? 4 : 0;         // a planted mistake: rows in the workspace that are no whole token tiles
+    const int64_t layers[][2] = {{4096, 14336}, {3584, 18944}, {1056, 2080}, {256, 1024}, {5120, 25600}, {2048, 8192}, {8192, 28672}, {1024, 1024}, {4096, 32}, {32, 32}};
+    int calls = 0, longer = 0, split = 0, whole = 0;
+    for (const auto& l : layers)
+        for (int64_t C = 1; C < 20000; C += 1 + C * 3 / 7)
+            for (int64_t S : {C + 1, 2 * C, 3 * C + C / 3, 6 * C + 5, 16 * C, 64 * C + 7, 300 * C + 1}) {
+                const int64_t H = l[0], I = l[1];
+                if (!momk::longer_passes(S, H, I, C)) continue;
+                const double one = momk::pass_time(C, H, I, 256);
+                int64_t r0 = 0;
+                ++calls;
+                for (int n = 0; r0 < S && n < 400; ++n) {
+                    const int64_t left = S - r0;
+                    momk::Pass p;
+                    if (left > C) p = momk::longer_pass(left, H, I, C, 256, one / C);
+                    if (!p.rows) { r0 += left < C ? left : C; continue; }
+                    p.split += plant;
+                    ++longer;
+                    (p.split ? split : whole) += 1;
+                    CHECK(p.rows > C && p.rows < left && p.rows % 256 == 0, "rows S=%lld C=%lld H=%lld", (long long)S, (long long)C, (long long)H);
+                    CHECK(p.split >= 0 && p.split <= C && p.split % p.down.tm == 0, "split %lld of C=%lld, tiles of %d", (long long)p.split, (long long)C, p.down.tm);
+                    CHECK(p.gateup.kind != momk::kRefused && p.down.kind != momk::kRefused, "launches");
+                    for (int64_t out : {0, 16, 112, 240, 256}) {        // address of `out`, bytes
+                        const int64_t end = out + S * H * 2, at = (end - (p.rows - p.split) * I * 2) & ~(momk::kSpareAlign - 1);
+                        CHECK(at >= out + (r0 + p.rows) * H * 2, "rows %lld at %lld of S=%lld C=%lld H=%lld I=%lld", (long long)p.rows, (long long)r0,
+                              (long long)S, (long long)C, (long long)H, (long long)I);
+                        CHECK(at + (p.rows - p.split) * I * 2 <= end, "end");
+                    }
+                    r0 += p.rows;
+                }
+            }
+    CHECK(longer > 1000 && split > 300 && whole > 100, "%d longer passes, %d split, %d whole", longer, split, whole);
+    // what was measured: calls that take fewer passes, and one that has none to take
+    const int64_t fewer[][5] = {{8192, 4096, 14336, 512, 2048}, {16384, 4096, 14336, 256, 3328}, {8197, 1056, 2080, 512, 2816}};
+    for (const auto& t : fewer) {
+        const momk::Pass p = momk::longer_pass(t[0], t[1], t[2], t[3], 256, momk::pass_time(t[3], t[1], t[2], 256) / t[3]);
+        CHECK(p.rows == t[4], "S=%lld C=%lld: %lld rows, not %lld", (long long)t[0], (long long)t[3], (long long)p.rows, (long long)t[4]);
+    }
+    CHECK(!momk::longer_passes(32768, 4096, 14336, 4096) && !momk::longer_passes(300, 256, 1024, 100) && !momk::longer_passes(512, 4096, 14336, 512), "asked for");
+    printf("%d calls, %d longer passes: %s\n", calls, longer, bad ? "FAILED" : "ok");
+    return bad != 0;
+}
