@@ -312,11 +312,16 @@ hipError_t launch_gemm(const momk::Launch& l, const unsigned short* X, const uns
 // All S rows by blocks of form `form` (mom_gemm_forms.h).
 hipError_t launch_blocks(int form, const unsigned short* x, const unsigned short* wg, const unsigned short* wu, const unsigned short* wd,
                          unsigned short* out, int64_t S, int64_t H, int64_t I, hipStream_t st) {
+    const int cus = compute_units();
+    if (cus <= 0 || form >= momk::kBlockFormCount) return hipErrorInvalidValue;
+    const uint32_t blocks = momk::block_count(momk::kBlockForms[form], S);
+    const int share = momk::block_share(blocks, H, cus);
+    const dim3 grid(blocks, momk::block_parts(H, share));
     int i = 0;
 #define MOM_LAUNCH_BLOCK(TB, WAVES, R)                                                                            \
     if (i++ == form)                                                                                              \
-        return launch(momk::mlp_block_kernel<TB, WAVES, R>, dim3((unsigned)((S + 16 * TB - 1) / (16 * TB))), dim3(WAVES * 64),  \
-                      (size_t)momk::block_lds(16 * TB, H, I, WAVES * R), st, x, wg, wu, wd, out, (int)S, (int)H, (int)I);
+        return launch(momk::mlp_block_kernel<TB, WAVES, R>, grid, dim3(WAVES * 64), (size_t)momk::block_lds(16 * TB, H, I, WAVES * R), st,  \
+                      x, wg, wu, wd, out, (int)S, (int)H, (int)I, share);
     MOM_BLOCK_FORMS(MOM_LAUNCH_BLOCK)
 #undef MOM_LAUNCH_BLOCK
     return hipErrorInvalidValue;

@@ -537,9 +537,24 @@ constexpr BlockForm kBlockForms[] = {MOM_BLOCK_FORMS(MOM_SHAPE)};
 #undef MOM_SHAPE
 constexpr int kBlockFormCount = sizeof(kBlockForms) / sizeof(kBlockForms[0]);
 inline bool block_fits(const BlockForm& f, int64_t H, int64_t I) { return H + I <= 8192 && block_lds(16 * f.tb, H, I, f.waves * f.r) <= 163840; }
+// (32-bit arithmetic, as in tile_grid: a call of one launch is not much longer than the choice.)
+inline uint32_t block_count(const BlockForm& f, int64_t S) { return ((uint32_t)S + 16 * f.tb - 1) / (16 * (uint32_t)f.tb); }
+// Groups of 32 output columns per workgroup: where CUs are left idle, up to eight workgroups share those of a block, four groups each at least (half
+// the wavefronts have one then).  H = 256, I = 1024, 512 rows: one workgroup per block 18.3 us, two 16.8, four 16.9, eight 17.4; H = 1056, I = 2080:
+// one 174, two 142, four 129, eight 124; 1024 rows in four 133 instead of 169.
+inline int block_share(uint32_t blocks, int64_t H, int cus) {
+    const uint32_t groups = (uint32_t)H / 32;
+    if (groups <= 4 || 2 * blocks > (uint32_t)cus) return (int)groups;
+    const uint32_t spare = (uint32_t)cus / blocks, parts = spare > 8 ? 8 : spare, share = (groups + parts - 1) / parts;
+    return (int)(share > 4 ? share : 4);
+}
+inline uint32_t block_parts(int64_t H, int share) { return ((uint32_t)H / 32 + share - 1) / (uint32_t)share; }
+// With shares a microsecond per 16 rows goes to the shorter last phase (H = 256, I = 1024, 32 rows: 19.8 us in two, 18.8 without it).
 inline double block_time(const BlockForm& f, int64_t S, int64_t H, int64_t I, int cus) {
-    const int64_t blocks = (S + 16 * f.tb - 1) / (16 * f.tb);
-    return 4.0 + (double)((blocks + cus - 1) / cus) * (6.0 * H * I) / f.bytes_per_us + 1.0e-6 * S * H;
+    const uint32_t blocks = block_count(f, S);
+    const int share = block_share(blocks, H, cus);
+    const double bytes = 4.0 * H * I + 64.0 * I * share;
+    return 4.0 + (double)((blocks + cus - 1) / (uint32_t)cus) * bytes / f.bytes_per_us + 1.0e-6 * S * H + (share < H / 32 ? f.tb : 0);
 }
 
 // The form in which S token rows take less time than as mini-sequences of C of them, whose two launches are given; -1: none.  A
@@ -555,7 +570,7 @@ inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, con
     double least = 0;
     for (int i = 0; i < kBlockFormCount; ++i) {
         const BlockForm& f = kBlockForms[i];
-        if (!block_fits(f, H, I) || (S + 16 * f.tb - 1) / (16 * f.tb) * f.waves * 64 > (int64_t)0x7fffffff) continue;
+        if (!block_fits(f, H, I) || (int64_t)block_count(f, S) * f.waves * 64 > (int64_t)0x7fffffff) continue;
         const double t = block_time(f, S, H, I, cus);
         if (best < 0 || t < least) { best = i; least = t; }
     }
@@ -564,7 +579,7 @@ inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, con
     if (least >= 0.93 * one * ((S + C - 1) / C)) return -1;
     // Longer passes, asked for only where the blocks take several rounds of the CUs (the asking takes some 20 us): 8192 rows of H = 1056, I = 2080 by
     // 256 339 us in blocks, 224 so.
-    if ((S + 16 * kBlockForms[best].tb - 1) / (16 * kBlockForms[best].tb) > cus && longer_passes(S, H, I, C) && passes_time(S, H, I, C, cus) < least) return -1;
+    if (block_count(kBlockForms[best], S) > (uint32_t)cus && longer_passes(S, H, I, C) && passes_time(S, H, I, C, cus) < least) return -1;
     return best;
 }
 
