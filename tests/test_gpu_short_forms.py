@@ -85,6 +85,23 @@ def test_gate_up_form_with_non_temporal_weights(tm, tn, large_layer, short_form)
             assert torch.equal(got[1], ref[1]), f"intermediate S={S}"
 
 
+@pytest.mark.parametrize("H,I", [(96, 466080), (224, 199808), (352, 127136), (736, 60832), (1120, 40000), (4128, 10880)])
+def test_non_temporal_weights_at_every_end_of_a_group_of_stages(H, I, short_form):
+    # rows shorter than the ring, and ends in the first and in the second stage of a group, whole and shorter; weights of 256 MiB and more
+    assert 6 * H * I > 256 << 20
+    x, *w = _inputs(140, H, I, H, 0.05)
+    for S in (1, 61, 140):
+        t = (x[:S].contiguous(), *w)
+        ref = _full_tiles(*t)
+        for tm, tn in _SHAPES["GATEUP"]:
+            if S > 2 * tm:
+                continue                                        # three token tiles read plain weights
+            short_form(tm, tn)
+            got = _run(*t)
+            torch.cuda.synchronize()
+            assert torch.equal(got[1], ref[1]) and torch.equal(got[0], ref[0]), f"{tm}x{tn} S={S}"
+
+
 def test_the_second_ring_of_the_64_row_gate_up_form(large_layer, short_form):
     # chosen at these sizes, with weights by non-temporal and by plain loads (tests/gemm_forms_check.cpp says so)
     x, wg, wu, wd = large_layer
