@@ -207,8 +207,9 @@ int mom_kv_offload(const void *k, const void *v, void *pinned_host, void *stream
  * Section 3.2): the mirror of mom_kv_offload.  Asynchronous copy of bytes_each bytes from
  * `pinned_host` (host, page-locked; k at offset 0, v at offset bytes_each) into device k and v
  * on `stream`; `done_event`, if not NULL, is recorded after the last byte.  Buffers of whole 16-byte chunks (16-byte aligned, each
- * of the current device and in one allocation, k and v apart) go by one kernel that reads the host memory: 48 wavefronts
- * that find a place beside every other kernel of this library.  Everything else, and more than 256 KiB each under stream capture,
+ * of the current device and in one allocation, k and v apart) go by one kernel that reads the host memory, 48 wavefronts
+ * that find a place beside every other kernel of this library: up to 1 MiB each, and more where `stream` still has work to do when the
+ * call is made.  Everything else, and more than 256 KiB each under stream capture,
  * goes by two copies of the runtime.  Pageable host
  * memory is refused with MOM_ERR_HOST.  Ordering is the caller's: make `stream` wait for the last work that still reads the old
  * contents of k and v before this call, and make the consumers of k and v wait for `done_event`.

@@ -138,15 +138,27 @@ bool in_one_allocation(const void* p, size_t n) {
     return at <= size && n <= size - at;
 }
 
+// Whether stream st has nothing left to do.  Asked in relaxed capture mode: in another the question ends a capture that is
+// under way on any stream (hipErrorStreamCaptureUnsupported, and hipErrorStreamCaptureInvalidated at its end).
+bool is_ready(hipStream_t st) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (!answered(hipThreadExchangeStreamCaptureMode(&mode))) return true;
+    const hipError_t e = hipStreamQuery(st);
+    (void)answered(hipThreadExchangeStreamCaptureMode(&mode));
+    return e != hipErrorNotReady && (answered(e), true);         // (hipErrorNotReady is no error that the runtime keeps)
+}
+
 // The device address of pinned_host if kv_reload_kernel is to copy bytes_each bytes each into k and v on stream st, else nullptr:
-// whole 16-byte chunks, buffers of the current device, which is also the stream's, each in one allocation and not overlapping.  Of
-// any size (up to 16 GiB each, for its 32-bit chunk numbers), because the runtime's copies hold the calling thread (mom_kv.hip.inc has
-// the times); a captured call, whose copies the graph starts, takes the kernel up to 256 KiB each, where it is the faster one by itself
-// (34 -> 14 us), and beyond that the copies, which leave the CUs to the kernels beside them.
+// whole 16-byte chunks, buffers of the current device, which is also the stream's, each in one allocation and not overlapping, up to
+// 16 GiB each (its 32-bit chunk numbers).  Up to 1 MiB each the kernel is the faster one by itself (256 KiB 34 -> 14 us, 512 KiB 46 -> 34)
+// and costs the kernels beside it no more than copies do.  Larger ones do (mom_kv.hip.inc has the times), so they go by copies on a
+// stream that is ready.  Behind work that is still to be done the runtime may hold the calling thread in a copy, so there it is the kernel;
+// the question takes some 6 us then.  Captured calls, whose copies the graph starts, take the kernel up to 256 KiB each.
 const void* reload_source(const void* pinned_host, const void* k, const void* v, size_t bytes_each, hipStream_t st) {
     if (bytes_each > ((size_t)16 << 30) || bytes_each % 16 || !aligned16(pinned_host) || !aligned16(k) || !aligned16(v)) return nullptr;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (bytes_each > ((size_t)256 << 10) && (!answered(hipStreamIsCapturing(st, &capture)) || capture != hipStreamCaptureStatusNone)) return nullptr;
+    if (bytes_each > ((size_t)1 << 20) && is_ready(st)) return nullptr;
     if (overlaps(k, bytes_each, v, bytes_each)) return nullptr;
     int dev = 0, stream_dev = 0;
     if (!answered(hipGetDevice(&dev)) || (st && (!answered(hipStreamGetDevice(st, &stream_dev)) || stream_dev != dev))) return nullptr;

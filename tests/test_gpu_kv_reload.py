@@ -76,6 +76,82 @@ def test_a_large_reload_only_enqueues():
     assert torch.equal(k.cpu(), host[:n]) and torch.equal(v.cpu(), host[n:])
 
 
+def _some_work():
+    """call(): some milliseconds on the current stream."""
+    t = synth.mlp_inputs(synth.Workload("ahead", S=8192, H=2048, I=8192, mini_seq=0, seed=4), device="cuda")
+    out, ws = torch.empty_like(t[0]), torch.empty(8192 * 8192 * 2, dtype=torch.uint8, device="cuda")
+    return lambda: [binding.mom_mlp_prefill(*t, 0, out, ws) for _ in range(6)]
+
+
+def _buffers(each):
+    host = torch.randint(-32768, 32767, (each,), dtype=torch.int16).pin_memory().view(torch.bfloat16)
+    k, v = (torch.zeros(each // 2, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    torch.cuda.synchronize()
+    return host, k, v
+
+
+def _assert_bytes(host, k, v):
+    torch.cuda.synchronize()
+    assert torch.equal(torch.cat([k, v]).view(torch.int16).cpu(), host.view(torch.int16))
+
+
+def test_what_an_eager_reload_takes():
+    """The kernel up to 1 MiB each and behind work that is still to be done; copies, which take nothing from the kernels beside them, on a
+    stream that is ready."""
+    from torch.profiler import ProfilerActivity, profile
+    work, side = _some_work(), torch.cuda.Stream()
+    cases = [(each, behind) for each in (16, 1 << 20, (1 << 20) + 16, 16 << 20) for behind in (False, True)]
+    buffers = {each: _buffers(each) for each, _ in cases}
+    taken = []
+    for each, behind in cases:
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            if behind:
+                work()
+                side.wait_stream(torch.cuda.current_stream())
+            binding.mom_kv_reload(*buffers[each], side)
+            torch.cuda.synchronize()
+        names = [e.name for e in p.events()]
+        taken.append((any("kv_reload_kernel" in n for n in names), any("Memcpy HtoD" in n for n in names)))
+        _assert_bytes(*buffers[each])
+    for (each, behind), (kernel, copies) in zip(cases, taken):
+        assert (kernel, copies) == ((True, False) if each <= 1 << 20 or behind else (False, True)), f"{each} bytes each, behind work: {behind}"
+
+
+@pytest.mark.parametrize("behind", [False, True])
+@pytest.mark.parametrize("each", [4096, 512 << 10, 4 << 20])
+def test_a_capture_on_another_stream_goes_on(each, behind):
+    runtime, vp = hip(), ctypes.c_void_p
+    work, side, captured = _some_work(), torch.cuda.Stream(), torch.cuda.Stream()
+    buffers, graph, mode = _buffers(each), vp(), ctypes.c_int(-1)
+    if behind:
+        work()
+        side.wait_stream(torch.cuda.current_stream())
+    assert runtime.hipStreamBeginCapture(vp(captured.cuda_stream), 0) == 0           # global: no call that it forbids, on any stream
+    rc = binding.mom_kv_reload(*buffers, side, check=False)
+    end = runtime.hipStreamEndCapture(vp(captured.cuda_stream), ctypes.byref(graph))
+    assert (rc, end) == (binding.MOM_OK, 0)
+    assert runtime.hipGraphDestroy(graph) == 0
+    mode.value = 2
+    assert runtime.hipThreadExchangeStreamCaptureMode(ctypes.byref(mode)) == 0
+    was, back = mode.value, ctypes.c_int(mode.value)
+    assert runtime.hipThreadExchangeStreamCaptureMode(ctypes.byref(back)) == 0 and was == 0       # the thread's mode is what it was
+    _assert_bytes(*buffers)
+
+
+def test_an_error_of_the_program_stays_behind_work():
+    runtime, work, side = hip(), _some_work(), torch.cuda.Stream()
+    buffers = _buffers(4 << 20)
+    work()
+    side.wait_stream(torch.cuda.current_stream())
+    error = runtime.hipSetDevice(12345)
+    assert error != 0 and runtime.hipPeekAtLastError() == error
+    rc = binding.mom_kv_reload(*buffers, side, check=False)
+    left = runtime.hipGetLastError()
+    assert rc == binding.MOM_OK and left == error
+    _assert_bytes(*buffers)
+
+
 def test_overlapping_buffers_are_copied_one_after_the_other():
     host = torch.randint(-32768, 32767, (2 * 4096,), dtype=torch.int16).pin_memory()
     buf = torch.zeros(4096 + 64, dtype=torch.int16, device="cuda")
