@@ -50,7 +50,7 @@ const char *mom_status_string(int status);
 /*
  * Optional set-up for the current HIP device: looks up what the other calls otherwise look up
  * on their first use on a device (the compute-unit count, the device address of the static
- * workspace of mom_mlp_prefill_static), so that those calls make no runtime query afterwards.
+ * workspace of mom_mlp_prefill_static), so that those calls need not look it up afterwards.
  * Call it once per device, with that device current, e.g. before a stream capture.  Returns
  * MOM_ERR_HIP when there is no usable device.
  */
@@ -73,7 +73,8 @@ size_t mom_mlp_workspace_bytes(int64_t S, int64_t H, int64_t I, int64_t mini_seq
  * written to `workspace` and consumed before the next one overwrites it, and its
  * output rows land directly at their place in `out` (the concat).  Several mini-sequences go through as one
  * where that takes less time and the rest of their intermediate has room in the rows of `out` that are still to
- * come: until the call is done those rows may hold anything, and nothing beside `workspace` and `out` is written.
+ * come, which has to be memory of the current device then: until the call is done those rows may hold anything, and
+ * nothing beside `workspace` and `out` is written.
  *
  *   x        [S,H] bf16      in
  *   W_gate   [I,H] bf16      in

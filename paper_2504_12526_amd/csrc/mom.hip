@@ -148,6 +148,13 @@ bool is_ready(hipStream_t st) {
     return e != hipErrorNotReady && (answered(e), true);         // (hipErrorNotReady is no error that the runtime keeps)
 }
 
+// Whether p is memory of the current device.
+bool on_current_device(const void* p) {
+    int dev = 0;
+    hipPointerAttribute_t at;
+    return answered(hipGetDevice(&dev)) && answered(hipPointerGetAttributes(&at, p)) && at.type == hipMemoryTypeDevice && at.device == dev;
+}
+
 // The device address of pinned_host if kv_reload_kernel is to copy bytes_each bytes each into k and v on stream st, else nullptr:
 // whole 16-byte chunks, buffers of the current device, which is also the stream's, each in one allocation and not overlapping, up to
 // 16 GiB each (its 32-bit chunk numbers).  Up to 1 MiB each the kernel is the faster one by itself (256 KiB 34 -> 14 us, 512 KiB 46 -> 34)
@@ -339,8 +346,8 @@ hipError_t launch_blocks(int form, const unsigned short* x, const unsigned short
     return hipErrorInvalidValue;
 }
 
-// The form of launch_blocks for a call whose mini-sequences of C rows would take the launches given, or -1.
-int block_form(int64_t S, int64_t H, int64_t I, int64_t C, const momk::Launch& gateup, const momk::Launch& down) {
+// The form of launch_blocks for a call whose mini-sequences of C rows would take the launches given, or -1.  longer: or longer passes.
+int block_form(int64_t S, int64_t H, int64_t I, int64_t C, const momk::Launch& gateup, const momk::Launch& down, bool longer) {
     const int forced = g_force_block.load(std::memory_order_relaxed);
     if (forced) {
         for (int i = 0; i < momk::kBlockFormCount; ++i)
@@ -351,7 +358,7 @@ int block_form(int64_t S, int64_t H, int64_t I, int64_t C, const momk::Launch& g
         g_force_rect.load(std::memory_order_relaxed))
         return -1;
     const int cus = compute_units();
-    return cus > 0 ? momk::choose_block(S, H, I, C, cus, gateup, down) : -1;
+    return cus > 0 ? momk::choose_block(S, H, I, C, cus, gateup, down, longer) : -1;
 }
 
 template <int MODE>
@@ -398,8 +405,11 @@ int mlp_loop(const void* x, const void* wg, const void* wu, const void* wd, int6
     if (events && hipEventRecord(static_cast<hipEvent_t>(events[0]), st) != hipSuccess) return MOM_ERR_HIP;
     int planned = (int)C;                // token rows that `gateup` and `down` are for
     momk::Launch gateup = gateup_launch(C, H, I, n > 1), down = down_launch(C, H, I, gateup, 0);
+    // Passes of several mini-sequences keep part of the intermediate in `out`, which then has to be memory of this device: in page-locked
+    // host memory or a peer's, which `out` may also be, every column tile would read it through a link.
+    const bool longer = !events && momk::longer_passes(S, H, I, C) && on_current_device(out);
     if (!events) {
-        const int form = block_form(S, H, I, C, gateup, down);
+        const int form = block_form(S, H, I, C, gateup, down, longer);
         if (form >= 0)
             return launch_blocks(form, xs, static_cast<const unsigned short*>(wg), static_cast<const unsigned short*>(wu),
                                  static_cast<const unsigned short*>(wd), os, S, H, I, st) == hipSuccess ? MOM_OK : MOM_ERR_HIP;
@@ -407,13 +417,12 @@ int mlp_loop(const void* x, const void* wg, const void* wu, const void* wd, int6
     // Algorithm 1, else-branch: O_i = MLP(A_i) for each mini-sequence, O_i written at its rows of O; several of them as one pass where the
     // rows of O that are still to come have room for the rest of the intermediate.
     const int cus = compute_units();
-    bool longer = !events && cus > 0 && momk::longer_passes(S, H, I, C);
-    const double per_row = longer ? momk::pass_time(C, H, I, cus) / C : 0;
+    const double per_row = longer && cus > 0 ? momk::pass_time(C, H, I, cus) / C : 0;
     int64_t kept = 0;                    // passes since the last that displaced W_down
     int64_t c = 0;
     for (int64_t r0 = 0; r0 < S; ++c) {
         momk::Pass p;
-        if (longer && S - r0 > C) p = next_longer_pass(S - r0, H, I, C, cus, per_row);
+        if (per_row > 0 && S - r0 > C) p = next_longer_pass(S - r0, H, I, C, cus, per_row);
         unsigned short* rest = nullptr;
         if (p.rows) {
             const uintptr_t end = reinterpret_cast<uintptr_t>(os + S * H), at = (end - (size_t)(p.rows - p.split) * I * 2) & ~(uintptr_t)(momk::kSpareAlign - 1);

@@ -557,14 +557,14 @@ inline double block_time(const BlockForm& f, int64_t S, int64_t H, int64_t I, in
     return 4.0 + (double)((blocks + cus - 1) / (uint32_t)cus) * bytes / f.bytes_per_us + 1.0e-6 * S * H + (share < H / 32 ? f.tb : 0);
 }
 
-// The form in which S token rows take less time than as mini-sequences of C of them, whose two launches are given; -1: none.  A
+// The form in which S token rows take less time than as mini-sequences of C of them, whose two launches are given; -1: none.  longer: or as longer passes.  A
 // mini-sequence takes 6 us less than the launches by themselves (H = 256, I = 1024: 128 rows 7.0 us, 512 8.0, 2048 11.0, formula
 // 13.1, 14.2, 17.2; H = 1056, I = 2080: 128 rows 12.3, formula 18.1; where both are longer, 512 rows 21.5 and 24.7, the loop
 // looks better than it is).  7 % off that: 2048 rows by 1024 of the former 17.2 us, formula 18.9, as blocks 18.7.  Up to 24576 rows
 // by mini-sequence: 40000 rows by 18022 take 104 us in blocks, 118 as mini-sequences, but 66000 by 26214 185 and 178, 34000 by 32440 102
 // and 92, which the formula overrates.
 constexpr int64_t kBlockLongest = 24576;
-inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, const Launch& gateup, const Launch& down) {
+inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, const Launch& gateup, const Launch& down, bool longer = true) {
     if (S <= C || C > kBlockLongest || !small_layer(I, H)) return -1;
     int best = -1;
     double least = 0;
@@ -579,7 +579,7 @@ inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, con
     if (least >= 0.93 * one * ((S + C - 1) / C)) return -1;
     // Longer passes, asked for only where the blocks take several rounds of the CUs (the asking takes some 20 us): 8192 rows of H = 1056, I = 2080 by
     // 256 339 us in blocks, 224 so.
-    if (block_count(kBlockForms[best], S) > (uint32_t)cus && longer_passes(S, H, I, C) && passes_time(S, H, I, C, cus) < least) return -1;
+    if (longer && block_count(kBlockForms[best], S) > (uint32_t)cus && longer_passes(S, H, I, C) && passes_time(S, H, I, C, cus) < least) return -1;
     return best;
 }
 

@@ -80,6 +80,25 @@ def test_bits_and_what_is_written(S, H, I, C, offset):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("S,H,I,C", [(3001, 1056, 2080, 512), (12000, 1056, 2080, 256), (3000, 2048, 8192, 256)])
+def test_out_in_host_memory_holds_results_only(S, H, I, C):
+    """... which would go through the link for every column tile: as many launches as mini-sequences take."""
+    from graph_nodes import KERNEL, node_types
+    t, ref, _, device_out, ws = _case(S, H, I, C)
+    out = torch.zeros((S, H), dtype=torch.bfloat16, pin_memory=True)
+
+    def nodes(out):
+        return node_types(lambda stream: binding.mom_mlp_prefill(*t, C, out, ws[:C * I], stream=stream))
+
+    assert len(nodes(device_out)) < 2 * -(-S // C)                 # where it is the device's, longer passes or blocks
+    blocks = nodes(out) == [KERNEL]                                # (these hold nothing there either)
+    assert blocks or nodes(out) == [KERNEL] * (2 * -(-S // C))
+    binding.mom_mlp_prefill(*t, C, out, ws[:C * I])
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), ref.cpu())
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("form", [("gemm", 256, 5, 224), ("gemm", 256, 5, 160), ("gemm", 128, 0, 0), ("rect", 192, 256), ("rect", 160, 160), ("rect", 224, 160),
                                   ("short", 96, 64), ("short", 160, 128), ("short", 48, 32), ("short", 80, 64)])
 def test_pieces_in_every_kind_of_tile(form):
