@@ -278,22 +278,6 @@ momk::Launch forced_launch(int64_t M, int64_t N, bool gateup) {
     return {momk::kRefused, -1, 0, 0, 0, {}, {}};
 }
 
-// What runs for M token rows of a layer (mom_gemm_forms.h).  more: the call has more than one mini-sequence.
-momk::Launch gateup_launch(int64_t M, int64_t H, int64_t I, bool more) {
-    const int cus = compute_units();
-    if (cus <= 0) return {momk::kRefused, -1, 0, 0, 0, {}, {}};
-    const momk::Launch l = forced_launch(M, I, true);
-    return l.form >= 0 ? l : momk::choose_gateup(M, I, H, cus, more);
-}
-
-// ... behind the gate/up launch of mini-sequence c.
-momk::Launch down_launch(int64_t M, int64_t H, int64_t I, const momk::Launch& gateup, int64_t c) {
-    const int cus = compute_units();
-    if (cus <= 0) return {momk::kRefused, -1, 0, 0, 0, {}, {}};
-    const momk::Launch l = forced_launch(M, H, false);
-    return l.form >= 0 ? l : momk::choose_down(M, H, I, cus, c >= momk::kKeptFrom && momk::kept_down(gateup, M, H, I));
-}
-
 // O[m, n] of M token rows x N output columns by launch l, the intermediate from row `split` on at `rest` (GemmArgs).  more: the call has more
 // than one mini-sequence.
 template <int EPI>
@@ -381,16 +365,15 @@ hipError_t launch_gemv(const unsigned short* x, const unsigned short* Wa, const 
                   x, Wa, Wb, y, (int)R, (int)K);
 }
 
-// The next pass of more than C of the `left` rows, with the launches that are forced, if any.
-momk::Pass next_longer_pass(int64_t left, int64_t H, int64_t I, int64_t C, int cus, double per_row) {
-    momk::Pass p = momk::longer_pass(left, H, I, C, cus, per_row);
-    if (!p.rows) return p;
+// p, the next pass of `passes`, with the launches that are forced, if any, and its rows where these want them.
+momk::Pass as_forced(momk::Pass p, const momk::Passes& passes, int64_t H, int64_t I, int64_t C) {
     const momk::Launch g = forced_launch(p.rows, I, true), d = forced_launch(p.rows, H, false);
     if (g.form >= 0) p.gateup = g;
     if (d.form >= 0) p.down = d;
+    if (p.split == momk::kWhole) return p;
     p.split = momk::split_of(p.down, C);
-    if (p.gateup.kind == momk::kRefused || p.down.kind == momk::kRefused || p.rows > momk::most_rows(left, H, I, p.split)) p.rows = 0;
-    return p;
+    if (p.gateup.kind != momk::kRefused && p.down.kind != momk::kRefused && p.rows <= momk::most_rows(passes.left, H, I, p.split)) return p;
+    return as_forced(passes.plain(), passes, H, I, C);          // no room
 }
 
 // The loop over mini-sequences of C rows on one stream.  The arguments have been validated for a workspace of C x I.
@@ -403,41 +386,30 @@ int mlp_loop(const void* x, const void* wg, const void* wu, const void* wd, int6
     unsigned short* os = static_cast<unsigned short*>(out);
     unsigned short* w = static_cast<unsigned short*>(ws);
     if (events && hipEventRecord(static_cast<hipEvent_t>(events[0]), st) != hipSuccess) return MOM_ERR_HIP;
-    int planned = (int)C;                // token rows that `gateup` and `down` are for
-    momk::Launch gateup = gateup_launch(C, H, I, n > 1), down = down_launch(C, H, I, gateup, 0);
+    const int cus = compute_units();
+    if (cus <= 0) return MOM_ERR_HIP;
     // Passes of several mini-sequences keep part of the intermediate in `out`, which then has to be memory of this device: in page-locked
     // host memory or a peer's, which `out` may also be, every column tile would read it through a link.
     const bool longer = !events && momk::longer_passes(S, H, I, C) && on_current_device(out);
+    momk::Passes passes(S, H, I, C, cus, longer);
     if (!events) {
-        const int form = block_form(S, H, I, C, gateup, down, longer);
+        const momk::Pass p = passes.plain();
+        const int form = block_form(S, H, I, C, p.gateup, p.down, longer);
         if (form >= 0)
             return launch_blocks(form, xs, static_cast<const unsigned short*>(wg), static_cast<const unsigned short*>(wu),
                                  static_cast<const unsigned short*>(wd), os, S, H, I, st) == hipSuccess ? MOM_OK : MOM_ERR_HIP;
     }
     // Algorithm 1, else-branch: O_i = MLP(A_i) for each mini-sequence, O_i written at its rows of O; several of them as one pass where the
     // rows of O that are still to come have room for the rest of the intermediate.
-    const int cus = compute_units();
-    const double per_row = longer && cus > 0 ? momk::pass_time(C, H, I, cus) / C : 0;
-    int64_t kept = 0;                    // passes since the last that displaced W_down
     int64_t c = 0;
     for (int64_t r0 = 0; r0 < S; ++c) {
-        momk::Pass p;
-        if (per_row > 0 && S - r0 > C) p = next_longer_pass(S - r0, H, I, C, cus, per_row);
+        const momk::Pass p = as_forced(passes.next(), passes, H, I, C);
+        const int rows = (int)p.rows, split = (int)p.split;
         unsigned short* rest = nullptr;
-        if (p.rows) {
+        if (p.split != momk::kWhole) {
             const uintptr_t end = reinterpret_cast<uintptr_t>(os + S * H), at = (end - (size_t)(p.rows - p.split) * I * 2) & ~(uintptr_t)(momk::kSpareAlign - 1);
             rest = reinterpret_cast<unsigned short*>(at - (size_t)p.split * I * 2);
-            planned = -1;
-        } else {
-            p.rows = r0 + C <= S ? C : S - r0;
-            p.split = 0x7fffffff;
-            if (p.rows != planned) gateup = gateup_launch(p.rows, H, I, n > 1);
-            if (p.rows != planned || kept == momk::kKeptFrom) down = down_launch(p.rows, H, I, gateup, kept);
-            planned = (int)p.rows;
-            p.gateup = gateup;
-            p.down = down;
         }
-        const int rows = (int)p.rows, split = (int)p.split;
         if (launch_gemm<momk::EPI_GATEUP>(p.gateup, xs + r0 * H, static_cast<const unsigned short*>(wg),
                                           static_cast<const unsigned short*>(wu), w, rest, split, rows, (int)I, (int)H,
                                           st, n > 1) != hipSuccess)
@@ -450,7 +422,7 @@ int mlp_loop(const void* x, const void* wg, const void* wu, const void* wd, int6
         if (events && hipEventRecord(static_cast<hipEvent_t>(events[2 + 2 * c]), st) != hipSuccess)
             return MOM_ERR_HIP;
         r0 += p.rows;
-        kept = split == 0x7fffffff || momk::kept_down(p.gateup, rows, H, I) ? kept + 1 : 0;
+        passes.done(p);
     }
     return MOM_OK;
 }

@@ -466,18 +466,15 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus, bool more)
 constexpr int64_t kSpareAlign = 256;
 inline int64_t most_rows(int64_t left, int64_t H, int64_t I, int64_t split) { return (left * H + split * I - kSpareAlign / 2) / (H + I); }
 
+constexpr int64_t kWhole = 0x7fffffff;
 struct Pass {
-    int64_t rows = 0, split = 0;         // rows 0: none
+    int64_t rows = 0, split = 0;         // rows 0: none; split kWhole: all rows lie in the workspace
     Launch gateup, down;
+    double time() const { return gateup.time + down.time; }
 };
 // Rows of the pass that lie in the workspace of C rows: whole token tiles of the down launch, so that none of them needs both pieces.
 inline int64_t split_of(const Launch& down, int64_t C) { return C / down.tm * down.tm; }
 
-// What a pass of C rows is expected to take, us, W_down kept from the one before where it is.
-inline double pass_time(int64_t C, int64_t H, int64_t I, int cus) {
-    const Launch g = choose_gateup(C, I, H, cus, true);
-    return g.time + choose_down(C, H, I, cus, kept_down(g, C, H, I)).time;
-}
 // Whether to ask for longer passes at all (1 ... 4 us on the host for each one looked at): where there is one, of calls of some 20 us and
 // more, and with mini-sequences of less than about 0.9 ms, which a longer pass betters by a percent at most (H = 4096, I = 14336: 3000 rows
 // 0 ... 2.4 %, 4096 none).
@@ -485,38 +482,97 @@ inline bool longer_passes(int64_t S, int64_t H, int64_t I, int64_t C) {
     return S > C && S * H >= ((int64_t)1 << 31) / I && C * H < ((int64_t)3 << 36) / I && most_rows(S, H, I, C / 256 * 256) / 256 * 256 > C;
 }
 
-// The pass of whole 256-row tiles, more than C rows, that takes the least time per row, of the longest `candidates`; none where
-// it is not 3 % less than per_row (of a pass of C rows).  Of 651 calls of eight layers 246 take less time so, 19 % on average, none of the
+// The passes of a call of S rows with a workspace for C of them, one after the other: what the driver runs, and what is weighed against
+// blocks.  Passes of C rows (or what is left), and longer ones, if `longer` and longer_passes say so.
+class Passes {
+public:
+    int64_t left;                        // rows still to do
+
+    Passes(int64_t S, int64_t H, int64_t I, int64_t C, int cus, bool longer)
+        : left(S), H(H), I(I), C(C), cus(cus), more_(S > C), longer_(longer && longer_passes(S, H, I, C)) {
+        gateup_ = choose_gateup(C, I, H, cus, more_);
+        down_ = choose_down(C, H, I, cus, false);
+        kept_ = S > kKeptFrom * C && !small_layer(I, H) && kept_down(gateup_, C, H, I) ? choose_down(C, H, I, cus, true) : down_;
+    }
+    // The next pass, and the next as long as the workspace.
+    Pass next() const {
+        const Pass p = has_room() ? longer_pass() : Pass();
+        return p.rows ? p : plain();
+    }
+    Pass plain() const { return of_rows(left < C ? left : C, since_); }
+    // Go on behind p (next or plain, its launches may be others of the same rows).
+    void done(const Pass& p) {
+        left -= p.rows;
+        since_ = p.split == kWhole || kept_down(p.gateup, p.rows, H, I) ? since_ + 1 : 0;
+    }
+    // What all that is left is expected to take, us.
+    double time() const { return time_to(kAll); }
+    // Whether that is less than `limit`: known as soon as the rest would be so without longer passes, or, since shorter passes take more
+    // time per row, reaches the limit at 0.9 of the last one's.  That is mostly behind the first; all would take 20 ... 100 us on the host.
+    bool take_less_than(double limit) const { return time_to(limit) < limit; }
+
+private:
+    static constexpr double kAll = 1e30;
+    Pass of_rows(int64_t rows, int64_t since) const {
+        Pass p;
+        p.rows = rows;
+        p.split = kWhole;
+        if (rows == C) {
+            p.gateup = gateup_;
+            p.down = since >= kKeptFrom ? kept_ : down_;
+        } else {
+            p.gateup = choose_gateup(rows, I, H, cus, more_);
+            p.down = choose_down(rows, H, I, cus, since >= kKeptFrom && kept_down(p.gateup, rows, H, I));
+        }
+        return p;
+    }
+    // `rows` of them without longer passes, behind `since` that kept W_down.
+    double plain_time(int64_t rows, int64_t since) const {
+        const int64_t n = rows / C, cold = since >= kKeptFrom ? 0 : n < kKeptFrom - since ? n : kKeptFrom - since, rest = rows % C;
+        return cold * (gateup_.time + down_.time) + (n - cold) * (gateup_.time + kept_.time) + (rest ? of_rows(rest, since + n).time() : 0);
+    }
+    double time_to(double limit) const {
+        Passes then = *this;
+        double t = 0;
+        while (then.has_room()) {
+            const Pass p = then.next();
+            t += p.time();
+            then.done(p);
+            if (t + 0.9 * p.time() / p.rows * then.left >= limit) return limit;
+            if (limit < kAll && t + then.plain_time(then.left, then.since_) < limit) break;
+        }
+        return t + then.plain_time(then.left, then.since_);
+    }
+    bool has_room() const { return longer_ && longest() > C; }
+    int64_t longest() const { return most_rows(left, H, I, C / 256 * 256) / 256 * 256; }
+    Pass longer_pass() const;
+
+    int64_t H, I, C;
+    int cus;
+    bool more_, longer_;                 // more: the call has more than one mini-sequence
+    int64_t since_ = 0;                  // passes since the last that displaced W_down
+    Launch gateup_, down_, kept_;        // of C rows; kept: with W_down in the Infinity Cache, where it stays there
+};
+
+// The pass of whole 256-row tiles, more than C rows, that takes the least time per row, of the three longest; none where
+// it is not 3 % less than in a pass of C rows.  Of 651 calls of eight layers 246 take less time so, 19 % on average, none of the
 // rest more, but for 3072 rows by 1024 of two small layers (H = 512, I = 1536 and H = 1024, I = 4096), where 1280 + 1024 + 768 take 6 % more
 // (1280 rows 31 % more than 1024 by the clock, 10 % by the formula).
-inline Pass longer_pass(int64_t left, int64_t H, int64_t I, int64_t C, int cus, double per_row, int candidates = 3) {
+inline Pass Passes::longer_pass() const {
     Pass best;
-    double least = 0.97 * per_row;
-    int64_t rows = most_rows(left, H, I, C / 256 * 256) / 256 * 256;
-    for (int i = 0; i < candidates && rows > C; ++i, rows -= 256) {
+    double least = 0.97 * (gateup_.time + kept_.time) / C;
+    int64_t rows = longest();
+    for (int i = 0; i < 3 && rows > C; ++i, rows -= 256) {
         Pass p;
         p.rows = rows;
         p.gateup = choose_gateup(rows, I, H, cus, true);
         p.down = choose_down(rows, H, I, cus, false);
         if (p.gateup.kind == kRefused || p.down.kind == kRefused) continue;
         p.split = split_of(p.down, C);
-        const double t = (p.gateup.time + p.down.time) / rows;
+        const double t = p.time() / rows;
         if (t < least && rows <= most_rows(left, H, I, p.split)) { best = p; least = t; }
     }
     return best;
-}
-
-// What the S rows are expected to take so, us.
-inline double passes_time(int64_t S, int64_t H, int64_t I, int64_t C, int cus) {
-    const double one = pass_time(C, H, I, cus);
-    double t = 0;
-    for (int64_t left = S; left > 0;) {
-        const Pass p = left > C ? longer_pass(left, H, I, C, cus, one / C, 1) : Pass();
-        if (!p.rows) return t + one * ((left + C - 1) / C);
-        t += p.gateup.time + p.down.time;
-        left -= p.rows;
-    }
-    return t;
 }
 
 // ---- Whole blocks of token rows in one launch (mom_block.hip.inc), for calls of several mini-sequences on a small layer.
@@ -577,9 +633,9 @@ inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, con
     if (best < 0) return -1;
     const double one = gateup.time + down.time - 6;
     if (least >= 0.93 * one * ((S + C - 1) / C)) return -1;
-    // Longer passes, asked for only where the blocks take several rounds of the CUs (the asking takes some 20 us): 8192 rows of H = 1056, I = 2080 by
-    // 256 339 us in blocks, 224 so.
-    if (longer && block_count(kBlockForms[best], S) > (uint32_t)cus && longer_passes(S, H, I, C) && passes_time(S, H, I, C, cus) < least) return -1;
+    // Longer passes, asked for only where the blocks take several rounds of the CUs: 8192 rows of H = 1056, I = 2080 by 256 339 us in
+    // blocks, 224 so.
+    if (longer && block_count(kBlockForms[best], S) > (uint32_t)cus && longer_passes(S, H, I, C) && Passes(S, H, I, C, cus, true).take_less_than(least)) return -1;
     return best;
 }
 

@@ -17,14 +17,15 @@ int main(int argc, char**) {
             for (int64_t S : {C + 1, 2 * C, 3 * C + C / 3, 6 * C + 5, 16 * C, 64 * C + 7, 300 * C + 1}) {
                 const int64_t H = l[0], I = l[1];
                 if (!momk::longer_passes(S, H, I, C)) continue;
-                const double one = momk::pass_time(C, H, I, 256);
+                momk::Passes passes(S, H, I, C, 256, true);
                 int64_t r0 = 0;
                 ++calls;
                 for (int n = 0; r0 < S && n < 400; ++n) {
                     const int64_t left = S - r0;
-                    momk::Pass p;
-                    if (left > C) p = momk::longer_pass(left, H, I, C, 256, one / C);
-                    if (!p.rows) { r0 += left < C ? left : C; continue; }
+                    momk::Pass p = passes.next();
+                    CHECK(passes.left == left && p.rows > 0 && p.rows <= left, "left");
+                    passes.done(p);
+                    if (p.split == momk::kWhole) { CHECK(p.rows == (left < C ? left : C), "rows"); r0 += p.rows; continue; }
                     p.split += plant;
                     ++longer;
                     (p.split ? split : whole) += 1;
@@ -44,10 +45,28 @@ int main(int argc, char**) {
     // what was measured: calls that take fewer passes, and one that has none to take
     const int64_t fewer[][5] = {{8192, 4096, 14336, 512, 2048}, {16384, 4096, 14336, 256, 3328}, {8197, 1056, 2080, 512, 2816}};
     for (const auto& t : fewer) {
-        const momk::Pass p = momk::longer_pass(t[0], t[1], t[2], t[3], 256, momk::pass_time(t[3], t[1], t[2], 256) / t[3]);
+        const momk::Pass p = momk::Passes(t[0], t[1], t[2], t[3], 256, true).next();
         CHECK(p.rows == t[4], "S=%lld C=%lld: %lld rows, not %lld", (long long)t[0], (long long)t[3], (long long)p.rows, (long long)t[4]);
     }
     CHECK(!momk::longer_passes(32768, 4096, 14336, 4096) && !momk::longer_passes(300, 256, 1024, 100) && !momk::longer_passes(512, 4096, 14336, 512), "asked for");
+    // What blocks are weighed against is what the driver runs: calls in blocks of several rounds of the CUs take no more than its passes would.
+    int blocks = 0, instead = 0;
+    for (int64_t C : {128, 181, 256, 300, 512, 1024})
+        for (int64_t S = 4100; S < 24000; S += 37) {
+            const int64_t H = 1056, I = 2080;
+            momk::Passes passes(S, H, I, C, 256, true);
+            const momk::Pass p = passes.plain();
+            const double expected = passes.time();
+            double t = 0;
+            while (passes.left > 0) { const momk::Pass q = passes.next(); t += q.time(); passes.done(q); }
+            CHECK(t > 0.9999 * expected && t < 1.0001 * expected, "S=%lld C=%lld: %.1f us, by pass %.1f", (long long)S, (long long)C, expected, t);
+            const int form = momk::choose_block(S, H, I, C, 256, p.gateup, p.down);
+            if (form < 0) { ++instead; continue; }
+            ++blocks;
+            const double b = momk::block_time(momk::kBlockForms[form], S, H, I, 256);
+            CHECK(b <= 1.02 * t || momk::block_count(momk::kBlockForms[form], S) <= 256, "S=%lld C=%lld in blocks: %.1f us, passes %.1f", (long long)S, (long long)C, b, t);
+        }
+    CHECK(instead > 1000, "%d calls in blocks, %d in passes", blocks, instead);
     printf("%d calls, %d longer passes: %s\n", calls, longer, bad ? "FAILED" : "ok");
     return bad != 0;
 }

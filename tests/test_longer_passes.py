@@ -29,6 +29,7 @@ def test_rows_and_places(tmp_path):
     ("return C / down.tm * down.tm;", "return C;", "split"),                                    # a token tile of the down launch in both pieces
     ("- kSpareAlign / 2) / (H + I)", ") / (H + I)", "rows "),                                   # no room for the alignment
     ("if (t < least && rows <= most_rows(left, H, I, p.split))", "if (t < least)", "rows "),      # room counted for more rows in the workspace
+    ("if (t + 0.9 * p.time()", "if (t + 3.0 * p.time()", "in blocks"),                           # longer passes given up too early
 ])
 def test_a_planted_mistake_is_caught(tmp_path, old, new, says):
     text = open(os.path.join(CSRC, "mom_gemm_forms.h")).read()
