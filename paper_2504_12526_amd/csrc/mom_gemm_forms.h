@@ -495,14 +495,21 @@ public:
         kept_ = S > kKeptFrom * C && !small_layer(I, H) && kept_down(gateup_, C, H, I) ? choose_down(C, H, I, cus, true) : down_;
     }
     // The next pass, and the next as long as the workspace.
-    Pass next() const {
+    Pass next() {
         const Pass p = has_room() ? longer_pass() : Pass();
-        return p.rows ? p : plain();
+        if (!p.rows) return plain();
+        // Where the first saves no two passes, longer ones are weighed against none; where they save too little, none are looked for again.
+        if (!taken_ && p.rows < 2 * C && !they_save_time(p)) {
+            longer_ = false;
+            return plain();
+        }
+        return p;
     }
     Pass plain() const { return of_rows(left < C ? left : C, since_); }
     // Go on behind p (next or plain, its launches may be others of the same rows).
     void done(const Pass& p) {
         left -= p.rows;
+        taken_ |= p.split != kWhole;
         since_ = p.split == kWhole || kept_down(p.gateup, p.rows, H, I) ? since_ + 1 : 0;
     }
     // What all that is left is expected to take, us.
@@ -546,18 +553,17 @@ private:
     bool has_room() const { return longer_ && longest() > C; }
     int64_t longest() const { return most_rows(left, H, I, C / 256 * 256) / 256 * 256; }
     Pass longer_pass() const;
+    bool they_save_time(const Pass& first) const;
 
     int64_t H, I, C;
     int cus;
-    bool more_, longer_;                 // more: the call has more than one mini-sequence
+    bool more_, longer_, taken_ = false; // more: the call has more than one mini-sequence; taken: one of its passes was longer
     int64_t since_ = 0;                  // passes since the last that displaced W_down
     Launch gateup_, down_, kept_;        // of C rows; kept: with W_down in the Infinity Cache, where it stays there
 };
 
 // The pass of whole 256-row tiles, more than C rows, that takes the least time per row, of the three longest; none where
-// it is not 3 % less than in a pass of C rows.  Of 651 calls of eight layers 246 take less time so, 19 % on average, none of the
-// rest more, but for 3072 rows by 1024 of two small layers (H = 512, I = 1536 and H = 1024, I = 4096), where 1280 + 1024 + 768 take 6 % more
-// (1280 rows 31 % more than 1024 by the clock, 10 % by the formula).
+// it is not 3 % less than in a pass of C rows.  Of 651 calls of eight layers 246 take less time so, 19 % on average.
 inline Pass Passes::longer_pass() const {
     Pass best;
     double least = 0.97 * (gateup_.time + kept_.time) / C;
@@ -573,6 +579,29 @@ inline Pass Passes::longer_pass() const {
         if (t < least && rows <= most_rows(left, H, I, p.split)) { best = p; least = t; }
     }
     return best;
+}
+
+// Whether the whole call takes less time with longer passes, `first` the first of them.  They leave another last pass behind: 3072 rows
+// of H = 512, I = 1536 by 1024 went as 1280 + 1024 + 768 in 46.6 us, as three of 1024 take 44.1, and 7471 by 2500 as 3584 + 2500 + 1387
+// in 67.9, 62.0 as mini-sequences.  With as many passes they have to save 1 % of all, less than which the formula does not
+// tell (its error is 5 ... 8 % of a launch); with fewer, anything, and a pass counts 5 us less than its launches by themselves, which is what they
+// take less one behind the other in layers that the Infinity Cache holds (measured 4 ... 8).  Of 1785 calls of eleven layers 61 change: 23 had
+// lost 1 ... 10 % by longer passes and have it back, but for 6 that still lose 1.0 ... 1.7 %; 15 had gained 1 ... 4.6 %, which go (2000 rows of H = 1056, I =
+// 2080 by 800 66.4 -> 69.9 us).
+inline bool Passes::they_save_time(const Pass& first) const {
+    const double otherwise = plain_time(left, since_), overlap = 6 * H * I <= ((int64_t)256 << 20) ? 5 : 0;
+    Passes then = *this;
+    double t = 0;
+    int64_t n = 0;
+    for (Pass p = first; p.rows; p = then.has_room() ? then.longer_pass() : Pass()) {
+        t += p.time();
+        ++n;
+        then.done(p);
+        const int64_t fewer = (left + C - 1) / C - n - (then.left + C - 1) / C;
+        const double saved = otherwise - t - then.plain_time(then.left, then.since_) - overlap * fewer;
+        if (saved >= (fewer > 0 ? 0 : 0.01 * otherwise)) return true;
+    }
+    return false;
 }
 
 // ---- Whole blocks of token rows in one launch (mom_block.hip.inc), for calls of several mini-sequences on a small layer.

@@ -48,6 +48,18 @@ int main(int argc, char**) {
         const momk::Pass p = momk::Passes(t[0], t[1], t[2], t[3], 256, true).next();
         CHECK(p.rows == t[4], "S=%lld C=%lld: %lld rows, not %lld", (long long)t[0], (long long)t[3], (long long)p.rows, (long long)t[4]);
     }
+    // ... and calls that longer passes made slower: as many passes, of lengths that take as long or longer
+    const int64_t none[][4] = {{3072, 512, 1536, 1024}, {3072, 1024, 4096, 1024}, {7471, 512, 1536, 2500}, {2328, 1056, 2080, 1280}, {3361, 1056, 2080, 1280},
+                               {2494, 1056, 2080, 1280}, {3000, 1056, 2080, 1600}, {3000, 1056, 2080, 1024}, {2084, 1024, 4096, 800}, {2939, 1056, 2080, 1500},
+                               {1000, 1056, 2080, 200}};
+    for (const auto& t : none) {
+        momk::Passes passes(t[0], t[1], t[2], t[3], 256, true);
+        while (passes.left > 0) {
+            const momk::Pass p = passes.next();
+            CHECK(p.split == momk::kWhole, "S=%lld C=%lld H=%lld: %lld rows", (long long)t[0], (long long)t[3], (long long)t[1], (long long)p.rows);
+            passes.done(p);
+        }
+    }
     CHECK(!momk::longer_passes(32768, 4096, 14336, 4096) && !momk::longer_passes(300, 256, 1024, 100) && !momk::longer_passes(512, 4096, 14336, 512), "asked for");
     // What blocks are weighed against is what the driver runs: calls in blocks of several rounds of the CUs take no more than its passes would.
     int blocks = 0, instead = 0;
