@@ -563,10 +563,13 @@ private:
 };
 
 // The pass of whole 256-row tiles, more than C rows, that takes the least time per row, of the three longest; none where
-// it is not 3 % less than in a pass of C rows.  Of 651 calls of eight layers 246 take less time so, 19 % on average.
+// it is not 3 % less than in the pass of C rows that would be the next.  Of 651 calls of eight layers 246 took less time so, 19 % on average, where
+// that pass was taken to find W_down in the Infinity Cache, which the first ones don't (512 rows of H = 3584, I = 18944: 0.445 us a row and 0.385).  With
+// what it takes itself 241 more of 1785 calls of eleven layers change, 193 of them by more than 1 %, to 3 % less time on average, and 7 by
+// more than 1 % for the worse (2.2 % at most).
 inline Pass Passes::longer_pass() const {
     Pass best;
-    double least = 0.97 * (gateup_.time + kept_.time) / C;
+    double least = 0.97 * of_rows(C, since_).time() / C;
     int64_t rows = longest();
     for (int i = 0; i < 3 && rows > C; ++i, rows -= 256) {
         Pass p;
