@@ -512,14 +512,24 @@ public:
         taken_ |= p.split != kWhole;
         since_ = p.split == kWhole || kept_down(p.gateup, p.rows, H, I) ? since_ + 1 : 0;
     }
-    // What all that is left is expected to take, us.
-    double time() const { return time_to(kAll); }
-    // Whether that is less than `limit`: known as soon as the rest would be so without longer passes, or, since shorter passes take more
-    // time per row, reaches the limit at 0.9 of the last one's.  That is mostly behind the first; all would take 20 ... 100 us on the host.
-    bool take_less_than(double limit) const { return time_to(limit) < limit; }
+    // What all that is left is expected to take, us, if that is less than `limit`.  Whether it is is known as soon as the rest would be so
+    // without longer passes (and this is returned), or, since shorter passes take more time per row, reaches the limit at 0.9 of the last
+    // one's: mostly behind the first.  All take 20 ... 100 us on the host.
+    double time(double limit = kAll) const {
+        Passes then = *this;
+        double t = 0;
+        while (then.has_room()) {
+            const Pass p = then.next();
+            t += p.time();
+            then.done(p);
+            if (t + 0.9 * p.time() / p.rows * then.left >= limit) return limit;
+            if (limit < kAll && t + then.plain_time(then.left, then.since_) < limit) break;
+        }
+        return t + then.plain_time(then.left, then.since_);
+    }
+    static constexpr double kAll = 1e30;
 
 private:
-    static constexpr double kAll = 1e30;
     Pass of_rows(int64_t rows, int64_t since) const {
         Pass p;
         p.rows = rows;
@@ -537,18 +547,6 @@ private:
     double plain_time(int64_t rows, int64_t since) const {
         const int64_t n = rows / C, cold = since >= kKeptFrom ? 0 : n < kKeptFrom - since ? n : kKeptFrom - since, rest = rows % C;
         return cold * (gateup_.time + down_.time) + (n - cold) * (gateup_.time + kept_.time) + (rest ? of_rows(rest, since + n).time() : 0);
-    }
-    double time_to(double limit) const {
-        Passes then = *this;
-        double t = 0;
-        while (then.has_room()) {
-            const Pass p = then.next();
-            t += p.time();
-            then.done(p);
-            if (t + 0.9 * p.time() / p.rows * then.left >= limit) return limit;
-            if (limit < kAll && t + then.plain_time(then.left, then.since_) < limit) break;
-        }
-        return t + then.plain_time(then.left, then.since_);
     }
     bool has_room() const { return longer_ && longest() > C; }
     int64_t longest() const { return most_rows(left, H, I, C / 256 * 256) / 256 * 256; }
@@ -667,35 +665,38 @@ inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, con
     if (least >= 0.93 * one * ((S + C - 1) / C)) return -1;
     // Longer passes, asked for only where the blocks take several rounds of the CUs: 8192 rows of H = 1056, I = 2080 by 256 339 us in
     // blocks, 224 so.
-    if (longer && block_count(kBlockForms[best], S) > (uint32_t)cus && longer_passes(S, H, I, C) && Passes(S, H, I, C, cus, true).take_less_than(least)) return -1;
+    if (longer && block_count(kBlockForms[best], S) > (uint32_t)cus && longer_passes(S, H, I, C) && Passes(S, H, I, C, cus, true).time(least) < least) return -1;
     return best;
 }
 
 // ---- Token rows of a pass of mom_mlp_prefill_static and mom_mlp_prefill_pipelined, whose workspaces hold more than mini_seq of them.
 
-// What the choices expect a call of S rows, R at a time, to take, us.
-inline double call_time(int64_t S, int64_t H, int64_t I, int64_t R, int cus) {
+// What a call of S rows, R at a time, is expected to take, us, if that is less than `limit`.  longer: by the passes that run, or without longer
+// ones.
+inline double call_time(int64_t S, int64_t H, int64_t I, int64_t R, int cus, bool longer, double limit = Passes::kAll) {
+    const Passes passes(S, H, I, R, cus, longer);
     if (S > R && small_layer(I, H)) {
-        const int form = choose_block(S, H, I, R, cus, choose_gateup(R, I, H, cus, true), choose_down(R, H, I, cus, false));
+        const Pass p = passes.plain();
+        const int form = choose_block(S, H, I, R, cus, p.gateup, p.down, longer);
         if (form >= 0) return block_time(kBlockForms[form], S, H, I, cus);
     }
-    auto pass = [&](int64_t rows, int64_t c) {
-        const Launch gateup = choose_gateup(rows, I, H, cus, S > R);
-        return gateup.time + choose_down(rows, H, I, cus, c >= kKeptFrom && kept_down(gateup, rows, H, I)).time;
-    };
-    const int64_t whole = S / R, first = whole < kKeptFrom ? whole : kKeptFrom;
-    return (first ? first * pass(R, 0) : 0) + (whole > first ? (whole - first) * pass(R, first) : 0) + (S % R ? pass(S % R, whole) : 0);
+    return passes.time(limit);
 }
 
 // `rows` at a time, or, of as few passes as a workspace for `most` rows allows, all of the same length in whole 256-row tiles, where that is
 // expected to take 3.5 % less.  1350 rows of H = 6144, I = 16384 by 600 take 857 us, as 512, 512 and 326 695; static, 33875 rows of H =
 // 1056, I = 2080 by 16128 416, by 11520 379.  Of 1557 calls with two mini-sequences' workspace (S 1.05 ... 4.5 C, 14 layers) 165 change, by
-// 5.5 % on average, 4 for the worse by 2 % or a little more; with 1 % promised 319, 17 for the worse.  Not asked of calls of less than some
+// 5.5 % on average, 4 for the worse by 2 % or a little more; with 1 % promised 319, 17 for the worse.  That is without longer passes; where
+// there may be some, not if these take less time with `rows`, whose workspace holds more: 7757 rows of H = 2048, I = 8192 by 2578, as 3072, 2816 and
+// 1869 of them, 572 us, by 2048 602.  Of 1633 calls of twelve layers 30 take `rows` so, all in less time (2.7 %).  Not asked of calls of less than some
 // 40 us, which the asking (3 ... 10 us on the host) would make longer: 690 rows of a 256 x 1024 layer 16.1 -> 17.5 us.
 inline int64_t even_rows(int64_t S, int64_t H, int64_t I, int64_t rows, int64_t most, int cus) {
     const int64_t n = (S + most - 1) / most, even = ((S + n - 1) / n + 255) / 256 * 256;
     if (n == 1 || even >= most || even == rows || S * H < ((int64_t)1 << 33) / I) return rows;
-    return call_time(S, H, I, even, cus) < 0.965 * call_time(S, H, I, rows, cus) ? even : rows;
+    if (call_time(S, H, I, even, cus, false) >= 0.965 * call_time(S, H, I, rows, cus, false)) return rows;
+    if (!longer_passes(S, H, I, rows)) return even;
+    const double t = call_time(S, H, I, even, cus, true);
+    return call_time(S, H, I, rows, cus, true, t) < t ? rows : even;
 }
 
 // Static: the array of `bytes` is there at its full size whatever mini_seq (C rows) is, and a pass of more rows takes less time per row

@@ -131,6 +131,22 @@ static void passes() {
         const int64_t r = momk::pipelined_rows(t[0], t[1], t[2], t[3], 256);
         CHECK(r == t[4], "pipelined S=%lld C=%lld: %lld rows, not %lld", (long long)t[0], (long long)t[3], (long long)r, (long long)t[4]);
     }
+    // Passes of the same length give way where the driver's longer passes take less time with all of the workspace.
+    const int64_t whole[][5] = {{18497, 1056, 2080, 4391, 8782}, {7757, 2048, 8192, 1289, 2578}, {15154, 512, 1536, 2143, 4286}, {3093, 1024, 4096, 772, 1544}};
+    for (const auto& t : whole) {
+        const int64_t r = momk::pipelined_rows(t[0], t[1], t[2], t[3], 256);
+        CHECK(r == t[4], "pipelined S=%lld C=%lld: %lld rows, not %lld", (long long)t[0], (long long)t[3], (long long)r, (long long)t[4]);
+    }
+    for (const auto& l : layers)
+        for (int64_t C = 100; C < 6000; C += 1 + C / 11)
+            for (int64_t S = 2 * C + 1; S < 9 * C; S += 1 + C * 3 / 5) {
+                const int64_t p = momk::pipelined_rows(S, l[0], l[1], C, 256);
+                if (p == C || p == 2 * C || p == S) continue;
+                const double even = momk::call_time(S, l[0], l[1], p, 256, true), both = momk::call_time(S, l[0], l[1], 2 * C < S ? 2 * C : S, 256, true);
+                const double one = momk::call_time(S, l[0], l[1], C, 256, true);         // (long mini-sequences go one at a time)
+                CHECK(even <= 1.0001 * both || even <= 1.0001 * one, "pipelined S=%lld C=%lld H=%lld: %lld rows %.1f us, %.1f with all", (long long)S, (long long)C,
+                      (long long)l[0], (long long)p, even, both);
+            }
     const int64_t fixed[][5] = {{33875, 1056, 2080, 128, 11520}, {20766, 1056, 2080, 10752, 10496}, {33875, 1056, 2080, 8000, 11520}, {12000, 4096, 14336, 128, 2304},
                                 {2304, 4096, 14336, 128, 2304}, {2457, 4096, 14336, 128, 2304}, {12000, 4096, 14336, 2000, 2000}};
     for (const auto& t : fixed) {
