@@ -126,6 +126,22 @@ constexpr RingLoad ring_load(bool gateup, int TM, int TN, int KSUB, int wave, in
 // Whether weight load j reads W_up, whichever wavefront it is (gate/up).
 constexpr bool ring_load_up(int TM, int TN, int KSUB, int j) { return j - KSUB * TM / 32 >= KSUB * TN / 64; }
 
+// In which order the stages of a short form's ring (nstg of them, `loads` loads per wavefront and stage) are requested, and what the kernel waits
+// for.  Stage 0 ... nstg - 1 before the first is multiplied, then, while stage t is and the last of its group by place is done, those of the next group:
+// `group` stages together, load by load, one behind the other.  Group boundaries lie so that the stages in front of nstg end one.
+//   ring_place       place of stage t in its group
+//   ring_first       the first stage that is requested while stage t is multiplied, and group - 1 behind it; -1: none.  All go to slots (stage %
+//                    nstg) of stages up to t, which are in registers.
+//   ring_in_flight   loads that may still be on their way when stage t is needed and `ahead` stages are requested behind it
+constexpr int ring_place(int t, int nstg, int group) { return ((t - nstg) % group + group) % group; }
+constexpr int ring_first(int t, int nstg, int group) { return t % group == group - 1 ? t + nstg - group + 1 : -1; }
+constexpr int ring_in_flight(int t, int ahead, int nstg, int group, int loads) {
+    const int r = group - 1 - ring_place(t, nstg, group), n = r + (ahead - r) * loads;
+    return n > 63 ? 63 : n;
+}
+// ... when stage t + 1 is needed at the barrier of stage t: that many stages are requested behind it.
+constexpr int ring_ahead(int t, int nstg, int group) { return nstg - 2 - t % group; }
+
 // The time of a launch in us: what a CU spends on a tile, times the tiles it runs.
 //   start, output   once per tile: launch, ring prologue, epilogue; per output element (silu for gate/up).  The workgroups
 //                   that share a CU (ShortShape::per_cu) overlap it.

@@ -9,11 +9,46 @@
 static int bad = 0;
 #define CHECK(c, ...) do { if (!(c)) { printf("FAILED %s: ", #c); printf(__VA_ARGS__); printf("\n"); ++bad; } } while (0)
 
+// The requests of a ring in the order of the kernel: every load of a stage once, into a slot whose stage is in registers, and each wait is for
+// the stage that is needed next and no other.
+static void ring(int tm, int tn, int nstg, int loads, int group) {
+    std::vector<int> stage;                           // of every load, in the order of the requests
+    auto request = [&](int first, int n) {
+        for (int j = 0; j < loads; ++j)
+            for (int g = 0; g < n; ++g) stage.push_back(first + g);
+    };
+    auto landed = [&](int t, int in_flight) {         // loads up to all of stage t, and how many are not waited for
+        int behind = 0;
+        for (size_t i = stage.size(); i > 0 && stage[i - 1] != t; --i) ++behind;
+        CHECK(in_flight == (behind > 63 ? 63 : behind), "%d x %d, %d stages, groups of %d: stage %d waited for at %d in flight, %d behind it", tm, tn, nstg,
+              group, t, in_flight, behind);
+    };
+    for (int t = 0; t < nstg; ++t)
+        if (t == 0 || momk::ring_place(t, nstg, group) == 0) request(t, group - momk::ring_place(t, nstg, group));
+    landed(0, momk::ring_in_flight(0, nstg - 1, nstg, group, loads));
+    for (int t = 0; t < 40; ++t) {
+        // (the phases of the kernel: t % group stands for t)
+        landed(t + 1, momk::ring_in_flight(t % group + 1, momk::ring_ahead(t % group, nstg, group), nstg, group, loads));
+        const int first = momk::ring_first(t, nstg, group);
+        const int phase = t % group, phase_first = momk::ring_first(phase, nstg, group);
+        CHECK((first < 0) == (phase_first < 0) && (first < 0 || phase_first - phase == first - t), "requests at stage %d and at its phase", t);
+        if (first < 0) continue;
+        for (int g = 0; g < group; ++g)               // slot of stage first + g: that of stage first + g - nstg, in the kernel's count t - group + 1 + g
+            CHECK(first + g - nstg == t - group + 1 + g && first + g - nstg <= t, "slot of stage %d at stage %d, %d stages", first + g, t, nstg);
+        request(first, group);
+    }
+    std::vector<int> seen(stage.back() + 1);
+    for (int t : stage) ++seen[t];
+    for (size_t t = 0; t < seen.size(); ++t) CHECK(seen[t] == loads, "stage %d of %d x %d requested %d times", (int)t, tm, tn, seen[t] / loads);
+}
+
 static void form(bool gu, int f, int tm, int tn, int wm, int wn, int ksub, int nstg) {
     const int stage = ksub * (tm + tn) * 128, loads = ksub * (tm + tn) / 32;
     const int cols = gu ? tn / 2 : tn;
     CHECK(nstg * stage <= 163840 && stage <= 65536 && nstg >= 2, "ring of %d x %d", tm, tn);
     CHECK((nstg - 2) * loads <= 63, "loads in flight of %d x %d", tm, tn);
+    for (int group : {1, 2})
+        if (group == 1 || (gu && nstg >= 5)) ring(tm, tn, nstg, loads, group);
     CHECK(wm * wn <= 4 && tm % (16 * wm) == 0 && tn % (16 * wn) == 0, "wavefront grid of %d x %d", tm, tn);
     CHECK(!gu || (tn / 16 / wn) % 2 == 0, "gate and up blocks of %d x %d", tm, tn);
     CHECK((ksub * tm) % 32 == 0 && (ksub * tn) % (gu ? 64 : 32) == 0, "loads per wavefront of %d x %d", tm, tn);

@@ -36,6 +36,12 @@ def test_forms_and_choice(tmp_path):
     ("const int gsz = tiles_m - first_m < group_m ? tiles_m - first_m : group_m;", "const int gsz = group_m;", "of M="),
     # the rows of W_up behind those of a whole tile instead of half a one
     ("half * HR + src, src}", "half * TN + src, src}", "block of"),
+    # a wait that lets one load too many of the stage be on its way, that forgets the other stage of its group, and that waits for more than it needs
+    ("n = r + (ahead - r) * loads;", "n = r + (ahead - r) * loads + 1;", "waited for at"),
+    ("n = r + (ahead - r) * loads;", "n = ahead * loads + 0 * r;", "waited for at"),
+    ("return nstg - 2 - t % group; }", "return nstg - 3 - t % group; }", "waited for at"),
+    # a group requested one stage early: into a slot that is still to be read
+    ("t % group == group - 1 ? t + nstg - group + 1 : -1", "t % group == group - 1 ? t + nstg - group + 2 : -1", "slot of stage"),
 ])
 def test_a_planted_mistake_is_caught(tmp_path, old, new, says):
     """Planted in a copy of the header, on the CPU."""
