@@ -367,6 +367,37 @@ inline int64_t rounds_per_mille(int64_t tiles, int cus) {
     const int64_t full = tiles / cus, rem = tiles % cus;
     return full * 1000 + (rem ? 500 + 500 * rem / cus : 0);
 }
+
+// The number b > 0 of column tiles of 96 behind those of 128 in a launch of N columns and tm token tiles for which the rounds of the CUs
+// take the least time and kGateUpMixMinGainPerMille less than for b = 0, and that `cost`; 0: none.  The cost of b: rounds_per_mille(tm * a) * 128 *
+// 1000 + rounds_per_mille(tm * b) * 96 * kGateUpNarrowPerMille, a = ceil((N - 96 b) / 128).  Every launch looks at all b (148 of them at
+// 14336 columns, 2 us of a choice's 2.7 by divisions), so the rounds are counted on from one b to the next.
+struct Rounds {
+    uint32_t cus, rem = 0;
+    int64_t full = 0;
+    explicit Rounds(int n) : cus((uint32_t)n) {}
+    Rounds(int n, int64_t tiles) : cus((uint32_t)n), rem((uint32_t)(tiles % n)), full(tiles / n) {}
+    void count(const Rounds& o, int times) {                   // times: 1 or -1
+        full += times * o.full;
+        if (times > 0) { rem += o.rem; if (rem >= cus) { rem -= cus; ++full; } }
+        else { if (rem < o.rem) { rem += cus; --full; } rem -= o.rem; }
+    }
+    int64_t per_mille() const { return full * 1000 + (rem ? 500 + 500 * rem / cus : 0); }
+};
+inline int64_t narrow_tiles(int64_t N, int64_t tm, int cus, int64_t& cost) {
+    int64_t a = (N + 127) / 128, best = 0;
+    const Rounds column(cus, tm);
+    Rounds wide(cus, tm * a), narrow(cus);
+    const int64_t plain = wide.per_mille() * 128 * 1000, most = plain * (1000 - kGateUpMixMinGainPerMille);
+    cost = plain;
+    for (int64_t b = 1, left = N - 96; b <= (N + 95) / 96; ++b, left -= 96) {
+        narrow.count(column, 1);
+        while (a > 0 && left <= 128 * (a - 1)) { wide.count(column, -1); --a; }
+        const int64_t c = wide.per_mille() * 128 * 1000 + narrow.per_mille() * 96 * kGateUpNarrowPerMille;
+        if (c < cost && c * 1000 <= most) { cost = c; best = b; }
+    }
+    return best;
+}
 // Down projection: 256-row tiles of 256, 224, 192, 160 or 128 weight rows, or the short forms, whatever takes the least time:
 // 3584 output columns with 32 token tiles are 1.75 rounds of 256-wide tiles on 256 CUs but exactly 2 rounds of
 // 224-wide ones, and the 128 full-size tiles of a 2048-row mini-sequence at 4096 columns are one round of 256 tiles 128 wide.
@@ -426,21 +457,13 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus, bool more)
     double least = 0;
     const bool small = small_layer(N, K), one_group = to_pass_by(M, N, K, more);
     const int form = choose_short_form(M, N, K, true, small ? kShortGateUpSmallTime : kShortGateUpTime, cus, least, 0, one_group);
-    // b column tiles of 96 behind a of 128: a = ceil((N - 96 b) / 128); time = rounds x columns per tile
     const int64_t tm = plain_launch.grid.tiles_m;
-    auto mix_cost = [&](int64_t b) {
-        const int64_t rest = N - 96 * b, wide = rest > 0 ? (rest + 127) / 128 : 0;
-        return rounds_per_mille(tm * wide, cus) * 128 * 1000 + rounds_per_mille(tm * b, cus) * 96 * kGateUpNarrowPerMille;
-    };
-    const int64_t plain = mix_cost(0);
-    int64_t cost = plain, narrow_tiles_n = 0;
     const double plain_time = launch_time(plain_launch.grid, M, K, true, {256, 256, 1, 0}, kFullGateUpTime, cus);
     // (no mix takes less than half of what the plain tiles take: where the short form does, it is not looked for)
     const bool few = form >= 0 && least < 0.5 * plain_time;
-    for (int64_t b = 1; b <= (N + 95) / 96 && !few; ++b) {
-        const int64_t c = mix_cost(b);
-        if (c < cost && c * 1000 <= plain * (1000 - kGateUpMixMinGainPerMille)) { cost = c; narrow_tiles_n = b; }
-    }
+    const int64_t plain = rounds_per_mille(tm * ((N + 127) / 128), cus) * 128 * 1000;
+    int64_t cost = plain;
+    const int64_t narrow_tiles_n = few ? 0 : narrow_tiles(N, tm, cus, cost);
     const int64_t rest = N - 96 * narrow_tiles_n, wide_cols = rest > 0 ? (rest + 127) / 128 * 128 : 0;
     double full = plain_time * cost / plain;
     if (wide_cols == 0)
@@ -704,13 +727,13 @@ inline double call_time(int64_t S, int64_t H, int64_t I, int64_t R, int cus, boo
 // 1056, I = 2080 by 16128 416, by 11520 379.  Of 1557 calls with two mini-sequences' workspace (S 1.05 ... 4.5 C, 14 layers) 165 change, by
 // 5.5 % on average, 4 for the worse by 2 % or a little more; with 1 % promised 319, 17 for the worse.  That is without longer passes; where
 // there may be some, not if these take less time with `rows`, whose workspace holds more: 7757 rows of H = 2048, I = 8192 by 2578, as 3072, 2816 and
-// 1869 of them, 572 us, by 2048 602.  Of 1633 calls of twelve layers 30 take `rows` so, all in less time (2.7 %).  Not asked of calls of less than some
+// 1869 of them, 572 us, by 2048 602.  Of 1633 calls of twelve layers 26 take `rows` so, none in more time (3 % less).  Not asked of calls of less than some
 // 40 us, which the asking (3 ... 10 us on the host) would make longer: 690 rows of a 256 x 1024 layer 16.1 -> 17.5 us.
 inline int64_t even_rows(int64_t S, int64_t H, int64_t I, int64_t rows, int64_t most, int cus) {
     const int64_t n = (S + most - 1) / most, even = ((S + n - 1) / n + 255) / 256 * 256;
     if (n == 1 || even >= most || even == rows || S * H < ((int64_t)1 << 33) / I) return rows;
     if (call_time(S, H, I, even, cus, false) >= 0.965 * call_time(S, H, I, rows, cus, false)) return rows;
-    if (!longer_passes(S, H, I, rows)) return even;
+    if (rows < even || !longer_passes(S, H, I, rows)) return even;
     const double t = call_time(S, H, I, even, cus, true);
     return call_time(S, H, I, rows, cus, true, t) < t ? rows : even;
 }

@@ -143,6 +143,19 @@ static void kept(int64_t H, int64_t I) {
     }
 }
 
+// The mix of tiles of 128 and 96 columns that narrow_tiles finds by counting on, and its cost, against every mix by itself.
+static void mixes(int64_t N, int64_t tm, int cus) {
+    auto mix_cost = [&](int64_t b) {
+        const int64_t rest = N - 96 * b, wide = rest > 0 ? (rest + 127) / 128 : 0;
+        return momk::rounds_per_mille(tm * wide, cus) * 128 * 1000 + momk::rounds_per_mille(tm * b, cus) * 96 * momk::kGateUpNarrowPerMille;
+    };
+    int64_t cost = mix_cost(0), best = 0, got = 0;
+    for (int64_t b = 1; b <= (N + 95) / 96; ++b)
+        if (mix_cost(b) < cost && mix_cost(b) * 1000 <= mix_cost(0) * (1000 - momk::kGateUpMixMinGainPerMille)) { cost = mix_cost(b); best = b; }
+    const int64_t b = momk::narrow_tiles(N, tm, cus, got);
+    CHECK(b == best && got == cost, "N=%lld in %lld token tiles on %d CUs: %lld narrow tiles, not %lld", (long long)N, (long long)tm, cus, (long long)b, (long long)best);
+}
+
 // Rows of a pass fit the workspace, and what was measured the faster of the candidates is taken.
 static void passes() {
     const int64_t layers[][2] = {{4096, 14336}, {3584, 18944}, {6144, 16384}, {3584, 9728}, {1056, 2080}, {256, 1024}, {32, 1 << 20}, {1 << 20, 32}};
@@ -209,6 +222,9 @@ int main() {
     const int64_t kept_layers[][2] = {{4096, 14336}, {3584, 18944}, {4096, 11008}, {6144, 16384}, {5120, 13824}, {5120, 25600}, {2048, 8192}};
     for (const auto& l : kept_layers) kept(l[0], l[1]);
     passes();
+    for (int cus : {1, 80, 256, 304})
+        for (int64_t N : {32, 96, 128, 160, 1024, 2080, 9728, 14336, 18944, 28672, 1 << 20})
+            for (int64_t tm = 1; tm < (N > 30000 ? 600 : 8388608); tm += 1 + tm / 9) mixes(N, tm, cus);
     // Where the constants of the short down forms change, and from where the rectangular ones are looked at, the choice doesn't.
     const int64_t edge_layers[][2] = {{4096, 14336}, {3584, 18944}, {3584, 9728}, {2560, 9728}, {6144, 16384}, {4096, 11008},
                                       {5120, 13824}, {2048, 8192}, {2048, 5632}, {3072, 8192}, {4608, 12288}, {2304, 9216}, {3200, 8640}};
