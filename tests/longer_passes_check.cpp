@@ -8,8 +8,7 @@
 static int bad = 0;
 #define CHECK(c, ...) do { if (!(c)) { printf("FAILED %s: ", #c); printf(__VA_ARGS__); printf("\n"); ++bad; } } while (0)
 
-int main(int argc, char**) {
-    const int64_t plant = argc > 1 ? 4 : 0;         // a planted mistake: rows in the workspace that are no whole token tiles
+int main() {
     const int64_t layers[][2] = {{4096, 14336}, {3584, 18944}, {1056, 2080}, {256, 1024}, {5120, 25600}, {2048, 8192}, {8192, 28672}, {1024, 1024}, {4096, 32}, {32, 32}};
     int calls = 0, longer = 0, split = 0, whole = 0;
     for (const auto& l : layers)
@@ -22,11 +21,10 @@ int main(int argc, char**) {
                 ++calls;
                 for (int n = 0; r0 < S && n < 400; ++n) {
                     const int64_t left = S - r0;
-                    momk::Pass p = passes.next();
+                    const momk::Pass p = passes.next();
                     CHECK(passes.left == left && p.rows > 0 && p.rows <= left, "left");
                     passes.done(p);
                     if (p.split == momk::kWhole) { CHECK(p.rows == (left < C ? left : C), "rows"); r0 += p.rows; continue; }
-                    p.split += plant;
                     ++longer;
                     (p.split ? split : whole) += 1;
                     CHECK(p.rows > C && p.rows < left && p.rows % 256 == 0, "rows S=%lld C=%lld H=%lld", (long long)S, (long long)C, (long long)H);

@@ -1,5 +1,5 @@
-"""KV-cache reload of few tokens by a kernel and of others by copies: the bytes, and none beside them, at the edges of a
-workgroup's pass, of the kernel's range and of its alignment; and captured."""
+"""KV-cache reload by a kernel and by copies: the bytes, and none beside them, at the edges of the kernel's passes, of the sizes at
+which the one or the other is taken and of its alignment; which of them is taken, captured and not; beside other work and errors."""
 import ctypes
 
 import pytest
@@ -10,8 +10,8 @@ from paper_2504_12526_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
-PASS = 16 * 256 * 4 * 16          # bytes of one pass of all workgroups
-LARGEST = 256 << 10               # bytes each of the kernel's range
+PASS = 16 * 256 * 4 * 16          # bytes
+LARGEST = 256 << 10               # bytes each of the kernel's range under stream capture (elsewhere 1 MiB, and any behind work)
 GUARD = 64                         # elements on either side
 
 
@@ -57,23 +57,31 @@ def test_bytes_of_several_passes(each):
 def test_a_large_reload_only_enqueues():
     """The calling thread is not held until the work ahead of the reload is done."""
     n = 2 << 20
-    host = torch.randint(-32768, 32767, (2 * n,), dtype=torch.int16).pin_memory()
-    k, v = (torch.zeros(n, dtype=torch.int16, device="cuda") for _ in range(2))
+    main, ahead = torch.cuda.current_stream(), torch.cuda.Event()
     t = synth.mlp_inputs(synth.Workload("ahead", S=8192, H=2048, I=8192, mini_seq=0, seed=4), device="cuda")
     out, ws = torch.empty_like(t[0]), torch.empty(8192 * 8192 * 2, dtype=torch.uint8, device="cuda")
-    main, sides, ahead = torch.cuda.current_stream(), [torch.cuda.Stream() for _ in range(3)], torch.cuda.Event()
-    for side in sides:                                          # (the first reload maps the pages)
+    sides = [(torch.cuda.Stream(), torch.zeros(2 * n, dtype=torch.int16).pin_memory(), *(torch.zeros(n, dtype=torch.int16, device="cuda") for _ in range(2)))
+             for _ in range(3)]
+    torch.cuda.synchronize()                                    # (the zeros are there before another stream writes)
+
+    def reload(side, host, k, v):
         binding.mom_kv_reload(host.view(torch.bfloat16), k.view(torch.bfloat16), v.view(torch.bfloat16), side)
+
+    for s in sides:                                             # (the first reload maps the pages)
+        reload(*s)
     torch.cuda.synchronize()
+    for i, (_, host, _, _) in enumerate(sides):                 # other bytes than those that are there now
+        host.copy_(torch.randint(-32768, 32767, (2 * n,), dtype=torch.int16, generator=torch.Generator().manual_seed(i)))
     for _ in range(24):                                         # some 15 ms
         binding.mom_mlp_prefill(*t, 0, out, ws, stream=main)
     ahead.record(main)
-    for side in sides:
-        side.wait_event(ahead)
-        binding.mom_kv_reload(host.view(torch.bfloat16), k.view(torch.bfloat16), v.view(torch.bfloat16), side)
+    for s in sides:
+        s[0].wait_event(ahead)
+        reload(*s)
     assert not ahead.query()
     torch.cuda.synchronize()
-    assert torch.equal(k.cpu(), host[:n]) and torch.equal(v.cpu(), host[n:])
+    for _, host, k, v in sides:
+        assert bool((host != 0).any()) and torch.equal(k.cpu(), host[:n]) and torch.equal(v.cpu(), host[n:])
 
 
 def _some_work():

@@ -103,29 +103,68 @@ def test_out_in_host_memory_holds_results_only(S, H, I, C):
 @pytest.mark.parametrize("form", [("gemm", 256, 5, 224), ("gemm", 256, 5, 160), ("gemm", 128, 0, 0), ("rect", 192, 256), ("rect", 160, 160), ("rect", 224, 160),
                                   ("short", 96, 64), ("short", 160, 128), ("short", 48, 32), ("short", 80, 64)])
 def test_pieces_in_every_kind_of_tile(form):
-    # C = 400: 224, 160, 256, 192, 400, 320, 384 rows of the first pass in the workspace, and none with tiles of more rows
-    S, H, I, C = 4500, 1056, 2080, 400
-    t, ref, whole, out, ws = _case(S, H, I, C, 8)
+    # workspaces of 400 rows, of which 256, 256, (down not forced), 384, 320, 224, 384, 320, 384 and 400 are whole tiles of the down launch, and of 130,
+    # none or 96, 96 and 80
+    from graph_nodes import node_types
+    S, H, I = 4500, 1056, 2080
+    t, ref, whole, out, ws = _case(S, H, I, 400, 8)
     force = {"gemm": binding.mom_debug_force_gemm_form, "rect": binding.mom_debug_force_rect_form, "short": binding.mom_debug_force_short_form}[form[0]]
     try:
         force(*form[1:])
-        for c in (C, 130):
-            binding.mom_mlp_prefill(*t, c, out, ws[:c * I])
-            _assert_result(ref, whole, out, ws, C * I, f"{form} C={c}")
+        for c in (400, 130):
             out.view(torch.int16).fill_(0x5a5a)
+            ws.fill_(0x5a5a)
+
+            def call(stream):
+                binding.mom_mlp_prefill(*t, c, out, ws[:c * I], stream=stream)
+
+            assert len(node_types(call)) < 2 * -(-S // c), f"{form} C={c}: no longer pass"
+            call(torch.cuda.current_stream())
+            _assert_result(ref, whole, out, ws, c * I, f"{form} C={c}")
     finally:
         force(*([0] * len(form[1:])))
 
 
 @pytest.mark.gpu
-def test_two_streams_static_and_captured():
+def test_two_streams():
+    from graph_nodes import node_types
     S, H, I, C = 5000, 1056, 2080, 300
     t, ref, whole, out, ws = _case(S, H, I, 2 * C, 8)
     side, events = torch.cuda.Stream(), [torch.cuda.Event() for _ in range(5)]
     for e in events:
         e.record()
-    binding.mom_mlp_prefill_pipelined(*t, C, out, ws[:2 * C * I], torch.cuda.current_stream(), side, events)
+
+    def call(stream):
+        binding.mom_mlp_prefill_pipelined(*t, C, out, ws[:2 * C * I], stream, side, events)
+
+    assert len(node_types(call)) < 2 * -(-S // (2 * C))                    # fewer than two mini-sequences at a time take
+    call(torch.cuda.current_stream())
     _assert_result(ref, whole, out, ws, 2 * C * I, "pipelined")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("S,H,I,C", [(4797, 4096, 14336, 2340), (8169, 4096, 14336, 2340)])
+def test_static(S, H, I, C):
+    from graph_nodes import node_types
+    t, ref, whole, out, _ = _case(S, H, I, 1, 8)
+    binding.mom_init()
+
+    def call(stream):
+        binding.mom_mlp_prefill_static(*t, C, out, stream=stream)
+
+    fit = binding.MOM_STATIC_WORKSPACE_BYTES // (2 * I)
+    assert 2 < len(node_types(call)) < 2 * -(-S // fit)                    # fewer than the array's rows at a time take
+    call(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    lo = (out.data_ptr() - whole.data_ptr()) // 2
+    assert torch.equal(out.view(torch.int16), ref)
+    assert bool((whole[:lo] == 0x5a5a).all()) and bool((whole[lo + out.numel():] == 0x5a5a).all())
+
+
+@pytest.mark.gpu
+def test_captured():
+    S, H, I, C = 5000, 1056, 2080, 300
+    t, ref, whole, out, ws = _case(S, H, I, C, 8)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         binding.mom_mlp_prefill(*t, C, out, ws[:C * I])
@@ -133,6 +172,7 @@ def test_two_streams_static_and_captured():
         t[0].mul_(-0.5)
         binding.mom_mlp_prefill(*t, 0, (want := torch.empty_like(out)), torch.empty(S * I * 2, dtype=torch.uint8, device="cuda"))
         out.view(torch.int16).fill_(0x5a5a)
+        ws.fill_(0x5a5a)
         torch.cuda.synchronize()
         graph.replay()
-        _assert_result(want.view(torch.int16), whole, out, ws, 2 * C * I, f"replay {r}")
+        _assert_result(want.view(torch.int16), whole, out, ws, C * I, f"replay {r}")
