@@ -159,8 +159,9 @@ bool on_current_device(const void* p) {
 // whole 16-byte chunks, buffers of the current device, which is also the stream's, each in one allocation and not overlapping, up to
 // 16 GiB each (its 32-bit chunk numbers).  Up to 1 MiB each the kernel is the faster one by itself (256 KiB 34 -> 14 us, 512 KiB 46 -> 34)
 // and costs the kernels beside it no more than copies do.  Larger ones do (mom_kv.hip.inc has the times), so they go by copies on a
-// stream that is ready.  Behind work that is still to be done the runtime may hold the calling thread in a copy, so there it is the kernel;
-// the question takes some 6 us then.  Captured calls, whose copies the graph starts, take the kernel up to 256 KiB each.
+// stream that is ready (five last-token branches beside 2 x 16 MiB 1242 -> 1097 us).  Behind work that is still to be done the runtime may
+// hold the calling thread in a copy, so there it is the kernel (8192 tokens, 40 and more passes enqueued ahead, 863 -> 647 us); the question
+// takes 6 ... 10 us then.  Captured calls, whose copies the graph starts, take the kernel up to 256 KiB each.
 const void* reload_source(const void* pinned_host, const void* k, const void* v, size_t bytes_each, hipStream_t st) {
     if (bytes_each > ((size_t)16 << 30) || bytes_each % 16 || !aligned16(pinned_host) || !aligned16(k) || !aligned16(v)) return nullptr;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;

@@ -193,6 +193,8 @@ constexpr LaunchTime kShortDownKeptTime = {2.28, 9.78e-5, 1.14e-5, 4.14e-5, 7.43
 // W_down still in the Infinity Cache.  Then nobody needs to run ahead: 1024 rows x 4096 columns in tiles of
 // 160 x 128: 117 us, in eight of 128 x 128: 109 us; 512 rows in tiles of 160 x 64 80 us, of 128 x 64 70 us.
 constexpr LaunchTime kShortDownSmallTime = {5.9, 1.40e-4, 1.02e-5, 3.58e-5, 1.36e-7, 1.0, kFromCache, true, 0, 0};
+// (Gate/up: fitted before rings of five stages and more requested two together.  Those with weights from memory take less than the formula
+// where K is a multiple of 4096: 96 rows x 14336 columns, K = 4096, 47 us, 51 by the formula, 128 rows 50 and 55.)
 constexpr LaunchTime kShortGateUpTime = {5.95, 1.97e-4, 1.11e-5, 5.61e-5, 1.42e-7, 1.0, kFromHbm, false, 0, 0};
 constexpr LaunchTime kShortGateUpSmallTime = {6.15, 2.28e-4, 1.20e-5, 3.92e-5, 1.41e-7, 1.0, kFromCache, false, 0, 0};
 constexpr LaunchTime kFullDownTime = {4.0, 2.4e-5, 1.09e-5, 4.87e-5, 1.52e-7, 0.80, 0, true, 0, 0};
@@ -500,8 +502,8 @@ inline Launch choose_gateup(int64_t M, int64_t N, int64_t K, int cus, bool more)
 //
 // A pass of R of the `left` rows that are still to do puts its rows from `split` on at the end of `out`, which must not reach down to row R:
 // 2 (R - split) I bytes, and up to 256 for the alignment, of the 2 (left - R) H that are free.  A longer pass takes less time per row, down to
-// some 4096 of them: one mini-sequence at a time -> so, H = 4096, I = 14336: 8192 rows by 128 5592 us -> 2931, by 512 2671 -> 2431, 32768 by
-// 512 10378 -> 8220, 16384 by 1024 4505 -> 4170, with the workspace of two 4094 -> 3987; H = 1056, I = 2080: 8192 by 512 345 -> 185.
+// some 4096 of them: one mini-sequence at a time -> so, H = 4096, I = 14336: 8192 rows by 128 5635 us -> 2970, by 512 2552 -> 2335, 32768 by
+// 512 10215 -> 8062, 16384 by 1024 4364 -> 4090, with the workspace of two 4136 -> 4009; H = 1056, I = 2080: 8192 by 512 351 -> 193.
 constexpr int64_t kSpareAlign = 256;
 inline int64_t most_rows(int64_t left, int64_t H, int64_t I, int64_t split) { return (left * H + split * I - kSpareAlign / 2) / (H + I); }
 
@@ -703,7 +705,7 @@ inline int choose_block(int64_t S, int64_t H, int64_t I, int64_t C, int cus, con
     const double one = gateup.time + down.time - 6;
     if (least >= 0.93 * one * ((S + C - 1) / C)) return -1;
     // Longer passes, asked for only where the blocks take several rounds of the CUs: 8192 rows of H = 1056, I = 2080 by 256 339 us in
-    // blocks, 224 so.
+    // blocks, 224 so, 16384 673 and 335.
     if (longer && block_count(kBlockForms[best], S) > (uint32_t)cus && longer_passes(S, H, I, C) && Passes(S, H, I, C, cus, true).time(least) < least) return -1;
     return best;
 }
