@@ -729,13 +729,14 @@ inline double call_time(int64_t S, int64_t H, int64_t I, int64_t R, int cus, boo
 // 1056, I = 2080 by 16128 416, by 11520 379.  Of 1557 calls with two mini-sequences' workspace (S 1.05 ... 4.5 C, 14 layers) 165 change, by
 // 5.5 % on average, 4 for the worse by 2 % or a little more; with 1 % promised 319, 17 for the worse.  That is without longer passes; where
 // there may be some, not if these take less time with `rows`, whose workspace holds more: 7757 rows of H = 2048, I = 8192 by 2578, as 3072, 2816 and
-// 1869 of them, 572 us, by 2048 602.  Of 1633 calls of twelve layers 26 take `rows` so, none in more time (3 % less).  Not asked of calls of less than some
-// 40 us, which the asking (3 ... 10 us on the host) would make longer: 690 rows of a 256 x 1024 layer 16.1 -> 17.5 us.
+// 1869 of them, 572 us, by 2048 602.  Of 1633 calls of twelve layers 26 take `rows` so, none in more time (3 % less).  Of more than 64 passes
+// that is not asked, as each may have to be looked at.  Nothing is asked of calls of less than some 40 us, which the asking (3 ... 10 us on the
+// host, 20 ... 60 with longer passes) would make longer: 690 rows of a 256 x 1024 layer 16.1 -> 17.5 us.
 inline int64_t even_rows(int64_t S, int64_t H, int64_t I, int64_t rows, int64_t most, int cus) {
     const int64_t n = (S + most - 1) / most, even = ((S + n - 1) / n + 255) / 256 * 256;
     if (n == 1 || even >= most || even == rows || S * H < ((int64_t)1 << 33) / I) return rows;
     if (call_time(S, H, I, even, cus, false) >= 0.965 * call_time(S, H, I, rows, cus, false)) return rows;
-    if (rows < even || !longer_passes(S, H, I, rows)) return even;
+    if (rows < even || n > 64 || !longer_passes(S, H, I, rows)) return even;
     const double t = call_time(S, H, I, even, cus, true);
     return call_time(S, H, I, rows, cus, true, t) < t ? rows : even;
 }
