@@ -535,7 +535,7 @@ public:
         down_ = choose_down(C, H, I, cus, false);
         kept_ = S > kKeptFrom * C && !small_layer(I, H) && kept_down(gateup_, C, H, I) ? choose_down(C, H, I, cus, true) : down_;
     }
-    // The next pass, and the next as long as the workspace.
+    // The next pass, and (plain) what it is where no longer one is looked for.
     Pass next() {
         const Pass p = has_room() ? longer_pass() : Pass();
         if (!p.rows) return plain();
